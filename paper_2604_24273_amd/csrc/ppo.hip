@@ -4,8 +4,10 @@
 // The backbone is frozen, so a rollout stores h_t once and the update touches only the two small
 // MLPs: every mini-batch is a forward pass of both heads, the clipped-surrogate / entropy / value
 // gradients at their outputs, back-propagation, one global gradient-norm clip and an Adam step.
-// The products are tiny (64 x 2560 x 256), so the work is laid out as a few wide kernels per
-// step, each with fp64 accumulation in a fixed order: results do not depend on scheduling.
+// The products are tiny (64 x 2560 x 256), so a step is latency: it is laid out as four kernels
+// (first layer of both heads; everything between the first layer's outputs and its deltas, one
+// workgroup per sample; all weight gradients; gradient norm and Adam), the two large contractions
+// on the fp64 matrix cores, every sum in fp64 in a fixed order: results do not depend on scheduling.
 // Parameters and optimiser state are fp32 in one flat buffer each (policy W_1, b_1, ..., W_L, b_L,
 // then the value head likewise); activations, deltas and gradients of a step live in fp64 scratch.
 #include "common.hpp"
@@ -29,7 +31,6 @@ struct HeadShape {
 struct Layout {
     HeadShape head[2];               // 0 policy, 1 value
     size_t n_params, n_policy;
-    int max_dim;                     // widest layer output
 };
 
 int make_layout(const brl_ppo_config* c, Layout& L) {
@@ -40,7 +41,6 @@ int make_layout(const brl_ppo_config* c, Layout& L) {
                 "ppo: 1..%d layers per head", PPO_MAX_LAYERS);
     BRL_REQUIRE(c->act == BRL_ACT_TANH || c->act == BRL_ACT_RELU, "ppo: unknown activation %d", c->act);
     size_t off = 0;
-    L.max_dim = 1;
     for (int hd = 0; hd < 2; ++hd) {
         HeadShape& H = L.head[hd];
         H.n = hd == 0 ? c->policy_layers : c->value_layers;
@@ -48,7 +48,6 @@ int make_layout(const brl_ppo_config* c, Layout& L) {
         for (int i = 0; i <= H.n; ++i) {
             BRL_REQUIRE(dims[i] >= 1 && dims[i] <= (1 << 20), "ppo: layer size %d", dims[i]);
             H.dims[i] = dims[i];
-            if (i > 0 && dims[i] > L.max_dim) L.max_dim = dims[i];
         }
         for (int l = 0; l < H.n; ++l) {
             H.w_off[l] = off;
@@ -67,23 +66,58 @@ int make_layout(const brl_ppo_config* c, Layout& L) {
 
 // ---- kernels ---------------------------------------------------------------------------------
 
-// adv[e, t], ret[e, t] for E independent rollouts of T steps, one thread per rollout, backwards in fp64:
+// adv[e, t], ret[e, t] for E independent rollouts of T steps, backwards in fp64:
 // delta = r + gamma V' (1 - done) - V;  A = delta + gamma lambda (1 - done) A'
-__global__ void gae_kernel(const float* __restrict__ rewards, const float* __restrict__ values,
-                           const float* __restrict__ dones, const float* __restrict__ last_value, int E, int T,
-                           double gamma, double lam, float* __restrict__ adv, float* __restrict__ ret) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= E) return;
-    double nxt_adv = 0.0, nxt_val = (double)last_value[e];
-    for (int t = T - 1; t >= 0; --t) {
-        const size_t i = (size_t)e * T + t;
-        const double live = 1.0 - (double)dones[i];
-        const double v = (double)values[i];
-        const double delta = (double)rewards[i] + gamma * nxt_val * live - v;
-        nxt_adv = delta + gamma * lam * live * nxt_adv;
-        adv[i] = (float)nxt_adv;
-        ret[i] = (float)(nxt_adv + v);
-        nxt_val = v;
+// The recurrence A_t = delta_t + c_t A_{t+1} is a composition of affine maps.  A workgroup takes one rollout: each
+// thread composes the maps of a contiguous stretch of steps, a suffix scan over the threads (in a fixed order) gives
+// every stretch the value that enters it from the right, and a second walk writes the results.  One thread per rollout
+// walked 2048 dependent steps in 303 us; this takes 5 us.
+constexpr int GAE_THREADS = 256;
+__global__ __launch_bounds__(GAE_THREADS) void gae_kernel(const float* __restrict__ rewards, const float* __restrict__ values,
+                                                          const float* __restrict__ dones, const float* __restrict__ last_value,
+                                                          int T, double gamma, double lam, float* __restrict__ adv,
+                                                          float* __restrict__ ret) {
+    __shared__ double sm[2][GAE_THREADS], sa[2][GAE_THREADS];       // composed maps x -> sm x + sa, ping-pong
+    const int tid = threadIdx.x;
+    const size_t row = (size_t)blockIdx.x * T;
+    const int per = (T + GAE_THREADS - 1) / GAE_THREADS;
+    const int t0 = min(T, tid * per), t1 = min(T, t0 + per);         // steps t0 .. t1 - 1
+    const double v_after = t1 < T ? (double)values[row + t1] : (double)last_value[blockIdx.x];
+    double m = 1.0, a = 0.0, nxt = v_after;
+#pragma unroll 8
+    for (int t = t1 - 1; t >= t0; --t) {
+        const double live = 1.0 - (double)dones[row + t], v = (double)values[row + t];
+        const double delta = (double)rewards[row + t] + gamma * nxt * live - v, c = gamma * lam * live;
+        a = delta + c * a;
+        m = c * m;
+        nxt = v;
+    }
+    sm[0][tid] = m;
+    sa[0][tid] = a;
+    __syncthreads();
+    // suffix composition: afterwards sa[tid] is the value at t0 of thread tid (nothing enters after the last step)
+    int cur = 0;
+    for (int off = 1; off < GAE_THREADS; off <<= 1) {
+        double mm = sm[cur][tid], aa = sa[cur][tid];
+        if (tid + off < GAE_THREADS) {
+            aa = aa + mm * sa[cur][tid + off];
+            mm = mm * sm[cur][tid + off];
+        }
+        sm[cur ^ 1][tid] = mm;
+        sa[cur ^ 1][tid] = aa;
+        cur ^= 1;
+        __syncthreads();
+    }
+    double A = tid + 1 < GAE_THREADS ? sa[cur][tid + 1] : 0.0;
+    nxt = v_after;
+#pragma unroll 8
+    for (int t = t1 - 1; t >= t0; --t) {
+        const double live = 1.0 - (double)dones[row + t], v = (double)values[row + t];
+        const double delta = (double)rewards[row + t] + gamma * nxt * live - v;
+        A = delta + gamma * lam * live * A;
+        adv[row + t] = (float)A;
+        ret[row + t] = (float)(A + v);
+        nxt = v;
     }
 }
 
@@ -95,6 +129,301 @@ __global__ void gae_kernel(const float* __restrict__ rewards, const float* __res
 // entry can never address memory outside the rollout or the logits (its result is then meaningless, not a fault).
 __device__ inline int clamp_index(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2d_u __attribute__((ext_vector_type(2), aligned(8)));      // rows of the flat buffers start anywhere
+typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));
+
+// ---- first layer of both heads: z[b, o] = sum_i W[o, i] h[rows[b], i], columns of the policy head first -----------
+// v_mfma_f64_16x16x4: a lane gives row / column (lane & 15) and one of four k = lane >> 4; its four results are rows
+// 4 v + (lane >> 4), column lane & 15.  The order of k inside a chunk of 16 is free, so a lane reads four consecutive
+// floats.  A wavefront takes 16 output units x 64 samples (the weights, the larger operand, are read once) over a
+// range of k, the four wavefronts of a workgroup neighbouring ranges, summed in order through LDS; up to L1_SPLITS
+// workgroups share a tile of outputs so that the launch fills the chip (their sums meet in the next kernel).
+// 64 x 2560 -> 2 x 256: 32 us with vector FMAs and four units per workgroup, 9.5 us here (bound by the latency of
+// gathering the rows and of the 80 dependent MFMAs of a wavefront; 14.3 us with one chunk requested ahead).
+// One more workgroup computes the mean and deviation of the mini-batch's advantages.
+constexpr int L1_SPLITS = 8;
+struct FirstArgs {
+    const float* h;
+    const int32_t* rows;
+    const float* W[2];
+    int out_dim[2], tiles[2];        // output units and their tiles of 16, per head
+    int B, T, d, splits, btiles;
+    double* z;                       // [splits][B][out_dim[0] + out_dim[1]]
+    const float* adv;
+    double adv_eps;
+    int normalize_adv;
+    double* scal;                    // [0] mean, [1] 1 / (deviation + eps)
+};
+
+// four inputs k .. k + 3 of a row of n values, zeros past the end
+__device__ inline v4f_u four_inputs(const float* row, int k, int n) {
+    if (k + 4 <= n) return *reinterpret_cast<const v4f_u*>(row + k);
+    v4f_u r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = k + e < n ? row[k + e] : 0.f;
+    return r;
+}
+
+__device__ void minibatch_scale(const float* adv, const int32_t* rows, int B, int T, double eps, int normalize, double* scal) {
+    __shared__ double red[256];
+    if (!normalize) {
+        if (threadIdx.x == 0) { scal[0] = 0.0; scal[1] = 1.0; }
+        return;
+    }
+    auto total = [&](double part) {                      // fixed tree
+        red[threadIdx.x] = part;
+        __syncthreads();
+        for (int st = 128; st >= 1; st >>= 1) {
+            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+            __syncthreads();
+        }
+        const double r = red[0];
+        __syncthreads();
+        return r;
+    };
+    double part = 0.0;
+    for (int b = threadIdx.x; b < B; b += 256) part += (double)adv[clamp_index(rows[b], T)];
+    const double mean = total(part) / (double)B;
+    part = 0.0;
+    for (int b = threadIdx.x; b < B; b += 256) {
+        const double d = (double)adv[clamp_index(rows[b], T)] - mean;
+        part += d * d;
+    }
+    const double ss = total(part);
+    if (threadIdx.x == 0) {
+        const double sd = B > 1 ? sqrt(ss / (double)(B - 1)) : 0.0;
+        scal[0] = mean;
+        scal[1] = 1.0 / (sd + eps);
+    }
+}
+
+__global__ __launch_bounds__(256) void ppo_first_layer_kernel(FirstArgs a) {
+    __shared__ double part[4][16][64];
+    const int tiles = a.tiles[0] + a.tiles[1];
+    if ((int)blockIdx.x == tiles * a.splits * a.btiles) {
+        minibatch_scale(a.adv, a.rows, a.B, a.T, a.adv_eps, a.normalize_adv, a.scal);
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int split = blockIdx.x % a.splits, tile = (blockIdx.x / a.splits) % tiles, bt = blockIdx.x / (a.splits * tiles);
+    const int hd = tile >= a.tiles[0] ? 1 : 0;
+    const int o0 = (tile - (hd ? a.tiles[0] : 0)) * 16;
+    const int kk = lane >> 4;
+    const float* wrow = a.W[hd] + (size_t)min(o0 + (lane & 15), a.out_dim[hd] - 1) * a.d;
+    const float* hrow[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) hrow[q] = a.h + (size_t)clamp_index(a.rows[min(bt * 64 + q * 16 + (lane & 15), a.B - 1)], a.T) * a.d;
+    const int chunks = (a.d + 15) / 16, units = a.splits * 4;
+    const int per = (chunks + units - 1) / units;
+    const int c0 = (split * 4 + wave) * per, c1 = min(chunks, c0 + per);
+    v4d acc[4] = {};
+    constexpr int NC = 5;                            // chunks requested together (2560 inputs over 32 wavefronts: all of them)
+    for (int cb = c0; cb < c1; cb += NC) {
+        v4f_u w[NC], x[NC][4];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int k = min(cb + c, c1 - 1) * 16 + 4 * kk;
+            w[c] = four_inputs(wrow, k, a.d);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[c][q] = four_inputs(hrow[q], k, a.d);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (cb + c >= c1) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[c][q][e], (double)w[c][e], acc[q], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[wave][q * 4 + v][lane] = acc[q][v];
+    __syncthreads();
+    const int ncol = a.out_dim[0] + a.out_dim[1];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int qv = u * 4 + wave;                                 // (sample tile, register)
+        const int b = bt * 64 + (qv >> 2) * 16 + 4 * (qv & 3) + kk, o = o0 + (lane & 15);
+        if (b < a.B && o < a.out_dim[hd])
+            a.z[((size_t)split * a.B + b) * ncol + (hd ? a.out_dim[0] : 0) + o] =
+                ((part[0][qv][lane] + part[1][qv][lane]) + part[2][qv][lane]) + part[3][qv][lane];
+    }
+}
+
+// ---- from the first layer's sums to every delta, one workgroup per sample ---------------------------------------
+// The layers above the first are small (256 -> 18, 256 -> 1): one workgroup runs the rest of both heads forward, the
+// clipped surrogate (Eq. 1), the entropy bonus and the value error with their gradients, and both heads backward on
+// activations and deltas in its LDS.  One launch (10 us, a chain of L2 and fp64 exp / log / tanh latencies) for what were
+// three (second layer 6 us, loss 14 us, deltas 5 us).  Used up to TAIL_MAX_UNITS (the LDS) and TAIL_MAX_WEIGHTS (1 MB of
+// weights per workgroup; beyond, sharing them over four samples as the level kernels below do reads less).
+constexpr int TAIL_MAX_UNITS = 2048;          // layer outputs of both heads together: activations and deltas in 32 KB of LDS
+constexpr size_t TAIL_MAX_WEIGHTS = 1 << 18;  // weights above the first layers: every sample's workgroup reads them all
+struct TailArgs {
+    const double* z;                 // first-layer sums [splits][B][..]
+    int splits, B, A, T, act;
+    int n[2];
+    int dims[2][PPO_MAX_LAYERS + 1];
+    const float* W[2][PPO_MAX_LAYERS];
+    const float* bias[2][PPO_MAX_LAYERS];
+    double* acts[2][PPO_MAX_LAYERS];     // [B, dims[l + 1]], hidden layers
+    double* delta[2][PPO_MAX_LAYERS];    // [B, dims[l + 1]]
+    const int32_t* rows;
+    const int32_t* actions;
+    const float* logp_old;
+    const float* adv;
+    const float* returns;
+    const double* scal;
+    double clip_eps, ent_coef;
+    double* row_terms;               // [4, B]
+};
+
+__device__ inline double wave_sum(double v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+__device__ inline double activate(double z, int act) { return act == BRL_ACT_RELU ? fmax(z, 0.0) : tanh(z); }
+__device__ inline double act_slope(double a, int act) { return act == BRL_ACT_RELU ? (a > 0.0 ? 1.0 : 0.0) : 1.0 - a * a; }
+
+__global__ __launch_bounds__(256) void ppo_tail_kernel(TailArgs a) {
+    __shared__ double out[TAIL_MAX_UNITS], del[TAIL_MAX_UNITS];      // layer outputs / deltas, policy head first
+    const int tid = threadIdx.x, b = blockIdx.x;
+    const int ncol = a.dims[0][1] + a.dims[1][1];
+    const int r = clamp_index(a.rows[b], a.T);
+    // the loss terms' inputs are requested ahead of the layers
+    const double adv_r = ((double)a.adv[r] - a.scal[0]) * a.scal[1];
+    const double logp_old = (double)a.logp_old[r], ret = (double)a.returns[r];
+    const int action = clamp_index(a.actions[r], a.A);
+    int off1 = 0;                                                    // where the value head's units start
+    for (int l = 0; l < a.n[0]; ++l) off1 += a.dims[0][l + 1];
+
+    for (int c = tid; c < ncol; c += 256) {
+        const int hd = c >= a.dims[0][1] ? 1 : 0, o = c - (hd ? a.dims[0][1] : 0);
+        double p[L1_SPLITS];
+#pragma unroll
+        for (int sp = 0; sp < L1_SPLITS; ++sp) p[sp] = a.z[((size_t)min(sp, a.splits - 1) * a.B + b) * ncol + c];
+        double v = 0.0;
+#pragma unroll
+        for (int sp = 0; sp < L1_SPLITS; ++sp) v += sp < a.splits ? p[sp] : 0.0;
+        v += (double)a.bias[hd][0][o];
+        if (a.n[hd] > 1) {
+            v = activate(v, a.act);
+            a.acts[hd][0][(size_t)b * a.dims[hd][1] + o] = v;
+        }
+        out[(hd ? off1 : 0) + o] = v;
+    }
+    __syncthreads();
+    // the layers above, level by level for both heads: eight lanes per output unit
+    constexpr int LG = 8;
+    const int depth = max(a.n[0], a.n[1]);
+    int in0[2] = {0, off1};
+    for (int l = 1; l < depth; ++l) {
+        const int od0 = l < a.n[0] ? a.dims[0][l + 1] : 0, od1 = l < a.n[1] ? a.dims[1][l + 1] : 0, total = od0 + od1;
+        for (int u = tid / LG; u < (total + 31) / 32 * 32; u += 256 / LG) {
+            const int uc = min(u, total - 1), hd = uc >= od0 ? 1 : 0, o = uc - (hd ? od0 : 0);
+            const int id = a.dims[hd][l], od = a.dims[hd][l + 1];
+            const float* w = a.W[hd][l] + (size_t)o * id;
+            const double* x = out + in0[hd];
+            double v = 0.0;
+            int i = tid % LG;
+            for (; i + 31 * LG < id; i += 32 * LG) {         // 32 weights of a lane in flight
+                float wv[32];
+#pragma unroll
+                for (int t = 0; t < 32; ++t) wv[t] = w[i + t * LG];
+#pragma unroll
+                for (int t = 0; t < 32; ++t) v += (double)wv[t] * x[i + t * LG];
+            }
+#pragma unroll 4
+            for (; i < id; i += LG) v += (double)w[i] * x[i];
+#pragma unroll
+            for (int off = 1; off < LG; off <<= 1) v += __shfl_xor(v, off, 64);
+            if (tid % LG == 0 && u < total) {
+                v += (double)a.bias[hd][l][o];
+                if (l + 1 < a.n[hd]) {
+                    v = activate(v, a.act);
+                    a.acts[hd][l][(size_t)b * od + o] = v;
+                }
+                out[in0[hd] + id + o] = v;
+            }
+        }
+        in0[0] += od0 ? a.dims[0][l] : 0;
+        in0[1] += od1 ? a.dims[1][l] : 0;
+        __syncthreads();
+    }
+    const int lp0 = off1 - a.A;                                      // logits
+    int lv = off1;                                                   // value
+    for (int l = 0; l + 1 < a.n[1]; ++l) lv += a.dims[1][l + 1];
+    if (tid < 64) {                                                  // one wavefront, a lane per action (and every 64th on)
+        const double* z = out + lp0;
+        double m = z[0];
+        for (int k = tid; k < a.A; k += 64) m = fmax(m, z[k]);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+        double se = 0.0;
+        for (int k = tid; k < a.A; k += 64) se += exp(z[k] - m);
+        const double lse = m + log(wave_sum(se));
+        const double ratio = exp((z[action] - lse) - logp_old);
+        const double surr1 = ratio * adv_r;
+        const double surr2 = fmin(fmax(ratio, 1.0 - a.clip_eps), 1.0 + a.clip_eps) * adv_r;
+        const double active = surr1 <= surr2 ? 1.0 : 0.0;
+        double ent = 0.0;
+        for (int k = tid; k < a.A; k += 64) {
+            const double lp = z[k] - lse;
+            ent -= exp(lp) * lp;
+        }
+        ent = wave_sum(ent);
+        const double coef = -(active * adv_r * ratio);
+        for (int k = tid; k < a.A; k += 64) {
+            const double lp = z[k] - lse, p = exp(lp);
+            const double d = (coef * ((k == action ? 1.0 : 0.0) - p) + a.ent_coef * p * (lp + ent)) / (double)a.B;
+            del[lp0 + k] = d;
+            a.delta[0][a.n[0] - 1][(size_t)b * a.A + k] = d;
+        }
+        if (tid == 0) {
+            const double diff = out[lv] - ret, dv = diff / (double)a.B;
+            del[lv] = dv;
+            a.delta[1][a.n[1] - 1][b] = dv;
+            a.row_terms[0 * a.B + b] = fmin(surr1, surr2);
+            a.row_terms[1 * a.B + b] = ent;
+            a.row_terms[2 * a.B + b] = diff * diff;
+            a.row_terms[3 * a.B + b] = 1.0 - active;
+        }
+    }
+    __syncthreads();
+    // backward, level by level for both heads: a thread per unit of the layer below
+    int at0 = lp0, at1 = lv;                                         // deltas of the level above
+    for (int t = 0; t < depth - 1; ++t) {
+        const int l0 = a.n[0] - 1 - t, l1 = a.n[1] - 1 - t;
+        const int id0 = l0 >= 1 ? a.dims[0][l0] : 0, id1 = l1 >= 1 ? a.dims[1][l1] : 0;
+        for (int u = tid; u < id0 + id1; u += 256) {
+            const int hd = u >= id0 ? 1 : 0, l = hd ? l1 : l0, i = u - (hd ? id0 : 0), id = hd ? id1 : id0;
+            const int od = a.dims[hd][l + 1], up = hd ? at1 : at0, in = up - id;
+            const float* w = a.W[hd][l] + i;
+            double v = 0.0;
+            int o = 0;
+            for (; o + 16 <= od; o += 16) {
+                float wv[16];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) wv[q] = w[(size_t)(o + q) * id];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) v += del[up + o + q] * (double)wv[q];
+            }
+            for (; o < od; ++o) v += del[up + o] * (double)w[(size_t)o * id];
+            v *= act_slope(out[in + i], a.act);
+            del[in + i] = v;
+            a.delta[hd][l - 1][(size_t)b * id + i] = v;
+        }
+        at0 -= id0;
+        at1 -= id1;
+        __syncthreads();
+    }
+}
+
+// ---- heads too wide for that: one launch per layer level forward and backward, one for the loss ------------------
 constexpr int FB = 4;        // samples per workgroup
 constexpr int FO = 4;        // output units per workgroup
 // One launch runs the same layer level of both heads (they read the same rows of h and depend on nothing of
@@ -202,7 +531,6 @@ struct LossArgs {
     int normalize_adv;
     double* dlogits;          // [B, A]
     double* dv;               // [B]
-    float* stats;             // [5]: policy loss, value loss, entropy, clip fraction, (gradient norm: written later) or null
     double* row_terms;        // [4, B] scratch
 };
 
@@ -293,93 +621,103 @@ __global__ __launch_bounds__(256) void ppo_loss_kernel(LossArgs a) {
             }
         }
     }
-    __syncthreads();
-    if (threadIdx.x == 0 && a.stats) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        for (int b = 0; b < a.B; ++b) {
-            s0 += a.row_terms[0 * a.B + b];
-            s1 += a.row_terms[1 * a.B + b];
-            s2 += a.row_terms[2 * a.B + b];
-            s3 += a.row_terms[3 * a.B + b];
-        }
-        const double n = (double)a.B;
-        a.stats[0] = (float)(-s0 / n - a.ent_coef * s1 / n);
-        a.stats[1] = (float)(0.5 * s2 / n);
-        a.stats[2] = (float)(s1 / n);
-        a.stats[3] = (float)(s3 / n);
-    }
 }
 
-// dW[o, i] = sum_b delta[b, o] in(b, i), db[o] = sum_b delta[b, o].  A wavefront takes GO output units and 64
-// consecutive inputs and sums over the samples in order; the four wavefronts of a workgroup take neighbouring
-// input chunks and share nothing.  The squares of a wavefront's gradients are summed (fixed tree) to one slot
-// of partial[] for the global norm.
-constexpr int GO = 4;
+// ---- weight gradients of every layer of both heads: dW[o, i] = sum_b delta[b, o] in(b, i), db[o] = sum_b delta[b, o] --
+// A wavefront takes 16 output units x 64 inputs on the fp64 matrix cores: a lane reads four consecutive inputs of a
+// sample, one for each of four result tiles, so that its results are four consecutive inputs again (32-byte stores).
+// The squares of its gradients are summed (fixed tree) to one slot of partial[] for the global norm.
+// 2 x 256 x 2560 from 64 samples: 29 us + 17 us for the second layers with vector FMAs and a launch per level, 18.4 us
+// here for all of them (without the 10.5 MB of results 16.6 us: gathered reads and their latency bound it).
 struct GradProblem {
-    const double* delta;
-    const double* in64;      // null: first layer, inputs are rows of h
+    const double* delta;     // [B, out_dim]
+    const double* in64;      // [B, in_dim]; null: first layer, inputs are rows of h
     double* gW;
     double* gb;
-    double* partial;
-    int in_dim, out_dim;
-    unsigned blocks;
+    int in_dim, out_dim, ichunks;
+    int first;               // first wavefront of the problem
 };
 struct GradArgs {
-    GradProblem p[2];
-    int n;
+    GradProblem p[2 * PPO_MAX_LAYERS];
+    int n, waves;
     const float* h;
     const int32_t* rows;
     int B, T;
+    double* partial;         // [waves]
 };
 __global__ __launch_bounds__(256) void ppo_weight_grad_kernel(GradArgs a) {
-    const int which = (a.n > 1 && blockIdx.x >= a.p[0].blocks) ? 1 : 0;
-    const unsigned block = blockIdx.x - (which ? a.p[0].blocks : 0u);
-    const double* __restrict__ delta = which ? a.p[1].delta : a.p[0].delta;
-    const double* __restrict__ in64 = which ? a.p[1].in64 : a.p[0].in64;
-    double* __restrict__ gW = which ? a.p[1].gW : a.p[0].gW;
-    double* __restrict__ gb = which ? a.p[1].gb : a.p[0].gb;
-    double* __restrict__ partial = which ? a.p[1].partial : a.p[0].partial;
-    const int in_dim = which ? a.p[1].in_dim : a.p[0].in_dim;
-    const int out_dim = which ? a.p[1].out_dim : a.p[0].out_dim;
-    const float* __restrict__ h = a.h;
-    const int32_t* __restrict__ rows = a.rows;
-    const int B = a.B;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int ichunks = (in_dim + 63) / 64;
-    const int cpw = (ichunks + 3) / 4;                 // groups of four input chunks, one chunk per wavefront
-    const int og = (int)(block / cpw), chunk = (int)(block % cpw) * 4 + wave;
-    if (chunk >= ichunks) return;
-    const int o0 = og * GO;
-    const int i = chunk * 64 + lane;
-    const int ii = min(i, in_dim - 1);
-    double acc[GO], accb[GO];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (w >= a.waves) return;
+    int pi = 0;
+    while (pi + 1 < a.n && w >= a.p[pi + 1].first) ++pi;
+    const GradProblem& P = a.p[pi];
+    const int in_dim = P.in_dim, out_dim = P.out_dim;
+    const int ot = (w - P.first) / P.ichunks, ic = (w - P.first) % P.ichunks;
+    const int o = ot * 16 + (lane & 15), i = ic * 64 + 4 * (lane & 15), kk = lane >> 4;
+    const bool o_ok = o < out_dim;
+    const int oc = min(o, out_dim - 1);
+    v4d acc[4] = {};
+    double db = 0.0;
+    constexpr int NS = 8;                            // groups of four samples requested together
+    for (int bb = 0; bb < a.B; bb += 64) {
+        const int my_row = clamp_index(a.rows[min(bb + lane, a.B - 1)], a.T);
+        const int b_end = min(a.B, bb + 64);
+        for (int b0 = bb; b0 < b_end; b0 += 4 * NS) {
+            double d[NS];
+            v4d x[NS];
 #pragma unroll
-    for (int q = 0; q < GO; ++q) { acc[q] = 0.0; accb[q] = 0.0; }
-#pragma unroll 8
-    for (int b = 0; b < B; ++b) {
-        const double x = in64 ? in64[(size_t)b * in_dim + ii] : (double)h[(size_t)clamp_index(rows[b], a.T) * in_dim + ii];
+            for (int u = 0; u < NS; ++u) {           // (sample past the end: any row, its delta counts as zero)
+                const int b = b0 + 4 * u + kk, bc = min(b, a.B - 1);
+                const double dv = P.delta[(size_t)bc * out_dim + oc];
+                d[u] = (o_ok && b < b_end) ? dv : 0.0;
+                if (!P.in64) {
+                    const v4f_u v = four_inputs(a.h + (size_t)__shfl(my_row, (4 * u + kk + b0 - bb) & 63, 64) * in_dim, i, in_dim);
+                    x[u] = v4d{(double)v.x, (double)v.y, (double)v.z, (double)v.w};
+                } else {
+                    const double* row = P.in64 + (size_t)bc * in_dim;
 #pragma unroll
-        for (int q = 0; q < GO; ++q) {
-            const double d = delta[(size_t)b * out_dim + min(o0 + q, out_dim - 1)];
-            acc[q] += d * x;
-            accb[q] += d;
+                    for (int e = 0; e < 4; ++e) x[u][e] = i + e < in_dim ? row[i + e] : 0.0;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                db += d[u];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[u], x[u][e], acc[e], 0, 0, 0);
+            }
         }
     }
     double sq = 0.0;
 #pragma unroll
-    for (int q = 0; q < GO; ++q) {
-        if (o0 + q < out_dim && i < in_dim) {
-            gW[(size_t)(o0 + q) * in_dim + i] = acc[q];
-            sq += acc[q] * acc[q];
-            if (i == 0) {
-                gb[o0 + q] = accb[q];
-                sq += accb[q] * accb[q];
-            }
+    for (int v = 0; v < 4; ++v) {
+        const int oo = ot * 16 + 4 * v + kk;
+        if (oo >= out_dim) continue;
+        double* g = P.gW + (size_t)oo * in_dim + i;
+        if (i + 4 <= in_dim) {
+            *reinterpret_cast<v2d_u*>(g) = v2d_u{acc[0][v], acc[1][v]};
+            *reinterpret_cast<v2d_u*>(g + 2) = v2d_u{acc[2][v], acc[3][v]};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sq += acc[e][v] * acc[e][v];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (i + e < in_dim) {
+                    g[e] = acc[e][v];
+                    sq += acc[e][v] * acc[e][v];
+                }
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sq += __shfl_xor(sq, off, 64);
-    if (lane == 0) partial[og * ichunks + chunk] = sq;
+    if (ic == 0) {
+        db += __shfl_xor(db, 16, 64);
+        db += __shfl_xor(db, 32, 64);
+        if (lane < 16 && o_ok) {
+            P.gb[o] = db;
+            sq += db * db;
+        }
+    }
+    sq = wave_sum(sq);
+    if (lane == 0) a.partial[w] = sq;
 }
 
 // delta_prev[b, i] = (sum_o delta[b, o] W[o, i]) * act'(a[b, i]), a = the activated output of the layer below
@@ -414,51 +752,105 @@ __global__ __launch_bounds__(256) void ppo_delta_kernel(DeltaArgs a) {
     delta_prev[idx] = acc * (act == BRL_ACT_RELU ? (av > 0.0 ? 1.0 : 0.0) : 1.0 - av * av);
 }
 
-// scal[0] = global L2 norm of the gradients, scal[1] = min(1, max_norm / (norm + 1e-6)); the partial sums are
-// added in a fixed order (thread t takes partials t, t + 256, ..., then a fixed tree): same result every run.
-__global__ __launch_bounds__(256) void ppo_norm_kernel(const double* __restrict__ partial, int n, double max_norm,
-                                                        double* __restrict__ scal, float* __restrict__ stats) {
+// ---- global gradient norm and Adam ------------------------------------------------------------------------------
+// Every workgroup adds the partial sums itself, in one fixed order (thread t takes partials t, t + 256, ..., then a
+// fixed tree): the same norm everywhere, and no launch of its own.  Then Adam with bias correction on the clipped
+// gradient, p -= lr (m / c1) / (sqrt(v / c2) + eps), scale min(1, max_norm / (norm + 1e-6)).  1.3 M parameters: 12.4 us
+// for 42 MB, against 7 us for the norm alone in its own launch and 8.6 us for Adam.
+struct AdamArgs {
+    float* p;
+    float* m;
+    float* v;
+    const double* g;
+    size_t n, n_policy;
+    const double* partial;
+    int n_partials, B;
+    double max_norm, lr_policy, lr_value, b1, b2, c1, c2, eps, ent_coef;
+    const double* row_terms;
+    float* stats;            // [5]: policy loss, value loss, entropy, clip fraction, gradient norm; or null
+};
+constexpr int ADAM_PER_THREAD = 4;
+__global__ __launch_bounds__(256) void ppo_adam_kernel(AdamArgs a) {
     __shared__ double red[256];
+    const size_t i0 = ((size_t)blockIdx.x * 256 + threadIdx.x) * ADAM_PER_THREAD;
+    // the elements are requested ahead of the norm (the buffers start 16-byte aligned)
+    const bool full = i0 + ADAM_PER_THREAD <= a.n;
+    float p[4], m[4], v[4];
+    double g[4];
+    if (full) {
+        const float4 pv = *reinterpret_cast<const float4*>(a.p + i0), mv = *reinterpret_cast<const float4*>(a.m + i0);
+        const float4 vv = *reinterpret_cast<const float4*>(a.v + i0);
+        const double2 g0 = *reinterpret_cast<const double2*>(a.g + i0), g1 = *reinterpret_cast<const double2*>(a.g + i0 + 2);
+        p[0] = pv.x; p[1] = pv.y; p[2] = pv.z; p[3] = pv.w;
+        m[0] = mv.x; m[1] = mv.y; m[2] = mv.z; m[3] = mv.w;
+        v[0] = vv.x; v[1] = vv.y; v[2] = vv.z; v[3] = vv.w;
+        g[0] = g0.x; g[1] = g0.y; g[2] = g1.x; g[3] = g1.y;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool in = i0 + e < a.n;
+            p[e] = in ? a.p[i0 + e] : 0.f; m[e] = in ? a.m[i0 + e] : 0.f; v[e] = in ? a.v[i0 + e] : 0.f;
+            g[e] = in ? a.g[i0 + e] : 0.0;
+        }
+    }
     double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) s += partial[i];
+    for (int i = threadIdx.x; i < a.n_partials; i += 256) s += a.partial[i];
     red[threadIdx.x] = s;
     __syncthreads();
-    for (int st = 128; st >= 1; st >>= 1) {
+    for (int st = 128; st >= 64; st >>= 1) {
         if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const double norm = sqrt(red[0]);
-        scal[0] = norm;
-        scal[1] = fmin(1.0, max_norm / (norm + 1e-6));
-        if (stats) stats[4] = (float)norm;
+    const double norm = sqrt(wave_sum(red[threadIdx.x & 63]));
+    const double scale = fmin(1.0, a.max_norm / (norm + 1e-6));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double gi = g[e] * scale;
+        const double mi = a.b1 * (double)m[e] + (1.0 - a.b1) * gi;
+        const double vi = a.b2 * (double)v[e] + (1.0 - a.b2) * gi * gi;
+        m[e] = (float)mi;
+        v[e] = (float)vi;
+        const double lr = i0 + e < a.n_policy ? a.lr_policy : a.lr_value;
+        p[e] = (float)((double)p[e] - lr * (mi / a.c1) / (sqrt(vi / a.c2) + a.eps));
     }
-}
-
-// Adam with bias correction on the clipped gradient: p -= lr (m / c1) / (sqrt(v / c2) + eps)
-__global__ __launch_bounds__(256) void ppo_adam_kernel(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                                                        const double* __restrict__ g, const double* __restrict__ scal,
-                                                        size_t n, size_t n_policy, double lr_policy, double lr_value,
-                                                        double b1, double b2, double c1, double c2, double eps) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const double gi = g[i] * scal[1];
-    const double mi = b1 * (double)m[i] + (1.0 - b1) * gi;
-    const double vi = b2 * (double)v[i] + (1.0 - b2) * gi * gi;
-    m[i] = (float)mi;
-    v[i] = (float)vi;
-    const double lr = i < n_policy ? lr_policy : lr_value;
-    p[i] = (float)((double)p[i] - lr * (mi / c1) / (sqrt(vi / c2) + eps));
+    if (full) {
+        *reinterpret_cast<float4*>(a.p + i0) = make_float4(p[0], p[1], p[2], p[3]);
+        *reinterpret_cast<float4*>(a.m + i0) = make_float4(m[0], m[1], m[2], m[3]);
+        *reinterpret_cast<float4*>(a.v + i0) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (i0 + e < a.n) { a.p[i0 + e] = p[e]; a.m[i0 + e] = m[e]; a.v[i0 + e] = v[e]; }
+    }
+    if (blockIdx.x == 0 && a.stats && threadIdx.x < 64) {
+        double t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            double x = 0.0;
+            for (int b = threadIdx.x; b < a.B; b += 64) x += a.row_terms[(size_t)k * a.B + b];
+            t[k] = wave_sum(x);
+        }
+        if (threadIdx.x == 0) {
+            const double n = (double)a.B;
+            a.stats[0] = (float)(-t[0] / n - a.ent_coef * t[1] / n);
+            a.stats[1] = (float)(0.5 * t[2] / n);
+            a.stats[2] = (float)(t[1] / n);
+            a.stats[3] = (float)(t[3] / n);
+            a.stats[4] = (float)norm;
+        }
+    }
 }
 
 // ---- workspace ---------------------------------------------------------------------------------
 
 struct PpoWs {
     size_t act_off[2][PPO_MAX_LAYERS];   // layer outputs [batch, dims[l+1]] fp64
-    size_t delta_off[2][2];              // ping-pong deltas per head [batch, max_dim] fp64
-    size_t dv_off, grad_off, partial_off, scal_off, rows_off, total;
-    int n_partials;
-    int partial_first[2][PPO_MAX_LAYERS];
+    size_t delta_off[2][PPO_MAX_LAYERS]; // their deltas
+    size_t z_off, grad_off, partial_off, scal_off, rows_off, total;
+    int grad_waves;
+    int grad_first[2][PPO_MAX_LAYERS];   // first wavefront of each layer's weight gradients
+    int splits, btiles;                  // of the first layer's contraction
+    bool tail;                           // both heads above their first layers fit one workgroup per sample
 };
 
 constexpr size_t PPO_ALIGN = 256;
@@ -472,20 +864,33 @@ PpoWs ppo_ws_layout(const Layout& L, int batch) {
         off += round_up_sz(bytes, PPO_ALIGN);
         return at;
     };
-    for (int hd = 0; hd < 2; ++hd)
-        for (int l = 0; l < L.head[hd].n; ++l) W.act_off[hd][l] = take((size_t)batch * L.head[hd].dims[l + 1] * 8);
-    for (int hd = 0; hd < 2; ++hd)
-        for (int k = 0; k < 2; ++k) W.delta_off[hd][k] = take((size_t)batch * L.max_dim * 8);
-    W.dv_off = take((size_t)batch * 8);
-    W.grad_off = take(L.n_params * 8);
-    int np = 0;
+    size_t units = 0, weights = 0;
     for (int hd = 0; hd < 2; ++hd)
         for (int l = 0; l < L.head[hd].n; ++l) {
-            W.partial_first[hd][l] = np;
-            np += ((L.head[hd].dims[l + 1] + GO - 1) / GO) * ((L.head[hd].dims[l] + 63) / 64);
+            W.act_off[hd][l] = take((size_t)batch * L.head[hd].dims[l + 1] * 8);
+            W.delta_off[hd][l] = take((size_t)batch * L.head[hd].dims[l + 1] * 8);
+            units += (size_t)L.head[hd].dims[l + 1];
+            if (l > 0) weights += (size_t)L.head[hd].dims[l + 1] * L.head[hd].dims[l];
         }
-    W.n_partials = np;
-    W.partial_off = take((size_t)np * 8);
+    W.tail = units <= TAIL_MAX_UNITS && weights <= TAIL_MAX_WEIGHTS;
+    const int ncol = L.head[0].dims[1] + L.head[1].dims[1];
+    const int tiles = (L.head[0].dims[1] + 15) / 16 + (L.head[1].dims[1] + 15) / 16;
+    W.btiles = (batch + 63) / 64;
+    // about 256 workgroups of four wavefronts, each wavefront at least one chunk of 16 inputs
+    const long want = 256 / ((long)tiles * W.btiles), most = ((long)L.head[0].dims[0] + 63) / 64;
+    W.splits = (int)(want < 1 ? 1 : want);
+    if (W.splits > L1_SPLITS) W.splits = L1_SPLITS;
+    if (W.splits > most) W.splits = (int)most;
+    W.z_off = W.tail ? take((size_t)W.splits * batch * ncol * 8) : 0;
+    W.grad_off = take(L.n_params * 8);
+    int nw = 0;
+    for (int hd = 0; hd < 2; ++hd)
+        for (int l = 0; l < L.head[hd].n; ++l) {
+            W.grad_first[hd][l] = nw;
+            nw += ((L.head[hd].dims[l + 1] + 15) / 16) * ((L.head[hd].dims[l] + 63) / 64);
+        }
+    W.grad_waves = nw;
+    W.partial_off = take((size_t)nw * 8);
     W.scal_off = take(2 * 8);
     W.rows_off = take((size_t)4 * batch * 8);
     W.total = off;
@@ -532,8 +937,8 @@ int ppo_gae(const float* rewards, const float* values, const float* dones, const
     BRL_REQUIRE(gamma >= 0.f && gamma <= 1.f && lam >= 0.f && lam <= 1.f, "ppo_gae: gamma and lambda must lie in [0, 1]");
     hipStream_t s = static_cast<hipStream_t>(stream);
     LaunchTimer tm(BRL_KC_OTHER, s);
-    hipLaunchKernelGGL(gae_kernel, dim3((n_envs + 63) / 64), dim3(64), 0, s, rewards, values, dones, last_value, n_envs, T,
-                       (double)gamma, (double)lam, adv, returns);
+    hipLaunchKernelGGL(gae_kernel, dim3(n_envs), dim3(GAE_THREADS), 0, s, rewards, values, dones, last_value, T, (double)gamma,
+                       (double)lam, adv, returns);
     BRL_LAUNCH_CHECK("gae_kernel");
     return BRL_OK;
 }
@@ -560,103 +965,130 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* base = static_cast<char*>(workspace);
-    double* grads = reinterpret_cast<double*>(base + W.grad_off);
-    double* partial = reinterpret_cast<double*>(base + W.partial_off);
-    double* scal = reinterpret_cast<double*>(base + W.scal_off);
-    double* dv = reinterpret_cast<double*>(base + W.dv_off);
-    double* delta[2][2];
-    for (int hd = 0; hd < 2; ++hd)
-        for (int k = 0; k < 2; ++k) delta[hd][k] = reinterpret_cast<double*>(base + W.delta_off[hd][k]);
+    auto at = [&](size_t off) { return reinterpret_cast<double*>(base + off); };
+    double* grads = at(W.grad_off);
+    double* partial = at(W.partial_off);
+    double* row_terms = at(W.rows_off);
     const int A = L.head[0].dims[L.head[0].n];
     const int steps_per_epoch = T / batch;
     LaunchTimer tm(BRL_KC_OTHER, s);
+
+    // what does not change from step to step
+    GradArgs ga;
+    memset(&ga, 0, sizeof(ga));
+    ga.waves = W.grad_waves; ga.h = h; ga.B = batch; ga.T = T; ga.partial = partial;
+    for (int hd = 0; hd < 2; ++hd) {
+        const HeadShape& H = L.head[hd];
+        for (int l = 0; l < H.n; ++l) {
+            GradProblem& G = ga.p[ga.n++];
+            G.delta = at(W.delta_off[hd][l]);
+            G.in64 = l == 0 ? nullptr : at(W.act_off[hd][l - 1]);
+            G.gW = grads + H.w_off[l]; G.gb = grads + H.b_off[l];
+            G.in_dim = H.dims[l]; G.out_dim = H.dims[l + 1]; G.ichunks = (H.dims[l] + 63) / 64;
+            G.first = W.grad_first[hd][l];
+        }
+    }
+    AdamArgs aa;
+    memset(&aa, 0, sizeof(aa));
+    aa.p = params; aa.m = adam_m; aa.v = adam_v; aa.g = grads; aa.n = L.n_params; aa.n_policy = L.n_policy;
+    aa.partial = partial; aa.n_partials = W.grad_waves; aa.B = batch;
+    aa.max_norm = (double)cfg->max_grad_norm; aa.lr_policy = (double)cfg->lr_policy; aa.lr_value = (double)cfg->lr_value;
+    aa.b1 = (double)cfg->adam_b1; aa.b2 = (double)cfg->adam_b2; aa.eps = (double)cfg->adam_eps; aa.ent_coef = (double)cfg->ent_coef;
+    aa.row_terms = row_terms;
+    FirstArgs fl;
+    TailArgs ta;
+    memset(&fl, 0, sizeof(fl));
+    memset(&ta, 0, sizeof(ta));
+    if (W.tail) {
+        fl.h = h; fl.B = batch; fl.T = T; fl.d = L.head[0].dims[0]; fl.splits = W.splits; fl.btiles = W.btiles;
+        fl.z = at(W.z_off); fl.adv = adv; fl.adv_eps = (double)cfg->adv_eps; fl.normalize_adv = cfg->normalize_adv;
+        fl.scal = at(W.scal_off);
+        ta.z = fl.z; ta.splits = W.splits; ta.B = batch; ta.A = A; ta.T = T; ta.act = cfg->act;
+        for (int hd = 0; hd < 2; ++hd) {
+            const HeadShape& H = L.head[hd];
+            fl.W[hd] = params + H.w_off[0]; fl.out_dim[hd] = H.dims[1]; fl.tiles[hd] = (H.dims[1] + 15) / 16;
+            ta.n[hd] = H.n;
+            for (int l = 0; l <= H.n; ++l) ta.dims[hd][l] = H.dims[l];
+            for (int l = 0; l < H.n; ++l) {
+                ta.W[hd][l] = params + H.w_off[l]; ta.bias[hd][l] = params + H.b_off[l];
+                ta.acts[hd][l] = at(W.act_off[hd][l]); ta.delta[hd][l] = at(W.delta_off[hd][l]);
+            }
+        }
+        ta.actions = actions; ta.logp_old = logp_old; ta.adv = adv; ta.returns = returns; ta.scal = fl.scal;
+        ta.clip_eps = (double)cfg->clip_eps; ta.ent_coef = (double)cfg->ent_coef; ta.row_terms = row_terms;
+    }
+    const int depth = L.head[0].n > L.head[1].n ? L.head[0].n : L.head[1].n;
     long long step = *adam_step;
     for (int e = 0; e < epochs; ++e) {
         for (int mb = 0; mb < steps_per_epoch; ++mb) {
             const int32_t* rows = perm + (size_t)e * T + (size_t)mb * batch;
-            float* st = stats ? stats + ((size_t)e * steps_per_epoch + mb) * 5 : nullptr;
-            // forward: level l of both heads in one launch
-            const int depth = L.head[0].n > L.head[1].n ? L.head[0].n : L.head[1].n;
-            for (int l = 0; l < depth; ++l) {
-                FwdArgs fa;
-                memset(&fa, 0, sizeof(fa));
-                fa.h = h; fa.rows = rows; fa.B = batch; fa.act = cfg->act; fa.T = T;
-                unsigned blocks = 0;
-                for (int hd = 0; hd < 2; ++hd) {
-                    const HeadShape& H = L.head[hd];
-                    if (l >= H.n) continue;
-                    FwdProblem& P = fa.p[fa.n++];
-                    P.in64 = l == 0 ? nullptr : reinterpret_cast<const double*>(base + W.act_off[hd][l - 1]);
-                    P.W = params + H.w_off[l];
-                    P.bias = params + H.b_off[l];
-                    P.out = reinterpret_cast<double*>(base + W.act_off[hd][l]);
-                    P.in_dim = H.dims[l]; P.out_dim = H.dims[l + 1]; P.last = l == H.n - 1 ? 1 : 0;
-                    P.blocks = (unsigned)(((batch + FB - 1) / FB) * ((H.dims[l + 1] + FO - 1) / FO));
-                    blocks += P.blocks;
+            if (W.tail) {
+                fl.rows = rows;
+                ta.rows = rows;
+                const unsigned blocks = (unsigned)((fl.tiles[0] + fl.tiles[1]) * W.splits * W.btiles) + 1;   // + the advantages' scale
+                hipLaunchKernelGGL(ppo_first_layer_kernel, dim3(blocks), dim3(256), 0, s, fl);
+                hipLaunchKernelGGL(ppo_tail_kernel, dim3(batch), dim3(256), 0, s, ta);
+            } else {
+                // forward: level l of both heads in one launch
+                for (int l = 0; l < depth; ++l) {
+                    FwdArgs fa;
+                    memset(&fa, 0, sizeof(fa));
+                    fa.h = h; fa.rows = rows; fa.B = batch; fa.act = cfg->act; fa.T = T;
+                    unsigned blocks = 0;
+                    for (int hd = 0; hd < 2; ++hd) {
+                        const HeadShape& H = L.head[hd];
+                        if (l >= H.n) continue;
+                        FwdProblem& P = fa.p[fa.n++];
+                        P.in64 = l == 0 ? nullptr : at(W.act_off[hd][l - 1]);
+                        P.W = params + H.w_off[l];
+                        P.bias = params + H.b_off[l];
+                        P.out = at(W.act_off[hd][l]);
+                        P.in_dim = H.dims[l]; P.out_dim = H.dims[l + 1]; P.last = l == H.n - 1 ? 1 : 0;
+                        P.blocks = (unsigned)(((batch + FB - 1) / FB) * ((H.dims[l + 1] + FO - 1) / FO));
+                        blocks += P.blocks;
+                    }
+                    hipLaunchKernelGGL(ppo_forward_kernel, dim3(blocks), dim3(256), 0, s, fa);
                 }
-                hipLaunchKernelGGL(ppo_forward_kernel, dim3(blocks), dim3(256), 0, s, fa);
-            }
-            // gradients at the outputs
-            LossArgs la;
-            la.logits = reinterpret_cast<const double*>(base + W.act_off[0][L.head[0].n - 1]);
-            la.v = reinterpret_cast<const double*>(base + W.act_off[1][L.head[1].n - 1]);
-            la.rows = rows; la.actions = actions; la.logp_old = logp_old; la.adv = adv; la.returns = returns;
-            la.B = batch; la.A = A; la.T = T;
-            la.clip_eps = (double)cfg->clip_eps; la.ent_coef = (double)cfg->ent_coef; la.adv_eps = (double)cfg->adv_eps;
-            la.normalize_adv = cfg->normalize_adv;
-            la.dlogits = delta[0][0];
-            la.dv = dv;
-            la.stats = st;
-            la.row_terms = reinterpret_cast<double*>(base + W.rows_off);
-            hipLaunchKernelGGL(ppo_loss_kernel, dim3(1), dim3(256), 0, s, la);
-            // backward: the same distance from the output of both heads in one launch; each head ping-pongs
-            // between its own two delta buffers (the policy head's first one holds dlogits)
-            const double* dcur[2] = {delta[0][0], dv};
-            int pp[2] = {1, 0};
-            for (int t = 0; t < depth; ++t) {
-                GradArgs ga;
-                DeltaArgs da;
-                memset(&ga, 0, sizeof(ga));
-                memset(&da, 0, sizeof(da));
-                ga.h = h; ga.rows = rows; ga.B = batch; ga.T = T;
-                da.B = batch; da.act = cfg->act;
-                unsigned gblocks = 0, dblocks = 0;
-                const double* dnext[2] = {dcur[0], dcur[1]};
-                for (int hd = 0; hd < 2; ++hd) {
-                    const HeadShape& H = L.head[hd];
-                    const int l = H.n - 1 - t;
-                    if (l < 0) continue;
-                    const double* in64 = l == 0 ? nullptr : reinterpret_cast<const double*>(base + W.act_off[hd][l - 1]);
-                    GradProblem& G = ga.p[ga.n++];
-                    G.delta = dcur[hd]; G.in64 = in64;
-                    G.gW = grads + H.w_off[l]; G.gb = grads + H.b_off[l];
-                    G.partial = partial + W.partial_first[hd][l];
-                    G.in_dim = H.dims[l]; G.out_dim = H.dims[l + 1];
-                    G.blocks = (unsigned)(((H.dims[l + 1] + GO - 1) / GO) * (((H.dims[l] + 63) / 64 + 3) / 4));
-                    gblocks += G.blocks;
-                    if (l > 0) {
+                // gradients at the outputs
+                LossArgs la;
+                la.logits = at(W.act_off[0][L.head[0].n - 1]);
+                la.v = at(W.act_off[1][L.head[1].n - 1]);
+                la.rows = rows; la.actions = actions; la.logp_old = logp_old; la.adv = adv; la.returns = returns;
+                la.B = batch; la.A = A; la.T = T;
+                la.clip_eps = (double)cfg->clip_eps; la.ent_coef = (double)cfg->ent_coef; la.adv_eps = (double)cfg->adv_eps;
+                la.normalize_adv = cfg->normalize_adv;
+                la.dlogits = at(W.delta_off[0][L.head[0].n - 1]);
+                la.dv = at(W.delta_off[1][L.head[1].n - 1]);
+                la.row_terms = row_terms;
+                hipLaunchKernelGGL(ppo_loss_kernel, dim3(1), dim3(256), 0, s, la);
+                // backward: the same distance from the output of both heads in one launch
+                for (int t = 0; t < depth - 1; ++t) {
+                    DeltaArgs da;
+                    memset(&da, 0, sizeof(da));
+                    da.B = batch; da.act = cfg->act;
+                    unsigned blocks = 0;
+                    for (int hd = 0; hd < 2; ++hd) {
+                        const HeadShape& H = L.head[hd];
+                        const int l = H.n - 1 - t;
+                        if (l < 1) continue;
                         DeltaProblem& D = da.p[da.n++];
-                        D.delta = dcur[hd]; D.W = params + H.w_off[l]; D.a_prev = in64;
-                        D.delta_prev = delta[hd][pp[hd]];
+                        D.delta = at(W.delta_off[hd][l]); D.W = params + H.w_off[l]; D.a_prev = at(W.act_off[hd][l - 1]);
+                        D.delta_prev = at(W.delta_off[hd][l - 1]);
                         D.in_dim = H.dims[l]; D.out_dim = H.dims[l + 1];
                         D.blocks = (unsigned)(((size_t)batch * H.dims[l] + 255) / 256);
-                        dblocks += D.blocks;
-                        dnext[hd] = D.delta_prev;
-                        pp[hd] ^= 1;
+                        blocks += D.blocks;
                     }
+                    hipLaunchKernelGGL(ppo_delta_kernel, dim3(blocks), dim3(256), 0, s, da);
                 }
-                hipLaunchKernelGGL(ppo_weight_grad_kernel, dim3(gblocks), dim3(256), 0, s, ga);
-                if (da.n > 0) hipLaunchKernelGGL(ppo_delta_kernel, dim3(dblocks), dim3(256), 0, s, da);
-                dcur[0] = dnext[0];
-                dcur[1] = dnext[1];
             }
-            hipLaunchKernelGGL(ppo_norm_kernel, dim3(1), dim3(256), 0, s, partial, W.n_partials, (double)cfg->max_grad_norm, scal, st);
+            ga.rows = rows;
+            hipLaunchKernelGGL(ppo_weight_grad_kernel, dim3((unsigned)((W.grad_waves + 3) / 4)), dim3(256), 0, s, ga);
             ++step;
-            const double c1 = 1.0 - pow((double)cfg->adam_b1, (double)step);
-            const double c2 = 1.0 - pow((double)cfg->adam_b2, (double)step);
-            hipLaunchKernelGGL(ppo_adam_kernel, dim3((unsigned)((L.n_params + 255) / 256)), dim3(256), 0, s, params, adam_m, adam_v,
-                               grads, scal, L.n_params, L.n_policy, (double)cfg->lr_policy, (double)cfg->lr_value,
-                               (double)cfg->adam_b1, (double)cfg->adam_b2, c1, c2, (double)cfg->adam_eps);
+            aa.c1 = 1.0 - pow((double)cfg->adam_b1, (double)step);
+            aa.c2 = 1.0 - pow((double)cfg->adam_b2, (double)step);
+            aa.stats = stats ? stats + ((size_t)e * steps_per_epoch + mb) * 5 : nullptr;
+            hipLaunchKernelGGL(ppo_adam_kernel, dim3((unsigned)((L.n_params + 256 * ADAM_PER_THREAD - 1) / (256 * ADAM_PER_THREAD))),
+                               dim3(256), 0, s, aa);
         }
     }
     BRL_LAUNCH_CHECK("ppo_head_update");

@@ -119,3 +119,38 @@ def test_no_normalisation_and_paper_hyperparameters_defaults():
     cfg, _ = B.make_ppo_config([8, 4, 2], [8, 4, 1], B.BRL_ACT_TANH)
     assert abs(cfg.clip_eps - 0.1) < 1e-7 and abs(cfg.ent_coef - 0.05) < 1e-7 and abs(cfg.max_grad_norm - 0.5) < 1e-7
     assert abs(cfg.lr_policy - 3e-4) < 1e-7 and abs(cfg.lr_value - 1e-3) < 1e-7
+
+
+@pytest.mark.parametrize("dims_p,dims_v,act,T,batch", [
+    ([2567, 250, 3], [2567, 17, 1], "tanh", 70, 67),      # inputs, units and samples off every tile; rows at odd addresses
+    ([9, 5], [9, 3, 1], "relu", 6, 3),                    # less than one tile in every direction, heads of unequal depth
+    ([1024, 40, 24, 70], [1024, 16, 1], "tanh", 260, 130),   # more actions than a wavefront, three sample blocks
+    ([48, 1040, 30], [48, 1030, 1], "tanh", 48, 16),      # too many units for one workgroup per sample: a launch per level
+    ([40, 640, 500, 4], [40, 8, 1], "relu", 24, 12),      # too many weights above the first layer: likewise
+])
+def test_head_update_at_tile_edges(dims_p, dims_v, act, T, batch):
+    """Bounds as above: first-step statistics from identical parameters, parameter change relative to its largest."""
+    B, R = _mods()
+    tr, stats, pol, val, out, init, c = _run_case(B, R, dims_p, dims_v, act, T, batch, 2, seed=17)
+    st = stats.cpu().numpy()
+    ref = np.array([[s["policy_loss"], s["value_loss"], s["entropy"], s["clip_fraction"], s["grad_norm"]] for s in out["stats"]])
+    assert np.allclose(st[0], ref[0], rtol=2e-6, atol=1e-7), (st[0], ref[0])
+    pw, pb, vw, vb = tr.tensors()
+    for g, w, s0 in zip(list(pw) + list(pb) + list(vw) + list(vb),
+                        list(pol.weights) + list(pol.biases) + list(val.weights) + list(val.biases),
+                        list(init[0]) + list(init[1]) + list(init[2]) + list(init[3])):
+        change = np.abs(w - s0.astype(np.float64)).max()
+        assert np.abs(g.astype(np.float64) - w).max() <= 2e-4 * change + 1e-7, (g.shape, np.abs(g - w).max(), change)
+
+
+@pytest.mark.parametrize("T", [1, 2, 255, 257, 2048])
+def test_gae_stretches(T):
+    """One thread composes a stretch of steps: shorter than the workgroup, one over, and the rollout's usual length."""
+    B, R = _mods()
+    c = synth.ppo_rollout_case(19, T, 4, 4, 0, n_envs=3)
+    adv, ret = R.gae(R.dev(c["rewards"]), R.dev(c["values"]), R.dev(c["dones"]), R.dev(c["last_value"]), 0.99, 0.95)
+    for e in range(3):
+        a_ref, r_ref = P.gae(c["rewards"][e], c["values"][e], c["dones"][e], c["last_value"][e], 0.99, 0.95)
+        scale = max(np.abs(a_ref).max(), np.abs(r_ref).max())
+        assert np.abs(adv[e].cpu().numpy() - a_ref).max() <= 2e-7 * scale + 1e-7
+        assert np.abs(ret[e].cpu().numpy() - r_ref).max() <= 2e-7 * scale + 1e-7
