@@ -96,6 +96,26 @@ ActBuf take_actbuf(Carver& c, int M, int K) {
     return a;
 }
 
+// Where the weight quantisers' kernels report bad weights: one pinned word per host thread, written over PCIe and
+// read after the stream has been waited for (a copy launch and its staging cost 12 us per matrix more).  Given back
+// when the thread ends; no call leaves a kernel behind that could still write it.
+struct PinnedFlag {
+    int* p = nullptr;
+    PinnedFlag() {
+        if (hipHostMalloc(reinterpret_cast<void**>(&p), sizeof(int), hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+    }
+    ~PinnedFlag() {
+        if (p) (void)hipHostFree(p);
+    }
+};
+int* pinned_flag() {
+    static thread_local PinnedFlag f;
+    return f.p;
+}
+
 int check_linear_shape(int N, int K, const char* who) {
     BRL_REQUIRE(N >= 1 && K >= 1, "%s: N = %d, K = %d must be positive", who, N, K);
     BRL_REQUIRE(K % 8 == 0, "%s: K = %d must be a multiple of 8", who, K);
@@ -369,14 +389,13 @@ int bitlinear_quantize_weights(const float* W, int n_out, int k_in, float eps, v
     hipStream_t s = static_cast<hipStream_t>(stream);
     Carver c(workspace);
     double* partials = c.take<double>(1024);
-    int* flag = c.take<int>(1);
+    int* flag = pinned_flag();
+    if (!flag) return hip_fail(hipErrorOutOfMemory, "quantize_weights: pinned flag");
     if (int rc = launch_quantize_weights(W, n_out, k_in, eps, static_cast<uint32_t*>(packed_out), beta_out, codes_dbg,
                                          partials, flag, s))
         return rc;
-    int bad = 0;
-    BRL_HIP_CHECK(hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, s));
     BRL_HIP_CHECK(hipStreamSynchronize(s));
-    BRL_REQUIRE(bad == 0, "quantize_weights: mean|W| is not finite");
+    BRL_REQUIRE(*static_cast<volatile int*>(flag) == 0, "quantize_weights: mean|W| is not finite");
     return BRL_OK;
 }
 
@@ -518,14 +537,13 @@ int bitlinear_quantize_weights_int8(const float* W, int n_out, int k_in, float e
     hipStream_t s = static_cast<hipStream_t>(stream);
     Carver c(workspace);
     float* partials = c.take<float>(1024);
-    int* flag = c.take<int>(1);
+    int* flag = pinned_flag();
+    if (!flag) return hip_fail(hipErrorOutOfMemory, "quantize_weights_int8: pinned flag");
     if (int rc = launch_quantize_weights_int8(W, n_out, k_in, eps, qmax, static_cast<int8_t*>(packed_out), scale_out, codes_dbg,
                                               partials, flag, s))
         return rc;
-    int bad = 0;
-    BRL_HIP_CHECK(hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, s));
     BRL_HIP_CHECK(hipStreamSynchronize(s));
-    BRL_REQUIRE(bad == 0, "quantize_weights_int8: max|W| is not finite");
+    BRL_REQUIRE(*static_cast<volatile int*>(flag) == 0, "quantize_weights_int8: max|W| is not finite");
     return BRL_OK;
 }
 

@@ -10,7 +10,7 @@
 // owning 16 consecutive k), padded with zeros, so the GEMM stages them as they are.
 // Two launches: per-block maxima, then a pack kernel in which every block
 // reduces the partial maxima again (a maximum does not depend on the order).
-#include "common.hpp"
+#include "weight_pack.hpp"
 
 namespace brl {
 
@@ -53,44 +53,47 @@ __global__ __launch_bounds__(W8_THREADS) void absmax_partials_kernel(const float
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-// one 16-byte lane slot of the tiled layout per thread
-__global__ __launch_bounds__(W8_THREADS) void int8_pack_kernel(const float* __restrict__ W, int N, int K, int nsb,
-                                                                size_t n_slots, float eps, float qmax, const float* __restrict__ partials,
-                                                                int n_partials, uint4* __restrict__ packed,
-                                                                float* __restrict__ scale_out, int8_t* __restrict__ codes_dbg,
-                                                                int* __restrict__ flag) {
+__global__ __launch_bounds__(PACK_THREADS) void int8_pack_kernel(const float* __restrict__ W, int N, int K, int nsb, float eps,
+                                                                 float qmax, const float* __restrict__ partials, int n_partials,
+                                                                 uint4* __restrict__ packed, float* __restrict__ scale_out,
+                                                                 int8_t* __restrict__ codes_dbg, int* __restrict__ flag) {
+    static_assert(W8_THREADS == PACK_THREADS, "the partial maxima are reduced by the whole workgroup");
     __shared__ float lds[W8_THREADS / 64];
+    __shared__ __attribute__((aligned(16))) uint32_t words[PACK_SB][1024];
+    pack_f4 v[PACK_SB][4];
+    pack_load(W, N, K, v);                       // in flight while the scale is reduced
     float m = 0.f;
     for (int i = threadIdx.x; i < n_partials; i += W8_THREADS) m = fmaxf(m, partials[i]);
     const float a = block_max(m, lds);
     const float ac = fmaxf(a, eps);
     const float s = qmax / ac;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         *scale_out = ac / qmax;
         *flag = isfinite(a) ? 0 : 1;
     }
-    const size_t u = (size_t)blockIdx.x * W8_THREADS + threadIdx.x;
-    if (u >= n_slots) return;
-    const int lane = (int)(u & 63);
-    const int dd = (int)((u >> 6) & 3);
-    const size_t blk = u >> 8;
-    const int sb = (int)(blk % (size_t)nsb);
-    const int nb = (int)(blk / (size_t)nsb);
-    const int n = nb * 32 + (lane & 31);
-    const int kbase = sb * 128 + dd * 32 + (lane >> 5) * 16;
-    uint32_t word[4] = {0u, 0u, 0u, 0u};
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sb0 = blockIdx.x * PACK_SB;
+    const int j = lane & 3, kk = (lane & 31) >> 2;                 // four columns of a 16-byte piece; the piece
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int k = kbase + i;
-        int code = 0;
-        if (n < N && k < K) {
-            const float v = W[(size_t)n * K + k];
-            code = (int)fminf(fmaxf(rintf(v * s), -qmax), qmax);
-            if (codes_dbg) codes_dbg[(size_t)n * K + k] = (int8_t)code;
+    for (int sb = 0; sb < PACK_SB; ++sb)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            int c[4];
+            uint32_t word = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                c[e] = (int)fminf(fmaxf(rintf(v[sb][p][e] * s), -qmax), qmax);
+                word |= ((uint32_t)c[e] & 0xffu) << (8 * e);
+            }
+            words[sb][((kk >> 1) * 64 + (kk & 1) * 32 + pack_row(p)) * 4 + j] = word;
+            if (codes_dbg) pack_tap(codes_dbg, blockIdx.y * NB + pack_row(p), (sb0 + sb) * SBK + pack_col(), N, K, c);
         }
-        word[i >> 2] |= ((uint32_t)code & 0xffu) << (8 * (i & 3));
+    __syncthreads();
+    if (sb0 + wave < nsb) {
+        uint4* dst = packed + ((size_t)blockIdx.y * nsb + sb0 + wave) * 256 + lane;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) dst[f * 64] = *reinterpret_cast<const uint4*>(&words[wave][(f * 64 + lane) * 4]);
     }
-    packed[u] = make_uint4(word[0], word[1], word[2], word[3]);
 }
 
 __global__ __launch_bounds__(W8_THREADS) void int8_unpack_kernel(const uint4* __restrict__ packed, int N, int K, int nsb,
@@ -126,10 +129,8 @@ int launch_quantize_weights_int8(const float* W, int N, int K, float eps, int qm
     hipLaunchKernelGGL(absmax_partials_kernel, dim3(g), dim3(W8_THREADS), 0, s, W, total, chunk, partials);
     BRL_LAUNCH_CHECK("absmax_partials_kernel");
     const int nsb = round_up(K, SBK) / SBK;
-    const size_t n_slots = (size_t)(round_up(N, NB) / NB) * nsb * 256;
-    const size_t blocks = (n_slots + W8_THREADS - 1) / W8_THREADS;
-    hipLaunchKernelGGL(int8_pack_kernel, dim3((unsigned)blocks), dim3(W8_THREADS), 0, s, W, N, K, nsb, n_slots, eps, (float)qmax, partials,
-                       g, reinterpret_cast<uint4*>(packed), scale, codes_dbg, flag);
+    hipLaunchKernelGGL(int8_pack_kernel, pack_grid(N, K), dim3(PACK_THREADS), 0, s, W, N, K, nsb, eps, (float)qmax, partials, g,
+                       reinterpret_cast<uint4*>(packed), scale, codes_dbg, flag);
     BRL_LAUNCH_CHECK("int8_pack_kernel");
     return BRL_OK;
 }

@@ -7,7 +7,7 @@
 // Two launches: per-block fp64 partial sums of |W|, then a pack kernel in which
 // every block re-reduces the partials in the same fixed order (so all blocks
 // see the same beta and the result does not depend on scheduling).
-#include "common.hpp"
+#include "weight_pack.hpp"
 
 namespace brl {
 
@@ -51,45 +51,48 @@ __global__ __launch_bounds__(QW_THREADS) void absum_partials_kernel(const float*
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-__global__ __launch_bounds__(QW_THREADS) void ternary_pack_kernel(const float* __restrict__ W, int N, int K, int nsb,
-                                                                    size_t n_words, float eps,
+__global__ __launch_bounds__(PACK_THREADS) void ternary_pack_kernel(const float* __restrict__ W, int N, int K, int nsb, float eps,
                                                                     const double* __restrict__ partials, int n_partials,
-                                                                    uint32_t* __restrict__ packed, float* __restrict__ beta_out,
+                                                                    uint4* __restrict__ packed, float* __restrict__ beta_out,
                                                                     int8_t* __restrict__ codes_dbg, int* __restrict__ flag) {
+    static_assert(QW_THREADS == PACK_THREADS, "the partial sums are reduced by the whole workgroup");
     __shared__ double lds[QW_THREADS / 64];
+    __shared__ __attribute__((aligned(16))) uint32_t words[PACK_SB][256];
+    pack_f4 v[PACK_SB][4];
+    pack_load(W, N, K, v);                       // in flight while the scale is reduced
     double acc = 0.0;
     for (int i = threadIdx.x; i < n_partials; i += QW_THREADS) acc += partials[i];
     const double total = block_sum_fixed(acc, lds);
     const float gamma = (float)(total / ((double)N * (double)K));
     const float beta = gamma + eps;
     const float tau = 0.5f * beta;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         *beta_out = beta;
         *flag = isfinite(gamma) ? 0 : 1;
     }
-    const size_t w = (size_t)blockIdx.x * QW_THREADS + threadIdx.x;
-    if (w >= n_words) return;
-    const int dd = (int)(w & 3);
-    const int lane = (int)((w >> 2) & 63);
-    const size_t blk = w >> 8;
-    const int sb = (int)(blk % (size_t)nsb);
-    const int nb = (int)(blk / (size_t)nsb);
-    const int n = nb * 32 + (lane & 31);
-    const int kbase = sb * 128 + dd * 32 + (lane >> 5) * 16;
-    uint32_t word = 0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sb0 = blockIdx.x * PACK_SB;
+    const int j = lane & 3, kk = (lane & 31) >> 2;                 // four columns of a word; the word's 16 columns
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int k = kbase + i;
-        int code = 0;
-        if (n < N && k < K) {
-            const float v = W[(size_t)n * K + k];
-            code = (int)(v > tau) - (int)(v < -tau);
-            if (codes_dbg) codes_dbg[(size_t)n * K + k] = (int8_t)code;
+    for (int s = 0; s < PACK_SB; ++s)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            int c[4];
+            uint32_t part = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                c[e] = (int)(v[s][p][e] > tau) - (int)(v[s][p][e] < -tau);
+                part |= (uint32_t)(c[e] + 1) << (8 * e);
+            }
+            part <<= 2 * j;
+            part |= (uint32_t)__builtin_amdgcn_mov_dpp((int)part, 0xB1, 0xf, 0xf, true);      // the four lanes of a quad
+            part |= (uint32_t)__builtin_amdgcn_mov_dpp((int)part, 0x4E, 0xf, 0xf, true);
+            if (j == 0) words[s][((kk & 1) * 32 + pack_row(p)) * 4 + (kk >> 1)] = part;
+            if (codes_dbg) pack_tap(codes_dbg, blockIdx.y * NB + pack_row(p), (sb0 + s) * SBK + pack_col(), N, K, c);
         }
-        const int j = i >> 2, b = i & 3;
-        word |= (uint32_t)(code + 1) << (2 * j + 8 * b);
-    }
-    packed[w] = word;
+    __syncthreads();
+    if (sb0 + wave < nsb)
+        packed[((size_t)blockIdx.y * nsb + sb0 + wave) * 64 + lane] = *reinterpret_cast<const uint4*>(&words[wave][lane * 4]);
 }
 
 __global__ __launch_bounds__(QW_THREADS) void unpack_codes_kernel(const uint32_t* __restrict__ packed, int N, int K, int nsb,
@@ -135,10 +138,8 @@ int launch_quantize_weights(const float* W, int N, int K, float eps, uint32_t* p
     hipLaunchKernelGGL(absum_partials_kernel, dim3(g), dim3(QW_THREADS), 0, s, W, total, chunk, partials);
     BRL_LAUNCH_CHECK("absum_partials_kernel");
     const int nsb = round_up(K, SBK) / SBK;
-    const size_t n_words = (size_t)(round_up(N, NB) / NB) * nsb * 256;
-    const size_t blocks = (n_words + QW_THREADS - 1) / QW_THREADS;
-    hipLaunchKernelGGL(ternary_pack_kernel, dim3((unsigned)blocks), dim3(QW_THREADS), 0, s, W, N, K, nsb, n_words, eps,
-                       partials, g, packed, beta, codes_dbg, flag);
+    hipLaunchKernelGGL(ternary_pack_kernel, pack_grid(N, K), dim3(PACK_THREADS), 0, s, W, N, K, nsb, eps, partials, g,
+                       reinterpret_cast<uint4*>(packed), beta, codes_dbg, flag);
     BRL_LAUNCH_CHECK("ternary_pack_kernel");
     return BRL_OK;
 }

@@ -64,6 +64,26 @@ def test_quantize_weights_bit_exact(n, k):
     assert torch.equal(pl.packed, pl2.packed) and torch.equal(pl.beta, pl2.beta)
 
 
+@pytest.mark.parametrize("n,k", [(1, 1), (31, 127), (33, 129), (32, 512), (40, 515), (65, 1030)])
+def test_quantize_weights_block_edges(n, k):
+    """Packing takes 32 rows x 512 columns per workgroup, four columns per load: sizes one below, at and above each,
+    and rows that start at odd addresses.  Codes, scale and the packed blob's round trip are exact."""
+    B, R = _mods()
+    W = synth.normal(71, 3, (n, k), 0.02)
+    codes_ref, beta_ref = O.ternary_quantize(W)
+    pl = R.quantize_linear(W, want_codes=True)
+    assert np.array_equal(pl.codes.cpu().numpy(), codes_ref) and np.float32(pl.beta.cpu().numpy()[0]) == beta_ref
+    back = torch.full((n, k), 9, dtype=torch.int8, device="cuda")
+    B.brl_unpack_codes(pl.packed, n, k, back)
+    assert np.array_equal(back.cpu().numpy(), codes_ref)
+    from oracle import critic_oracle as C
+    c8_ref, s8_ref = C.int8_quantize(W)
+    p8 = R.quantize_linear(W, want_codes=True, int8=True)
+    assert np.array_equal(p8.codes.cpu().numpy(), c8_ref) and np.float32(p8.beta.cpu().numpy()[0]) == s8_ref
+    B.brl_unpack_codes_int8(p8.packed, n, k, back)
+    assert np.array_equal(back.cpu().numpy(), c8_ref)
+
+
 def test_quantize_weights_special_matrices():
     B, R = _mods()
     for W in (np.zeros((40, 136), np.float32),                       # all zero: beta = eps, codes 0
