@@ -290,27 +290,36 @@ int check_mlp(const brl_mlp* m, const char* who, int out_expected) {
     return BRL_OK;
 }
 
-size_t mlp_hidden_max(const brl_mlp* m) {
-    size_t mx = 1;
-    for (int i = 1; i < m->n_layers; ++i)
-        if ((size_t)m->dims[i] > mx) mx = (size_t)m->dims[i];
-    return mx;
+void add_head(MlpSet& set, const brl_mlp* m, float* out) {
+    const int e = set.n++;
+    set.layers[e] = m->n_layers;
+    for (int l = 0; l <= m->n_layers; ++l) set.dims[e][l] = m->dims[l];
+    for (int l = 0; l < m->n_layers; ++l) {
+        set.W[e][l] = m->W ? m->W[l] : nullptr;
+        set.bias[e][l] = m->b ? m->b[l] : nullptr;
+    }
+    set.out[e] = out;
 }
 
-int run_mlp(const brl_mlp* m, const float* h, int B, float* out, double* buf0, double* buf1, hipStream_t s) {
-    const double* in64 = nullptr;
-    const float* in32 = h;
-    double* bufs[2] = {buf0, buf1};
-    for (int i = 0; i < m->n_layers; ++i) {
-        const bool last = i + 1 == m->n_layers;
-        double* o64 = last ? nullptr : bufs[i & 1];
-        if (int rc = launch_mlp_layer(in64, in32, m->W[i], m->b[i], B, m->dims[i], m->dims[i + 1], m->act, o64,
-                                      last ? out : nullptr, s))
-            return rc;
-        in64 = o64;
-        in32 = nullptr;
-    }
-    return BRL_OK;
+bool mlp_sized(const brl_mlp* m) {
+    if (!m->dims || m->n_layers < 1 || m->n_layers > 8) return false;
+    for (int l = 0; l <= m->n_layers; ++l)
+        if (m->dims[l] < 1) return false;
+    return true;
+}
+
+MlpSet one_head_set(const brl_mlp* m, int B) {
+    MlpSet set;
+    memset(&set, 0, sizeof(set));
+    set.B = B;
+    add_head(set, m, nullptr);
+    return set;
+}
+
+MlpSet head_set(const brl_head* head, int B) {
+    MlpSet set = one_head_set(&head->policy, B);
+    add_head(set, &head->value, nullptr);
+    return set;
 }
 
 }  // namespace
@@ -892,13 +901,14 @@ int attention_forward(const float* qkv, int B, int S, const int32_t* cu_seqlens,
 
 size_t brl_head_workspace_bytes(const brl_head* head, int B) {
     if (!head || B < 1) return 0;
-    if (!head->policy.dims || !head->value.dims || head->policy.n_layers < 1 || head->value.n_layers < 1 ||
-        head->policy.n_layers > 8 || head->value.n_layers > 8)
-        return 0;
-    size_t mx = mlp_hidden_max(&head->policy);
-    const size_t mv = mlp_hidden_max(&head->value);
-    if (mv > mx) mx = mv;
-    return 2 * round_up_sz((size_t)B * mx * sizeof(double), ALIGN);
+    if (!mlp_sized(&head->policy) || !mlp_sized(&head->value)) return 0;
+    // together, or one after the other where their activations differ (fewer tiles at a time can mean more partial sums)
+    size_t need = heads_workspace_bytes(head_set(head, B));
+    for (int e = 0; e < 2; ++e) {
+        const size_t alone = heads_workspace_bytes(one_head_set(e ? &head->value : &head->policy, B));
+        if (alone > need) need = alone;
+    }
+    return round_up_sz(need, ALIGN);
 }
 
 int policy_value_head(const brl_head* head, const float* h, int B, float* logits, float* value, void* workspace,
@@ -913,18 +923,29 @@ int policy_value_head(const brl_head* head, const float* h, int B, float* logits
         set_error("policy_value_head: workspace %zu < %zu", ws_bytes, need);
         return BRL_ENOSPC;
     }
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    double* buf0 = static_cast<double*>(workspace);
-    double* buf1 = reinterpret_cast<double*>(static_cast<char*>(workspace) + need / 2);
-    if (int rc = run_mlp(&head->policy, h, B, logits, buf0, buf1, s)) return rc;
-    return run_mlp(&head->value, h, B, value, buf0, buf1, s);
+    MlpSet set = head_set(head, B);
+    set.h = h;
+    set.out[0] = logits;
+    set.out[1] = value;
+    set.act = head->policy.act;
+    if (head->value.act == head->policy.act) return launch_heads(set, workspace, static_cast<hipStream_t>(stream));
+    // different activations: one head after the other in the same scratch
+    for (int e = 0; e < 2; ++e) {
+        const brl_mlp* m = e ? &head->value : &head->policy;
+        MlpSet one = one_head_set(m, B);
+        one.h = h;
+        one.act = m->act;
+        one.out[0] = e ? value : logits;
+        if (int rc = launch_heads(one, workspace, static_cast<hipStream_t>(stream))) return rc;
+    }
+    return BRL_OK;
 }
 
 namespace {
 
 int check_ensemble(const brl_mlp* members, int n_members, const char* who) {
     BRL_REQUIRE(members != nullptr, "%s: null member table", who);
-    BRL_REQUIRE(n_members >= 1 && n_members <= MAX_ENSEMBLE, "%s: %d members, 1..%d supported", who, n_members, MAX_ENSEMBLE);
+    BRL_REQUIRE(n_members >= 1 && n_members <= MAX_HEADS, "%s: %d members, 1..%d supported", who, n_members, MAX_HEADS);
     for (int e = 0; e < n_members; ++e) {
         if (int rc = check_mlp(&members[e], "value ensemble member", 1)) return rc;
         BRL_REQUIRE(members[e].n_layers == members[0].n_layers && members[e].act == members[0].act,
@@ -936,25 +957,32 @@ int check_ensemble(const brl_mlp* members, int n_members, const char* who) {
 }
 
 struct EnsembleWs {
-    size_t buf0_off, buf1_off, each_off, total;
+    size_t heads_off, each_off, total;
 };
 
-EnsembleWs ensemble_ws_layout(const brl_mlp* members, int n_members, int B) {
+MlpSet ensemble_set(const brl_mlp* members, int n_members, int B) {
+    MlpSet set;
+    memset(&set, 0, sizeof(set));
+    set.B = B;
+    for (int e = 0; e < n_members; ++e) add_head(set, &members[e], nullptr);
+    return set;
+}
+
+EnsembleWs ensemble_ws_layout(const MlpSet& set) {
     EnsembleWs L;
-    const size_t hid = round_up_sz((size_t)n_members * B * mlp_hidden_max(&members[0]) * sizeof(double), ALIGN);
-    L.buf0_off = 0;
-    L.buf1_off = hid;
-    L.each_off = 2 * hid;
-    L.total = L.each_off + round_up_sz((size_t)n_members * B * sizeof(float), ALIGN);
+    L.heads_off = 0;
+    L.each_off = round_up_sz(heads_workspace_bytes(set), ALIGN);
+    L.total = L.each_off + round_up_sz((size_t)set.n * set.B * sizeof(float), ALIGN);
     return L;
 }
 
 }  // namespace
 
 size_t brl_value_ensemble_workspace_bytes(const brl_mlp* members, int n_members, int B) {
-    if (!members || n_members < 1 || n_members > MAX_ENSEMBLE || B < 1) return 0;
-    if (!members[0].dims || members[0].n_layers < 1 || members[0].n_layers > 8) return 0;
-    return ensemble_ws_layout(members, n_members, B).total;
+    if (!members || n_members < 1 || n_members > MAX_HEADS || B < 1) return 0;
+    for (int e = 0; e < n_members; ++e)
+        if (!mlp_sized(&members[e])) return 0;
+    return ensemble_ws_layout(ensemble_set(members, n_members, B)).total;
 }
 
 int value_ensemble_forward(const brl_mlp* members, int n_members, const float* h, int B, float* value_mean,
@@ -962,33 +990,18 @@ int value_ensemble_forward(const brl_mlp* members, int n_members, const float* h
     BRL_REQUIRE(h && value_mean && workspace && aligned16(workspace), "value_ensemble_forward: null or misaligned pointer");
     BRL_REQUIRE(B >= 1, "value_ensemble_forward: B = %d", B);
     if (int rc = check_ensemble(members, n_members, "value_ensemble_forward")) return rc;
-    const EnsembleWs L = ensemble_ws_layout(members, n_members, B);
+    MlpSet set = ensemble_set(members, n_members, B);
+    const EnsembleWs L = ensemble_ws_layout(set);
     if (ws_bytes < L.total) {
         set_error("value_ensemble_forward: workspace %zu < %zu", ws_bytes, L.total);
         return BRL_ENOSPC;
     }
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    char* base = static_cast<char*>(workspace);
-    double* bufs[2] = {reinterpret_cast<double*>(base + L.buf0_off), reinterpret_cast<double*>(base + L.buf1_off)};
-    float* each = values_each ? values_each : reinterpret_cast<float*>(base + L.each_off);
-    const brl_mlp& m0 = members[0];
-    const double* in64 = nullptr;
-    for (int i = 0; i < m0.n_layers; ++i) {
-        EnsembleLayer a;
-        memset(&a, 0, sizeof(a));
-        for (int e = 0; e < n_members; ++e) {
-            a.W[e] = members[e].W[i];
-            a.bias[e] = members[e].b[i];
-        }
-        a.n_members = n_members; a.B = B; a.in_dim = m0.dims[i]; a.out_dim = m0.dims[i + 1]; a.act = m0.act;
-        a.last = (i + 1 == m0.n_layers) ? 1 : 0;
-        a.in64 = in64; a.in32 = h;
-        a.out64 = a.last ? nullptr : bufs[i & 1];
-        a.out32 = a.last ? each : nullptr;
-        if (int rc = launch_ensemble_layer(a, s)) return rc;
-        in64 = a.out64;
-    }
-    return launch_ensemble_mean(each, n_members, B, value_mean, s);
+    float* each = values_each ? values_each : reinterpret_cast<float*>(static_cast<char*>(workspace) + L.each_off);
+    set.h = h;
+    set.act = members[0].act;
+    for (int m = 0; m < n_members; ++m) set.out[m] = each + (size_t)m * B;
+    set.mean = value_mean;
+    return launch_heads(set, static_cast<char*>(workspace) + L.heads_off, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"

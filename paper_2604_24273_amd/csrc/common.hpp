@@ -176,20 +176,20 @@ int launch_embed(const uint16_t* table, const int32_t* ids, int M, int d, int vo
 // M rows in all; lengths (or nullptr) applies to the uniform layout only
 int launch_final_pool(const float* x, const float* gain, int B, int S, int M, int d, const int32_t* lengths,
                       const SeqMap& sm, float eps_norm, float* rinv, float* h, hipStream_t s);
-int launch_mlp_layer(const double* in64, const float* in32, const float* W, const float* b, int B, int in_dim,
-                     int out_dim, int act, double* out64, float* out32, hipStream_t s);
-// one layer of up to 8 equally shaped heads (an ensemble of critics) in one launch
-constexpr int MAX_ENSEMBLE = 8;
-struct EnsembleLayer {
-    const float* W[MAX_ENSEMBLE];
-    const float* bias[MAX_ENSEMBLE];
-    int n_members, B, in_dim, out_dim, act, last;
-    const double* in64;     // [n_members, B, in_dim] or nullptr: then every member reads in32
-    const float* in32;      // [B, in_dim]
-    double* out64;          // [n_members, B, out_dim] (hidden layers)
-    float* out32;           // [n_members, B] (last layer, out_dim == 1)
+// fp32 MLP heads evaluated together on the same h: policy and value, or an ensemble of value heads
+constexpr int MAX_HEADS = 8;
+constexpr int MAX_MLP_LAYERS = 8;
+struct MlpSet {
+    int n, B, act;
+    int layers[MAX_HEADS];
+    int dims[MAX_HEADS][MAX_MLP_LAYERS + 1];
+    const float* W[MAX_HEADS][MAX_MLP_LAYERS];
+    const float* bias[MAX_HEADS][MAX_MLP_LAYERS];
+    const float* h;              // [B, dims[.][0]]
+    float* out[MAX_HEADS];       // [B, last width]
+    float* mean;                 // [B] mean of the heads' results (all of width 1, out[e] = out[0] + e * B), or nullptr
 };
-int launch_ensemble_layer(const EnsembleLayer& a, hipStream_t s);
-int launch_ensemble_mean(const float* each, int n, int B, float* mean, hipStream_t s);
+size_t heads_workspace_bytes(const MlpSet& s);
+int launch_heads(const MlpSet& s, void* workspace, hipStream_t stream);
 
 }  // namespace brl

@@ -1,0 +1,117 @@
+// First-layer contraction of the fp32 heads on the fp64 matrix cores: shared by the forward heads and their training.
+//
+// v_mfma_f64_16x16x4: a lane gives row / column (lane & 15) and one of four k = lane >> 4; its four results are rows
+// 4 v + (lane >> 4), column lane & 15.  The order of k inside a chunk of 16 is free, so a lane reads four consecutive
+// floats.  A wavefront takes 16 output units x 64 samples (the weights, the larger operand, are read once) over a
+// range of k, the four wavefronts of a workgroup neighbouring ranges, summed in order through LDS; up to L1_SPLITS
+// workgroups share a tile of outputs so that the launch fills the chip (their sums meet in the next kernel).
+// 64 x 2560 -> 2 x 256: 32 us with vector FMAs (four units x four samples per workgroup), 43 us with a wavefront per
+// result, 9.5 us here (bound by the latency of gathering the rows and of the 80 dependent MFMAs of a wavefront; 14.3 us
+// with one chunk requested ahead).
+#pragma once
+
+#include "common.hpp"
+
+namespace brl {
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));      // rows of the flat buffers start anywhere
+
+constexpr int L1_SPLITS = 8;
+
+// about 256 workgroups of four wavefronts, each wavefront at least one chunk of 16 inputs
+inline int first_layer_splits(int tiles, int btiles, int d) {
+    const long want = 256 / ((long)tiles * btiles), most = ((long)d + 63) / 64;
+    long s = want < 1 ? 1 : want;
+    if (s > L1_SPLITS) s = L1_SPLITS;
+    return (int)(s > most ? most : s);
+}
+
+// four inputs k .. k + 3 of a row of n values, zeros past the end
+__device__ inline v4f_u four_inputs(const float* row, int k, int n) {
+    if (k + 4 <= n) return *reinterpret_cast<const v4f_u*>(row + k);
+    v4f_u r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = k + e < n ? row[k + e] : 0.f;
+    return r;
+}
+
+// wrow: the lane's weight row; hrow: its rows of the four sample tiles; unit of units: the wavefront's range of k.
+// part[wave][4 * sample tile + v][lane] receives the sums; a barrier has passed on return.
+typedef double FirstLayerSums[4][16][64];
+__device__ inline void first_layer_sums(const float* wrow, const float* const (&hrow)[4], int d, int unit, int units,
+                                        FirstLayerSums& part) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kk = lane >> 4;
+    const int chunks = (d + 15) / 16;
+    const int per = (chunks + units - 1) / units;
+    const int c0 = unit * per, c1 = min(chunks, c0 + per);
+    v4d acc[4] = {};
+    constexpr int NC = 5;                            // chunks requested together (2560 inputs over 32 wavefronts: all of them)
+    for (int cb = c0; cb < c1; cb += NC) {
+        v4f_u w[NC], x[NC][4];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int k = min(cb + c, c1 - 1) * 16 + 4 * kk;
+            w[c] = four_inputs(wrow, k, d);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[c][q] = four_inputs(hrow[q], k, d);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (cb + c >= c1) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[c][q][e], (double)w[c][e], acc[q], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[wave][q * 4 + v][lane] = acc[q][v];
+    __syncthreads();
+}
+
+// the four wavefronts' parts in order: sample (qv >> 2) * 16 + 4 (qv & 3) + (lane >> 4), output unit lane & 15
+__device__ inline double first_layer_sum(const FirstLayerSums& part, int qv, int lane) {
+    return ((part[0][qv][lane] + part[1][qv][lane]) + part[2][qv][lane]) + part[3][qv][lane];
+}
+
+// the workgroups' parts of one first-layer result, in order
+__device__ inline double first_layer_total(const double* __restrict__ z, int splits, size_t stride) {
+    double p[L1_SPLITS], v = 0.0;
+#pragma unroll
+    for (int sp = 0; sp < L1_SPLITS; ++sp) p[sp] = z[(size_t)min(sp, splits - 1) * stride];
+#pragma unroll
+    for (int sp = 0; sp < L1_SPLITS; ++sp) v += sp < splits ? p[sp] : 0.0;
+    return v;
+}
+
+__device__ inline double wave_sum(double v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+__device__ inline double activate(double z, int act) { return act == BRL_ACT_RELU ? fmax(z, 0.0) : tanh(z); }
+
+// sum_i w[i] x[i] over a group of LG adjacent lanes (every lane of the group gets it), 32 weights of a lane in flight
+template <int LG>
+__device__ inline double group_dot(const float* __restrict__ w, const double* x, int n) {
+    double v = 0.0;
+    int i = threadIdx.x % LG;
+    for (; i + 31 * LG < n; i += 32 * LG) {
+        float wv[32];
+#pragma unroll
+        for (int t = 0; t < 32; ++t) wv[t] = w[i + t * LG];
+#pragma unroll
+        for (int t = 0; t < 32; ++t) v += (double)wv[t] * x[i + t * LG];
+    }
+#pragma unroll 4
+    for (; i < n; i += LG) v += (double)w[i] * x[i];
+#pragma unroll
+    for (int off = 1; off < LG; off <<= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+}  // namespace brl

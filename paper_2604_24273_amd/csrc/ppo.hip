@@ -10,7 +10,7 @@
 // on the fp64 matrix cores, every sum in fp64 in a fixed order: results do not depend on scheduling.
 // Parameters and optimiser state are fp32 in one flat buffer each (policy W_1, b_1, ..., W_L, b_L,
 // then the value head likewise); activations, deltas and gradients of a step live in fp64 scratch.
-#include "common.hpp"
+#include "mlp_f64.hpp"
 
 #include <cmath>
 #include <cstring>
@@ -129,20 +129,10 @@ __global__ __launch_bounds__(GAE_THREADS) void gae_kernel(const float* __restric
 // entry can never address memory outside the rollout or the logits (its result is then meaningless, not a fault).
 __device__ inline int clamp_index(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
 
-typedef double v4d __attribute__((ext_vector_type(4)));
 typedef double v2d_u __attribute__((ext_vector_type(2), aligned(8)));      // rows of the flat buffers start anywhere
-typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));
 
-// ---- first layer of both heads: z[b, o] = sum_i W[o, i] h[rows[b], i], columns of the policy head first -----------
-// v_mfma_f64_16x16x4: a lane gives row / column (lane & 15) and one of four k = lane >> 4; its four results are rows
-// 4 v + (lane >> 4), column lane & 15.  The order of k inside a chunk of 16 is free, so a lane reads four consecutive
-// floats.  A wavefront takes 16 output units x 64 samples (the weights, the larger operand, are read once) over a
-// range of k, the four wavefronts of a workgroup neighbouring ranges, summed in order through LDS; up to L1_SPLITS
-// workgroups share a tile of outputs so that the launch fills the chip (their sums meet in the next kernel).
-// 64 x 2560 -> 2 x 256: 32 us with vector FMAs and four units per workgroup, 9.5 us here (bound by the latency of
-// gathering the rows and of the 80 dependent MFMAs of a wavefront; 14.3 us with one chunk requested ahead).
+// ---- first layer of both heads: z[b, o] = sum_i W[o, i] h[rows[b], i], columns of the policy head first (mlp_f64.hpp)
 // One more workgroup computes the mean and deviation of the mini-batch's advantages.
-constexpr int L1_SPLITS = 8;
 struct FirstArgs {
     const float* h;
     const int32_t* rows;
@@ -155,15 +145,6 @@ struct FirstArgs {
     int normalize_adv;
     double* scal;                    // [0] mean, [1] 1 / (deviation + eps)
 };
-
-// four inputs k .. k + 3 of a row of n values, zeros past the end
-__device__ inline v4f_u four_inputs(const float* row, int k, int n) {
-    if (k + 4 <= n) return *reinterpret_cast<const v4f_u*>(row + k);
-    v4f_u r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = k + e < n ? row[k + e] : 0.f;
-    return r;
-}
 
 __device__ void minibatch_scale(const float* adv, const int32_t* rows, int B, int T, double eps, int normalize, double* scal) {
     __shared__ double red[256];
@@ -199,7 +180,7 @@ __device__ void minibatch_scale(const float* adv, const int32_t* rows, int B, in
 }
 
 __global__ __launch_bounds__(256) void ppo_first_layer_kernel(FirstArgs a) {
-    __shared__ double part[4][16][64];
+    __shared__ FirstLayerSums part;
     const int tiles = a.tiles[0] + a.tiles[1];
     if ((int)blockIdx.x == tiles * a.splits * a.btiles) {
         minibatch_scale(a.adv, a.rows, a.B, a.T, a.adv_eps, a.normalize_adv, a.scal);
@@ -209,48 +190,17 @@ __global__ __launch_bounds__(256) void ppo_first_layer_kernel(FirstArgs a) {
     const int split = blockIdx.x % a.splits, tile = (blockIdx.x / a.splits) % tiles, bt = blockIdx.x / (a.splits * tiles);
     const int hd = tile >= a.tiles[0] ? 1 : 0;
     const int o0 = (tile - (hd ? a.tiles[0] : 0)) * 16;
-    const int kk = lane >> 4;
-    const float* wrow = a.W[hd] + (size_t)min(o0 + (lane & 15), a.out_dim[hd] - 1) * a.d;
     const float* hrow[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) hrow[q] = a.h + (size_t)clamp_index(a.rows[min(bt * 64 + q * 16 + (lane & 15), a.B - 1)], a.T) * a.d;
-    const int chunks = (a.d + 15) / 16, units = a.splits * 4;
-    const int per = (chunks + units - 1) / units;
-    const int c0 = (split * 4 + wave) * per, c1 = min(chunks, c0 + per);
-    v4d acc[4] = {};
-    constexpr int NC = 5;                            // chunks requested together (2560 inputs over 32 wavefronts: all of them)
-    for (int cb = c0; cb < c1; cb += NC) {
-        v4f_u w[NC], x[NC][4];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const int k = min(cb + c, c1 - 1) * 16 + 4 * kk;
-            w[c] = four_inputs(wrow, k, a.d);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) x[c][q] = four_inputs(hrow[q], k, a.d);
-        }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if (cb + c >= c1) break;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[c][q][e], (double)w[c][e], acc[q], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) part[wave][q * 4 + v][lane] = acc[q][v];
-    __syncthreads();
+    first_layer_sums(a.W[hd] + (size_t)min(o0 + (lane & 15), a.out_dim[hd] - 1) * a.d, hrow, a.d, split * 4 + wave, a.splits * 4, part);
     const int ncol = a.out_dim[0] + a.out_dim[1];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int qv = u * 4 + wave;                                 // (sample tile, register)
-        const int b = bt * 64 + (qv >> 2) * 16 + 4 * (qv & 3) + kk, o = o0 + (lane & 15);
+        const int b = bt * 64 + (qv >> 2) * 16 + 4 * (qv & 3) + (lane >> 4), o = o0 + (lane & 15);
         if (b < a.B && o < a.out_dim[hd])
-            a.z[((size_t)split * a.B + b) * ncol + (hd ? a.out_dim[0] : 0) + o] =
-                ((part[0][qv][lane] + part[1][qv][lane]) + part[2][qv][lane]) + part[3][qv][lane];
+            a.z[((size_t)split * a.B + b) * ncol + (hd ? a.out_dim[0] : 0) + o] = first_layer_sum(part, qv, lane);
     }
 }
 
@@ -281,12 +231,6 @@ struct TailArgs {
     double* row_terms;               // [4, B]
 };
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-__device__ inline double activate(double z, int act) { return act == BRL_ACT_RELU ? fmax(z, 0.0) : tanh(z); }
 __device__ inline double act_slope(double a, int act) { return act == BRL_ACT_RELU ? (a > 0.0 ? 1.0 : 0.0) : 1.0 - a * a; }
 
 __global__ __launch_bounds__(256) void ppo_tail_kernel(TailArgs a) {
@@ -303,13 +247,7 @@ __global__ __launch_bounds__(256) void ppo_tail_kernel(TailArgs a) {
 
     for (int c = tid; c < ncol; c += 256) {
         const int hd = c >= a.dims[0][1] ? 1 : 0, o = c - (hd ? a.dims[0][1] : 0);
-        double p[L1_SPLITS];
-#pragma unroll
-        for (int sp = 0; sp < L1_SPLITS; ++sp) p[sp] = a.z[((size_t)min(sp, a.splits - 1) * a.B + b) * ncol + c];
-        double v = 0.0;
-#pragma unroll
-        for (int sp = 0; sp < L1_SPLITS; ++sp) v += sp < a.splits ? p[sp] : 0.0;
-        v += (double)a.bias[hd][0][o];
+        double v = first_layer_total(a.z + (size_t)b * ncol + c, a.splits, (size_t)a.B * ncol) + (double)a.bias[hd][0][o];
         if (a.n[hd] > 1) {
             v = activate(v, a.act);
             a.acts[hd][0][(size_t)b * a.dims[hd][1] + o] = v;
@@ -326,21 +264,7 @@ __global__ __launch_bounds__(256) void ppo_tail_kernel(TailArgs a) {
         for (int u = tid / LG; u < (total + 31) / 32 * 32; u += 256 / LG) {
             const int uc = min(u, total - 1), hd = uc >= od0 ? 1 : 0, o = uc - (hd ? od0 : 0);
             const int id = a.dims[hd][l], od = a.dims[hd][l + 1];
-            const float* w = a.W[hd][l] + (size_t)o * id;
-            const double* x = out + in0[hd];
-            double v = 0.0;
-            int i = tid % LG;
-            for (; i + 31 * LG < id; i += 32 * LG) {         // 32 weights of a lane in flight
-                float wv[32];
-#pragma unroll
-                for (int t = 0; t < 32; ++t) wv[t] = w[i + t * LG];
-#pragma unroll
-                for (int t = 0; t < 32; ++t) v += (double)wv[t] * x[i + t * LG];
-            }
-#pragma unroll 4
-            for (; i < id; i += LG) v += (double)w[i] * x[i];
-#pragma unroll
-            for (int off = 1; off < LG; off <<= 1) v += __shfl_xor(v, off, 64);
+            double v = group_dot<LG>(a.W[hd][l] + (size_t)o * id, out + in0[hd], id);
             if (tid % LG == 0 && u < total) {
                 v += (double)a.bias[hd][l][o];
                 if (l + 1 < a.n[hd]) {
@@ -876,11 +800,7 @@ PpoWs ppo_ws_layout(const Layout& L, int batch) {
     const int ncol = L.head[0].dims[1] + L.head[1].dims[1];
     const int tiles = (L.head[0].dims[1] + 15) / 16 + (L.head[1].dims[1] + 15) / 16;
     W.btiles = (batch + 63) / 64;
-    // about 256 workgroups of four wavefronts, each wavefront at least one chunk of 16 inputs
-    const long want = 256 / ((long)tiles * W.btiles), most = ((long)L.head[0].dims[0] + 63) / 64;
-    W.splits = (int)(want < 1 ? 1 : want);
-    if (W.splits > L1_SPLITS) W.splits = L1_SPLITS;
-    if (W.splits > most) W.splits = (int)most;
+    W.splits = first_layer_splits(tiles, W.btiles, L.head[0].dims[0]);
     W.z_off = W.tail ? take((size_t)W.splits * batch * ncol * 8) : 0;
     W.grad_off = take(L.n_params * 8);
     int nw = 0;

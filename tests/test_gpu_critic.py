@@ -213,3 +213,29 @@ def test_value_ensemble(dims, n_members, act, batch):
         ws = R.Workspace(B.brl_head_workspace_bytes(head, batch))
         B.policy_value_head(head, R.dev(h), batch, logits, value, ws.buf)
         assert torch.equal(value, each[e])
+
+
+@pytest.mark.parametrize("dims_p,dims_v,acts,batch", [
+    ([2560, 256, 18], [2560, 256, 1], ("tanh", "tanh"), 1),
+    ([2560, 256, 128, 18], [2560, 256, 1], ("relu", "relu"), 65),       # heads of unequal depth, one sample past a tile block
+    ([37, 5], [37, 1], ("tanh", "tanh"), 67),                           # no hidden layer, inputs off every chunk
+    ([130, 17, 33, 9], [130, 15, 1], ("tanh", "relu"), 64),             # different activations: one head after the other
+    ([96, 2100, 700, 6], [96, 2050, 1], ("tanh", "tanh"), 5),           # too wide for a workgroup per sample: a launch per level
+])
+def test_policy_value_head_shapes(dims_p, dims_v, acts, batch):
+    """fp64 sums rounded once: fp32 outputs within 1e-6 of the oracle's (2^-24 and the fp64 activation's last bits)."""
+    B, R = _mods()
+    codes = [B.BRL_ACT_TANH if a == "tanh" else B.BRL_ACT_RELU for a in acts]
+    pw, pb = synth.mlp_params(23, 10, dims_p)
+    vw, vb = synth.mlp_params(23, 40, dims_v)
+    h = synth.normal(23, 70, (batch, dims_p[0]))
+    pol, k1 = B.make_mlp([R.dev(w) for w in pw], [R.dev(b) for b in pb], codes[0])
+    val, k2 = B.make_mlp([R.dev(w) for w in vw], [R.dev(b) for b in vb], codes[1])
+    head = B.brl_head(pol, val)
+    logits = torch.empty((batch, dims_p[-1]), dtype=torch.float32, device="cuda")
+    value = torch.empty((batch,), dtype=torch.float32, device="cuda")
+    ws = R.Workspace(B.brl_head_workspace_bytes(head, batch))
+    B.policy_value_head(head, R.dev(h), batch, logits, value, ws.buf)
+    l_ref, v_ref = O.policy_value_head(h, O.MLP(pw, pb, acts[0]), O.MLP(vw, vb, acts[1]))
+    assert np.abs(logits.cpu().numpy() - l_ref).max() <= 1e-6 * np.abs(l_ref).max()
+    assert np.abs(value.cpu().numpy() - np.asarray(v_ref).reshape(-1)).max() <= 1e-6 * max(np.abs(v_ref).max(), 1.0)
