@@ -73,10 +73,11 @@ __device__ inline int plane_offset(int r, int chunk) {
     return r * RS + ((chunk ^ ((r / RPB) & (CH - 1))) << 4);
 }
 
-template <int DHP, int VW>
-__device__ inline void stage_rope_rows(const float* rows, int ld, int n_valid, const float* cp, const float* sp,
-                                       int dh, float scale, char* region, int lane, int it_begin = 0,
-                                       int it_end = 32 / (64 / (DHP / VW))) {
+// NIT of the block's load instructions, from it_begin on: a share of the rows for each of several wavefronts.  The count
+// is a template argument so that all of a wavefront's loads are in flight together (at most 32 / VW of them).
+template <int DHP, int VW, int NIT = 32 / (64 / (DHP / VW))>
+__device__ __forceinline__ void stage_rope_rows(const float* rows, int ld, int n_valid, const float* cp, const float* sp,
+                                                int dh, float scale, char* region, int lane, int it_begin = 0) {
     typedef typename VecOf<VW>::type V;
     constexpr int LPR = DHP / VW, RPI = 64 / LPR;     // lanes per row, rows per instruction
     const int half = dh / 2;
@@ -88,8 +89,9 @@ __device__ inline void stage_rope_rows(const float* rows, int ld, int n_valid, c
     const int ds = in_head ? d : 0;
     const int i = in_head ? (first ? d : d - half) : 0;
     const int dp = in_head ? (first ? d + half : d - half) : 0;
-#pragma unroll(32 / VW)
-    for (int it = it_begin; it < it_end; ++it) {
+#pragma unroll(NIT < 32 / VW ? NIT : 32 / VW)
+    for (int u = 0; u < NIT; ++u) {
+        const int it = it_begin + u;
         const int r = it * RPI + lane / LPR;
         const int rc = min(r, n_valid - 1);
         const float* row = rows + (size_t)rc * ld;
@@ -146,9 +148,8 @@ __global__ __launch_bounds__(256) void attn_pack_kernel(PackArgs a) {
 
     // k head: each wavefront stages a quarter of the rows, then writes a quarter of the fragments
     constexpr int ITS = 32 / (64 / (DHP / VW));
-    stage_rope_rows<DHP, VW>(rows + dq + hd * a.dh, a.ld, n_valid, a.cos_t + (size_t)rb * 32 * half,
-                             a.sin_t + (size_t)rb * 32 * half, a.dh, 1.0f, park, lane, wave * (ITS / 4),
-                             (wave + 1) * (ITS / 4));
+    stage_rope_rows<DHP, VW, ITS / 4>(rows + dq + hd * a.dh, a.ld, n_valid, a.cos_t + (size_t)rb * 32 * half,
+                                      a.sin_t + (size_t)rb * 32 * half, a.dh, 1.0f, park, lane, wave * (ITS / 4));
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < KS / 2; ++q) {
@@ -201,21 +202,25 @@ struct AttnTile {
         }
     }
 
-    // one block of 32 keys against the wavefront's 32 queries
-    static __device__ inline void compute(const uint4* st, const v8h (&qh)[KS], const v8h (&ql)[KS], v16f (&o)[DB],
-                                          float& m_run, float& l_run, bool diagonal, int lane) {
-        const int qi = lane & 31, h = lane >> 5;
+    // scores of one block of 32 keys against the wavefront's 32 queries, kf(ks, plane) = key fragment
+    template <class KF>
+    static __device__ __forceinline__ v16f scores(KF&& kf, const v8h (&qh)[KS], const v8h (&ql)[KS]) {
         v16f s;
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[v] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const v8h kfh = __builtin_bit_cast(v8h, st[(ks * 2 + 0) * 64 + lane]);
-            const v8h kfl = __builtin_bit_cast(v8h, st[(ks * 2 + 1) * 64 + lane]);
+            const v8h kfh = kf(ks, 0), kfl = kf(ks, 1);
             s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kfl, qh[ks], s, 0, 0, 0);
             s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kfh, ql[ks], s, 0, 0, 0);
             s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kfh, qh[ks], s, 0, 0, 0);
         }
+        return s;
+    }
+
+    // running softmax: probabilities of the block as fp16 hi / lo, returns the factor of what was accumulated before
+    static __device__ __forceinline__ float softmax(v16f& s, float& m_run, float& l_run, bool diagonal, int lane, v8h (&ph)[2], v8h (&pl)[2]) {
+        const int qi = lane & 31, h = lane >> 5;
         float bmax = -INFINITY;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -227,7 +232,6 @@ struct AttnTile {
         const float m_new = fmaxf(m_run, bmax);                 // finite: key 0 of the block is visible
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         float psum = 0.f;
-        v8h ph[2], pl[2];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float pv = __builtin_amdgcn_exp2f(s[v] - m_new);
@@ -238,18 +242,32 @@ struct AttnTile {
         }
         l_run = l_run * alpha + psum;
         m_run = m_new;
+        return alpha;
+    }
+
+    // o += V^T P^T for 32 components, vf(t, plane) = transposed value fragment
+    template <class VF>
+    static __device__ __forceinline__ void values(VF&& vf, const v8h (&ph)[2], const v8h (&pl)[2], v16f& o) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const v8h vfh = vf(t, 0), vfl = vf(t, 1);
+            o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfl, ph[t], o, 0, 0, 0);
+            o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfh, pl[t], o, 0, 0, 0);
+            o = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfh, ph[t], o, 0, 0, 0);
+        }
+    }
+
+    // one staged block of 32 keys against the wavefront's 32 queries
+    static __device__ __forceinline__ void compute(const uint4* st, const v8h (&qh)[KS], const v8h (&ql)[KS], v16f (&o)[DB],
+                                          float& m_run, float& l_run, bool diagonal, int lane) {
+        v16f s = scores([&](int ks, int plane) { return __builtin_bit_cast(v8h, st[(ks * 2 + plane) * 64 + lane]); }, qh, ql);
+        v8h ph[2], pl[2];
+        const float alpha = softmax(s, m_run, l_run, diagonal, lane, ph, pl);
 #pragma unroll
         for (int r = 0; r < DB; ++r) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) o[r][v] *= alpha;
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const v8h vfh = __builtin_bit_cast(v8h, st[(KS * 2 + (r * 2 + t) * 2 + 0) * 64 + lane]);
-                const v8h vfl = __builtin_bit_cast(v8h, st[(KS * 2 + (r * 2 + t) * 2 + 1) * 64 + lane]);
-                o[r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfl, ph[t], o[r], 0, 0, 0);
-                o[r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfh, pl[t], o[r], 0, 0, 0);
-                o[r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfh, ph[t], o[r], 0, 0, 0);
-            }
+            values([&](int t, int plane) { return __builtin_bit_cast(v8h, st[(KS * 2 + (r * 2 + t) * 2 + plane) * 64 + lane]); }, ph, pl, o[r]);
         }
     }
 };
@@ -258,7 +276,11 @@ struct AttnTile {
 // Four is what is launched: eight halved the K / V traffic but ran 12-19 % slower on both
 // measured shapes (fewer resident workgroups, longer tails).
 constexpr int ATTN_WPG = 4;
-constexpr int SHORT_MAX_WORK = 1024;      // beyond this many workgroups the two-kernel path keeps more of them resident
+// One-key-block states: a workgroup per (state, query head).  From some 8000 workgroups on, groups of four or more query
+// heads do better with their K / V staged once per group by the two-kernel path (2000 x 32 tokens, 20 / 5 heads of 128:
+// 472 us against 508; 200 x 27: 46 against 44, 1 x 27: 9.5 - a four-head workgroup of its own - against 5.5); smaller
+// groups leave that path's wavefronts idle (1000 x 20, 32 / 32 heads of 100: 950 us against 431).
+constexpr int SHORT_MAX_WORK = 8192;
 // QPRE: the q rows arrive as fragments (rotated, scaled, split by the kernel that produced them) and are read
 // straight into the operand registers; otherwise they are staged from the fp32 rows here.
 template <int DHP, int VW, int WPG, bool QPRE = false>
@@ -373,118 +395,82 @@ __global__ __launch_bounds__(WPG * 64, 2) void attention_frag_kernel(FragArgs a)
     }
 }
 
-// States of at most 32 tokens (one key block): one kernel, no fragment round trip through
-// memory.  A workgroup = (state, key/value head, up to four query heads of its group).  All
-// global reads are requested in one phase by two sets of wavefronts side by side: four stage
-// one q head each, four stage a quarter of the k rows each and hold v in registers; after one
-// barrier the k and v fragments are laid out in LDS exactly as attn_pack_kernel lays them out
-// in memory, and the block is computed by the same code as in the general kernel.  Such a
-// launch is latency bound.
+// States of at most 32 tokens (one key block): one kernel, no fragment round trip through memory.  A workgroup = one
+// query head of one state; such a launch is latency bound, so everything is requested at once by as many wavefronts as
+// the work splits into: DB wavefronts stage a share of the q rows each and request the v components they will multiply
+// (32 of them, straight into the operand layout), DB more stage a share of the k rows.  After one barrier each of the
+// first DB wavefronts takes the whole 32 x 32 scores (redundant, but side by side) and finishes its 32 components.
+// Same MFMAs in the same order as the general kernel: same bits.
 template <int DHP, int VW>
-__global__ __launch_bounds__(512) void attention_short_kernel(FragArgs a) {
+__global__ __launch_bounds__(DHP * 4) void attention_short_kernel(FragArgs a) {
     using T = AttnTile<DHP>;
-    constexpr int KS = T::KS, DB = T::DB;
+    constexpr int KS = T::KS, DB = T::DB;                 // 2 DB wavefronts
     constexpr int REG = 128 * DHP;                        // bytes of one staged 32-row block (hi and lo planes)
-    __shared__ __attribute__((aligned(1024))) char qpark[4 * REG];
+    __shared__ __attribute__((aligned(1024))) char qpark[REG];
     __shared__ __attribute__((aligned(1024))) char kpark[REG];
-    __shared__ __attribute__((aligned(1024))) uint4 kvst[T::KVFR * 64];
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int group = a.Hq / a.Hkv;
-    const int chunks = (group + 3) / 4;
-    const int w = blockIdx.x;
-    const int c = w % chunks;
-    const int j = (w / chunks) % a.Hkv;
-    const int b = w / (chunks * a.Hkv);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int head = blockIdx.x % a.Hq, b = blockIdx.x / a.Hq;
+    const int j = head / (a.Hq / a.Hkv);
     const int len = seq_len(a.sm, b, a.S);                // 1 .. 32
     if (len <= 0) return;
     const size_t row0 = (size_t)seq_row0(a.sm, b, a.S);
-    const bool qside = wave < 4;                          // wavefronts 0-3: one q head each; 4-7: k and v
-    const int u = 4 * c + (wave & 3);
-    const bool live = qside && u < group;
-    const int head = j * group + (live ? u : 0);
     const int dq = a.Hq * a.dh, dkv = a.Hkv * a.dh;
     const float* rows = a.qkv + row0 * a.ld;
-
-    // ---- one phase of global reads, the two sides in parallel
-    char* region = qpark + (wave & 3) * REG;
-    constexpr int ITS = 32 / (64 / (DHP / VW));
-    constexpr int VR = (128 * DB + 255) / 256;            // v: thread t of 128 * DB owns lane slot (d, h) of (block r, step tt)
-    float vv[VR][8];
-    const int tk = threadIdx.x - 256;
-    if (qside) {
-        if (live) stage_rope_rows<DHP, VW>(rows + head * a.dh, a.ld, len, a.cos_t, a.sin_t, a.dh, a.qscale, region, lane);
-    } else {
-        const int col0 = dq + dkv + j * a.dh;
+    const int dl = lane & 31, h = lane >> 5;
+    constexpr int ITS = 32 / (64 / (DHP / VW));           // load instructions per 32-row block
+    static_assert(ITS % DB == 0, "the rows split evenly over DB wavefronts");
+    const bool first = wave < DB;
+    const int share = first ? wave : wave - DB;
+    float vv[2][8];
+    // lane (dl, h) of step tt: keys 16 tt + 8 (e >> 2) + 4 h + (e & 3) of component 32 wave + dl.  Keys past the state's
+    // end repeat its last row (their probabilities are exactly zero), components past the head are never stored: no
+    // condition on a load, which would keep the next one waiting
+    if (first) {
+        const int d = 32 * wave + dl;
+        const float* col = rows + dq + dkv + j * a.dh + min(d, a.dh - 1);
 #pragma unroll
-        for (int q = 0; q < VR; ++q) {
-            const int t = tk + 256 * q;
-            const int dl = t & 31, h = (t >> 5) & 1, tt = (t >> 6) & 1, r = t >> 7;
-            const int d = 32 * r + dl;
+        for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int row = 16 * tt + 8 * (e >> 2) + 4 * h + (e & 3);
-                vv[q][e] = (t < 128 * DB && row < len && d < a.dh) ? rows[(size_t)row * a.ld + col0 + d] : 0.f;
+                vv[tt][e] = col[(unsigned)(min(row, len - 1) * a.ld)];
             }
-        }
-        stage_rope_rows<DHP, VW>(rows + dq + j * a.dh, a.ld, len, a.cos_t, a.sin_t, a.dh, 1.0f, kpark, lane,
-                                 (wave - 4) * (ITS / 4), (wave - 3) * (ITS / 4));
     }
+    stage_rope_rows<DHP, VW, ITS / DB>(rows + (first ? head * a.dh : dq + j * a.dh), a.ld, len, a.cos_t, a.sin_t, a.dh,
+                                       first ? a.qscale : 1.0f, first ? qpark : kpark, lane, share * (ITS / DB));
     __syncthreads();
+    if (!first) return;
 
     v8h qh[KS], ql[KS];
-    if (qside) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            qh[ks] = __builtin_bit_cast(v8h, staged_fragment<DHP>(region, ks, lane, 0));
-            ql[ks] = __builtin_bit_cast(v8h, staged_fragment<DHP>(region, ks, lane, 1));
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < KS / 2; ++q) {
-            const int fr = (wave - 4) * (KS / 2) + q;     // fragment = (k-step, plane)
-            kvst[fr * 64 + lane] = staged_fragment<DHP>(kpark, fr >> 1, lane, fr & 1);
-        }
-#pragma unroll
-        for (int q = 0; q < VR; ++q) {
-            const int t = tk + 256 * q;
-            if (t < 128 * DB) {
-                const int dl = t & 31, h = (t >> 5) & 1, tt = (t >> 6) & 1, r = t >> 7;
-                const int ln = h * 32 + dl;
-                kvst[(KS * 2 + (r * 2 + tt) * 2 + 0) * 64 + ln] = pack8h(vv[q], false);
-                kvst[(KS * 2 + (r * 2 + tt) * 2 + 1) * 64 + ln] = pack8h(vv[q], true);
-            }
-        }
+    for (int ks = 0; ks < KS; ++ks) {
+        qh[ks] = __builtin_bit_cast(v8h, staged_fragment<DHP>(qpark, ks, lane, 0));
+        ql[ks] = __builtin_bit_cast(v8h, staged_fragment<DHP>(qpark, ks, lane, 1));
     }
-    __syncthreads();
-    if (!qside) return;
-
-    v16f o[DB];
-#pragma unroll
-    for (int r = 0; r < DB; ++r)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[r][v] = 0.f;
+    v16f s = T::scores([&](int ks, int plane) { return __builtin_bit_cast(v8h, staged_fragment<DHP>(kpark, ks, lane, plane)); }, qh, ql);
     float m_run = -INFINITY, l_run = 0.f;
-    T::compute(kvst, qh, ql, o, m_run, l_run, true, lane);
+    v8h ph[2], pl[2];
+    T::softmax(s, m_run, l_run, true, lane, ph, pl);
+    v16f o;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[v] = 0.f;
+    T::values([&](int t, int plane) { return __builtin_bit_cast(v8h, pack8h(vv[t], plane == 1)); }, ph, pl, o);
 
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-    const int pos = lane & 31;
-    if (live && pos < len) {
+    if (dl < len) {
         const float inv = 1.0f / l_tot;
-        const int h = lane >> 5;
-        float* op = a.out + (row0 + pos) * ((size_t)a.Hq * a.dh) + (size_t)head * a.dh;
+        float* op = a.out + (row0 + dl) * ((size_t)a.Hq * a.dh) + (size_t)head * a.dh;
 #pragma unroll
-        for (int r = 0; r < DB; ++r)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-                const int d = 32 * r + 8 * g4 + 4 * h;
-                if (d < a.dh) {
-                    float4 v;
-                    v.x = o[r][4 * g4 + 0] * inv; v.y = o[r][4 * g4 + 1] * inv;
-                    v.z = o[r][4 * g4 + 2] * inv; v.w = o[r][4 * g4 + 3] * inv;
-                    *reinterpret_cast<float4*>(op + d) = v;
-                }
+        for (int g4 = 0; g4 < 4; ++g4) {
+            const int d = 32 * wave + 8 * g4 + 4 * h;
+            if (d < a.dh) {
+                float4 v;
+                v.x = o[4 * g4 + 0] * inv; v.y = o[4 * g4 + 1] * inv;
+                v.z = o[4 * g4 + 2] * inv; v.w = o[4 * g4 + 3] * inv;
+                *reinterpret_cast<float4*>(op + d) = v;
             }
+        }
     }
 }
 
@@ -506,9 +492,8 @@ namespace {
 
 template <int DHP, int VW>
 void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, hipStream_t s) {
-    if (p.NRB == 1 && n_work <= SHORT_MAX_WORK) {         // few short states: the one-kernel path
-        const int chunks = (f.Hq / f.Hkv + 3) / 4;
-        hipLaunchKernelGGL((attention_short_kernel<DHP, VW>), dim3((unsigned)(f.B * f.Hkv * chunks)), dim3(512), 0, s, f);
+    if (p.NRB == 1 && (f.Hq / f.Hkv < 4 || (long)f.B * f.Hq <= SHORT_MAX_WORK)) {
+        hipLaunchKernelGGL((attention_short_kernel<DHP, VW>), dim3((unsigned)(f.B * f.Hq)), dim3(DHP * 4), 0, s, f);
         return;
     }
     hipLaunchKernelGGL((attn_pack_kernel<DHP, VW>), pgrid, dim3(256), 0, s, p);

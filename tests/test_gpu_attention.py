@@ -175,3 +175,17 @@ def test_attention_argument_checks():
     with pytest.raises(B.BitrlError) as e:
         B.attention_forward(qkv, 1, 8, None, None, 1, 1, 64, 10000.0, B.BRL_ATTN_MFMA, out, small.buf)
     assert e.value.status == B.BRL_ENOSPC
+
+
+@pytest.mark.parametrize("hq,hkv,dh,S", [(8, 2, 128, 27), (8, 1, 100, 32), (8, 2, 64, 1), (8, 2, 16, 9)])
+def test_short_state_kernels_meet_at_the_dispatch_line(hq, hkv, dh, S):
+    """1024 states x 8 heads are the last batch of the one-kernel path, one state more takes pack + fragment kernels:
+    the states they share get the same bits, and the last one matches the oracle."""
+    B, R = _mods()
+    qkv = synth.normal(37, 5, (1025 * S, (hq + 2 * hkv) * dh))
+    one = _run(B, R, qkv[:1024 * S], [S] * 1024, S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA)
+    two = _run(B, R, qkv, [S] * 1025, S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA)
+    assert np.array_equal(one, two[:1024 * S])
+    ref = _oracle(qkv[1024 * S:], [S], hq, hkv, dh, 10000.0)[0]
+    got = two[1024 * S:].reshape(ref.shape)
+    assert np.abs(got - ref).max() <= ATTN_REL * np.abs(ref).max()
