@@ -142,8 +142,6 @@ int bitlinear_forward(const void* packed, const float* beta, int N, int K,
  * capture).  Every call on one GPU shares that GPU's array: the contents are
  * rewritten by each call (nothing has to start at zero), and calls that
  * overlap in time on one GPU (different streams or threads) race - order them.
- * Products that bitlinear_forward would cut along k run uncut here (integer
- * sums: identical results).
  * ------------------------------------------------------------------------ */
 #define BRL_STATIC_SCRATCH_BYTES (16u << 20)
 int bitlinear_forward_static(const void* packed, const float* beta, int N, int K,

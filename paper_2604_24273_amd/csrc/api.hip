@@ -81,7 +81,7 @@ struct Carver {
 
 size_t actbuf_bytes(int M, int K) {
     const size_t Mp = round_up(M, NB), Kp = round_up(K, SBK);
-    return round_up_sz(Mp * Kp, ALIGN) + 3 * round_up_sz(Mp * 4, ALIGN) + round_up_sz(splitk_capacity_ints(M) * 4, ALIGN);
+    return round_up_sz(Mp * Kp, ALIGN) + 3 * round_up_sz(Mp * 4, ALIGN);
 }
 
 ActBuf take_actbuf(Carver& c, int M, int K) {
@@ -91,8 +91,6 @@ ActBuf take_actbuf(Carver& c, int M, int K) {
     a.absmax = c.take<float>(Mp);
     a.dscale = c.take<float>(Mp);
     a.sumq = c.take<int32_t>(Mp);
-    a.splitk_ints = splitk_capacity_ints(M);
-    a.splitk = a.splitk_ints ? c.take<int32_t>(a.splitk_ints) : nullptr;
     return a;
 }
 
@@ -478,11 +476,6 @@ int scratch_of_current_device(char** out) {
     return BRL_OK;
 }
 
-// the quantised activations alone: no k-split partial tiles (products that would cut k run uncut, same bits)
-size_t static_actbuf_bytes(int M, int K) {
-    const size_t Mp = round_up(M, NB), Kp = round_up(K, SBK);
-    return round_up_sz(Mp * Kp, ALIGN) + 3 * round_up_sz(Mp * 4, ALIGN);
-}
 }  // namespace
 
 int bitlinear_forward_static(const void* packed, const float* beta, int N, int K, const void* x, int x_dtype, int M,
@@ -500,7 +493,7 @@ int bitlinear_forward_static(const void* packed, const float* beta, int N, int K
         return launch_gemv(x, x_dtype, M, K, N, static_cast<const uint32_t*>(packed), beta, eps_act, y, residual, xq_dbg,
                            absmax_dbg, acc_dbg, s);
     }
-    const size_t need = static_actbuf_bytes(M, K);
+    const size_t need = actbuf_bytes(M, K);
     if (need > (size_t)BRL_STATIC_SCRATCH_BYTES) {
         set_error("bitlinear_forward_static: %d tokens x %d features need %zu bytes of scratch, the built-in array holds %zu; "
                   "use bitlinear_forward with a workspace",
@@ -509,15 +502,8 @@ int bitlinear_forward_static(const void* packed, const float* beta, int N, int K
     }
     char* base = nullptr;
     if (int rc = scratch_of_current_device(&base)) return rc;
-    const size_t Mp = round_up(M, NB), Kp = round_up(K, SBK);
     Carver c(base);
-    ActBuf act;
-    act.q = c.take<int8_t>(Mp * Kp);
-    act.absmax = c.take<float>(Mp);
-    act.dscale = c.take<float>(Mp);
-    act.sumq = c.take<int32_t>(Mp);
-    act.splitk = nullptr;
-    act.splitk_ints = 0;
+    const ActBuf act = take_actbuf(c, M, K);
     QuantArgs qa;
     memset(&qa, 0, sizeof(qa));
     qa.x = x; qa.x_dtype = x_dtype; qa.gain = nullptr; qa.eps_norm = 0.f; qa.eps_act = eps_act;

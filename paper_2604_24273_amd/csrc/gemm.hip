@@ -21,19 +21,16 @@
 //                      are staged in LDS with direct global->LDS loads, double
 //                      buffered; in GLU mode the epilogue writes
 //                      h = max(G,0)^2 U from interleaved gate / up blocks.
-//                      A launch of about one tile per compute unit or fewer puts
-//                      eight wavefronts of 64 x 32 on the 128 x 128 tile.
+//                      Launches of up to 450 tiles of 128 x 128 put eight wavefronts
+//                      of 64 x 32 on the tile.
 //                      gemm_lds_attn_kernel is the wide tile on the q | k | v product of a
 //                      uniform batch at head_dim 128: its epilogue rotates q and k and
 //                      writes them and v as the fp16 hi / lo fragments the attention
 //                      kernel reads (no fp32 rows, no pack kernel).
 //                      gemm_lds_w8_kernel is the same loop on int8 weight blobs.
-//                      With few tiles and a long k several workgroups share a
-//                      tile, each on its own k range (raw int32 partial tiles,
-//                      splitk_epilogue_kernel sums and rescales them).
-//   gemm_direct_kernel up to a few hundred tokens: no LDS staging, the 4 to 16
-//                      wavefronts of a workgroup split k and finish the tile
-//                      together through LDS.
+//   gemm_direct_kernel launches that would leave most compute units with one tile or
+//                      none: no LDS staging, the 4 to 16 wavefronts of a workgroup
+//                      split k and finish the tile together through LDS.
 // launch_gemm picks among them by how many workgroups each would make.
 #include <cstring>
 
@@ -45,11 +42,6 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-
-constexpr long DIRECT_MAX_WGS = 640;          // 64 x 32 tiles, 8 wavefronts
-constexpr long DIRECT16_MAX_WGS = 512;        // 32 x 32 tiles, 16 wavefronts
-constexpr long DIRECT16_MAX_WGS_GLU = 900;    // 32 x 32 output tiles of the GLU form, 8 wavefronts
-constexpr long NARROW8_MAX_TILES = 320;       // 128 x 128 tiles up to which eight wavefronts share a tile
 
 struct GemmArgs {
     const uint4* A;          // tiled activations, 16 bytes per lane per fragment
@@ -72,9 +64,6 @@ struct GemmArgs {
     double ops;              // int8 operations of the product (for the timing hooks)
     int glu;                 // 1: segments are (gate, up) of equal size, interleaved block by block;
                              //    the epilogue emits h = (max(G,0) * max(G,0)) * U, one column per pair
-    int splits;              // > 1: k is cut into `splits` ranges of sb_per_split super-blocks, one workgroup per
-    int sb_per_split;        //      (tile, range); raw int32 partial tiles go to `partials` [splits][M][nnb * 32]
-    int32_t* partials;       //      and splitk_epilogue_kernel finishes the product
     // attention-operand epilogue (the q | k | v product of a uniform batch, head_dim 128): instead of fp32 rows the
     // kernel writes what the attention kernel reads - q and k rotated (q also scaled) as fp16 hi / lo MFMA fragments,
     // v transposed fragments - see epilogue_attn
@@ -122,14 +111,11 @@ __device__ inline v4i as_v4i(const uint4& u) {
 // XCD-aware tile order: workgroup w runs on XCD (w & 7); each XCD gets a
 // contiguous run of tiles, walked in groups of `group_m` row tiles so that the
 // tiles resident on one XCD share activation and weight panels in its L2.
-__device__ inline bool tile_of_block(const GemmArgs& g, int& tile_m, int& tile_n, int& split) {
-    const int tiles = g.tiles_m * g.tiles_n;
-    const int total = tiles * g.splits;
+__device__ inline bool tile_of_block(const GemmArgs& g, int& tile_m, int& tile_n) {
+    const int total = g.tiles_m * g.tiles_n;
     const int per_xcd = (total + 7) / 8;
-    const int T0 = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_xcd || T0 >= total) return false;
-    split = T0 / tiles;
-    const int T = T0 - split * tiles;
+    const int T = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || T >= total) return false;
     const int gsz = g.group_m * g.tiles_n;
     const int grp = T / gsz;
     const int first_m = grp * g.group_m;
@@ -504,75 +490,6 @@ __device__ inline void epilogue_attn(const GemmArgs& g, v16i (&acc)[TM][TN], int
     }
 }
 
-// k-split launches: the raw accumulators of this workgroup's k range, row-major, 16 bytes per lane
-template <int TM, int TN>
-__device__ inline void epilogue_partial(const GemmArgs& g, v16i (&acc)[TM][TN], int mb0, int nb0, int split, int lane,
-                                        int* scr) {
-    constexpr int LD = Epi<TM, TN>::LD;
-    constexpr int LPR = TN * 8;
-    constexpr int RPP = 64 / LPR;
-    constexpr int NP = 16 / RPP;
-    static_assert(64 % LPR == 0, "TN must be a power of two");
-    const int c4 = lane % LPR, r0 = lane / LPR;
-    const int ldp = g.nnb * 32;
-    const bool col_ok = nb0 + (c4 >> 3) < g.nnb;
-    int32_t* dst = g.partials + (size_t)split * g.M * ldp + nb0 * 32 + 4 * c4;
-#pragma unroll
-    for (int idx = 0; idx < 2 * TM; ++idx) {
-        const int mbase = (mb0 + (idx >> 1)) * 32 + (idx & 1) * 16;
-        scatter_half<TM, TN>(acc, idx >> 1, idx & 1, lane, scr);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const int row = p * RPP + r0;
-            const int4 a = *reinterpret_cast<const int4*>(&scr[row * LD + 4 * c4]);
-            if (col_ok && mbase + row < g.M) *reinterpret_cast<int4*>(dst + (size_t)(mbase + row) * ldp) = a;
-        }
-    }
-}
-
-// Sums the partial tiles of a k-split launch (exact integer sums) and applies the same rescale as the
-// one-pass epilogues.  One thread per token row and four columns of a weight block (a gate / up pair in
-// GLU mode).
-__global__ __launch_bounds__(256) void splitk_epilogue_kernel(GemmArgs g) {
-    const int nob = g.glu ? g.nnb / 2 : g.nnb;                 // output column blocks
-    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (size_t)g.M * nob * 8) return;
-    const int c = 4 * (int)(t & 7), ob = (int)((t >> 3) % nob), m = (int)((t >> 3) / nob);
-    const int gnb = g.glu ? 2 * ob : ob;
-    int seg, col0, ncols;
-    block_columns(g, gnb, seg, col0, ncols);
-    if (c >= ncols) return;
-    const int ldp = g.nnb * 32;
-    int a0[4] = {0, 0, 0, 0}, a1[4] = {0, 0, 0, 0};
-    for (int sp = 0; sp < g.splits; ++sp) {
-        const int32_t* src = g.partials + ((size_t)sp * g.M + m) * ldp + gnb * 32 + c;
-        const int4 v = *reinterpret_cast<const int4*>(src);
-        a0[0] += v.x; a0[1] += v.y; a0[2] += v.z; a0[3] += v.w;
-        if (g.glu) {
-            const int4 u = *reinterpret_cast<const int4*>(src + 32);
-            a1[0] += u.x; a1[1] += u.y; a1[2] += u.z; a1[3] += u.w;
-        }
-    }
-    const float d = g.dscale[m];
-    const int sq = g.sumq ? g.sumq[m] : 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if (c + e >= ncols) break;
-        const size_t o = (size_t)m * g.ldy + col0 + c + e;
-        if (g.glu) {
-            const float G = ((float)(a0[e] - sq) * d) * (*g.beta[0]);
-            const float U = ((float)(a1[e] - sq) * d) * (*g.beta[1]);
-            const float pz = fmaxf(G, 0.f);
-            g.y[o] = (pz * pz) * U;
-        } else {
-            float val = ((float)(a0[e] - sq) * d) * (*g.beta[seg]);
-            if (g.residual) val = val + res_at(g, o);
-            g.y[o] = val;
-            if (g.acc_dbg) g.acc_dbg[o] = a0[e] - sq;
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Many-token kernel: WM x WN wavefronts, each TM x TN tiles; both operands staged
 // through LDS with direct global->LDS loads, double buffered.
@@ -656,8 +573,8 @@ __device__ __forceinline__ void gemm_lds_body(const GemmArgs& g) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int wn = wave % WN, wm = wave / WN;
-    int tile_m, tile_n, split;
-    if (!tile_of_block(g, tile_m, tile_n, split)) return;
+    int tile_m, tile_n;
+    if (!tile_of_block(g, tile_m, tile_n)) return;
 
     const int mb_tile0 = tile_m * WM * TM;
     const int mb0 = mb_tile0 + wm * TM;
@@ -704,9 +621,7 @@ __device__ __forceinline__ void gemm_lds_body(const GemmArgs& g) {
     // Double buffering with two distinct LDS objects: while one is read, the
     // other is filled.  A stage requested in one step is waited for (vmcnt 0)
     // at the top of the next, so its latency hides behind 4*TM*TN MFMAs.
-    // stages of this workgroup's k range (one range covering all of k when splits == 1)
-    const int sb_first = split * g.sb_per_split * Tile::SPB;
-    const int sb_last = min(g.nsb, (split + 1) * g.sb_per_split) * Tile::SPB;
+    const int sb_first = 0, sb_last = g.nsb * Tile::SPB;       // stages
     Tile::issue(asrc, bsrc, sb_first, stage0, wave);
     int sb = sb_first;
     for (; sb + 1 < sb_last; sb += 2) {
@@ -734,8 +649,6 @@ __device__ __forceinline__ void gemm_lds_body(const GemmArgs& g) {
     if constexpr (ATTN) {
         static_assert(WN == 4 && TN == 2, "a 256-column tile is two heads of 128: four wavefronts of 32 + 32 columns");
         epilogue_attn<TM, TN>(g, acc, mb0, nb0, beta, lane, scr);
-    } else if (g.splits > 1) {
-        epilogue_partial<TM, TN>(g, acc, mb0, nb0, split, lane, scr);
     } else {
         epilogue<TM, TN>(g, acc, mb0, nb0, beta, lane, scr);
     }
@@ -758,33 +671,78 @@ __global__ __launch_bounds__(WM * WN * 64, 4) void gemm_lds_w8_kernel(GemmArgs g
 }
 
 // ---------------------------------------------------------------------------
-// Few-token kernel: operands straight from L2 to registers; WK wavefronts split k.
+// Few-token kernel: operands straight from L2 to registers; one TM x TN tile per workgroup, WK wavefronts split k.
+// D super-blocks of k are in flight per wavefront: with one, each super-block of its share costs a memory latency.
 // ---------------------------------------------------------------------------
-template <int TM, int TN, int WM, int WN, int WK, bool W8 = false>
-__global__ __launch_bounds__(WM * WN * WK * 64) void gemm_direct_kernel(GemmArgs g) {
-    static_assert(WM * WN * WK == 4 || WM * WN * WK == 8 || WM * WN * WK == 16, "4, 8 or 16 wavefronts per workgroup");
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int wk = wave % WK;
-    const int wn = (wave / WK) % WN;
-    const int wm = wave / (WK * WN);
-    int tile_m, tile_n, split;
-    if (!tile_of_block(g, tile_m, tile_n, split)) return;      // splits == 1 here
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(1))) u32x4* gptr16;
 
-    const int mb0 = (tile_m * WM + wm) * TM;
-    const int nb0 = (tile_n * WN + wn) * TN;
-    const uint4* aptr[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int mb = min(mb0 + i, g.nmb - 1);
-        aptr[i] = g.A + (size_t)mb * g.nsb * 256 + lane;
+// Output item t of a TM x TN tile: E (four or one) consecutive columns of one token row.  `at` is its place in an
+// accumulator block parked as [16 registers][64 lanes] (see the epilogues above).
+template <int TM, int TN, int E>
+struct DirectOut {
+    int c, i, j0, m, at, seg, ncols;
+    size_t off;
+    bool in_tile;
+    __device__ inline DirectOut(const GemmArgs& g, int t, int mb0, int nb0) {
+        constexpr int IPB = 32 / E;                              // items per row of a 32-column block
+        constexpr int GB = TN > 1 ? TN / 2 : 1;                  // output column blocks of the tile in GLU mode (TN otherwise)
+        c = E * (t % IPB);
+        const int jb = g.glu ? (t / IPB) % GB : (t / IPB) % TN, r = g.glu ? t / (IPB * GB) : t / (IPB * TN), rr = r & 31;
+        i = r >> 5;
+        j0 = g.glu ? 2 * jb : jb;
+        m = mb0 * 32 + r;
+        at = (4 * (rr >> 3) + (rr & 3)) * 64 + c + 32 * ((rr >> 2) & 1);
+        in_tile = r < TM * 32 && nb0 + j0 < g.nnb;
+        int col0;
+        block_columns(g, min(nb0 + j0, g.nnb - 1), seg, col0, ncols);
+        off = (size_t)m * g.ldy + col0 + c;
     }
-    BCols<TN> bc;
-    bc.init(g, nb0, lane);
+    __device__ inline bool live(const GemmArgs& g) const { return in_tile && m < g.M && c < ncols; }
+};
+
+template <int TM, int TN, int WK, int D, int OCC, bool W8>
+__global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
+    constexpr int NT = WK * 64;
+    constexpr int BW = W8 ? 4 : 1;     // 16-byte weight pieces per lane, 32-row block and super-block
+    constexpr int OUT = TM * TN * 1024;
+    constexpr bool QUADS = OUT / NT >= 4;             // four columns per thread and pass, 16-byte stores
+    constexpr int NP = QUADS ? OUT / NT / 4 : 1;      // passes of the main finishing form
+    constexpr bool EARLY = NP == 1;                   // what it reads from memory is requested ahead of the k loop
+    typedef DirectOut<TM, TN, QUADS ? 4 : 1> Out;
+    typedef DirectOut<TM, TN, 1> OutOne;
+    static_assert(QUADS || OUT / NT == 1, "one item per thread");
+    // One 32 x 32 block: every wavefront parks its part and the finishing threads add them up (64 KB of LDS, one barrier;
+    // 0.3 us ahead of atomic adds there).  Larger tiles add into one copy, so that several workgroups fit a compute unit.
+    constexpr bool PARK = TM * TN == 1;
+    __shared__ __attribute__((aligned(16))) int red[(PARK ? WK : 1) * OUT];
+    const int lane = threadIdx.x & 63;
+    const int wk = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int tile_m, tile_n;
+    if (!tile_of_block(g, tile_m, tile_n)) return;
+    if constexpr (!PARK) {
+        for (int t = threadIdx.x; t < OUT; t += NT) red[t] = 0;
+        __syncthreads();
+    }
+
+    const int mb0 = tile_m * TM, nb0 = tile_n * TN;
+    gptr16 aptr[TM], bptr[TN];
     float beta[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) beta[j] = *g.beta[bc.seg[j]];
+    for (int i = 0; i < TM; ++i) aptr[i] = (gptr16)g.A + (size_t)min(mb0 + i, g.nmb - 1) * g.nsb * 256;
+    {
+        BCols<TN> bc;
+        bc.init(g, nb0, 0);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            bptr[j] = (gptr16)bc.ptr[j];
+            beta[j] = *g.beta[bc.seg[j]];
+        }
+    }
 
+    float d[NP];
+    int sq[NP];
+    float4 res[NP];
     v16i acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -793,147 +751,160 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_direct_kernel(GemmArgs
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
 
-    // k-split variants finish the tile with the whole workgroup, one output element per thread and
-    // pass; what an element needs from memory (its token's scale and code sum, its residual) is
-    // requested here, ahead of the k loop
-    constexpr int NT = WM * WN * WK * 64;
-    constexpr int EPT = WK > 1 ? (TM * TN * 1024 + NT - 1) / NT : 1;
-    float e_d[EPT], e_res[EPT];
-    int e_sq[EPT];
-    if constexpr (WK > 1) {
-        const int ncb = (g.glu && TN > 1) ? TN / 2 : TN;
+    auto request_outputs = [&] {
+        if (!EARLY || (QUADS && !g.fast_epilogue)) return;
 #pragma unroll
-        for (int q = 0; q < EPT; ++q) {
-            const int e = threadIdx.x + q * NT;
-            const int c = e & 31, jb = (e >> 5) % ncb, r = (e >> 5) / ncb;
-            const int m = min(mb0 * 32 + r, g.M - 1);
-            int seg, col0, ncols;
-            block_columns(g, min(nb0 + (g.glu ? 2 * jb : jb), g.nnb - 1), seg, col0, ncols);
-            e_d[q] = g.dscale[m];
-            e_sq[q] = g.sumq ? g.sumq[m] : 0;
-            e_res[q] = (g.residual && c < ncols) ? res_at(g, (size_t)m * g.ldy + col0 + c) : 0.f;
+        for (int p = 0; p < NP; ++p) {
+            Out o(g, (int)threadIdx.x + p * NT, mb0, nb0);
+            const int m = min(o.m, g.M - 1);
+            d[p] = g.dscale[m];
+            sq[p] = g.sumq ? g.sumq[m] : 0;
+            if (g.residual && o.live(g)) {
+                if constexpr (QUADS) res[p] = res4_at(g, o.off);
+                else res[p].x = res_at(g, o.off);
+            }
         }
-    }
-
-    const int sb_per = (g.nsb + WK - 1) / WK;
-    const int sb_begin = wk * sb_per;
-    const int sb_end = min(g.nsb, sb_begin + sb_per);
-
+    };
+    const int sb_begin = wk * g.nsb / WK, sb_end = (wk + 1) * g.nsb / WK;
     if (sb_begin < sb_end) {
-        // weights of a super-block per 32-row block: one packed 16-byte piece per lane (2-bit), or the four
-        // k-step fragments themselves (int8)
-        constexpr int BW = W8 ? 4 : 1;
-        uint4 aq[4][TM];
-        uint4 bq[BW][TN];
-#pragma unroll
-        for (int dd = 0; dd < 4; ++dd)
-#pragma unroll
-            for (int i = 0; i < TM; ++i) aq[dd][i] = aptr[i][((size_t)sb_begin * 4 + dd) * 64];
-#pragma unroll
-        for (int q = 0; q < BW; ++q)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bq[q][j] = bc.ptr[j][((size_t)sb_begin * BW + q) * 64];
-
-        for (int sb = sb_begin; sb < sb_end; ++sb) {
-            const int nxt = min(sb + 1, sb_end - 1);
-            uint4 bnext[BW][TN];
+        u32x4 aq[D][4][TM], bq[D][BW][TN];
+        auto load = [&](int d, int sb) {
 #pragma unroll
             for (int q = 0; q < BW; ++q)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) bnext[q][j] = bc.ptr[j][((size_t)nxt * BW + q) * 64];
+                for (int j = 0; j < TN; ++j) bq[d][q][j] = bptr[j][(unsigned)((sb * BW + q) * 64 + lane)];
+#pragma unroll
+            for (int dd = 0; dd < 4; ++dd)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) aq[d][dd][i] = aptr[i][(unsigned)((sb * 4 + dd) * 64 + lane)];
+        };
+        auto contract = [&](int d) {
 #pragma unroll
             for (int dd = 0; dd < 4; ++dd) {
                 v4i bf[TN];
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    if constexpr (W8) bf[j] = as_v4i(bq[dd][j]);
-                    else bf[j] = expand_codes(pick(bq[0][j], dd));
+                    if constexpr (W8) bf[j] = __builtin_bit_cast(v4i, bq[d][dd][j]);
+                    else bf[j] = expand_codes(bq[d][0][j][dd]);
                 }
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const v4i af = as_v4i(aq[dd][i]);
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af, bf[j], acc[i][j], 0, 0, 0);
-                }
-                // refill this slot with the same k-step of the next super-block
-#pragma unroll
-                for (int i = 0; i < TM; ++i) aq[dd][i] = aptr[i][((size_t)nxt * 4 + dd) * 64];
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(v4i, aq[d][dd][i]), bf[j],
+                                                                          acc[i][j], 0, 0, 0);
             }
+        };
 #pragma unroll
-            for (int q = 0; q < BW; ++q)
+        for (int d = 0; d < D; ++d) load(d, min(sb_begin + d, sb_end - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        request_outputs();
+        __builtin_amdgcn_sched_barrier(0);
+        int sb = sb_begin;
+        for (; sb + 2 * D <= sb_end; sb += D)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) bq[q][j] = bnext[q][j];
+            for (int d = 0; d < D; ++d) {
+                contract(d);
+                load(d, sb + d + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        if (sb + D < sb_end) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                contract(d);
+                load(d, min(sb + d + D, sb_end - 1));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            sb += D;
         }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (sb + d < sb_end) contract(d);
+    } else {
+        request_outputs();
     }
 
-    if constexpr (WK > 1) {
-        // k-split: every wavefront parks its partial accumulators in LDS; 32 consecutive threads then
-        // take 32 consecutive columns of one token row.  The sum over the k-parts is an exact integer sum.
-        static_assert(WM == 1 && WN == 1, "the k-split variants have one tile per workgroup");
-        __shared__ int red[WK * TM * TN * 16 * 64];
+    // The k-parts meet in LDS (integer sums: any order gives the same bits).
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) red[((wk * TM * TN + i * TN + j) * 16 + v) * 64 + lane] = acc[i][j][v];
-        __syncthreads();
-        const int ncb = (g.glu && TN > 1) ? TN / 2 : TN;                      // output column blocks of the tile
-        const int total = TM * 32 * ncb * 32;
-#pragma unroll
-        for (int q = 0; q < EPT; ++q) {
-            const int e = threadIdx.x + q * NT;
-            const int c = e & 31, jb = (e >> 5) % ncb, r = (e >> 5) / ncb;     // column, column block, token row of the tile
-            const int i = r >> 5, rr = r & 31;
-            const int m = mb0 * 32 + r;
-            const int v = 4 * (rr >> 3) + (rr & 3), ln = c + 32 * ((rr >> 2) & 1);
-            const int j0 = g.glu ? 2 * jb : jb;
-            int seg, col0, ncols;
-            block_columns(g, min(nb0 + j0, g.nnb - 1), seg, col0, ncols);
-            if (e >= total || m >= g.M || nb0 + j0 >= g.nnb || c >= ncols) continue;
-            const size_t o = (size_t)m * g.ldy + col0 + c;
-            int a0 = 0, a1 = 0;
-#pragma unroll
-            for (int p = 0; p < WK; ++p) {
-                a0 += red[((p * TM * TN + i * TN + j0) * 16 + v) * 64 + ln];
-                if (g.glu) a1 += red[((p * TM * TN + i * TN + j0 + 1) * 16 + v) * 64 + ln];
+            for (int v = 0; v < 16; ++v) {
+                if constexpr (PARK) red[(wk * 16 + v) * 64 + lane] = acc[i][j][v];
+                else atomicAdd(&red[((i * TN + j) * 16 + v) * 64 + lane], acc[i][j][v]);
             }
-            float bsel = beta[0];
+    __syncthreads();
+
+    if (QUADS && g.fast_epilogue) {
 #pragma unroll
-            for (int j = 1; j < TN; ++j)
-                if (j0 == j) bsel = beta[j];
+        for (int p = 0; p < NP; ++p) {
+            Out o(g, (int)threadIdx.x + p * NT, mb0, nb0);
+            if (!o.live(g)) continue;
+            if (!EARLY) { d[p] = g.dscale[o.m]; sq[p] = g.sumq ? g.sumq[o.m] : 0; }
+            const int4 a0 = *reinterpret_cast<const int4*>(&red[(o.i * TN + o.j0) * 1024 + o.at]);
+            float4 val;
             if (g.glu) {
-                const float G = ((float)(a0 - e_sq[q]) * e_d[q]) * beta[0];
-                const float U = ((float)(a1 - e_sq[q]) * e_d[q]) * beta[TN > 1 ? 1 : 0];
-                const float pz = fmaxf(G, 0.f);
-                g.y[o] = (pz * pz) * U;
+                const int4 a1 = *reinterpret_cast<const int4*>(&red[(o.i * TN + (TN > 1 ? o.j0 + 1 : 0)) * 1024 + o.at]);
+                const int gi[4] = {a0.x, a0.y, a0.z, a0.w}, ui[4] = {a1.x, a1.y, a1.z, a1.w};
+                float hv[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float G = ((float)(gi[q] - sq[p]) * d[p]) * beta[0];
+                    const float U = ((float)(ui[q] - sq[p]) * d[p]) * beta[TN > 1 ? 1 : 0];
+                    const float pz = fmaxf(G, 0.f);
+                    hv[q] = (pz * pz) * U;
+                }
+                val = make_float4(hv[0], hv[1], hv[2], hv[3]);
             } else {
-                float val = ((float)(a0 - e_sq[q]) * e_d[q]) * bsel;
-                if (g.residual) val = val + e_res[q];
-                g.y[o] = val;
-                if (g.acc_dbg) g.acc_dbg[o] = a0 - e_sq[q];
+                const float bsel = *g.beta[o.seg];
+                val.x = ((float)(a0.x - sq[p]) * d[p]) * bsel;
+                val.y = ((float)(a0.y - sq[p]) * d[p]) * bsel;
+                val.z = ((float)(a0.z - sq[p]) * d[p]) * bsel;
+                val.w = ((float)(a0.w - sq[p]) * d[p]) * bsel;
+                if (g.residual) {
+                    if (!EARLY) res[p] = res4_at(g, o.off);
+                    val.x = val.x + res[p].x; val.y = val.y + res[p].y; val.z = val.z + res[p].z; val.w = val.w + res[p].w;
+                }
             }
+            *reinterpret_cast<float4*>(g.y + o.off) = val;
         }
         return;
     }
-
-    __shared__ __attribute__((aligned(16))) int escr[4 * Epi<TM, TN>::REGION];
-    epilogue<TM, TN>(g, acc, mb0, nb0, beta, lane, escr + wave * Epi<TM, TN>::REGION);
+#pragma unroll
+    for (int p = 0; p < OUT / NT; ++p) {
+        OutOne o(g, (int)threadIdx.x + p * NT, mb0, nb0);
+        if (!o.live(g)) continue;
+        if (QUADS || !EARLY) { d[0] = g.dscale[o.m]; sq[0] = g.sumq ? g.sumq[o.m] : 0; }
+        int a0 = -sq[0];
+#pragma unroll
+        for (int w = 0; w < (PARK ? WK : 1); ++w) a0 += red[w * OUT + (o.i * TN + o.j0) * 1024 + o.at];
+        if (g.glu) {
+            const float G = ((float)a0 * d[0]) * beta[0];
+            const float U = ((float)(red[(o.i * TN + (TN > 1 ? o.j0 + 1 : 0)) * 1024 + o.at] - sq[0]) * d[0]) * beta[TN > 1 ? 1 : 0];
+            const float pz = fmaxf(G, 0.f);
+            g.y[o.off] = (pz * pz) * U;
+        } else {
+            float val = ((float)a0 * d[0]) * (*g.beta[o.seg]);
+            if (g.residual) val = val + ((QUADS || !EARLY) ? res_at(g, o.off) : res[0].x);
+            g.y[o.off] = val;
+            if (g.acc_dbg) g.acc_dbg[o.off] = a0;
+        }
+    }
 }
 
-template <int TM, int TN, int WM, int WN, int WK>
-int launch_direct(GemmArgs& g, hipStream_t s, bool w8 = false) {
-    g.tiles_m = (g.nmb + WM * TM - 1) / (WM * TM);
-    g.tiles_n = (g.nnb + WN * TN - 1) / (WN * TN);
+template <int TM, int TN, int WK, int D, int OCC>
+int launch_direct(GemmArgs& g, hipStream_t s, bool w8) {
+    g.tiles_m = (g.nmb + TM - 1) / TM;
+    g.tiles_n = (g.nnb + TN - 1) / TN;
     g.group_m = 4;
     const int total = g.tiles_m * g.tiles_n;
     const int grid = ((total + 7) / 8) * 8;
     LaunchTimer tm(BRL_KC_GEMM_NARROW, s, g.ops);
     if (w8)
-        hipLaunchKernelGGL((gemm_direct_kernel<TM, TN, WM, WN, WK, true>), dim3(grid), dim3(WM * WN * WK * 64), 0, s, g);
+        hipLaunchKernelGGL((gemm_direct_kernel<TM, TN, WK, D, OCC, true>), dim3(grid), dim3(WK * 64), 0, s, g);
     else
-        hipLaunchKernelGGL((gemm_direct_kernel<TM, TN, WM, WN, WK, false>), dim3(grid), dim3(WM * WN * WK * 64), 0, s, g);
+        hipLaunchKernelGGL((gemm_direct_kernel<TM, TN, WK, D, OCC, false>), dim3(grid), dim3(WK * 64), 0, s, g);
     BRL_LAUNCH_CHECK("gemm_direct_kernel");
     return BRL_OK;
 }
@@ -943,7 +914,7 @@ int launch_lds(GemmArgs& g, hipStream_t s) {
     g.tiles_m = (g.nmb + WM * TM - 1) / (WM * TM);
     g.tiles_n = (g.nnb + WN * TN - 1) / (WN * TN);
     g.group_m = 4;
-    const int total = g.tiles_m * g.tiles_n * g.splits;
+    const int total = g.tiles_m * g.tiles_n;
     const int grid = ((total + 7) / 8) * 8;
     LaunchTimer tm(WN * TN == 8 ? BRL_KC_GEMM : BRL_KC_GEMM_NARROW, s, g.ops);     // 256-column tiles are the wide class
     if constexpr (W8)
@@ -951,11 +922,6 @@ int launch_lds(GemmArgs& g, hipStream_t s) {
     else
         hipLaunchKernelGGL((gemm_lds_kernel<TM, TN, WM, WN>), dim3(grid), dim3(WM * WN * 64), 0, s, g);
     BRL_LAUNCH_CHECK("gemm_lds_kernel");
-    if (g.splits > 1) {
-        const size_t threads = (size_t)g.M * (g.glu ? g.nnb / 2 : g.nnb) * 8;
-        hipLaunchKernelGGL(splitk_epilogue_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, g);
-        BRL_LAUNCH_CHECK("splitk_epilogue_kernel");
-    }
     return BRL_OK;
 }
 
@@ -1018,8 +984,6 @@ int launch_gemm_attn(const ActBuf& a, const WeightSegs& w, int M, int K, const A
     g.nnb = w.nb_end[2];
     g.nsb = round_up(K, SBK) / SBK;
     g.ops = 2.0 * (double)M * (double)w.n_end[2] * (double)K;
-    g.splits = 1;
-    g.sb_per_split = g.nsb;
     g.att_cos = out.cos_t; g.att_sin = out.sin_t; g.att_qscale = out.qscale;
     g.att_kvf = static_cast<uint4*>(out.kvf); g.att_qf = static_cast<uint4*>(out.qf);
     g.att_S = out.S; g.att_nrb = out.S / 32; g.att_Hq = out.n_heads; g.att_Hkv = out.n_kv_heads;
@@ -1067,66 +1031,54 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
     g.residual = residual;
     g.res_bf16 = residual ? res_bf16 : 0;
     g.acc_dbg = acc_dbg;
-    g.splits = 1;
-    g.sb_per_split = g.nsb;
-    g.partials = nullptr;
     g.fast_epilogue = (acc_dbg == nullptr && ldy % 4 == 0) ? 1 : 0;
     for (int i = 0; i < w.count; ++i)
         if ((w.n_end[i] - (i ? w.n_end[i - 1] : 0)) % 32 != 0) g.fast_epilogue = 0;
     (void)N;
-    // Tile choice: k-split wavefronts for skinny (few-token) problems, where weight
-    // streaming bounds the time; LDS-staged big tiles once the grid fills the chip.
-    // (up to 16 wavefronts split k for one or two token blocks: the chain of dependent loads per
-    // wavefront is what a short state waits for)
+    // Which kernel.  The LDS-staged tiles are ahead once every compute unit has about two of them; below that the
+    // direct kernel's smaller tiles, with k over the wavefronts of a workgroup, spread the product evenly.  The limits
+    // are counts of tiles, measured at 16 to 2560 tokens, K = 2560 and 6912, N = 2560 to 13824 (times in us, kernel
+    // trace, weights from HBM; the tile named first is the one taken).
     const bool w8 = w.w8 != 0;
-    if (glu) {   // a wavefront needs the gate and the up block of a column pair: even TN only
-        if (g.nmb <= 1 || (long)g.nmb * (g.nnb / 2) <= DIRECT16_MAX_WGS_GLU) return launch_direct<1, 2, 1, 1, 8>(g, s, w8);
-        if (g.nmb <= 2) return launch_direct<2, 2, 1, 1, 4>(g, s, w8);
+    const long n32 = (long)g.nmb * g.nnb;                              // 32 x 32
+    const long n64 = (long)((g.nmb + 1) / 2) * ((g.nnb + 1) / 2);      // 64 x 64
+    const long t_narrow = (long)((g.nmb + 3) / 4) * ((g.nnb + 3) / 4);
+    if (w8) {
+        // int8 blobs: four times the weight bytes, so square tiles earlier (N = 2560, K = 6912: 900 tokens 36 against 54
+        // and 1750 tokens 54 against 74 for 128 x 128 tiles, K = 2560: 900 tokens 20 / 26, 1750 tokens 29.5 / 30.2)
+        if (n32 <= 256 && !glu) return launch_direct<1, 1, 16, 1, 4>(g, s, true);
+        if (g.nmb <= 1 || (glu && n32 <= 1024)) return launch_direct<1, 2, 8, 1, 4>(g, s, true);
+        if (!glu && (long)((g.nmb + 1) / 2) * g.nnb <= 700) return launch_direct<2, 1, 8, 1, 4>(g, s, true);
+        if (n64 <= (g.nsb >= 32 ? 1600 : 1000)) return launch_direct<2, 2, 4, 1, 3>(g, s, true);
+        return launch_lds<2, 2, 2, 2, true>(g, s);                     // 16 KB per stage
+    }
+    const long n32x64 = (long)g.nmb * ((g.nnb + 1) / 2);
+    if (glu) {
+        // (a wavefront needs the gate and the up block of a column pair: even TN only.)  2 x 6912 x 2560, tokens: 27:
+        // 5.5 / 6.2 for four column blocks; 128: 10 / 15 for 128 x 128 tiles; 256: 14.5 / 15.5; 700: 28.9 / 30.9.  A wide
+        // tile per compute unit on nearly all of them is better than either: 512 tokens (216 tiles) 20.2 / 21.5, 900
+        // tokens (432) 34.8 / 36.6; on 63 % of them (700 tokens) 33.
+        const long cus = device_cus();
+        const long t_wide = (long)((g.nmb + 3) / 4) * ((g.nnb + 7) / 8);
+        const bool wide_even = 5 * t_wide >= 4 * ((t_wide + cus - 1) / cus) * cus;
+        if (n32x64 <= 512) return launch_direct<1, 2, 4, 2, 4>(g, s, false);
+        if (wide_even) return launch_lds<2, 2, 2, 4, false>(g, s);
+        if (n32x64 <= 6000) return launch_direct<1, 4, 4, 1, 2>(g, s, false);
     } else {
-        // Measured at the 2B layer shapes: one 32-row block per workgroup with k over 16 wavefronts wins
-        // while that makes at most ~500 workgroups (M <= 128 ... 192); then 64 x 32 tiles with k over 8
-        // wavefronts up to ~640 workgroups (M <= ~400 at N = 2560), 1.5 to 3 times faster there than one
-        // 128 x 128 tile per compute unit on a fraction of the chip - also with a long k, where they beat
-        // the k-split tile launch below.  (The limits were measured with 2-bit weights and are applied to
-        // int8 weights as they are.)
-        if (g.nmb <= 1 || (long)g.nmb * g.nnb <= DIRECT16_MAX_WGS) return launch_direct<1, 1, 1, 1, 16>(g, s, w8);
-        if (g.nmb <= 2 || (long)((g.nmb + 1) / 2) * g.nnb <= DIRECT_MAX_WGS) return launch_direct<2, 1, 1, 1, 8>(g, s, w8);
-        if (g.nmb <= 4) return launch_direct<2, 1, 2, 2, 1>(g, s, w8);
+        // tokens x N x K: 27 x 2560 x 6912 7.1 / 7.7 for 32 x 64; 128 x 2560 x 2560 6.1 (32 x 64) / 6.8; 512 x 2560 x 6912
+        // 15.1 / 17.7 for 64 x 32; 900: 22 / 32 and 1750: 37 / 44 for 128 x 128, 2560: 52.6 / 48.4.  Four wavefronts
+        // instead of eight once there are enough workgroups and k is short: 1750 x 2560 x 2560 20.1 / 21.6 (22.6 for 128 x
+        // 128), 1300 x 3840 x 2560 21.5 / 23.5 (22.9), 1750 x 3840 x 2560 26.3 / 29 (24.8).
+        if (n32 <= 256) return launch_direct<1, 1, 16, 1, 4>(g, s, false);
+        if (n32x64 <= (g.nsb >= 32 ? 2500 : 960)) return launch_direct<1, 2, 8, 1, 4>(g, s, false);
+        if (n32x64 <= 2500) return launch_direct<1, 2, 4, 1, 4>(g, s, false);
+        // up to 450 tiles of 128 x 128: eight wavefronts of 64 x 32 on a tile (two per SIMD from one workgroup) instead of
+        // four of 64 x 64: 1750 x 3840 x 2560 (420 tiles) 24.8 / 26.4, 2560 x 2560 x 2560 (400) 25.0 / 27.0; 600 tiles 38 / 34
+        if (t_narrow <= 450) return launch_lds<2, 1, 2, 4, false>(g, s);
     }
-    // Few 128 x 128 tiles and a long k (a few hundred tokens, or a narrow output): k is cut so that about
-    // two workgroups per compute unit run; the partial tiles go through the scratch area of the
-    // activation buffer and a second small kernel.  Integer partial sums: the result is the same.
-    {
-        const long tiles = (long)((g.nmb + 3) / 4) * ((g.nnb + 3) / 4);
-        if (a.splitk && tiles < SPLITK_MAX_TILES) {
-            // (measured at the 2B layer shapes, 160 to 1024 tokens: with k = 2560 the second kernel costs more
-            //  than the idle compute units, with k = 6912 the cut saves 20 to 30 %)
-            int want = (int)((SPLITK_TARGET_WGS + tiles - 1) / tiles);
-            const int maxs = g.nsb >= SPLITK_MIN_SB ? g.nsb / 6 : 1;     // long k only, at least 768 k per range
-            if (want > maxs) want = maxs;
-            if (want >= 2) {
-                const int per = (g.nsb + want - 1) / want;
-                const int splits = (g.nsb + per - 1) / per;
-                if (splits >= 2 && (size_t)splits * M * g.nnb * 32 <= a.splitk_ints) {
-                    g.splits = splits;
-                    g.sb_per_split = per;
-                    g.partials = a.splitk;
-                    return w.w8 ? launch_lds<2, 2, 2, 2, true>(g, s) : launch_lds<2, 2, 2, 2, false>(g, s);
-                }
-            }
-        }
-    }
-    // int8 weights: the LDS-staged 128 x 128 tile (16 KB per stage)
-    if (w.w8) return launch_lds<2, 2, 2, 2, true>(g, s);
     // 128 x 256 workgroup tiles (8 wavefronts of 64 x 64, two workgroups per CU) or 128 x 128 tiles
     // (4 wavefronts, four per CU).  The wide tile does about 5 % more work per unit time; the narrow
     // one wins when it spreads the tiles more evenly over the compute units.
-    const long t_narrow = (long)((g.nmb + 3) / 4) * ((g.nnb + 3) / 4);
-    // About one 128 x 128 tile per compute unit or fewer: the same tile on eight wavefronts of 64 x 32 (two per
-    // SIMD from the one resident workgroup instead of one).  Measured at the 2B layer shapes: 640 tokens QKV 21 ->
-    // 17 us, O 19 -> 17; 1024 tokens QKV 21 -> 19, O 20 -> 17, down 37 -> 33; 1792 tokens (280 tiles) 4 to 7 %;
-    // from 400 tiles on the four-wavefront tile is ahead.  (The GLU epilogue needs column pairs: not for it.)
-    if (!glu && t_narrow <= NARROW8_MAX_TILES) return launch_lds<2, 1, 2, 4, false>(g, s);
     if (wide_tile_chosen(g.nmb, g.nnb)) return launch_lds<2, 2, 2, 4, false>(g, s);
     return launch_lds<2, 2, 2, 2, false>(g, s);
 }

@@ -127,6 +127,31 @@ def test_int8_bitlinear_forward(n, k, m):
     _close(y4.cpu().numpy(), C.int8_bitlinear_forward(xb.float().cpu().numpy(), codes, scale))
 
 
+@pytest.mark.parametrize("m,n,k", [
+    (64, 4096, 136), (64, 4100, 136), (20, 8224, 136),     # 256 tiles of 32 x 32, two more blocks, one token block of many columns
+    (320, 4480, 136), (448, 3232, 136),                    # 700 tiles of 64 x 32, 707 (64 x 64)
+    (1280, 3200, 136), (832, 4928, 136), (832, 4928, 4096),    # 1000 tiles of 64 x 64, 1001 (128 x 128), 1001 with a long k
+])
+def test_int8_dispatch_edges(m, n, k):
+    """Both sides of every limit of the int8-weight dispatch, through both epilogue forms (tap / residual)."""
+    B, R = _mods()
+    print("int8 dispatch edges", m, n, k, flush=True)
+    c = synth.bitlinear_case(9, n, k, m)
+    codes, scale = C.int8_quantize(c["W"])
+    pl = R.quantize_linear(c["W"], int8=True)
+    ws = R.Workspace(B.brl_bitlinear_workspace_bytes(m, n, k))
+    x, res = R.dev(c["X"]), synth.normal(9, 7, (m, n))
+    y = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    acc = torch.empty((m, n), dtype=torch.int32, device="cuda")
+    taps = {}
+    y_ref = C.int8_bitlinear_forward(c["X"], codes, scale, taps=taps)
+    B.bitlinear_int8_forward(pl.packed, pl.beta, n, k, x, m, 1e-5, y, None, None, None, acc, ws.buf)
+    assert np.array_equal(acc.cpu().numpy(), taps["acc"])
+    _close(y.cpu().numpy(), y_ref)
+    B.bitlinear_int8_forward(pl.packed, pl.beta, n, k, x, m, 1e-5, y, R.dev(res), None, None, None, ws.buf)
+    _close(y.cpu().numpy(), y_ref + res)
+
+
 def test_int8_bitlinear_2b_layer_shape():
     B, R = _mods()
     n, k, m = 2560, 6912, 512

@@ -149,6 +149,53 @@ def test_bitlinear_forward_parity(m, n, k):
         assert np.all(y.cpu().numpy()[1] == 0)
 
 
+@pytest.mark.parametrize("m,n,k", [
+    (64, 4096, 136), (64, 4100, 136),           # 256 tiles of 32 x 32, one block more (32 x 64 tiles, ragged n)
+    (480, 4096, 264), (990, 1984, 264),         # 960 tiles of 32 x 64 on eight wavefronts, 961 on four
+    (990, 1984, 4096), (990, 1990, 4088),       # ... and on eight again where k is long; ragged n and k
+    (1600, 3200, 136), (1312, 3904, 136),       # 2500 tiles of 32 x 64; 2501: 128 x 128 on eight wavefronts
+    (1920, 3840, 136), (1408, 5248, 136),       # 450 tiles of 128 x 128, 451
+    (70, 40, 8), (200, 70, 1032),               # fewer super-blocks of k than wavefronts, a remainder of one
+])
+def test_bitlinear_dispatch_edges(m, n, k):
+    """Both sides of every limit of the many-token dispatch, through both epilogue forms (taps / residual)."""
+    B, R = _mods()
+    print("dispatch edges", m, n, k, flush=True)
+    case = synth.bitlinear_case(5, n, k, m)
+    codes, beta = O.ternary_quantize(case["W"])
+    taps = {}
+    y_ref = O.bitlinear_forward(case["X"], codes, beta, taps=taps)
+    pl = R.quantize_linear(case["W"])
+    x = R.dev(case["X"])
+    y, _, _, acc, ws = _run_bitlinear(B, R, pl, x)
+    assert np.array_equal(acc.cpu().numpy(), taps["acc"])
+    assert np.array_equal(y.cpu().numpy(), y_ref)
+    res = synth.normal(5, 7, (m, n))
+    y2 = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    B.bitlinear_forward(pl.packed, pl.beta, n, k, x, m, 1e-5, y2, R.dev(res), None, None, None, ws.buf)
+    assert np.array_equal(y2.cpu().numpy(), O.bitlinear_forward(case["X"], codes, beta, residual=res))
+
+
+@pytest.mark.parametrize("m,d,f", [
+    (512, 136, 1024), (544, 136, 1000),         # 512 and 544 tiles of 32 tokens x 32 column pairs, the second ragged
+    (1536, 136, 2048), (1664, 136, 2048),       # 192 and 208 wide tiles: 75 and 81 % of 256 compute units
+    (20, 520, 40), (4000, 136, 1600), (3200, 136, 1920),   # smallest; past the direct kernel's last size (6250 and 6000 tiles)
+])
+def test_ffn_dispatch_edges(m, d, f):
+    """Both sides of the limits of the gate | up dispatch."""
+    B, R = _mods()
+    print("ffn dispatch edges", m, d, f, flush=True)
+    c = synth.ffn_case(0, m, d, f)
+    x32 = synth.normal(0, 26, (m, d))
+    T = O.TernaryLinear.from_fp32
+    y_ref = O.ffn_block_forward(x32, O.FFNWeights(c["norm_g"], T(c["W_gate"]), T(c["W_up"]), c["subln_g"], T(c["W_down"])))
+    hnd = R.FFNHandle(c["norm_g"], c["W_gate"], c["W_up"], c["subln_g"], c["W_down"])
+    y = torch.empty((m, d), dtype=torch.float32, device="cuda")
+    ws = R.Workspace(B.brl_ffn_workspace_bytes(m, d, f))
+    B.ffn_block_forward(hnd.struct, R.dev(x32), m, d, f, 1e-5, 1e-5, y, ws.buf)
+    assert_fp_close(y.cpu().numpy(), y_ref)
+
+
 def test_bitlinear_forward_shape_sweep():
     """Seeded random shapes across the dispatch boundaries (1-4 token path, 16- and 8-wavefront k-split tiles,
     k-split tile launches, narrow and wide LDS tiles): integer stages exact, outputs identical, with and
