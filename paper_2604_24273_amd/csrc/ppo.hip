@@ -551,8 +551,8 @@ __global__ __launch_bounds__(256) void ppo_loss_kernel(LossArgs a) {
 // A wavefront takes 16 output units x 64 inputs on the fp64 matrix cores: a lane reads four consecutive inputs of a
 // sample, one for each of four result tiles, so that its results are four consecutive inputs again (32-byte stores).
 // The squares of its gradients are summed (fixed tree) to one slot of partial[] for the global norm.
-// 2 x 256 x 2560 from 64 samples: 29 us + 17 us for the second layers with vector FMAs and a launch per level, 18.4 us
-// here for all of them (without the 10.5 MB of results 16.6 us: gathered reads and their latency bound it).
+// 2 x 256 x 2560 from 64 samples: 29 us + 17 us for the second layers with vector FMAs and a launch per level, 11.8 us
+// here for all of them (1292 wavefronts on 1024 SIMDs; one round of gathered reads, then 64 MFMAs each).
 struct GradProblem {
     const double* delta;     // [B, out_dim]
     const double* in64;      // [B, in_dim]; null: first layer, inputs are rows of h
@@ -569,6 +569,61 @@ struct GradArgs {
     int B, T;
     double* partial;         // [waves]
 };
+// The sums over the samples, 64 samples' loads in flight (32 for fp64 inputs).  IN: 0 rows of h read 16 bytes at a time
+// (in_dim a multiple of 4), 1 rows of h of any width, 2 fp64 activations.  Every load is unconditional with a clamped
+// address and nothing is converted before all are requested: inputs past the row's end only reach results that are
+// never stored, and under a branch each load would be waited for before the next (18.4 us that way, 11.8 us this).
+template <int IN>
+__device__ __forceinline__ void weight_grad_sums(const GradProblem& P, const GradArgs& a, int lane, int oc, bool o_ok, int i,
+                                                 v4d (&acc)[4], double& db) {
+    constexpr int NS = IN == 2 ? 8 : 16;             // groups of four samples requested together
+    const int in_dim = P.in_dim, out_dim = P.out_dim, kk = lane >> 4;
+    int at[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) at[e] = min(IN == 0 ? min(i, in_dim - 4) + e : i + e, in_dim - 1);
+    for (int bb = 0; bb < a.B; bb += 64) {
+        const int my_row = clamp_index(a.rows[min(bb + lane, a.B - 1)], a.T);
+        const int b_end = min(a.B, bb + 64);
+        for (int b0 = bb; b0 < b_end; b0 += 4 * NS) {
+            double d[NS];
+            v4f_u xf[IN == 2 ? 1 : NS];
+            v4d xd[IN == 2 ? NS : 1];
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {           // (sample past the end: any row, its delta counts as zero)
+                const int bc = min(b0 + 4 * u + kk, a.B - 1);
+                d[u] = P.delta[(size_t)bc * out_dim + oc];
+                if constexpr (IN == 2) {
+                    const double* row = P.in64 + (size_t)bc * in_dim;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) xd[u][e] = row[at[e]];
+                } else {
+                    const float* row = a.h + (size_t)__shfl(my_row, (4 * u + kk + b0 - bb) & 63, 64) * in_dim;
+                    if constexpr (IN == 0) {
+                        xf[u] = *reinterpret_cast<const v4f_u*>(row + at[0]);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) xf[u][e] = row[at[e]];
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                if (b0 + 4 * u >= b_end) break;
+                const double dv = (o_ok && b0 + 4 * u + kk < b_end) ? d[u] : 0.0;
+                db += dv;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    double x;
+                    if constexpr (IN == 2) x = xd[u][e];
+                    else x = (double)xf[u][e];
+                    acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, x, acc[e], 0, 0, 0);
+                }
+            }
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void ppo_weight_grad_kernel(GradArgs a) {
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
@@ -583,35 +638,9 @@ __global__ __launch_bounds__(256) void ppo_weight_grad_kernel(GradArgs a) {
     const int oc = min(o, out_dim - 1);
     v4d acc[4] = {};
     double db = 0.0;
-    constexpr int NS = 8;                            // groups of four samples requested together
-    for (int bb = 0; bb < a.B; bb += 64) {
-        const int my_row = clamp_index(a.rows[min(bb + lane, a.B - 1)], a.T);
-        const int b_end = min(a.B, bb + 64);
-        for (int b0 = bb; b0 < b_end; b0 += 4 * NS) {
-            double d[NS];
-            v4d x[NS];
-#pragma unroll
-            for (int u = 0; u < NS; ++u) {           // (sample past the end: any row, its delta counts as zero)
-                const int b = b0 + 4 * u + kk, bc = min(b, a.B - 1);
-                const double dv = P.delta[(size_t)bc * out_dim + oc];
-                d[u] = (o_ok && b < b_end) ? dv : 0.0;
-                if (!P.in64) {
-                    const v4f_u v = four_inputs(a.h + (size_t)__shfl(my_row, (4 * u + kk + b0 - bb) & 63, 64) * in_dim, i, in_dim);
-                    x[u] = v4d{(double)v.x, (double)v.y, (double)v.z, (double)v.w};
-                } else {
-                    const double* row = P.in64 + (size_t)bc * in_dim;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) x[u][e] = i + e < in_dim ? row[i + e] : 0.0;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < NS; ++u) {
-                db += d[u];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[u], x[u][e], acc[e], 0, 0, 0);
-            }
-        }
-    }
+    if (P.in64) weight_grad_sums<2>(P, a, lane, oc, o_ok, i, acc, db);
+    else if (in_dim % 4 == 0) weight_grad_sums<0>(P, a, lane, oc, o_ok, i, acc, db);
+    else weight_grad_sums<1>(P, a, lane, oc, o_ok, i, acc, db);
     double sq = 0.0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -679,8 +708,9 @@ __global__ __launch_bounds__(256) void ppo_delta_kernel(DeltaArgs a) {
 // ---- global gradient norm and Adam ------------------------------------------------------------------------------
 // Every workgroup adds the partial sums itself, in one fixed order (thread t takes partials t, t + 256, ..., then a
 // fixed tree): the same norm everywhere, and no launch of its own.  Then Adam with bias correction on the clipped
-// gradient, p -= lr (m / c1) / (sqrt(v / c2) + eps), scale min(1, max_norm / (norm + 1e-6)).  1.3 M parameters: 12.4 us
-// for 42 MB, against 7 us for the norm alone in its own launch and 8.6 us for Adam.
+// gradient, p -= lr (m / c1) / (sqrt(v / c2) + eps), scale min(1, max_norm / (norm + 1e-6)).  1.3 M parameters: 10.4 us
+// for 42 MB, against 7 us for the norm alone in its own launch and 8.6 us for Adam (12.2 us with the partial sums read one
+// after the other and three divisions per parameter).
 struct AdamArgs {
     float* p;
     float* m;
@@ -689,7 +719,7 @@ struct AdamArgs {
     size_t n, n_policy;
     const double* partial;
     int n_partials, B;
-    double max_norm, lr_policy, lr_value, b1, b2, c1, c2, eps, ent_coef;
+    double max_norm, step_policy, step_value, b1, b2, inv_c2, eps, ent_coef;   // steps: learning rate / (1 - b1^t)
     const double* row_terms;
     float* stats;            // [5]: policy loss, value loss, entropy, clip fraction, gradient norm; or null
 };
@@ -718,7 +748,13 @@ __global__ __launch_bounds__(256) void ppo_adam_kernel(AdamArgs a) {
         }
     }
     double s = 0.0;
-    for (int i = threadIdx.x; i < a.n_partials; i += 256) s += a.partial[i];
+    for (int i0p = 0; i0p < a.n_partials; i0p += 256 * 8) {          // eight of a thread's partial sums in flight
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = a.partial[min(i0p + u * 256 + (int)threadIdx.x, a.n_partials - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += i0p + u * 256 + (int)threadIdx.x < a.n_partials ? t[u] : 0.0;
+    }
     red[threadIdx.x] = s;
     __syncthreads();
     for (int st = 128; st >= 64; st >>= 1) {
@@ -734,8 +770,8 @@ __global__ __launch_bounds__(256) void ppo_adam_kernel(AdamArgs a) {
         const double vi = a.b2 * (double)v[e] + (1.0 - a.b2) * gi * gi;
         m[e] = (float)mi;
         v[e] = (float)vi;
-        const double lr = i0 + e < a.n_policy ? a.lr_policy : a.lr_value;
-        p[e] = (float)((double)p[e] - lr * (mi / a.c1) / (sqrt(vi / a.c2) + a.eps));
+        const double step = i0 + e < a.n_policy ? a.step_policy : a.step_value;
+        p[e] = (float)((double)p[e] - step * mi / (sqrt(vi * a.inv_c2) + a.eps));
     }
     if (full) {
         *reinterpret_cast<float4*>(a.p + i0) = make_float4(p[0], p[1], p[2], p[3]);
@@ -912,7 +948,7 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
     memset(&aa, 0, sizeof(aa));
     aa.p = params; aa.m = adam_m; aa.v = adam_v; aa.g = grads; aa.n = L.n_params; aa.n_policy = L.n_policy;
     aa.partial = partial; aa.n_partials = W.grad_waves; aa.B = batch;
-    aa.max_norm = (double)cfg->max_grad_norm; aa.lr_policy = (double)cfg->lr_policy; aa.lr_value = (double)cfg->lr_value;
+    aa.max_norm = (double)cfg->max_grad_norm;
     aa.b1 = (double)cfg->adam_b1; aa.b2 = (double)cfg->adam_b2; aa.eps = (double)cfg->adam_eps; aa.ent_coef = (double)cfg->ent_coef;
     aa.row_terms = row_terms;
     FirstArgs fl;
@@ -1004,8 +1040,10 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
             ga.rows = rows;
             hipLaunchKernelGGL(ppo_weight_grad_kernel, dim3((unsigned)((W.grad_waves + 3) / 4)), dim3(256), 0, s, ga);
             ++step;
-            aa.c1 = 1.0 - pow((double)cfg->adam_b1, (double)step);
-            aa.c2 = 1.0 - pow((double)cfg->adam_b2, (double)step);
+            const double c1 = 1.0 - pow((double)cfg->adam_b1, (double)step);
+            aa.step_policy = (double)cfg->lr_policy / c1;
+            aa.step_value = (double)cfg->lr_value / c1;
+            aa.inv_c2 = 1.0 / (1.0 - pow((double)cfg->adam_b2, (double)step));
             aa.stats = stats ? stats + ((size_t)e * steps_per_epoch + mb) * 5 : nullptr;
             hipLaunchKernelGGL(ppo_adam_kernel, dim3((unsigned)((L.n_params + 256 * ADAM_PER_THREAD - 1) / (256 * ADAM_PER_THREAD))),
                                dim3(256), 0, s, aa);
