@@ -207,11 +207,12 @@ __global__ __launch_bounds__(256) void ppo_first_layer_kernel(FirstArgs a) {
 // ---- from the first layer's sums to every delta, one workgroup per sample ---------------------------------------
 // The layers above the first are small (256 -> 18, 256 -> 1): one workgroup runs the rest of both heads forward, the
 // clipped surrogate (Eq. 1), the entropy bonus and the value error with their gradients, and both heads backward on
-// activations and deltas in its LDS.  One launch (10 us, a chain of L2 and fp64 exp / log / tanh latencies) for what were
+// activations and deltas in its LDS.  One launch (9.4 us, a chain of L2 and fp64 exp / log / tanh latencies) for what were
 // three (second layer 6 us, loss 14 us, deltas 5 us).  Used up to TAIL_MAX_UNITS (the LDS) and TAIL_MAX_WEIGHTS (1 MB of
 // weights per workgroup; beyond, sharing them over four samples as the level kernels below do reads less).
 constexpr int TAIL_MAX_UNITS = 2048;          // layer outputs of both heads together: activations and deltas in 32 KB of LDS
 constexpr size_t TAIL_MAX_WEIGHTS = 1 << 18;  // weights above the first layers: every sample's workgroup reads them all
+constexpr int TAIL_THREADS = 512;             // (256: 10.9 us against 9.4 at 512 first-layer units: every loop over units has two rounds)
 struct TailArgs {
     const double* z;                 // first-layer sums [splits][B][..]
     int splits, B, A, T, act;
@@ -233,7 +234,7 @@ struct TailArgs {
 
 __device__ inline double act_slope(double a, int act) { return act == BRL_ACT_RELU ? (a > 0.0 ? 1.0 : 0.0) : 1.0 - a * a; }
 
-__global__ __launch_bounds__(256) void ppo_tail_kernel(TailArgs a) {
+__global__ __launch_bounds__(TAIL_THREADS) void ppo_tail_kernel(TailArgs a) {
     __shared__ double out[TAIL_MAX_UNITS], del[TAIL_MAX_UNITS];      // layer outputs / deltas, policy head first
     const int tid = threadIdx.x, b = blockIdx.x;
     const int ncol = a.dims[0][1] + a.dims[1][1];
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(256) void ppo_tail_kernel(TailArgs a) {
     int off1 = 0;                                                    // where the value head's units start
     for (int l = 0; l < a.n[0]; ++l) off1 += a.dims[0][l + 1];
 
-    for (int c = tid; c < ncol; c += 256) {
+    for (int c = tid; c < ncol; c += TAIL_THREADS) {
         const int hd = c >= a.dims[0][1] ? 1 : 0, o = c - (hd ? a.dims[0][1] : 0);
         double v = first_layer_total(a.z + (size_t)b * ncol + c, a.splits, (size_t)a.B * ncol) + (double)a.bias[hd][0][o];
         if (a.n[hd] > 1) {
@@ -256,12 +257,12 @@ __global__ __launch_bounds__(256) void ppo_tail_kernel(TailArgs a) {
     }
     __syncthreads();
     // the layers above, level by level for both heads: eight lanes per output unit
-    constexpr int LG = 8;
+    constexpr int LG = 8, GROUPS = TAIL_THREADS / LG;
     const int depth = max(a.n[0], a.n[1]);
     int in0[2] = {0, off1};
     for (int l = 1; l < depth; ++l) {
         const int od0 = l < a.n[0] ? a.dims[0][l + 1] : 0, od1 = l < a.n[1] ? a.dims[1][l + 1] : 0, total = od0 + od1;
-        for (int u = tid / LG; u < (total + 31) / 32 * 32; u += 256 / LG) {
+        for (int u = tid / LG; u < (total + GROUPS - 1) / GROUPS * GROUPS; u += GROUPS) {
             const int uc = min(u, total - 1), hd = uc >= od0 ? 1 : 0, o = uc - (hd ? od0 : 0);
             const int id = a.dims[hd][l], od = a.dims[hd][l + 1];
             double v = group_dot<LG>(a.W[hd][l] + (size_t)o * id, out + in0[hd], id);
@@ -323,7 +324,7 @@ __global__ __launch_bounds__(256) void ppo_tail_kernel(TailArgs a) {
     for (int t = 0; t < depth - 1; ++t) {
         const int l0 = a.n[0] - 1 - t, l1 = a.n[1] - 1 - t;
         const int id0 = l0 >= 1 ? a.dims[0][l0] : 0, id1 = l1 >= 1 ? a.dims[1][l1] : 0;
-        for (int u = tid; u < id0 + id1; u += 256) {
+        for (int u = tid; u < id0 + id1; u += TAIL_THREADS) {
             const int hd = u >= id0 ? 1 : 0, l = hd ? l1 : l0, i = u - (hd ? id0 : 0), id = hd ? id1 : id0;
             const int od = a.dims[hd][l + 1], up = hd ? at1 : at0, in = up - id;
             const float* w = a.W[hd][l] + i;
@@ -983,7 +984,7 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
                 ta.rows = rows;
                 const unsigned blocks = (unsigned)((fl.tiles[0] + fl.tiles[1]) * W.splits * W.btiles) + 1;   // + the advantages' scale
                 hipLaunchKernelGGL(ppo_first_layer_kernel, dim3(blocks), dim3(256), 0, s, fl);
-                hipLaunchKernelGGL(ppo_tail_kernel, dim3(batch), dim3(256), 0, s, ta);
+                hipLaunchKernelGGL(ppo_tail_kernel, dim3(batch), dim3(TAIL_THREADS), 0, s, ta);
             } else {
                 // forward: level l of both heads in one launch
                 for (int l = 0; l < depth; ++l) {
