@@ -4,11 +4,16 @@
 // k range, so no partial sums ever cross workgroups (no atomics, no fences).
 // The packed weights are streamed once with 16-byte-per-lane loads (a wavefront
 // reads contiguous 1 KB blocks of 32 rows x 128 columns), all of them issued
-// before anything else: the whole matrix is in flight while the activation
-// rows are quantised (every workgroup redoes that cheap step on its own).
+// before anything is waited for: the whole matrix is in flight while the activation
+// rows are quantised (every workgroup redoes that cheap step on its own).  Loads return
+// in order, so the activations, which are needed first, are requested first, then the
+// weights, then what the finishing threads need; all of them unconditionally (clamped
+// addresses), so that none waits for another.
 // The 2-bit fields are expanded in registers to offset codes c = code + 1 and
 // contracted with v_dot4_i32_i8 against the int8 activations held in LDS;
 // sum_k q is subtracted at the end.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace brl {
@@ -18,9 +23,7 @@ namespace {
 constexpr int GV_THREADS = 1024;
 constexpr int GV_WAVES = GV_THREADS / 64;
 constexpr int GV_MAX_SB = MAX_K / SBK;                                   // 72 super-blocks
-constexpr int GV_SB_PER_WAVE = (GV_MAX_SB + GV_WAVES - 1) / GV_WAVES;    // 5
-constexpr int GV_X4 = (MAX_K / 4 + GV_THREADS - 1) / GV_THREADS;         // float4 of one row per thread: 3
-
+constexpr int GV_X4 = (MAX_K / 4 + GV_THREADS - 1) / GV_THREADS;         // float4 of one row per thread in the batched kernel: 3
 struct GemvArgs {
     const void* x;
     int x_dtype;
@@ -44,37 +47,67 @@ __device__ inline float4 load_x4(const void* x, int dtype, size_t idx) {
     return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(x) + idx);
 }
 
-template <int MT>
+// NX float4 of a row per thread (K <= 4096 NX), NS super-blocks per wavefront
+template <int MT, int NX, int NS>
 __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
-    __shared__ __attribute__((aligned(16))) int xq[MT][MAX_K / 4];     // int8 activations as dwords (zero padded)
+    __shared__ __attribute__((aligned(16))) int xq[MT][NX * GV_THREADS];     // int8 activations as dwords (zero padded)
     __shared__ float wmax[MT][GV_WAVES];
     __shared__ int wsum[MT][GV_WAVES];
     __shared__ int red[GV_WAVES][MT][32];
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nb = blockIdx.x;
     const int K = g.K, Kp = g.nsb * SBK;
+    const bool bf16 = g.x_dtype == BRL_BF16;
 
-    // 1. weight loads first: they do not depend on the activations
-    uint4 wreg[GV_SB_PER_WAVE];
+    // 1. everything this workgroup reads
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(1))) char* gptr;
+    u32x4 raw[MT][NX];
+    if (bf16) {
 #pragma unroll
-    for (int u = 0; u < GV_SB_PER_WAVE; ++u) {
-        const int sb = wave + GV_WAVES * u;
-        wreg[u] = make_uint4(0x55555555u, 0x55555555u, 0x55555555u, 0x55555555u);   // code 0 everywhere
-        if (sb < g.nsb) wreg[u] = g.packed[((size_t)nb * g.nsb + sb) * 64 + lane];
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int u = 0; u < NX; ++u) {
+                const int k = min(4 * ((int)threadIdx.x + GV_THREADS * u), K - 4);
+                const u32x2 r = *(const __attribute__((address_space(1))) u32x2*)((gptr)g.x + (size_t)min(t, g.M - 1) * K * 2 + (unsigned)k * 2u);
+                raw[t][u].xy = r;
+            }
+    } else {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int u = 0; u < NX; ++u) {
+                const int k = min(4 * ((int)threadIdx.x + GV_THREADS * u), K - 4);
+                raw[t][u] = *(const __attribute__((address_space(1))) u32x4*)((gptr)g.x + (size_t)min(t, g.M - 1) * K * 4 + (unsigned)k * 4u);
+            }
     }
+    u32x4 wreg[NS];                                   // (super-blocks past the end of k are never contracted)
+    const __attribute__((address_space(1))) u32x4* wp = (const __attribute__((address_space(1))) u32x4*)g.packed + (size_t)nb * g.nsb * 64;
+#pragma unroll
+    for (int u = 0; u < NS; ++u) wreg[u] = wp[(unsigned)(min(wave + GV_WAVES * u, g.nsb - 1) * 64 + lane)];
+    const float beta = *g.beta;
+    const int t_of = threadIdx.x >> 5, r_of = threadIdx.x & 31;          // the finishing threads' (token, row)
+    const bool finishes = t_of < MT && t_of < g.M && nb * 32 + r_of < g.N;
+    const size_t o = (size_t)t_of * g.N + nb * 32 + r_of;
+    const float res = g.residual && finishes ? g.residual[o] : 0.f;
 
-    // 2. activation rows into registers, per-token absmax
-    float4 xv[MT][GV_X4];
+    // 2. per-token absmax
+    float4 xv[MT][NX];
     float tmax[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         tmax[t] = 0.f;
 #pragma unroll
-        for (int u = 0; u < GV_X4; ++u) {
-            const int k = 4 * ((int)threadIdx.x + GV_THREADS * u);
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (t < g.M && k < K) v = load_x4(g.x, g.x_dtype, (size_t)t * K + k);
+        for (int u = 0; u < NX; ++u) {
+            const bool in = t < g.M && 4 * ((int)threadIdx.x + GV_THREADS * u) < K;
+            const u32x4 r = raw[t][u];
+            float4 v;
+            v.x = in ? __uint_as_float(bf16 ? r.x << 16 : r.x) : 0.f;
+            v.y = in ? __uint_as_float(bf16 ? r.x & 0xffff0000u : r.y) : 0.f;
+            v.z = in ? __uint_as_float(bf16 ? r.y << 16 : r.z) : 0.f;
+            v.w = in ? __uint_as_float(bf16 ? r.y & 0xffff0000u : r.w) : 0.f;
             xv[t][u] = v;
             tmax[t] = fmaxf(tmax[t], fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
         }
@@ -95,7 +128,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
         const float sc = 127.0f / ac[t];
         int qsum = 0;
 #pragma unroll
-        for (int u = 0; u < GV_X4; ++u) {
+        for (int u = 0; u < NX; ++u) {
             const int k = 4 * ((int)threadIdx.x + GV_THREADS * u);
             if (k < Kp) {
                 const float4 v = xv[t][u];
@@ -126,7 +159,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
     for (int t = 0; t < MT; ++t) acc[t] = 0;
     const int hh = lane >> 5;
 #pragma unroll
-    for (int u = 0; u < GV_SB_PER_WAVE; ++u) {
+    for (int u = 0; u < NS; ++u) {
         const int sb = wave + GV_WAVES * u;
         if (sb >= g.nsb) continue;
         const uint32_t wd[4] = {wreg[u].x, wreg[u].y, wreg[u].z, wreg[u].w};
@@ -154,27 +187,21 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
     __syncthreads();
 
     // 5. finish: threads 0 .. 32 MT - 1 each own one (token, row)
-    const int t_of = threadIdx.x >> 5, r_of = threadIdx.x & 31;
-    if (t_of < MT && t_of < g.M) {
+    if (finishes) {
         int part = 0, sq = 0;
+        float m = wmax[t_of][0];
 #pragma unroll
         for (int w = 0; w < GV_WAVES; ++w) {
             part += red[w][t_of][r_of];
             sq += wsum[t_of][w];
+            m = fmaxf(m, wmax[t_of][w]);
         }
         part -= sq;
-        const int n = nb * 32 + r_of;
-        if (n < g.N) {
-            float m = wmax[t_of][0];
-#pragma unroll
-            for (int w = 1; w < GV_WAVES; ++w) m = fmaxf(m, wmax[t_of][w]);
-            const float d = fmaxf(m, g.eps_act) / 127.0f;
-            const size_t o = (size_t)t_of * g.N + n;
-            float val = ((float)part * d) * (*g.beta);
-            if (g.residual) val = val + g.residual[o];
-            g.y[o] = val;
-            if (g.acc_dbg) g.acc_dbg[o] = part;
-        }
+        const float d = fmaxf(m, g.eps_act) / 127.0f;
+        float val = ((float)part * d) * beta;
+        if (g.residual) val = val + res;
+        g.y[o] = val;
+        if (g.acc_dbg) g.acc_dbg[o] = part;
     }
 }
 
@@ -439,11 +466,17 @@ int launch_gemv(const void* x, int x_dtype, int M, int K, int N, const uint32_t*
     g.xq_dbg = xq_dbg; g.absmax_dbg = absmax_dbg; g.acc_dbg = acc_dbg;
     const int grid = round_up(N, NB) / NB;
     LaunchTimer tm(BRL_KC_GEMV, s);
+    auto launch = [&](auto mt) {
+        constexpr int MT = decltype(mt)::value;
+        if (K <= 4096) hipLaunchKernelGGL((gemv_kernel<MT, 1, 2>), dim3(grid), dim3(GV_THREADS), 0, s, g);
+        else if (K <= 8192) hipLaunchKernelGGL((gemv_kernel<MT, 2, 4>), dim3(grid), dim3(GV_THREADS), 0, s, g);
+        else hipLaunchKernelGGL((gemv_kernel<MT, 3, 5>), dim3(grid), dim3(GV_THREADS), 0, s, g);
+    };
     switch (M) {
-        case 1: hipLaunchKernelGGL(gemv_kernel<1>, dim3(grid), dim3(GV_THREADS), 0, s, g); break;
-        case 2: hipLaunchKernelGGL(gemv_kernel<2>, dim3(grid), dim3(GV_THREADS), 0, s, g); break;
+        case 1: launch(std::integral_constant<int, 1>()); break;
+        case 2: launch(std::integral_constant<int, 2>()); break;
         case 3:
-        case 4: hipLaunchKernelGGL(gemv_kernel<4>, dim3(grid), dim3(GV_THREADS), 0, s, g); break;
+        case 4: launch(std::integral_constant<int, 4>()); break;
         default: set_error("gemv: M = %d out of range 1..4", M); return BRL_EINVAL;
     }
     BRL_LAUNCH_CHECK("gemv_kernel");
