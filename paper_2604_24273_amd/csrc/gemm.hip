@@ -708,7 +708,9 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
     constexpr int OUT = TM * TN * 1024;
     constexpr bool QUADS = OUT / NT >= 4;             // four columns per thread and pass, 16-byte stores
     constexpr int NP = QUADS ? OUT / NT / 4 : 1;      // passes of the main finishing form
-    constexpr bool EARLY = NP == 1;                   // what it reads from memory is requested ahead of the k loop
+    // What the finishing pass reads from memory is requested with the first loads where the launch is bound by latency
+    // (the one-block tile: 0.5 us); held through the k loop it costs the larger tiles wavefronts (256 x 2560 x 6912: 1 us).
+    constexpr bool EARLY = TM * TN == 1;
     typedef DirectOut<TM, TN, QUADS ? 4 : 1> Out;
     typedef DirectOut<TM, TN, 1> OutOne;
     static_assert(QUADS || OUT / NT == 1, "one item per thread");
@@ -740,9 +742,8 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
         }
     }
 
-    float d[NP];
-    int sq[NP];
-    float4 res[NP];
+    float early_d = 0.f, early_res = 0.f;
+    int early_sq = 0;
     v16i acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -752,18 +753,11 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
 
     auto request_outputs = [&] {
-        if (!EARLY || (QUADS && !g.fast_epilogue)) return;
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            Out o(g, (int)threadIdx.x + p * NT, mb0, nb0);
-            const int m = min(o.m, g.M - 1);
-            d[p] = g.dscale[m];
-            sq[p] = g.sumq ? g.sumq[m] : 0;
-            if (g.residual && o.live(g)) {
-                if constexpr (QUADS) res[p] = res4_at(g, o.off);
-                else res[p].x = res_at(g, o.off);
-            }
-        }
+        OutOne o(g, (int)threadIdx.x, mb0, nb0);
+        const int m = min(o.m, g.M - 1);
+        early_d = g.dscale[m];
+        early_sq = g.sumq ? g.sumq[m] : 0;
+        if (g.residual && o.live(g)) early_res = res_at(g, o.off);
     };
     const int sb_begin = wk * g.nsb / WK, sb_end = (wk + 1) * g.nsb / WK;
     if (sb_begin < sb_end) {
@@ -798,7 +792,7 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
 #pragma unroll
         for (int d = 0; d < D; ++d) load(d, min(sb_begin + d, sb_end - 1));
         __builtin_amdgcn_sched_barrier(0);
-        request_outputs();
+        if (EARLY) request_outputs();
         __builtin_amdgcn_sched_barrier(0);
         int sb = sb_begin;
         for (; sb + 2 * D <= sb_end; sb += D)
@@ -820,7 +814,7 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
 #pragma unroll
         for (int d = 0; d < D; ++d)
             if (sb + d < sb_end) contract(d);
-    } else {
+    } else if (EARLY) {
         request_outputs();
     }
 
@@ -841,7 +835,8 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
         for (int p = 0; p < NP; ++p) {
             Out o(g, (int)threadIdx.x + p * NT, mb0, nb0);
             if (!o.live(g)) continue;
-            if (!EARLY) { d[p] = g.dscale[o.m]; sq[p] = g.sumq ? g.sumq[o.m] : 0; }
+            const float d = g.dscale[o.m];
+            const int sq = g.sumq ? g.sumq[o.m] : 0;
             const int4 a0 = *reinterpret_cast<const int4*>(&red[(o.i * TN + o.j0) * 1024 + o.at]);
             float4 val;
             if (g.glu) {
@@ -850,21 +845,23 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
                 float hv[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const float G = ((float)(gi[q] - sq[p]) * d[p]) * beta[0];
-                    const float U = ((float)(ui[q] - sq[p]) * d[p]) * beta[TN > 1 ? 1 : 0];
+                    const float G = ((float)(gi[q] - sq) * d) * beta[0];
+                    const float U = ((float)(ui[q] - sq) * d) * beta[TN > 1 ? 1 : 0];
                     const float pz = fmaxf(G, 0.f);
                     hv[q] = (pz * pz) * U;
                 }
                 val = make_float4(hv[0], hv[1], hv[2], hv[3]);
             } else {
-                const float bsel = *g.beta[o.seg];
-                val.x = ((float)(a0.x - sq[p]) * d[p]) * bsel;
-                val.y = ((float)(a0.y - sq[p]) * d[p]) * bsel;
-                val.z = ((float)(a0.z - sq[p]) * d[p]) * bsel;
-                val.w = ((float)(a0.w - sq[p]) * d[p]) * bsel;
+                float bsel = beta[0];
+#pragma unroll
+                for (int j = 1; j < TN; ++j) bsel = o.j0 == j ? beta[j] : bsel;
+                val.x = ((float)(a0.x - sq) * d) * bsel;
+                val.y = ((float)(a0.y - sq) * d) * bsel;
+                val.z = ((float)(a0.z - sq) * d) * bsel;
+                val.w = ((float)(a0.w - sq) * d) * bsel;
                 if (g.residual) {
-                    if (!EARLY) res[p] = res4_at(g, o.off);
-                    val.x = val.x + res[p].x; val.y = val.y + res[p].y; val.z = val.z + res[p].z; val.w = val.w + res[p].w;
+                    const float4 res = res4_at(g, o.off);
+                    val.x = val.x + res.x; val.y = val.y + res.y; val.z = val.z + res.z; val.w = val.w + res.w;
                 }
             }
             *reinterpret_cast<float4*>(g.y + o.off) = val;
@@ -875,36 +872,37 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
     for (int p = 0; p < OUT / NT; ++p) {
         OutOne o(g, (int)threadIdx.x + p * NT, mb0, nb0);
         if (!o.live(g)) continue;
-        if (QUADS || !EARLY) { d[0] = g.dscale[o.m]; sq[0] = g.sumq ? g.sumq[o.m] : 0; }
-        int a0 = -sq[0];
+        const float d = EARLY ? early_d : g.dscale[o.m];
+        const int sq = EARLY ? early_sq : (g.sumq ? g.sumq[o.m] : 0);
+        int a0 = -sq;
 #pragma unroll
         for (int w = 0; w < (PARK ? WK : 1); ++w) a0 += red[w * OUT + (o.i * TN + o.j0) * 1024 + o.at];
         if (g.glu) {
-            const float G = ((float)a0 * d[0]) * beta[0];
-            const float U = ((float)(red[(o.i * TN + (TN > 1 ? o.j0 + 1 : 0)) * 1024 + o.at] - sq[0]) * d[0]) * beta[TN > 1 ? 1 : 0];
+            const float G = ((float)a0 * d) * beta[0];
+            const float U = ((float)(red[(o.i * TN + (TN > 1 ? o.j0 + 1 : 0)) * 1024 + o.at] - sq) * d) * beta[TN > 1 ? 1 : 0];
             const float pz = fmaxf(G, 0.f);
             g.y[o.off] = (pz * pz) * U;
         } else {
-            float val = ((float)a0 * d[0]) * (*g.beta[o.seg]);
-            if (g.residual) val = val + ((QUADS || !EARLY) ? res_at(g, o.off) : res[0].x);
+            float bsel = beta[0];
+#pragma unroll
+            for (int j = 1; j < TN; ++j) bsel = o.j0 == j ? beta[j] : bsel;
+            float val = ((float)a0 * d) * bsel;
+            if (g.residual) val = val + (EARLY ? early_res : res_at(g, o.off));
             g.y[o.off] = val;
             if (g.acc_dbg) g.acc_dbg[o.off] = a0;
         }
     }
 }
 
-template <int TM, int TN, int WK, int D, int OCC>
-int launch_direct(GemmArgs& g, hipStream_t s, bool w8) {
+template <int TM, int TN, int WK, int D, int OCC, bool W8>
+int launch_direct(GemmArgs& g, hipStream_t s) {
     g.tiles_m = (g.nmb + TM - 1) / TM;
     g.tiles_n = (g.nnb + TN - 1) / TN;
     g.group_m = 4;
     const int total = g.tiles_m * g.tiles_n;
     const int grid = ((total + 7) / 8) * 8;
     LaunchTimer tm(BRL_KC_GEMM_NARROW, s, g.ops);
-    if (w8)
-        hipLaunchKernelGGL((gemm_direct_kernel<TM, TN, WK, D, OCC, true>), dim3(grid), dim3(WK * 64), 0, s, g);
-    else
-        hipLaunchKernelGGL((gemm_direct_kernel<TM, TN, WK, D, OCC, false>), dim3(grid), dim3(WK * 64), 0, s, g);
+    hipLaunchKernelGGL((gemm_direct_kernel<TM, TN, WK, D, OCC, W8>), dim3(grid), dim3(WK * 64), 0, s, g);
     BRL_LAUNCH_CHECK("gemm_direct_kernel");
     return BRL_OK;
 }
@@ -1039,17 +1037,16 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
     // direct kernel's smaller tiles, with k over the wavefronts of a workgroup, spread the product evenly.  The limits
     // are counts of tiles, measured at 16 to 2560 tokens, K = 2560 and 6912, N = 2560 to 13824 (times in us, kernel
     // trace, weights from HBM; the tile named first is the one taken).
-    const bool w8 = w.w8 != 0;
     const long n32 = (long)g.nmb * g.nnb;                              // 32 x 32
     const long n64 = (long)((g.nmb + 1) / 2) * ((g.nnb + 1) / 2);      // 64 x 64
     const long t_narrow = (long)((g.nmb + 3) / 4) * ((g.nnb + 3) / 4);
-    if (w8) {
+    if (w.w8) {
         // int8 blobs: four times the weight bytes, so square tiles earlier (N = 2560, K = 6912: 900 tokens 36 against 54
         // and 1750 tokens 54 against 74 for 128 x 128 tiles, K = 2560: 900 tokens 20 / 26, 1750 tokens 29.5 / 30.2)
-        if (n32 <= 256 && !glu) return launch_direct<1, 1, 16, 1, 4>(g, s, true);
-        if (g.nmb <= 1 || (glu && n32 <= 1024)) return launch_direct<1, 2, 8, 1, 4>(g, s, true);
-        if (!glu && (long)((g.nmb + 1) / 2) * g.nnb <= 700) return launch_direct<2, 1, 8, 1, 4>(g, s, true);
-        if (n64 <= (g.nsb >= 32 ? 1600 : 1000)) return launch_direct<2, 2, 4, 1, 3>(g, s, true);
+        if (n32 <= 256 && !glu) return launch_direct<1, 1, 16, 1, 4, true>(g, s);
+        if (g.nmb <= 1 || (glu && n32 <= 1024)) return launch_direct<1, 2, 8, 1, 4, true>(g, s);
+        if (!glu && (long)((g.nmb + 1) / 2) * g.nnb <= 700) return launch_direct<2, 1, 8, 1, 4, true>(g, s);
+        if (n64 <= (g.nsb >= 32 ? 1600 : 1000)) return launch_direct<2, 2, 4, 1, 3, true>(g, s);
         return launch_lds<2, 2, 2, 2, true>(g, s);                     // 16 KB per stage
     }
     const long n32x64 = (long)g.nmb * ((g.nnb + 1) / 2);
@@ -1061,17 +1058,17 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
         const long cus = device_cus();
         const long t_wide = (long)((g.nmb + 3) / 4) * ((g.nnb + 7) / 8);
         const bool wide_even = 5 * t_wide >= 4 * ((t_wide + cus - 1) / cus) * cus;
-        if (n32x64 <= 512) return launch_direct<1, 2, 4, 2, 4>(g, s, false);
+        if (n32x64 <= 512) return launch_direct<1, 2, 4, 2, 4, false>(g, s);
         if (wide_even) return launch_lds<2, 2, 2, 4, false>(g, s);
-        if (n32x64 <= 6000) return launch_direct<1, 4, 4, 1, 2>(g, s, false);
+        if (n32x64 <= 6000) return launch_direct<1, 4, 4, 1, 4, false>(g, s);
     } else {
         // tokens x N x K: 27 x 2560 x 6912 7.1 / 7.7 for 32 x 64; 128 x 2560 x 2560 6.1 (32 x 64) / 6.8; 512 x 2560 x 6912
         // 15.1 / 17.7 for 64 x 32; 900: 22 / 32 and 1750: 37 / 44 for 128 x 128, 2560: 52.6 / 48.4.  Four wavefronts
         // instead of eight once there are enough workgroups and k is short: 1750 x 2560 x 2560 20.1 / 21.6 (22.6 for 128 x
         // 128), 1300 x 3840 x 2560 21.5 / 23.5 (22.9), 1750 x 3840 x 2560 26.3 / 29 (24.8).
-        if (n32 <= 256) return launch_direct<1, 1, 16, 1, 4>(g, s, false);
-        if (n32x64 <= (g.nsb >= 32 ? 2500 : 960)) return launch_direct<1, 2, 8, 1, 4>(g, s, false);
-        if (n32x64 <= 2500) return launch_direct<1, 2, 4, 1, 4>(g, s, false);
+        if (n32 <= 256) return launch_direct<1, 1, 16, 1, 4, false>(g, s);
+        if (n32x64 <= (g.nsb >= 32 ? 2500 : 960)) return launch_direct<1, 2, 8, 1, 4, false>(g, s);
+        if (n32x64 <= 2500) return launch_direct<1, 2, 4, 1, 4, false>(g, s);
         // up to 450 tiles of 128 x 128: eight wavefronts of 64 x 32 on a tile (two per SIMD from one workgroup) instead of
         // four of 64 x 64: 1750 x 3840 x 2560 (420 tiles) 24.8 / 26.4, 2560 x 2560 x 2560 (400) 25.0 / 27.0; 600 tiles 38 / 34
         if (t_narrow <= 450) return launch_lds<2, 1, 2, 4, false>(g, s);
