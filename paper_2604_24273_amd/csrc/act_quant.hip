@@ -125,8 +125,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_kernel(QK a) {
                 ss += (double)v[i].z * (double)v[i].z;
                 ss += (double)v[i].w * (double)v[i].w;
             }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+            ss = wave_total(ss);
             if (lane == 0) red_ss[rl][part] = ss;
             __syncthreads();
             double tot = red_ss[rl][0];
@@ -151,8 +150,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_kernel(QK a) {
         for (int i = 0; i < HV4; ++i) {
             amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[i].x), fabsf(v[i].y)), fmaxf(fabsf(v[i].z), fabsf(v[i].w))));
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+        amax = wave_max(amax);
         if (lane == 0) red_max[rl][part] = amax;
         __syncthreads();
         float ac = a.eps_act;
@@ -178,8 +176,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_kernel(QK a) {
                     *reinterpret_cast<uint32_t*>(a.xq_rowmajor + (size_t)row * K + k) = word;
             }
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        sum = wave_total(sum);
         if (lane == 0) red_sum[rl][part] = sum;
         __syncthreads();
         if (lane == 0 && part == 0 && live) {
@@ -305,8 +302,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_wave_kernel(QK a) {
                 ss += (double)v[c].w * (double)v[c].w;
                 __builtin_amdgcn_sched_barrier(0);      // one chunk at a time: the row itself fills the registers
             }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+            ss = wave_total(ss);
             const float r = (float)(1.0 / sqrt(ss / (double)K + (double)a.eps_norm));
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
@@ -322,8 +318,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_wave_kernel(QK a) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[c].x), fabsf(v[c].y)), fmaxf(fabsf(v[c].z), fabsf(v[c].w))));
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+        amax = wave_max(amax);
         const float ac = fmaxf(amax, a.eps_act);
         const float sc = 127.0f / ac;
 
@@ -343,8 +338,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_wave_kernel(QK a) {
             if (a.xq_rowmajor && live && k < K) *reinterpret_cast<uint32_t*>(a.xq_rowmajor + (size_t)row * K + k) = word;
             __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        sum = wave_total(sum);
         if (lane == 0 && live) {
             a.absmax[row] = ac;
             a.dscale[row] = ac / 127.0f;
@@ -401,8 +395,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_row_kernel(QK a) {
             ss += (double)v[i].z * (double)v[i].z;
             ss += (double)v[i].w * (double)v[i].w;
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        ss = wave_total(ss);
         if (lane == 0) red_ss[wave] = ss;
         __syncthreads();
         double tot = red_ss[0];
@@ -421,8 +414,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_row_kernel(QK a) {
 #pragma unroll
     for (int i = 0; i < HV4; ++i)
         amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[i].x), fabsf(v[i].y)), fmaxf(fabsf(v[i].z), fabsf(v[i].w))));
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+    amax = wave_max(amax);
     if (lane == 0) red_max[wave] = amax;
     __syncthreads();
     float ac = a.eps_act;
@@ -443,12 +435,12 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_row_kernel(QK a) {
         const uint32_t word = (uint32_t)(q0 & 0xff) | ((uint32_t)(q1 & 0xff) << 8) | ((uint32_t)(q2 & 0xff) << 16) |
                               ((uint32_t)(q3 & 0xff) << 24);
         if (a.xq_rowmajor && k < K) *reinterpret_cast<uint32_t*>(a.xq_rowmajor + (size_t)row * K + k) = word;
-        // lanes 4 j .. 4 j + 3 hold 16 consecutive k: lane 4 j writes them as one piece of the tile
+        // lanes 4 j .. 4 j + 3 hold 16 consecutive k: lane 4 j writes them as one piece of the tile (quad_perm broadcasts)
         uint4 piece;
         piece.x = word;
-        piece.y = __shfl_down(word, 1, 64);
-        piece.z = __shfl_down(word, 2, 64);
-        piece.w = __shfl_down(word, 3, 64);
+        piece.y = lane_exchange<0x55>(word);
+        piece.z = lane_exchange<0xaa>(word);
+        piece.w = lane_exchange<0xff>(word);
         if ((lane & 3) == 0 && k < a.Kp) {
             const int kc = k >> 4;
             const int sb = kc >> 3, dd = (kc >> 1) & 3, hh = kc & 1;
@@ -456,8 +448,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_row_kernel(QK a) {
             *reinterpret_cast<uint4*>(a.q_tiled + off) = piece;
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    sum = wave_total(sum);
     if (lane == 0) red_sum[wave] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -111,8 +111,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
             xv[t][u] = v;
             tmax[t] = fmaxf(tmax[t], fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) tmax[t] = fmaxf(tmax[t], __shfl_xor(tmax[t], off, 64));
+        tmax[t] = wave_max(tmax[t]);
         if (lane == 0) wmax[t][wave] = tmax[t];
     }
     __syncthreads();
@@ -142,8 +141,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
                 if (g.xq_dbg && nb == 0 && t < g.M && k < K) *reinterpret_cast<int*>(g.xq_dbg + (size_t)t * K + k) = word;
             }
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) qsum += __shfl_xor(qsum, off, 64);
+        qsum = wave_total(qsum);
         if (lane == 0) wsum[t][wave] = qsum;
     }
     if (g.absmax_dbg && nb == 0 && threadIdx.x == 0) {
@@ -331,8 +329,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_batch_kernel(GemvBatchArgs g)
                     xv[t][u] = v;
                     tm = fmaxf(tm, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
                 }
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) tm = fmaxf(tm, __shfl_xor(tm, off, 64));
+                tm = wave_max(tm);
                 if (lane == 0) wmax[t][wave] = tm;
             }
             __syncthreads();
@@ -358,8 +355,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_batch_kernel(GemvBatchArgs g)
                         xq[t][k >> 2] = (q0 & 0xff) | ((q1 & 0xff) << 8) | ((q2 & 0xff) << 16) | ((q3 & 0xff) << 24);
                     }
                 }
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) qsum += __shfl_xor(qsum, off, 64);
+                qsum = wave_total(qsum);
                 if (lane == 0) wsum[t][wave] = qsum;
             }
             __syncthreads();

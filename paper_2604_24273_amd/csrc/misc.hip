@@ -41,8 +41,7 @@ __global__ __launch_bounds__(256) void row_rinv_kernel(const float* __restrict__
         ss += (double)v.z * (double)v.z;
         ss += (double)v.w * (double)v.w;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+    ss = wave_total(ss);
     if (lane == 0) rinv[row] = (float)(1.0 / sqrt(ss / (double)d + (double)eps));
 }
 

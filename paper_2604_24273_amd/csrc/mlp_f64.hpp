@@ -98,11 +98,7 @@ __device__ inline double first_layer_total(const double* __restrict__ z, int spl
     return v;
 }
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
+__device__ inline double wave_sum(double v) { return wave_total(v); }
 __device__ inline double activate(double z, int act) { return act == BRL_ACT_RELU ? fmax(z, 0.0) : tanh(z); }
 
 // sum_i w[i] x[i] over a group of LG adjacent lanes (every lane of the group gets it), 32 weights of a lane in flight
@@ -119,8 +115,11 @@ __device__ inline double group_dot(const float* __restrict__ w, const double* x,
     }
 #pragma unroll 4
     for (; i < n; i += LG) v += (double)w[i] * x[i];
-#pragma unroll
-    for (int off = 1; off < LG; off <<= 1) v += __shfl_xor(v, off, 64);
+    static_assert(LG == 1 || LG == 2 || LG == 4 || LG == 8 || LG == 16, "groups inside a row of 16 lanes");
+    if constexpr (LG > 1) v += lane_exchange<DPP_XOR1>(v);
+    if constexpr (LG > 2) v += lane_exchange<DPP_XOR2>(v);
+    if constexpr (LG > 4) v += lane_exchange<DPP_HALF_MIRROR>(v);
+    if constexpr (LG > 8) v += lane_exchange<DPP_MIRROR>(v);
     return v;
 }
 

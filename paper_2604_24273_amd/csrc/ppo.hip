@@ -286,8 +286,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void ppo_tail_kernel(TailArgs a) {
         const double* z = out + lp0;
         double m = z[0];
         for (int k = tid; k < a.A; k += 64) m = fmax(m, z[k]);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+        m = wave_reduce(m, [](double a, double b) { return fmax(a, b); });
         double se = 0.0;
         for (int k = tid; k < a.A; k += 64) se += exp(z[k] - m);
         const double lse = m + log(wave_sum(se));
