@@ -478,14 +478,11 @@ inline int padded_head_dim(int dh) { return dh <= 32 ? 32 : (dh <= 64 ? 64 : 128
 
 }  // namespace
 
-size_t attention_mfma_ws_bytes(int B, int S, int n_heads, int n_kv_heads, int head_dim, bool q_frags) {
+size_t attention_mfma_ws_bytes(int B, int S, int n_heads, int n_kv_heads, int head_dim) {
+    (void)n_heads;
     const int dhp = padded_head_dim(head_dim);
     const size_t nrb = (size_t)(S + 31) / 32, ks = dhp / 16, db = dhp / 32;
-    return (size_t)B * n_kv_heads * nrb * (ks * 2 + db * 4) * 1024 + (q_frags ? (size_t)B * n_heads * nrb * ks * 2 * 1024 : 0);
-}
-
-void* attention_q_fragments(void* frag_ws, int B, int S, int n_kv_heads, int head_dim) {
-    return static_cast<char*>(frag_ws) + attention_mfma_ws_bytes(B, S, 0, n_kv_heads, head_dim, false);
+    return (size_t)B * n_kv_heads * nrb * (ks * 2 + db * 4) * 1024;
 }
 
 namespace {
@@ -540,8 +537,9 @@ int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& 
     return BRL_OK;
 }
 
-// The fragments are already in frag_ws (K / V, then q): written by the epilogue of the q | k | v product.
-int launch_attention_mfma_prepacked(int B, int S, int n_heads, int n_kv_heads, void* frag_ws, float* out, hipStream_t s) {
+// The fragments (K / V and q) were written by the epilogue of the q | k | v product.
+int launch_attention_mfma_prepacked(int B, int S, int n_heads, int n_kv_heads, const void* kvf, const void* qf, float* out,
+                                    hipStream_t s) {
     constexpr int dh = 128;
     if (S % 32 != 0 || n_heads % n_kv_heads != 0) {
         set_error("attention: prepacked operands need 32 | S (S = %d) and whole head groups", S);
@@ -553,8 +551,8 @@ int launch_attention_mfma_prepacked(int B, int S, int n_heads, int n_kv_heads, v
     FragArgs f;
     f.qkv = nullptr; f.ld = 0; f.cos_t = nullptr; f.sin_t = nullptr;
     f.qscale = 0.f;
-    f.KVF = static_cast<const uint4*>(frag_ws);
-    f.QF = static_cast<const uint4*>(attention_q_fragments(frag_ws, B, S, n_kv_heads, dh));
+    f.KVF = static_cast<const uint4*>(kvf);
+    f.QF = static_cast<const uint4*>(qf);
     f.B = B; f.S = S; f.NRB = nrb; f.Hq = n_heads; f.Hkv = n_kv_heads; f.dh = dh;
     f.sm.cu = nullptr; f.sm.b0 = 0;
     f.n_work = B * n_kv_heads * chunks;

@@ -199,9 +199,9 @@ __device__ inline int seq_len(const SeqMap& m, int b, int S) {
 int launch_rope_table(float* cos_t, float* sin_t, int S, int head_dim, float theta, hipStream_t s);
 int launch_attention_f32(const float* qkv, int ld, int B, int S, const SeqMap& sm, int n_heads, int n_kv_heads,
                          int head_dim, const float* cos_t, const float* sin_t, float* out, hipStream_t s);
-size_t attention_mfma_ws_bytes(int B, int S, int n_heads, int n_kv_heads, int head_dim, bool q_frags = false);
-void* attention_q_fragments(void* frag_ws, int B, int S, int n_kv_heads, int head_dim);   // where the q fragments start
-int launch_attention_mfma_prepacked(int B, int S, int n_heads, int n_kv_heads, void* frag_ws, float* out, hipStream_t s);
+size_t attention_mfma_ws_bytes(int B, int S, int n_heads, int n_kv_heads, int head_dim);
+int launch_attention_mfma_prepacked(int B, int S, int n_heads, int n_kv_heads, const void* kvf, const void* qf, float* out,
+                                    hipStream_t s);
 int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& sm, int n_heads, int n_kv_heads,
                           int head_dim, const float* cos_t, const float* sin_t, void* frag_ws, float* out, hipStream_t s);
 int launch_embed(const uint16_t* table, const int32_t* ids, int M, int d, int vocab, float* x, hipStream_t s);

@@ -201,6 +201,22 @@ def test_int8_weight_encoder(kw, b, s):
     assert np.array_equal(h_p, h)
 
 
+@pytest.mark.parametrize("n_states,S", [(128, 128), (170, 96)])
+def test_int8_qkv_product_writing_attention_operands_matches_two_step_path(n_states, S):
+    """Uniform batches at head_dim 128 with enough rows: the int8-weight q | k | v product writes the attention operands
+    itself.  The same states one per call and back to back take fp32 rows and the pack kernel: every bit agrees."""
+    B, R = _mods()
+    shape = synth.tiny_shape(n_layers=2, d=256, n_heads=4, n_kv_heads=2, head_dim=128, f=512, vocab=300, rope_theta=500000.0)
+    enc = R.EncoderHandle(shape, seed=5, int8_weights=True)
+    ids = synth.token_ids(5, 500, (n_states, S), shape.vocab)
+    print("fused int8 q|k|v epilogue: %d states x %d tokens" % (n_states, S), flush=True)
+    h = enc.forward(R.dev(ids))
+    for b in (0, 1, n_states // 2, n_states - 1):
+        assert torch.equal(h[b:b + 1], enc.forward(R.dev(ids[b:b + 1]))), b
+    cu = (np.arange(n_states + 1) * S).astype(np.int32)
+    assert torch.equal(h, enc.forward_packed(R.dev(ids.reshape(-1).astype(np.int32)), cu, max_len=S))
+
+
 @pytest.mark.parametrize("dims,n_members,act,batch", [
     ([2560, 256, 1], 3, "tanh", 64),
     ([2560, 256, 1], 5, "tanh", 7),
