@@ -869,28 +869,46 @@ __global__ __launch_bounds__(WK * 64, OCC) void gemm_direct_kernel(GemmArgs g) {
         }
         return;
     }
+    // ragged columns, debug taps: an element per thread and pass; what four passes read from memory is requested together
+    // (unconditionally: under the bounds test each would be waited for before the next)
+    constexpr int P4 = OUT / NT < 4 ? OUT / NT : 4;
+#pragma unroll 1
+    for (int p0 = 0; p0 < OUT / NT; p0 += P4) {
+        float dv[P4], rv[P4];
+        int sv[P4];
 #pragma unroll
-    for (int p = 0; p < OUT / NT; ++p) {
-        OutOne o(g, (int)threadIdx.x + p * NT, mb0, nb0);
-        if (!o.live(g)) continue;
-        const float d = EARLY ? early_d : g.dscale[o.m];
-        const int sq = EARLY ? early_sq : (g.sumq ? g.sumq[o.m] : 0);
-        int a0 = -sq;
+        for (int p = 0; p < P4; ++p) {
+            if constexpr (EARLY) {
+                dv[p] = early_d; sv[p] = early_sq; rv[p] = early_res;
+            } else {
+                const OutOne o(g, (int)threadIdx.x + (p0 + p) * NT, mb0, nb0);
+                const int m = min(o.m, g.M - 1);
+                dv[p] = g.dscale[m];
+                sv[p] = g.sumq ? g.sumq[m] : 0;
+                rv[p] = g.residual ? res_at(g, o.live(g) ? o.off : 0) : 0.f;
+            }
+        }
 #pragma unroll
-        for (int w = 0; w < (PARK ? WK : 1); ++w) a0 += red[w * OUT + (o.i * TN + o.j0) * 1024 + o.at];
-        if (g.glu) {
-            const float G = ((float)a0 * d) * beta[0];
-            const float U = ((float)(red[(o.i * TN + (TN > 1 ? o.j0 + 1 : 0)) * 1024 + o.at] - sq) * d) * beta[TN > 1 ? 1 : 0];
-            const float pz = fmaxf(G, 0.f);
-            g.y[o.off] = (pz * pz) * U;
-        } else {
-            float bsel = beta[0];
+        for (int p = 0; p < P4; ++p) {
+            const OutOne o(g, (int)threadIdx.x + (p0 + p) * NT, mb0, nb0);
+            if (!o.live(g)) continue;
+            int a0 = -sv[p];
 #pragma unroll
-            for (int j = 1; j < TN; ++j) bsel = o.j0 == j ? beta[j] : bsel;
-            float val = ((float)a0 * d) * bsel;
-            if (g.residual) val = val + (EARLY ? early_res : res_at(g, o.off));
-            g.y[o.off] = val;
-            if (g.acc_dbg) g.acc_dbg[o.off] = a0;
+            for (int w = 0; w < (PARK ? WK : 1); ++w) a0 += red[w * OUT + (o.i * TN + o.j0) * 1024 + o.at];
+            if (g.glu) {
+                const float G = ((float)a0 * dv[p]) * beta[0];
+                const float U = ((float)(red[(o.i * TN + (TN > 1 ? o.j0 + 1 : 0)) * 1024 + o.at] - sv[p]) * dv[p]) * beta[TN > 1 ? 1 : 0];
+                const float pz = fmaxf(G, 0.f);
+                g.y[o.off] = (pz * pz) * U;
+            } else {
+                float bsel = beta[0];
+#pragma unroll
+                for (int j = 1; j < TN; ++j) bsel = o.j0 == j ? beta[j] : bsel;
+                float val = ((float)a0 * dv[p]) * bsel;
+                if (g.residual) val = val + rv[p];
+                g.y[o.off] = val;
+                if (g.acc_dbg) g.acc_dbg[o.off] = a0;
+            }
         }
     }
 }
@@ -1068,7 +1086,8 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
         // 15.1 / 17.7 for 64 x 32; 900: 22 / 32 and 1750: 37 / 44 for 128 x 128, 2560: 52.6 / 48.4.  Four wavefronts
         // instead of eight once there are enough workgroups and k is short: 1750 x 2560 x 2560 20.1 / 21.6 (22.6 for 128 x
         // 128), 1300 x 3840 x 2560 21.5 / 23.5 (22.9), 1750 x 3840 x 2560 26.3 / 29 (24.8).
-        if (n32 <= 256) return launch_direct<1, 1, 16, 1, 4, false>(g, s);
+        // (ragged columns finish element by element: one per thread there, 817 x 606 x 3200 13.4 / 15.9)
+        if (n32 <= (g.fast_epilogue ? 256 : 512)) return launch_direct<1, 1, 16, 1, 4, false>(g, s);
         if (n32x64 <= (g.nsb >= 32 ? 2500 : 960)) return launch_direct<1, 2, 8, 1, 4, false>(g, s);
         if (n32x64 <= 2500) return launch_direct<1, 2, 4, 1, 4, false>(g, s);
         // up to 450 tiles of 128 x 128: eight wavefronts of 64 x 32 on a tile (two per SIMD from one workgroup) instead of

@@ -150,7 +150,8 @@ def test_bitlinear_forward_parity(m, n, k):
 
 
 @pytest.mark.parametrize("m,n,k", [
-    (64, 4096, 136), (64, 4100, 136),           # 256 tiles of 32 x 32, one block more (32 x 64 tiles, ragged n)
+    (64, 4096, 136), (64, 4128, 136),           # 256 tiles of 32 x 32, one block more (32 x 64 tiles)
+    (512, 1000, 136), (512, 1030, 136),         # ragged n: 512 tiles of 32 x 32, one block more
     (480, 4096, 264), (990, 1984, 264),         # 960 tiles of 32 x 64 on eight wavefronts, 961 on four
     (990, 1984, 4096), (990, 1990, 4088),       # ... and on eight again where k is long; ragged n and k
     (1600, 3200, 136), (1312, 3904, 136),       # 2500 tiles of 32 x 64; 2501: 128 x 128 on eight wavefronts
