@@ -21,7 +21,8 @@
  *    must stay valid until the enqueued work has run.
  *  - The caller owns all memory.  The library never allocates or frees device
  *    memory: scratch space comes in through `workspace` / `ws_bytes`, whose
- *    minimum size the matching brl_*_workspace_bytes() query returns.  A
+ *    minimum size the matching brl_*_workspace_bytes() query returns (for the
+ *    head entry points never less than for a smaller batch).  A
  *    workspace carries no state between calls (its contents may be anything on
  *    entry); calls that share a workspace must be ordered on one stream.
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).

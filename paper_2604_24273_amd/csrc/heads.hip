@@ -171,12 +171,12 @@ void first_layer_layout(const MlpSet& s, SetArgs& a) {
 
 }  // namespace
 
-// scratch: the first layers' partial sums, or (wide heads) every hidden layer's outputs
+// scratch: the first layers' partial sums, or (wide heads) every hidden layer's outputs; never less than a smaller batch needs
 size_t heads_workspace_bytes(const MlpSet& s) {
     if (!tail_fits(s)) return round_up_sz((size_t)s.B * hidden_units(s) * sizeof(double), 256) + 256;
     SetArgs a;
     first_layer_layout(s, a);
-    return (size_t)a.splits * s.B * a.col_end[s.n - 1] * sizeof(double);
+    return first_layer_rows(a.tile_end[s.n - 1], s.B, s.dims[0][0]) * a.col_end[s.n - 1] * sizeof(double);
 }
 
 int launch_heads(const MlpSet& s, void* workspace, hipStream_t stream) {

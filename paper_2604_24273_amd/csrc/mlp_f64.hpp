@@ -27,6 +27,18 @@ inline int first_layer_splits(int tiles, int btiles, int d) {
     return (int)(s > most ? most : s);
 }
 
+// rows of partial sums (splits x samples) that hold every launch of up to B samples: the splits drop where a batch passes
+// a block of 64 samples, so a smaller batch can need more rows than B itself
+inline size_t first_layer_rows(int tiles, int B, int d) {
+    size_t rows = 0;
+    for (int bt = 1; bt <= (B + 63) / 64; ++bt) {
+        const int splits = first_layer_splits(tiles, bt, d), b = bt * 64L < B ? bt * 64 : B;
+        if ((size_t)splits * b > rows) rows = (size_t)splits * b;
+        if (splits == 1) return rows > (size_t)B ? rows : (size_t)B;
+    }
+    return rows;
+}
+
 // four inputs k .. k + 3 of a row of n values, zeros past the end
 __device__ inline v4f_u four_inputs(const float* row, int k, int n) {
     if (k + 4 <= n) return *reinterpret_cast<const v4f_u*>(row + k);

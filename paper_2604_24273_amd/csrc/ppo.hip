@@ -837,7 +837,7 @@ PpoWs ppo_ws_layout(const Layout& L, int batch) {
     const int tiles = (L.head[0].dims[1] + 15) / 16 + (L.head[1].dims[1] + 15) / 16;
     W.btiles = (batch + 63) / 64;
     W.splits = first_layer_splits(tiles, W.btiles, L.head[0].dims[0]);
-    W.z_off = W.tail ? take((size_t)W.splits * batch * ncol * 8) : 0;
+    W.z_off = W.tail ? take(first_layer_rows(tiles, batch, L.head[0].dims[0]) * ncol * 8) : 0;
     W.grad_off = take(L.n_params * 8);
     int nw = 0;
     for (int hd = 0; hd < 2; ++hd)

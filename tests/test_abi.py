@@ -57,6 +57,23 @@ def test_size_queries(B):
     assert B.brl_quantize_workspace_bytes(10, 10) >= 8192
 
 
+@pytest.mark.parametrize("policy,value", [((2560, 256, 18), (2560, 256, 1)), ((100, 16, 3), (100, 1)), ((2560, 5), (2560, 1)),
+                                          ((96, 2100, 700, 6), (96, 2050, 1)), ((640, 256, 4), (640, 2050, 1))])
+def test_head_workspaces_never_shrink_with_the_batch(B, policy, value):
+    """One workspace sized for the largest batch serves every smaller one."""
+    dims = [(C.c_int * len(d))(*d) for d in (policy, value)]
+    mlp = [B.brl_mlp(len(d) - 1, C.cast(d, C.POINTER(C.c_int)), None, None, B.BRL_ACT_TANH) for d in dims]
+    head = B.brl_head(*mlp)
+    cfg, keep = B.make_ppo_config(policy, value, B.BRL_ACT_TANH)
+    queries = [lambda b: B.brl_head_workspace_bytes(head, b), lambda b: B.brl_ppo_workspace_bytes(cfg, b)]
+    for n in (1, 3, 5, 8):
+        members = B.make_mlp_array([mlp[1]] * n)
+        queries.append(lambda b, m=members, n=n: B.brl_value_ensemble_workspace_bytes(m, n, b))
+    for i, q in enumerate(queries):
+        sizes = [q(b) for b in range(1, 700)]
+        assert sizes[0] > 0 and sizes == sorted(sizes), i
+
+
 def test_bad_arguments_are_rejected_on_the_host(B):
     lib = B.lib()
     fake = C.c_void_p(0x1000)          # aligned, never dereferenced: checks fail first
