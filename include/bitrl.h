@@ -392,9 +392,10 @@ int policy_value_head(const brl_head* head /* HOST */, const float* h, int B,
 
 /* ------------------------------------------------------------------------
  * Ensemble critic (Sec. 5.3, component ablations: "3x / 5x 1-bit critics
- * (avg)"): n_members value heads of identical shape read the same h; every
- * layer of all members runs in one launch.  values_each[e][b] is member e's
- * head output exactly as policy_value_head computes a value; value_mean[b] =
+ * (avg)"): n_members value heads of identical shape read the same h and run
+ * side by side.  values_each[e][b] is member e's head output exactly as
+ * policy_value_head computes a value (a head's sums run in one order, whatever
+ * heads and samples share the call); value_mean[b] =
  * (sum over members in member order, in fp64) / n_members, rounded to fp32.
  * members: HOST array of n_members (1..8) heads with equal n_layers, dims and
  * act, output width 1.  h [B, dims[0]]; value_mean [B]; values_each

@@ -1,10 +1,13 @@
 // Forward pass of the fp32 MLP heads (policy and value, or an ensemble of value heads): all heads of a call together.
 //
-// Two launches: the first layers of every head as one fp64 matrix-core contraction (mlp_f64.hpp), then one workgroup
-// per sample for everything above (the layers there are small: 256 -> 18, 256 -> 1) and, for an ensemble, the mean.
+// The first layers of every head are one fp64 matrix-core contraction (mlp_f64.hpp).  What is above them is small (256 ->
+// 18, 256 -> 1): one workgroup per sample for all of it and, for an ensemble, the mean; or a launch per layer level where a
+// workgroup would be long at it or its LDS too small.  Every sum runs in an order of its own layer's width alone, so
+// the bits of a head do not depend on the launch form, the batch or the heads beside it: an ensemble's member gives what
+// it gives as a value head.
 // One launch per layer and head with a wavefront per result took 86 us for 64 samples of 2560 -> 256 -> 18 and 1 (four
-// launches; 81 us even for one sample: 40 dependent rounds of loads per wavefront), this takes 18 us from one to 64
-// samples; 1024 samples 1167 -> 90 us (78 us of it the contraction).  Heads whose upper layers are too wide for a workgroup per sample keep a launch per layer level.
+// launches; 81 us even for one sample: 40 dependent rounds of loads per wavefront); the two launches take 15 us for 64
+// samples, 13 us for one, 77 us for 1024.
 #include <cstring>
 
 #include "mlp_f64.hpp"
@@ -14,34 +17,44 @@ namespace brl {
 namespace {
 
 constexpr int HEAD_MAX_UNITS = 4096;           // layer outputs of all heads together: 32 KB of LDS
-constexpr size_t HEAD_MAX_WEIGHTS = 1 << 18;   // weights above the first layers: every sample's workgroup reads them all
 
+// What is the same for every form.  Units of a layer level lie head after head; a head that has no such layer has none.
 struct SetArgs {
     MlpSet s;
-    int splits, btiles;
-    int tile_end[MAX_HEADS], col_end[MAX_HEADS];     // first-layer tiles of 16 units / columns, cumulative
-    double* z;                                       // [splits][B][col_end[n - 1]]
+    int splits, btiles, depth;
+    int tile_end[MAX_HEADS];                         // first-layer tiles of 16 units, cumulative
+    int unit_end[MAX_MLP_LAYERS][MAX_HEADS];         // outputs of a level, cumulative
+    double* z;                                       // [splits][B][units of level 0]
 };
 
-__global__ __launch_bounds__(256) void heads_first_kernel(SetArgs a) {
-    __shared__ FirstLayerSums part;
+// the head that entry u of a cumulative table belongs to
+__device__ inline int head_of(const int (&end)[MAX_HEADS], int n, int u) {
+    int hd = 0;
+#pragma unroll
+    for (int e = 0; e + 1 < MAX_HEADS; ++e) hd += (e + 1 < n && u >= end[e]) ? 1 : 0;
+    return hd;
+}
+
+// ALL: a workgroup takes all of its tile's inputs (a.splits is 1).  QT: tiles of 16 samples of a workgroup.
+template <bool ALL, int QT>
+__global__ __launch_bounds__(256, 3) void heads_first_kernel(SetArgs a) {
+    __shared__ FirstLayerSums<ALL, QT> part;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int tiles = a.tile_end[a.s.n - 1];
     const int split = blockIdx.x % a.splits, tile = (blockIdx.x / a.splits) % tiles, bt = blockIdx.x / (a.splits * tiles);
-    int hd = 0;
-    while (tile >= a.tile_end[hd]) ++hd;
+    const int hd = head_of(a.tile_end, a.s.n, tile);
     const int d = a.s.dims[hd][0], od = a.s.dims[hd][1];
     const int o0 = (tile - (hd ? a.tile_end[hd - 1] : 0)) * 16;
-    const float* hrow[4];
+    const float* hrow[QT];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) hrow[q] = a.s.h + (size_t)min(bt * 64 + q * 16 + (lane & 15), a.s.B - 1) * d;
-    first_layer_sums(a.s.W[hd][0] + (size_t)min(o0 + (lane & 15), od - 1) * d, hrow, d, split * 4 + wave, a.splits * 4, part);
-    const int ncol = a.col_end[a.s.n - 1], col0 = hd ? a.col_end[hd - 1] : 0;
+    for (int q = 0; q < QT; ++q) hrow[q] = a.s.h + (size_t)min(bt * 64 + q * 16 + (lane & 15), a.s.B - 1) * d;
+    double sum[QT];
+    first_layer_sums<ALL, QT>(a.s.W[hd][0] + (size_t)min(o0 + (lane & 15), od - 1) * d, hrow, d, split, part, sum);
+    const int ncol = a.unit_end[0][a.s.n - 1], col0 = hd ? a.unit_end[0][hd - 1] : 0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int qv = u * 4 + wave;
-        const int b = bt * 64 + (qv >> 2) * 16 + 4 * (qv & 3) + (lane >> 4), o = o0 + (lane & 15);
-        if (b < a.s.B && o < od) a.z[((size_t)split * a.s.B + b) * ncol + col0 + o] = first_layer_sum(part, qv, lane);
+    for (int u = 0; u < QT; ++u) {
+        const int b = bt * 64 + u * 16 + 4 * wave + (lane >> 4), o = o0 + (lane & 15);
+        if (b < a.s.B && o < od) a.z[((size_t)split * a.s.B + b) * ncol + col0 + o] = sum[u];
     }
 }
 
@@ -52,17 +65,16 @@ __device__ inline float head_mean(const float* vals, int n, size_t stride) {
     return (float)(t / (double)n);
 }
 
-__global__ __launch_bounds__(256) void heads_tail_kernel(SetArgs a) {
-    __shared__ double out[HEAD_MAX_UNITS];           // layer outputs, level by level, head by head inside a level
+constexpr int LG = 8;                                // lanes per output unit above the first layer
+
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void heads_tail_kernel(SetArgs a) {
+    __shared__ double out[HEAD_MAX_UNITS];           // layer outputs, level by level
     __shared__ float last[MAX_HEADS];                // results of width 1 (for the mean)
     const int tid = threadIdx.x, b = blockIdx.x;
-    const int ncol = a.col_end[a.s.n - 1];
-    int depth = 1;
-    for (int e = 0; e < a.s.n; ++e) depth = max(depth, a.s.layers[e]);
-    for (int c = tid; c < ncol; c += 256) {
-        int hd = 0;
-        while (c >= a.col_end[hd]) ++hd;
-        const int o = c - (hd ? a.col_end[hd - 1] : 0);
+    const int ncol = a.unit_end[0][a.s.n - 1];
+    for (int c = tid; c < ncol; c += THREADS) {
+        const int hd = head_of(a.unit_end[0], a.s.n, c), o = c - (hd ? a.unit_end[0][hd - 1] : 0);
         const double v = first_layer_total(a.z + (size_t)b * ncol + c, a.splits, (size_t)a.s.B * ncol) + (double)a.s.bias[hd][0][o];
         if (a.s.layers[hd] > 1) {
             out[c] = activate(v, a.s.act);
@@ -72,23 +84,14 @@ __global__ __launch_bounds__(256) void heads_tail_kernel(SetArgs a) {
         }
     }
     __syncthreads();
-    constexpr int LG = 8;                            // lanes per output unit
+    constexpr int GROUPS = THREADS / LG;
     int in_base = 0, out_base = ncol;
-    for (int l = 1; l < depth; ++l) {
-        int total = 0;
-        for (int e = 0; e < a.s.n; ++e) total += l < a.s.layers[e] ? a.s.dims[e][l + 1] : 0;
-        for (int u = tid / LG; u < (total + 31) / 32 * 32; u += 256 / LG) {
-            // head of this unit, its place in the level, and where its inputs start in the level below
-            int hd = 0, o = min(u, total - 1), in0 = in_base;
-            for (;;) {
-                const int od = l < a.s.layers[hd] ? a.s.dims[hd][l + 1] : 0;
-                if (o < od) break;
-                o -= od;
-                in0 += l <= a.s.layers[hd] ? a.s.dims[hd][l] : 0;
-                ++hd;
-            }
+    for (int l = 1; l < a.depth; ++l) {
+        const int total = a.unit_end[l][a.s.n - 1];
+        for (int u = tid / LG; u < (total + GROUPS - 1) / GROUPS * GROUPS; u += GROUPS) {
+            const int uc = min(u, total - 1), hd = head_of(a.unit_end[l], a.s.n, uc), o = uc - (hd ? a.unit_end[l][hd - 1] : 0);
             const int id = a.s.dims[hd][l], od = a.s.dims[hd][l + 1];
-            double v = group_dot<LG>(a.s.W[hd][l] + (size_t)o * id, out + in0, id);
+            double v = group_dot<LG>(a.s.W[hd][l] + (size_t)o * id, out + in_base + (hd ? a.unit_end[l - 1][hd - 1] : 0), id);
             if (tid % LG == 0 && u < total) {
                 v += (double)a.s.bias[hd][l][o];
                 if (l + 1 < a.s.layers[hd]) {
@@ -107,34 +110,33 @@ __global__ __launch_bounds__(256) void heads_tail_kernel(SetArgs a) {
     if (a.s.mean && tid == 0) a.s.mean[b] = head_mean(last, a.s.n, 1);
 }
 
-// One layer level of every head, a wavefront per result
+// One layer level of every head and sample: a thread per result of the first layer, LG lanes per result above
 struct LevelArgs {
-    MlpSet s;
+    SetArgs a;
     int level;
-    size_t first[MAX_HEADS + 1];                     // first result of each head
-    const double* in64[MAX_HEADS];                   // null on the first level: every head reads h
-    double* out64[MAX_HEADS];
+    const double* in;                                // [B][units of the level below]
+    double* out;                                     // [B][units of the level]
 };
-__global__ __launch_bounds__(256) void heads_level_kernel(LevelArgs a) {
-    const size_t wid = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (wid >= a.first[a.s.n]) return;
-    int hd = 0;
-    while (wid >= a.first[hd + 1]) ++hd;
-    const int id = a.s.dims[hd][a.level], od = a.s.dims[hd][a.level + 1];
-    const int b = (int)((wid - a.first[hd]) / od), o = (int)((wid - a.first[hd]) % od);
-    const float* w = a.s.W[hd][a.level] + (size_t)o * id;
-    const double* x64 = a.in64[hd] ? a.in64[hd] + (size_t)b * id : nullptr;
-    const float* x32 = a.s.h + (size_t)b * id;
-    double acc = 0.0;
-#pragma unroll 4
-    for (int i = lane; i < id; i += 64) acc += (double)w[i] * (x64 ? x64[i] : (double)x32[i]);
-    acc = wave_sum(acc);
-    if (lane == 0) {
-        const double z = acc + (double)a.s.bias[hd][a.level][o];
-        if (a.level + 1 == a.s.layers[hd]) a.s.out[hd][(size_t)b * od + o] = (float)z;
-        else a.out64[hd][(size_t)b * od + o] = activate(z, a.s.act);
+template <bool FIRST>
+__global__ __launch_bounds__(256) void heads_level_kernel(LevelArgs g) {
+    const SetArgs& a = g.a;
+    const int l = FIRST ? 0 : g.level, total = a.unit_end[l][a.s.n - 1];
+    const size_t n = (size_t)a.s.B * total, r = ((size_t)blockIdx.x * 256 + threadIdx.x) / (FIRST ? 1 : LG);
+    const size_t rc = r < n ? r : n - 1;             // (every lane of a group has to be there)
+    const int b = (int)(rc / total), u = (int)(rc % total);
+    const int hd = head_of(a.unit_end[l], a.s.n, u), o = u - (hd ? a.unit_end[l][hd - 1] : 0);
+    const int id = a.s.dims[hd][l], od = a.s.dims[hd][l + 1];
+    double v;
+    if constexpr (FIRST) {
+        v = first_layer_total(a.z + (size_t)b * total + u, a.splits, n);
+    } else {
+        const int in0 = hd ? a.unit_end[l - 1][hd - 1] : 0;
+        v = group_dot<LG>(a.s.W[hd][l] + (size_t)o * id, g.in + (size_t)b * a.unit_end[l - 1][a.s.n - 1] + in0, id);
     }
+    if (r >= n || (!FIRST && threadIdx.x % LG != 0)) return;
+    v += (double)a.s.bias[hd][l][o];
+    if (l + 1 == a.s.layers[hd]) a.s.out[hd][(size_t)b * od + o] = (float)v;
+    else g.out[(size_t)b * total + u] = activate(v, a.s.act);
 }
 
 __global__ __launch_bounds__(256) void heads_mean_kernel(MlpSet s) {
@@ -142,78 +144,74 @@ __global__ __launch_bounds__(256) void heads_mean_kernel(MlpSet s) {
     if (b < s.B) s.mean[b] = head_mean(s.out[0] + b, s.n, (size_t)s.B);      // the members' results lie one after another
 }
 
-size_t hidden_units(const MlpSet& s) {
-    size_t t = 0;
-    for (int e = 0; e < s.n; ++e)
-        for (int l = 1; l < s.layers[e]; ++l) t += (size_t)s.dims[e][l];
-    return t;
-}
-
-bool tail_fits(const MlpSet& s) {
-    size_t units = 0, weights = 0;
-    for (int e = 0; e < s.n; ++e)
-        for (int l = 0; l < s.layers[e]; ++l) {
-            units += (size_t)s.dims[e][l + 1];
-            if (l > 0) weights += (size_t)s.dims[e][l] * s.dims[e][l + 1];
-        }
-    return units <= (size_t)HEAD_MAX_UNITS && weights <= HEAD_MAX_WEIGHTS;
-}
-
-void first_layer_layout(const MlpSet& s, SetArgs& a) {
-    int tiles = 0, cols = 0;
+SetArgs set_layout(const MlpSet& s) {
+    SetArgs a;
+    memset(&a, 0, sizeof(a));
+    a.s = s;
+    int tiles = 0;
+    a.depth = 1;
     for (int e = 0; e < s.n; ++e) {
         a.tile_end[e] = tiles += (s.dims[e][1] + 15) / 16;
-        a.col_end[e] = cols += s.dims[e][1];
+        if (s.layers[e] > a.depth) a.depth = s.layers[e];
+        for (int l = 0; l < MAX_MLP_LAYERS; ++l)
+            a.unit_end[l][e] = (e ? a.unit_end[l][e - 1] : 0) + (l < s.layers[e] ? s.dims[e][l + 1] : 0);
     }
     a.btiles = (s.B + 63) / 64;
     a.splits = first_layer_splits(tiles, a.btiles, s.dims[0][0]);
+    return a;
+}
+
+// The first layers' partial sums (never less than a smaller batch needs), then the hidden layers of the launch-per-level form
+size_t sums_bytes(const SetArgs& a) {
+    const MlpSet& s = a.s;
+    return round_up_sz(first_layer_rows(a.tile_end[s.n - 1], s.B, s.dims[0][0]) * a.unit_end[0][s.n - 1] * sizeof(double), 256);
+}
+size_t hidden_units(const SetArgs& a) {
+    size_t t = 0;
+    for (int l = 0; l + 1 < a.depth; ++l) t += (size_t)a.unit_end[l][a.s.n - 1];
+    return t;
+}
+
+constexpr size_t HEAD_TAIL_WEIGHTS = 1 << 18;  // weights above the first layers: every sample's workgroup reads them all
+
+bool one_workgroup_per_sample(const SetArgs& a) {
+    size_t units = 0, weights = 0;
+    for (int l = 0; l < a.depth; ++l) units += (size_t)a.unit_end[l][a.s.n - 1];
+    for (int e = 0; e < a.s.n; ++e)
+        for (int l = 1; l < a.s.layers[e]; ++l) weights += (size_t)a.s.dims[e][l] * a.s.dims[e][l + 1];
+    return units <= (size_t)HEAD_MAX_UNITS && weights <= HEAD_TAIL_WEIGHTS;
 }
 
 }  // namespace
 
-// scratch: the first layers' partial sums, or (wide heads) every hidden layer's outputs; never less than a smaller batch needs
 size_t heads_workspace_bytes(const MlpSet& s) {
-    if (!tail_fits(s)) return round_up_sz((size_t)s.B * hidden_units(s) * sizeof(double), 256) + 256;
-    SetArgs a;
-    first_layer_layout(s, a);
-    return first_layer_rows(a.tile_end[s.n - 1], s.B, s.dims[0][0]) * a.col_end[s.n - 1] * sizeof(double);
+    const SetArgs a = set_layout(s);
+    return sums_bytes(a) + round_up_sz((size_t)s.B * hidden_units(a) * sizeof(double), 256);
 }
 
 int launch_heads(const MlpSet& s, void* workspace, hipStream_t stream) {
     LaunchTimer tm(BRL_KC_OTHER, stream);
-    if (tail_fits(s)) {
-        SetArgs a;
-        memset(&a, 0, sizeof(a));
-        a.s = s;
-        first_layer_layout(s, a);
-        a.z = static_cast<double*>(workspace);
-        hipLaunchKernelGGL(heads_first_kernel, dim3((unsigned)(a.tile_end[s.n - 1] * a.splits * a.btiles)), dim3(256), 0, stream, a);
-        hipLaunchKernelGGL(heads_tail_kernel, dim3((unsigned)s.B), dim3(256), 0, stream, a);
-        BRL_LAUNCH_CHECK("heads");
-        return BRL_OK;
-    }
-    int depth = 1;
-    for (int e = 0; e < s.n; ++e) depth = s.layers[e] > depth ? s.layers[e] : depth;
-    double* next = static_cast<double*>(workspace);
-    const double* in[MAX_HEADS] = {};
-    for (int l = 0; l < depth; ++l) {
-        LevelArgs a;
-        memset(&a, 0, sizeof(a));
-        a.s = s;
-        a.level = l;
-        for (int e = 0; e < s.n; ++e) {
-            const bool runs = l < s.layers[e];
-            a.first[e + 1] = a.first[e] + (runs ? (size_t)s.B * s.dims[e][l + 1] : 0);
-            a.in64[e] = in[e];
-            if (runs && l + 1 < s.layers[e]) {
-                a.out64[e] = next;
-                in[e] = next;
-                next += (size_t)s.B * s.dims[e][l + 1];
-            }
+    LevelArgs g;
+    memset(&g, 0, sizeof(g));
+    SetArgs& a = g.a;
+    a = set_layout(s);
+    a.z = static_cast<double*>(workspace);
+    const dim3 grid((unsigned)a.tile_end[s.n - 1] * (unsigned)a.splits * (unsigned)a.btiles);
+    if (a.splits == 1) hipLaunchKernelGGL((heads_first_kernel<true, 4>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((heads_first_kernel<false, 4>), grid, dim3(256), 0, stream, a);
+    if (one_workgroup_per_sample(a)) {
+        hipLaunchKernelGGL(heads_tail_kernel<256>, dim3((unsigned)s.B), dim3(256), 0, stream, a);
+    } else {
+        g.out = reinterpret_cast<double*>(static_cast<char*>(workspace) + sums_bytes(a));
+        for (g.level = 0; g.level < a.depth; ++g.level) {
+            const size_t results = (size_t)s.B * a.unit_end[g.level][s.n - 1];
+            if (g.level == 0) hipLaunchKernelGGL(heads_level_kernel<true>, dim3((unsigned)((results + 255) / 256)), dim3(256), 0, stream, g);
+            else hipLaunchKernelGGL(heads_level_kernel<false>, dim3((unsigned)((results * LG + 255) / 256)), dim3(256), 0, stream, g);
+            g.in = g.out;
+            g.out += results;
         }
-        hipLaunchKernelGGL(heads_level_kernel, dim3((unsigned)((a.first[s.n] + 3) / 4)), dim3(256), 0, stream, a);
+        if (s.mean) hipLaunchKernelGGL(heads_mean_kernel, dim3((s.B + 255) / 256), dim3(256), 0, stream, s);
     }
-    if (s.mean) hipLaunchKernelGGL(heads_mean_kernel, dim3((s.B + 255) / 256), dim3(256), 0, stream, s);
     BRL_LAUNCH_CHECK("heads");
     return BRL_OK;
 }

@@ -179,8 +179,10 @@ __device__ void minibatch_scale(const float* adv, const int32_t* rows, int B, in
     }
 }
 
-__global__ __launch_bounds__(256) void ppo_first_layer_kernel(FirstArgs a) {
-    __shared__ FirstLayerSums part;
+// ALL: a workgroup takes all of its tile's inputs (a.splits is 1)
+template <bool ALL>
+__global__ __launch_bounds__(256, 3) void ppo_first_layer_kernel(FirstArgs a) {
+    __shared__ FirstLayerSums<ALL, 4> part;
     const int tiles = a.tiles[0] + a.tiles[1];
     if ((int)blockIdx.x == tiles * a.splits * a.btiles) {
         minibatch_scale(a.adv, a.rows, a.B, a.T, a.adv_eps, a.normalize_adv, a.scal);
@@ -193,14 +195,14 @@ __global__ __launch_bounds__(256) void ppo_first_layer_kernel(FirstArgs a) {
     const float* hrow[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) hrow[q] = a.h + (size_t)clamp_index(a.rows[min(bt * 64 + q * 16 + (lane & 15), a.B - 1)], a.T) * a.d;
-    first_layer_sums(a.W[hd] + (size_t)min(o0 + (lane & 15), a.out_dim[hd] - 1) * a.d, hrow, a.d, split * 4 + wave, a.splits * 4, part);
+    double sum[4];
+    first_layer_sums<ALL, 4>(a.W[hd] + (size_t)min(o0 + (lane & 15), a.out_dim[hd] - 1) * a.d, hrow, a.d, split, part, sum);
     const int ncol = a.out_dim[0] + a.out_dim[1];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int qv = u * 4 + wave;                                 // (sample tile, register)
-        const int b = bt * 64 + (qv >> 2) * 16 + 4 * (qv & 3) + (lane >> 4), o = o0 + (lane & 15);
+        const int b = bt * 64 + u * 16 + 4 * wave + (lane >> 4), o = o0 + (lane & 15);
         if (b < a.B && o < a.out_dim[hd])
-            a.z[((size_t)split * a.B + b) * ncol + (hd ? a.out_dim[0] : 0) + o] = first_layer_sum(part, qv, lane);
+            a.z[((size_t)split * a.B + b) * ncol + (hd ? a.out_dim[0] : 0) + o] = sum[u];
     }
 }
 
@@ -982,7 +984,8 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
                 fl.rows = rows;
                 ta.rows = rows;
                 const unsigned blocks = (unsigned)((fl.tiles[0] + fl.tiles[1]) * W.splits * W.btiles) + 1;   // + the advantages' scale
-                hipLaunchKernelGGL(ppo_first_layer_kernel, dim3(blocks), dim3(256), 0, s, fl);
+                if (W.splits == 1) hipLaunchKernelGGL(ppo_first_layer_kernel<true>, dim3(blocks), dim3(256), 0, s, fl);
+                else hipLaunchKernelGGL(ppo_first_layer_kernel<false>, dim3(blocks), dim3(256), 0, s, fl);
                 hipLaunchKernelGGL(ppo_tail_kernel, dim3(batch), dim3(TAIL_THREADS), 0, s, ta);
             } else {
                 // forward: level l of both heads in one launch

@@ -280,3 +280,53 @@ def test_policy_value_head_shapes(dims_p, dims_v, acts, batch):
     l_ref, v_ref = O.policy_value_head(h, O.MLP(pw, pb, acts[0]), O.MLP(vw, vb, acts[1]))
     assert np.abs(logits.cpu().numpy() - l_ref).max() <= 1e-6 * np.abs(l_ref).max()
     assert np.abs(value.cpu().numpy() - np.asarray(v_ref).reshape(-1)).max() <= 1e-6 * max(np.abs(v_ref).max(), 1.0)
+
+
+@pytest.mark.parametrize("dims", [[2560, 1], [2560, 256, 1], [1000, 40, 24, 1], [640, 512, 512, 1], [96, 2100, 1], [60, 700, 400, 1]])
+def test_value_head_bits_do_not_depend_on_what_shares_the_call(dims):
+    """A value head gives the same bits beside any policy head, in an ensemble of any size and in a batch of any size.
+    The inputs of the first layer cancel to about 1e-9 of their size, so that another order of the fp64 sums would show
+    in the fp32 results.  The last two: wide heads (a launch per level), alone and beside a policy head that is not."""
+    B, R = _mods()
+    rng = np.random.default_rng(7)
+    d, n = dims[0], 8
+    pairs = rng.permutation(d - 2).reshape(-1, 2)
+    rest = [i for i in range(d) if i >= d - 2]
+
+    def params(e):
+        ws, bs = synth.mlp_params(31, 20 * e, dims)
+        w = ws[0].copy()
+        w[:, pairs[:, 1]] = -w[:, pairs[:, 0]]
+        w[:, rest] *= np.float32(2.0 ** -30)
+        return [w] + list(ws[1:]), [np.zeros_like(b) for b in bs]
+
+    h = synth.normal(31, 399, (200, d))
+    h[:, pairs[:, 1]] = h[:, pairs[:, 0]]
+    h_dev = R.dev(h)
+    members = [params(e) for e in range(n)]
+
+    def value(e, policy_dims, batch):
+        pw, pb = synth.mlp_params(31, 390, policy_dims)
+        pol, k1 = B.make_mlp([R.dev(w) for w in pw], [R.dev(b) for b in pb], B.BRL_ACT_RELU)
+        val, k2 = B.make_mlp([R.dev(w) for w in members[e][0]], [R.dev(b) for b in members[e][1]], B.BRL_ACT_RELU)
+        head = B.brl_head(pol, val)
+        logits = torch.empty((batch, policy_dims[-1]), dtype=torch.float32, device="cuda")
+        out = torch.empty((batch,), dtype=torch.float32, device="cuda")
+        ws = R.Workspace(B.brl_head_workspace_bytes(head, batch))
+        B.policy_value_head(head, h_dev[:batch].contiguous(), batch, logits, out, ws.buf)
+        p_ref = O.policy_value_head(h[:batch], O.MLP(pw, pb, "relu"), O.MLP(*members[e], "relu"))[0]
+        assert np.abs(logits.cpu().numpy() - p_ref).max() <= 1e-6 * np.abs(p_ref).max()
+        return out
+
+    want = [value(e, [d, 4], 200) for e in (0, n - 1)]
+    assert all(float(w.abs().max()) < 1e-3 for w in want)
+    for policy_dims, batch in (([d, 4], 1), ([d, 4], 64), ([d, 700], 65), ([d, 256, 18], 64), ([d, 1200, 6], 129)):
+        print("value head", dims, "beside", policy_dims, batch, flush=True)
+        assert torch.equal(value(0, policy_dims, batch), want[0][:batch]), (policy_dims, batch)
+    for members_n, batch in ((1, 64), (2, 200), (3, 64), (5, 65), (8, 1), (8, 200)):
+        print("ensemble", dims, members_n, batch, flush=True)
+        ens = R.ValueEnsemble(members[:members_n - 1] + members[-1:] if members_n > 1 else members[:1], act=B.BRL_ACT_RELU)
+        mean, each = ens.forward(h_dev[:batch].contiguous())
+        assert torch.equal(each[0], want[0][:batch]), (members_n, batch)
+        if members_n > 1:
+            assert torch.equal(each[-1], want[1][:batch]), (members_n, batch)
