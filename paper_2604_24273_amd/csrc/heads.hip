@@ -6,8 +6,8 @@
 // the bits of a head do not depend on the launch form, the batch or the heads beside it: an ensemble's member gives what
 // it gives as a value head.
 // One launch per layer and head with a wavefront per result took 86 us for 64 samples of 2560 -> 256 -> 18 and 1 (four
-// launches; 81 us even for one sample: 40 dependent rounds of loads per wavefront); the two launches take 15 us for 64
-// samples, 13 us for one, 77 us for 1024.
+// launches; 81 us even for one sample: 40 dependent rounds of loads per wavefront); the two launches take 14 us for 64
+// samples, 9.4 us for one, 75 us for 1024 (the launches per layer and head 1147 us).
 #include <cstring>
 
 #include "mlp_f64.hpp"
@@ -17,6 +17,10 @@ namespace brl {
 namespace {
 
 constexpr int HEAD_MAX_UNITS = 4096;           // layer outputs of all heads together: 32 KB of LDS
+// threads of a sample's workgroup: 512 up to two workgroups per compute unit, where every loop over units costs its
+// latency (64 samples of 2560 -> 256 -> 256 -> 18 and 1: 32 us, 51 us with 256), 256 beyond (1024 samples of 2560 -> 256 ->
+// 18 and 1: 77 us, 81 us with 512)
+constexpr int HEAD_TAIL_FEW = 512;
 
 // What is the same for every form.  Units of a layer level lie head after head; a head that has no such layer has none.
 struct SetArgs {
@@ -35,7 +39,8 @@ __device__ inline int head_of(const int (&end)[MAX_HEADS], int n, int u) {
     return hd;
 }
 
-// ALL: a workgroup takes all of its tile's inputs (a.splits is 1).  QT: tiles of 16 samples of a workgroup.
+// ALL: a workgroup takes all of its tile's inputs (a.splits is 1).  QT: tiles of 16 samples of a workgroup, one where the
+// call has no more than 16 (five members of 2560 -> 256 -> 1, one sample: 21.4 us with four, 14.9 us with one).
 template <bool ALL, int QT>
 __global__ __launch_bounds__(256, 3) void heads_first_kernel(SetArgs a) {
     __shared__ FirstLayerSums<ALL, QT> part;
@@ -172,14 +177,19 @@ size_t hidden_units(const SetArgs& a) {
     return t;
 }
 
-constexpr size_t HEAD_TAIL_WEIGHTS = 1 << 18;  // weights above the first layers: every sample's workgroup reads them all
+// Weights above the first layers that a lone workgroup goes through before a launch per level would be done, and the batch
+// from which there are workgroups enough to fill the chip.  2560 inputs, one workgroup per sample / a launch per level, us:
+// five members of 64, 64 (21 k weights) on 1 sample 18.9 / 15.5, on 64 23.1 / 21.9, on 200 28.3 / 33.2; policy and value
+// head of 256 (5 k) 9.5 / 10.6, 14.1 / 16.2, 26.3 / 28.3; of 256, 256 (136 k) 27.3 / 15.7, 32.0 / 26.1, 43.9 / 53.7.
+constexpr size_t HEAD_TAIL_WEIGHTS = 1 << 14;
+constexpr int HEAD_TAIL_BATCH = 128;
 
 bool one_workgroup_per_sample(const SetArgs& a) {
     size_t units = 0, weights = 0;
     for (int l = 0; l < a.depth; ++l) units += (size_t)a.unit_end[l][a.s.n - 1];
     for (int e = 0; e < a.s.n; ++e)
         for (int l = 1; l < a.s.layers[e]; ++l) weights += (size_t)a.s.dims[e][l] * a.s.dims[e][l + 1];
-    return units <= (size_t)HEAD_MAX_UNITS && weights <= HEAD_TAIL_WEIGHTS;
+    return units <= (size_t)HEAD_MAX_UNITS && (weights <= HEAD_TAIL_WEIGHTS || a.s.B >= HEAD_TAIL_BATCH);
 }
 
 }  // namespace
@@ -197,10 +207,14 @@ int launch_heads(const MlpSet& s, void* workspace, hipStream_t stream) {
     a = set_layout(s);
     a.z = static_cast<double*>(workspace);
     const dim3 grid((unsigned)a.tile_end[s.n - 1] * (unsigned)a.splits * (unsigned)a.btiles);
-    if (a.splits == 1) hipLaunchKernelGGL((heads_first_kernel<true, 4>), grid, dim3(256), 0, stream, a);
+    const bool few = s.B <= 16;
+    if (a.splits == 1 && few) hipLaunchKernelGGL((heads_first_kernel<true, 1>), grid, dim3(256), 0, stream, a);
+    else if (a.splits == 1) hipLaunchKernelGGL((heads_first_kernel<true, 4>), grid, dim3(256), 0, stream, a);
+    else if (few) hipLaunchKernelGGL((heads_first_kernel<false, 1>), grid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL((heads_first_kernel<false, 4>), grid, dim3(256), 0, stream, a);
     if (one_workgroup_per_sample(a)) {
-        hipLaunchKernelGGL(heads_tail_kernel<256>, dim3((unsigned)s.B), dim3(256), 0, stream, a);
+        if (s.B <= HEAD_TAIL_FEW) hipLaunchKernelGGL(heads_tail_kernel<512>, dim3((unsigned)s.B), dim3(512), 0, stream, a);
+        else hipLaunchKernelGGL(heads_tail_kernel<256>, dim3((unsigned)s.B), dim3(256), 0, stream, a);
     } else {
         g.out = reinterpret_cast<double*>(static_cast<char*>(workspace) + sums_bytes(a));
         for (g.level = 0; g.level < a.depth; ++g.level) {
