@@ -435,7 +435,8 @@ int value_ensemble_forward(const brl_mlp* members /* HOST */, int n_members, con
  * Parameters live in ONE flat fp32 DEVICE buffer (policy W_1, b_1, ..., W_L,
  * b_L, then the value head likewise; brl_ppo_param_offsets gives each tensor's
  * offset so a brl_head for policy_value_head can point into it), adam_m and
- * adam_v likewise (zero them before the first update).  *adam_step (HOST)
+ * adam_v likewise (zero them before the first update); these three, like the
+ * heads' parameters and h, may start at any element of a larger buffer.  *adam_step (HOST)
  * counts optimiser steps across calls.  h [T, dims[0]] fp32, actions [T]
  * int32, logp_old / adv / returns [T] fp32.  stats (DEVICE, or NULL):
  * [epochs * (T / batch), 5] = policy loss, value loss, mean entropy, fraction

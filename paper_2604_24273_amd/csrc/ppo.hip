@@ -729,14 +729,14 @@ constexpr int ADAM_PER_THREAD = 4;
 __global__ __launch_bounds__(256) void ppo_adam_kernel(AdamArgs a) {
     __shared__ double red[256];
     const size_t i0 = ((size_t)blockIdx.x * 256 + threadIdx.x) * ADAM_PER_THREAD;
-    // the elements are requested ahead of the norm (the buffers start 16-byte aligned)
+    // the elements are requested ahead of the norm; the buffers may start at any element, so the accesses ask for no more
     const bool full = i0 + ADAM_PER_THREAD <= a.n;
     float p[4], m[4], v[4];
     double g[4];
     if (full) {
-        const float4 pv = *reinterpret_cast<const float4*>(a.p + i0), mv = *reinterpret_cast<const float4*>(a.m + i0);
-        const float4 vv = *reinterpret_cast<const float4*>(a.v + i0);
-        const double2 g0 = *reinterpret_cast<const double2*>(a.g + i0), g1 = *reinterpret_cast<const double2*>(a.g + i0 + 2);
+        const v4f_u pv = *reinterpret_cast<const v4f_u*>(a.p + i0), mv = *reinterpret_cast<const v4f_u*>(a.m + i0);
+        const v4f_u vv = *reinterpret_cast<const v4f_u*>(a.v + i0);
+        const v2d_u g0 = *reinterpret_cast<const v2d_u*>(a.g + i0), g1 = *reinterpret_cast<const v2d_u*>(a.g + i0 + 2);
         p[0] = pv.x; p[1] = pv.y; p[2] = pv.z; p[3] = pv.w;
         m[0] = mv.x; m[1] = mv.y; m[2] = mv.z; m[3] = mv.w;
         v[0] = vv.x; v[1] = vv.y; v[2] = vv.z; v[3] = vv.w;
@@ -776,9 +776,9 @@ __global__ __launch_bounds__(256) void ppo_adam_kernel(AdamArgs a) {
         p[e] = (float)((double)p[e] - step * mi / (sqrt(vi * a.inv_c2) + a.eps));
     }
     if (full) {
-        *reinterpret_cast<float4*>(a.p + i0) = make_float4(p[0], p[1], p[2], p[3]);
-        *reinterpret_cast<float4*>(a.m + i0) = make_float4(m[0], m[1], m[2], m[3]);
-        *reinterpret_cast<float4*>(a.v + i0) = make_float4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<v4f_u*>(a.p + i0) = v4f_u{p[0], p[1], p[2], p[3]};
+        *reinterpret_cast<v4f_u*>(a.m + i0) = v4f_u{m[0], m[1], m[2], m[3]};
+        *reinterpret_cast<v4f_u*>(a.v + i0) = v4f_u{v[0], v[1], v[2], v[3]};
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)

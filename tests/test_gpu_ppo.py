@@ -154,3 +154,29 @@ def test_gae_stretches(T):
         scale = max(np.abs(a_ref).max(), np.abs(r_ref).max())
         assert np.abs(adv[e].cpu().numpy() - a_ref).max() <= 2e-7 * scale + 1e-7
         assert np.abs(ret[e].cpu().numpy() - r_ref).max() <= 2e-7 * scale + 1e-7
+
+
+@pytest.mark.parametrize("dims_p,dims_v,offsets", [([130, 36, 5], [130, 30, 1], (1, 2, 3)), ([96, 2100, 3], [96, 8, 1], (3, 1, 0))])
+def test_head_update_on_buffers_that_start_anywhere(dims_p, dims_v, offsets):
+    """params, adam_m and adam_v as views at odd elements of larger buffers: the bits of the aligned buffers, and nothing
+    beside the views is touched."""
+    B, R = _mods()
+    T, batch = 64, 32
+    c = synth.ppo_rollout_case(23, T, dims_p[0], dims_p[-1], 2)
+    pwb, vwb = synth.mlp_params(23, 60, dims_p), synth.mlp_params(23, 80, dims_v)
+    args = (R.dev(c["h"]), R.dev(c["actions"]), R.dev(c["logp_old"]), R.dev(synth.normal(23, 90, (T,))),
+            R.dev(synth.normal(23, 91, (T,))))
+    a = R.PPOTrainer(pwb, vwb)
+    n = a.params.numel()
+    bufs = [torch.full((n + 8,), 7.0, dtype=torch.float32, device="cuda") for _ in range(3)]
+    views = [b[o:o + n] for b, o in zip(bufs, offsets)]
+    for v, src in zip(views, (a.params, a.adam_m, a.adam_v)):
+        v.copy_(src)
+    print("ppo_head_update on views at", offsets, flush=True)
+    sa = a.update(*args, R.dev(c["perm"]), batch)
+    sb = torch.zeros_like(sa)
+    B.ppo_head_update(a.cfg, *views, 0, *args, T, R.dev(c["perm"]), 2, batch, sb, a.ws.buf)
+    assert torch.equal(sa, sb)
+    for b, v, o, want in zip(bufs, views, offsets, (a.params, a.adam_m, a.adam_v)):
+        assert torch.equal(v, want)
+        assert bool((b[:o] == 7.0).all()) and bool((b[o + n:] == 7.0).all())
