@@ -708,8 +708,9 @@ __global__ __launch_bounds__(256) void ppo_delta_kernel(DeltaArgs a) {
 }
 
 // ---- global gradient norm and Adam ------------------------------------------------------------------------------
-// Every workgroup adds the partial sums itself, in one fixed order (thread t takes partials t, t + 256, ..., then a
-// fixed tree): the same norm everywhere, and no launch of its own.  Then Adam with bias correction on the clipped
+// Up to ADAM_OWN_NORM partial sums every workgroup adds them itself, in one fixed order (thread t takes partials t,
+// t + 256, ..., then a fixed tree): the same norm everywhere, and no launch of its own.  Beyond, where that work would grow
+// with the square of the heads' size, a launch ahead leaves their total and the workgroups read one value.  Then Adam with bias correction on the clipped
 // gradient, p -= lr (m / c1) / (sqrt(v / c2) + eps), scale min(1, max_norm / (norm + 1e-6)).  1.3 M parameters: 10.4 us
 // for 42 MB, against 7 us for the norm alone in its own launch and 8.6 us for Adam (12.2 us with the partial sums read one
 // after the other and three divisions per parameter).
@@ -726,6 +727,32 @@ struct AdamArgs {
     float* stats;            // [5]: policy loss, value loss, entropy, clip fraction, gradient norm; or null
 };
 constexpr int ADAM_PER_THREAD = 4;
+// (64 samples, 2560 inputs, a step with the workgroups' own sums / with the launch, us: hidden 256 (1292 partials) 38.0 /
+// 40.4, 384 (1938) 46.5 / 49.1, 640 (3230) 68.1 / 68.0, 1000 (5088) 92.5 / 89.7, 2048 (10336) 325 / 302, 4096 and 2048
+// (36960) 2109 / 1650)
+constexpr int ADAM_OWN_NORM = 3072;
+
+// sum of the partials, in a fixed order
+constexpr int NORM_THREADS = 1024;
+__global__ __launch_bounds__(NORM_THREADS) void ppo_norm_kernel(const double* __restrict__ partial, int n, double* __restrict__ total) {
+    __shared__ double red[NORM_THREADS / 64];
+    double s = 0.0;
+    for (int i0 = 0; i0 < n; i0 += NORM_THREADS * 8) {
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = partial[min(i0 + u * NORM_THREADS + (int)threadIdx.x, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += i0 + u * NORM_THREADS + (int)threadIdx.x < n ? t[u] : 0.0;
+    }
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < NORM_THREADS / 64; ++w) s += red[w];
+        *total = s;
+    }
+}
+
 __global__ __launch_bounds__(256) void ppo_adam_kernel(AdamArgs a) {
     __shared__ double red[256];
     const size_t i0 = ((size_t)blockIdx.x * 256 + threadIdx.x) * ADAM_PER_THREAD;
@@ -849,7 +876,7 @@ PpoWs ppo_ws_layout(const Layout& L, int batch) {
         }
     W.grad_waves = nw;
     W.partial_off = take((size_t)nw * 8);
-    W.scal_off = take(2 * 8);
+    W.scal_off = take(3 * 8);            // mean and scale of the advantages, total of the partial sums
     W.rows_off = take((size_t)4 * batch * 8);
     W.total = off;
     return W;
@@ -949,7 +976,9 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
     AdamArgs aa;
     memset(&aa, 0, sizeof(aa));
     aa.p = params; aa.m = adam_m; aa.v = adam_v; aa.g = grads; aa.n = L.n_params; aa.n_policy = L.n_policy;
-    aa.partial = partial; aa.n_partials = W.grad_waves; aa.B = batch;
+    const bool norm_launch = W.grad_waves > ADAM_OWN_NORM;
+    double* total = at(W.scal_off) + 2;
+    aa.partial = norm_launch ? total : partial; aa.n_partials = norm_launch ? 1 : W.grad_waves; aa.B = batch;
     aa.max_norm = (double)cfg->max_grad_norm;
     aa.b1 = (double)cfg->adam_b1; aa.b2 = (double)cfg->adam_b2; aa.eps = (double)cfg->adam_eps; aa.ent_coef = (double)cfg->ent_coef;
     aa.row_terms = row_terms;
@@ -1042,6 +1071,7 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
             }
             ga.rows = rows;
             hipLaunchKernelGGL(ppo_weight_grad_kernel, dim3((unsigned)((W.grad_waves + 3) / 4)), dim3(256), 0, s, ga);
+            if (norm_launch) hipLaunchKernelGGL(ppo_norm_kernel, dim3(1), dim3(NORM_THREADS), 0, s, partial, W.grad_waves, total);
             ++step;
             const double c1 = 1.0 - pow((double)cfg->adam_b1, (double)step);
             aa.step_policy = (double)cfg->lr_policy / c1;

@@ -180,3 +180,21 @@ def test_head_update_on_buffers_that_start_anywhere(dims_p, dims_v, offsets):
     for b, v, o, want in zip(bufs, views, offsets, (a.params, a.adam_m, a.adam_v)):
         assert torch.equal(v, want)
         assert bool((b[:o] == 7.0).all()) and bool((b[o + n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("value_hidden", [1000, 1100])
+def test_head_update_norm_on_both_sides_of_its_launch(value_hidden):
+    """3039 partial sums of squares (added by Adam's workgroups) and 3089 (a launch of their own): the gradient norm of the
+    first step from identical parameters, and the parameters after it, bounds as above."""
+    B, R = _mods()
+    print("gradient norm, value head of", value_hidden, flush=True)
+    tr, stats, pol, val, out, init, c = _run_case(B, R, [512, 2100, 700, 3], [512, value_hidden, 1], "tanh", 16, 8, 1, seed=29)
+    st, ref = stats.cpu().numpy(), [s["grad_norm"] for s in out["stats"]]
+    assert np.isclose(st[0, 4], ref[0], rtol=2e-6) and np.allclose(st[:, 4], ref, rtol=2e-4)
+    assert min(ref) > 0.5                            # clipped, so the norm reaches every parameter
+    pw, pb, vw, vb = tr.tensors()
+    for g, w, s0 in zip(list(pw) + list(pb) + list(vw) + list(vb),
+                        list(pol.weights) + list(pol.biases) + list(val.weights) + list(val.biases),
+                        list(init[0]) + list(init[1]) + list(init[2]) + list(init[3])):
+        change = np.abs(w - s0.astype(np.float64)).max()
+        assert np.abs(g.astype(np.float64) - w).max() <= 2e-4 * change + 1e-7, (g.shape, np.abs(g - w).max(), change)
