@@ -198,3 +198,18 @@ def test_head_update_norm_on_both_sides_of_its_launch(value_hidden):
                         list(init[0]) + list(init[1]) + list(init[2]) + list(init[3])):
         change = np.abs(w - s0.astype(np.float64)).max()
         assert np.abs(g.astype(np.float64) - w).max() <= 2e-4 * change + 1e-7, (g.shape, np.abs(g - w).max(), change)
+
+
+@pytest.mark.parametrize("n_envs,T", [(1, 8), (257, 8), (300, 9), (129, 16), (131, 17), (40, 63), (9, 130), (2, 2049)])
+def test_gae_rollouts_share_workgroups(n_envs, T):
+    """A power of two of threads per rollout, one per eight steps: both sides of its steps, and a last workgroup not full."""
+    B, R = _mods()
+    print("gae", n_envs, T, flush=True)
+    c = synth.ppo_rollout_case(37, T, 4, 4, 0, n_envs=n_envs)
+    adv, ret = R.gae(R.dev(c["rewards"]), R.dev(c["values"]), R.dev(c["dones"]), R.dev(c["last_value"]), 0.99, 0.95)
+    adv, ret = adv.cpu().numpy(), ret.cpu().numpy()
+    for e in range(n_envs):
+        a_ref, r_ref = P.gae(c["rewards"][e], c["values"][e], c["dones"][e], c["last_value"][e], 0.99, 0.95)
+        scale = max(np.abs(a_ref).max(), np.abs(r_ref).max())
+        assert np.abs(adv[e] - a_ref).max() <= 2e-7 * scale + 1e-7
+        assert np.abs(ret[e] - r_ref).max() <= 2e-7 * scale + 1e-7
