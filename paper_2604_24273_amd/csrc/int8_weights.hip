@@ -53,6 +53,7 @@ __global__ __launch_bounds__(W8_THREADS) void absmax_partials_kernel(const float
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
+template <bool NARROW>
 __global__ __launch_bounds__(PACK_THREADS) void int8_pack_kernel(const float* __restrict__ W, int N, int K, int nsb, float eps,
                                                                  float qmax, const float* __restrict__ partials, int n_partials,
                                                                  uint4* __restrict__ packed, float* __restrict__ scale_out,
@@ -61,18 +62,18 @@ __global__ __launch_bounds__(PACK_THREADS) void int8_pack_kernel(const float* __
     __shared__ float lds[W8_THREADS / 64];
     __shared__ __attribute__((aligned(16))) uint32_t words[PACK_SB][1024];
     pack_f4 v[PACK_SB][4];
-    pack_load(W, N, K, v);                       // in flight while the scale is reduced
+    const PackPlace<NARROW> at(nsb);
+    pack_load(W, N, K, at, v);                   // in flight while the scale is reduced
     float m = 0.f;
     for (int i = threadIdx.x; i < n_partials; i += W8_THREADS) m = fmaxf(m, partials[i]);
     const float a = block_max(m, lds);
     const float ac = fmaxf(a, eps);
     const float s = qmax / ac;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         *scale_out = ac / qmax;
         *flag = isfinite(a) ? 0 : 1;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int sb0 = blockIdx.x * PACK_SB;
     const int j = lane & 3, kk = (lane & 31) >> 2;                 // four columns of a 16-byte piece; the piece
 #pragma unroll
     for (int sb = 0; sb < PACK_SB; ++sb)
@@ -86,11 +87,11 @@ __global__ __launch_bounds__(PACK_THREADS) void int8_pack_kernel(const float* __
                 word |= ((uint32_t)c[e] & 0xffu) << (8 * e);
             }
             words[sb][((kk >> 1) * 64 + (kk & 1) * 32 + pack_row(p)) * 4 + j] = word;
-            if (codes_dbg) pack_tap(codes_dbg, blockIdx.y * NB + pack_row(p), (sb0 + sb) * SBK + pack_col(), N, K, c);
+            if (codes_dbg) pack_tap(codes_dbg, at.row0(sb) + pack_row(p), at.col0(sb) + pack_col(), N, K, c);
         }
     __syncthreads();
-    if (sb0 + wave < nsb) {
-        uint4* dst = packed + ((size_t)blockIdx.y * nsb + sb0 + wave) * 256 + lane;
+    if (at.wave_writes(wave, N)) {
+        uint4* dst = packed + at.blob(wave) * 256 + lane;
 #pragma unroll
         for (int f = 0; f < 4; ++f) dst[f * 64] = *reinterpret_cast<const uint4*>(&words[wave][(f * 64 + lane) * 4]);
     }
@@ -129,7 +130,8 @@ int launch_quantize_weights_int8(const float* W, int N, int K, float eps, int qm
     hipLaunchKernelGGL(absmax_partials_kernel, dim3(g), dim3(W8_THREADS), 0, s, W, total, chunk, partials);
     BRL_LAUNCH_CHECK("absmax_partials_kernel");
     const int nsb = round_up(K, SBK) / SBK;
-    hipLaunchKernelGGL(int8_pack_kernel, pack_grid(N, K), dim3(PACK_THREADS), 0, s, W, N, K, nsb, eps, (float)qmax, partials, g,
+    auto pack = pack_narrow(K) ? int8_pack_kernel<true> : int8_pack_kernel<false>;
+    hipLaunchKernelGGL(pack, pack_grid(N, K), dim3(PACK_THREADS), 0, s, W, N, K, nsb, eps, (float)qmax, partials, g,
                        reinterpret_cast<uint4*>(packed), scale, codes_dbg, flag);
     BRL_LAUNCH_CHECK("int8_pack_kernel");
     return BRL_OK;

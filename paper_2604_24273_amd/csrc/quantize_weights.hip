@@ -51,6 +51,7 @@ __global__ __launch_bounds__(QW_THREADS) void absum_partials_kernel(const float*
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
+template <bool NARROW>
 __global__ __launch_bounds__(PACK_THREADS) void ternary_pack_kernel(const float* __restrict__ W, int N, int K, int nsb, float eps,
                                                                     const double* __restrict__ partials, int n_partials,
                                                                     uint4* __restrict__ packed, float* __restrict__ beta_out,
@@ -59,19 +60,19 @@ __global__ __launch_bounds__(PACK_THREADS) void ternary_pack_kernel(const float*
     __shared__ double lds[QW_THREADS / 64];
     __shared__ __attribute__((aligned(16))) uint32_t words[PACK_SB][256];
     pack_f4 v[PACK_SB][4];
-    pack_load(W, N, K, v);                       // in flight while the scale is reduced
+    const PackPlace<NARROW> at(nsb);
+    pack_load(W, N, K, at, v);                   // in flight while the scale is reduced
     double acc = 0.0;
     for (int i = threadIdx.x; i < n_partials; i += QW_THREADS) acc += partials[i];
     const double total = block_sum_fixed(acc, lds);
     const float gamma = (float)(total / ((double)N * (double)K));
     const float beta = gamma + eps;
     const float tau = 0.5f * beta;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         *beta_out = beta;
         *flag = isfinite(gamma) ? 0 : 1;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int sb0 = blockIdx.x * PACK_SB;
     const int j = lane & 3, kk = (lane & 31) >> 2;                 // four columns of a word; the word's 16 columns
 #pragma unroll
     for (int s = 0; s < PACK_SB; ++s)
@@ -88,11 +89,11 @@ __global__ __launch_bounds__(PACK_THREADS) void ternary_pack_kernel(const float*
             part |= (uint32_t)__builtin_amdgcn_mov_dpp((int)part, 0xB1, 0xf, 0xf, true);      // the four lanes of a quad
             part |= (uint32_t)__builtin_amdgcn_mov_dpp((int)part, 0x4E, 0xf, 0xf, true);
             if (j == 0) words[s][((kk & 1) * 32 + pack_row(p)) * 4 + (kk >> 1)] = part;
-            if (codes_dbg) pack_tap(codes_dbg, blockIdx.y * NB + pack_row(p), (sb0 + s) * SBK + pack_col(), N, K, c);
+            if (codes_dbg) pack_tap(codes_dbg, at.row0(s) + pack_row(p), at.col0(s) + pack_col(), N, K, c);
         }
     __syncthreads();
-    if (sb0 + wave < nsb)
-        packed[((size_t)blockIdx.y * nsb + sb0 + wave) * 64 + lane] = *reinterpret_cast<const uint4*>(&words[wave][lane * 4]);
+    if (at.wave_writes(wave, N))
+        packed[at.blob(wave) * 64 + lane] = *reinterpret_cast<const uint4*>(&words[wave][lane * 4]);
 }
 
 __global__ __launch_bounds__(QW_THREADS) void unpack_codes_kernel(const uint32_t* __restrict__ packed, int N, int K, int nsb,
@@ -138,7 +139,8 @@ int launch_quantize_weights(const float* W, int N, int K, float eps, uint32_t* p
     hipLaunchKernelGGL(absum_partials_kernel, dim3(g), dim3(QW_THREADS), 0, s, W, total, chunk, partials);
     BRL_LAUNCH_CHECK("absum_partials_kernel");
     const int nsb = round_up(K, SBK) / SBK;
-    hipLaunchKernelGGL(ternary_pack_kernel, pack_grid(N, K), dim3(PACK_THREADS), 0, s, W, N, K, nsb, eps, partials, g,
+    auto pack = pack_narrow(K) ? ternary_pack_kernel<true> : ternary_pack_kernel<false>;
+    hipLaunchKernelGGL(pack, pack_grid(N, K), dim3(PACK_THREADS), 0, s, W, N, K, nsb, eps, partials, g,
                        reinterpret_cast<uint4*>(packed), beta, codes_dbg, flag);
     BRL_LAUNCH_CHECK("ternary_pack_kernel");
     return BRL_OK;

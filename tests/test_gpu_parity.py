@@ -84,6 +84,24 @@ def test_quantize_weights_block_edges(n, k):
     assert np.array_equal(back.cpu().numpy(), c8_ref)
 
 
+@pytest.mark.parametrize("n,k", [(129, 16), (97, 640), (70, 700), (2097153, 8)])
+def test_quantize_weights_super_blocks_through_the_blob(n, k):
+    """A workgroup packs four consecutive super-blocks wherever they lie: several row blocks of a narrow matrix, row blocks
+    that end inside a workgroup, and more row blocks than a second grid dimension has room for."""
+    B, R = _mods()
+    from oracle import critic_oracle as C
+    print("quantize_weights", n, k, flush=True)
+    W = synth.normal(73, 3, (n, k), 0.02)
+    back = torch.empty((n, k), dtype=torch.int8, device="cuda")
+    for int8, ref, unpack in ((False, O.ternary_quantize, B.brl_unpack_codes), (True, C.int8_quantize, B.brl_unpack_codes_int8)):
+        codes_ref, scale_ref = ref(W)
+        pl = R.quantize_linear(W, want_codes=True, int8=int8)
+        assert np.float32(pl.beta.cpu().numpy()[0]) == scale_ref
+        assert np.array_equal(pl.codes.cpu().numpy(), codes_ref)
+        unpack(pl.packed, n, k, back.fill_(9))
+        assert np.array_equal(back.cpu().numpy(), codes_ref)
+
+
 def test_quantize_weights_special_matrices():
     B, R = _mods()
     for W in (np.zeros((40, 136), np.float32),                       # all zero: beta = eps, codes 0
