@@ -276,11 +276,6 @@ struct AttnTile {
 // Four is what is launched: eight halved the K / V traffic but ran 12-19 % slower on both
 // measured shapes (fewer resident workgroups, longer tails).
 constexpr int ATTN_WPG = 4;
-// One-key-block states: a workgroup per (state, query head).  From some 8000 workgroups on, groups of four or more query
-// heads do better with their K / V staged once per group by the two-kernel path (2000 x 32 tokens, 20 / 5 heads of 128:
-// 472 us against 508; 200 x 27: 46 against 44, 1 x 27: 9.5 - a four-head workgroup of its own - against 5.5); smaller
-// groups leave that path's wavefronts idle (1000 x 20, 32 / 32 heads of 100: 950 us against 431).
-constexpr int SHORT_MAX_WORK = 8192;
 // QPRE: the q rows arrive as fragments (rotated, scaled, split by the kernel that produced them) and are read
 // straight into the operand registers; otherwise they are staged from the fp32 rows here.
 template <int DHP, int VW, int WPG, bool QPRE = false>
@@ -474,6 +469,119 @@ __global__ __launch_bounds__(DHP * 4) void attention_short_kernel(FragArgs a) {
     }
 }
 
+// The same states with a workgroup = (state, key/value head, up to four query heads of its group): k and v are staged once
+// for four heads.  All global reads are requested in one phase by two sets of wavefronts side by side: four stage one q head
+// each, four stage a quarter of the k rows each and hold v in registers; after one barrier the k and v fragments are laid
+// out in LDS exactly as attn_pack_kernel lays them out in memory, and the block is computed by the same code as in the
+// general kernel: same bits.  Where each form runs and what it measured: short_form below.
+template <int DHP, int VW>
+__global__ __launch_bounds__(512) void attention_group_kernel(FragArgs a) {
+    using T = AttnTile<DHP>;
+    constexpr int KS = T::KS, DB = T::DB;
+    constexpr int REG = 128 * DHP;                        // bytes of one staged 32-row block (hi and lo planes)
+    __shared__ __attribute__((aligned(1024))) char qpark[4 * REG];
+    __shared__ __attribute__((aligned(1024))) char kpark[REG];
+    __shared__ __attribute__((aligned(1024))) uint4 kvst[T::KVFR * 64];
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int group = a.Hq / a.Hkv;
+    const int chunks = (group + 3) / 4;
+    const int w = blockIdx.x;
+    const int c = w % chunks;
+    const int j = (w / chunks) % a.Hkv;
+    const int b = w / (chunks * a.Hkv);
+    const int len = seq_len(a.sm, b, a.S);                // 1 .. 32
+    if (len <= 0) return;
+    const size_t row0 = (size_t)seq_row0(a.sm, b, a.S);
+    const bool qside = wave < 4;                          // wavefronts 0-3: one q head each; 4-7: k and v
+    const int u = 4 * c + (wave & 3);
+    const bool live = qside && u < group;
+    const int head = j * group + (live ? u : 0);
+    const int dq = a.Hq * a.dh, dkv = a.Hkv * a.dh;
+    const float* rows = a.qkv + row0 * a.ld;
+
+    // ---- one phase of global reads, the two sides in parallel
+    char* region = qpark + (wave & 3) * REG;
+    constexpr int ITS = 32 / (64 / (DHP / VW));
+    constexpr int VR = (128 * DB + 255) / 256;            // v: thread t of 128 * DB owns lane slot (d, h) of (block r, step tt)
+    float vv[VR][8];
+    const int tk = threadIdx.x - 256;
+    if (qside) {
+        if (live) stage_rope_rows<DHP, VW>(rows + head * a.dh, a.ld, len, a.cos_t, a.sin_t, a.dh, a.qscale, region, lane);
+    } else {
+        const int col0 = dq + dkv + j * a.dh;
+#pragma unroll
+        for (int q = 0; q < VR; ++q) {
+            const int t = tk + 256 * q;
+            const int dl = t & 31, h = (t >> 5) & 1, tt = (t >> 6) & 1, r = t >> 7;
+            const int d = 32 * r + dl;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int row = 16 * tt + 8 * (e >> 2) + 4 * h + (e & 3);
+                vv[q][e] = (t < 128 * DB && row < len && d < a.dh) ? rows[(size_t)row * a.ld + col0 + d] : 0.f;
+            }
+        }
+        stage_rope_rows<DHP, VW, ITS / 4>(rows + dq + j * a.dh, a.ld, len, a.cos_t, a.sin_t, a.dh, 1.0f, kpark, lane,
+                                          (wave - 4) * (ITS / 4));
+    }
+    __syncthreads();
+
+    v8h qh[KS], ql[KS];
+    if (qside) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            qh[ks] = __builtin_bit_cast(v8h, staged_fragment<DHP>(region, ks, lane, 0));
+            ql[ks] = __builtin_bit_cast(v8h, staged_fragment<DHP>(region, ks, lane, 1));
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < KS / 2; ++q) {
+            const int fr = (wave - 4) * (KS / 2) + q;     // fragment = (k-step, plane)
+            kvst[fr * 64 + lane] = staged_fragment<DHP>(kpark, fr >> 1, lane, fr & 1);
+        }
+#pragma unroll
+        for (int q = 0; q < VR; ++q) {
+            const int t = tk + 256 * q;
+            if (t < 128 * DB) {
+                const int dl = t & 31, h = (t >> 5) & 1, tt = (t >> 6) & 1, r = t >> 7;
+                const int ln = h * 32 + dl;
+                kvst[(KS * 2 + (r * 2 + tt) * 2 + 0) * 64 + ln] = pack8h(vv[q], false);
+                kvst[(KS * 2 + (r * 2 + tt) * 2 + 1) * 64 + ln] = pack8h(vv[q], true);
+            }
+        }
+    }
+    __syncthreads();
+    if (!qside) return;
+
+    v16f o[DB];
+#pragma unroll
+    for (int r = 0; r < DB; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[r][v] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    T::compute(kvst, qh, ql, o, m_run, l_run, true, lane);
+
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const int pos = lane & 31;
+    if (live && pos < len) {
+        const float inv = 1.0f / l_tot;
+        const int h = lane >> 5;
+        float* op = a.out + (row0 + pos) * ((size_t)a.Hq * a.dh) + (size_t)head * a.dh;
+#pragma unroll
+        for (int r = 0; r < DB; ++r)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const int d = 32 * r + 8 * g4 + 4 * h;
+                if (d < a.dh) {
+                    float4 v;
+                    v.x = o[r][4 * g4 + 0] * inv; v.y = o[r][4 * g4 + 1] * inv;
+                    v.z = o[r][4 * g4 + 2] * inv; v.w = o[r][4 * g4 + 3] * inv;
+                    *reinterpret_cast<float4*>(op + d) = v;
+                }
+            }
+    }
+}
+
 inline int padded_head_dim(int dh) { return dh <= 32 ? 32 : (dh <= 64 ? 64 : 128); }
 
 }  // namespace
@@ -487,10 +595,45 @@ size_t attention_mfma_ws_bytes(int B, int S, int n_heads, int n_kv_heads, int he
 
 namespace {
 
+// Which form states of one key block take.  N: a workgroup per (state, query head), O: per (state, four query heads of one
+// key/value head), P: the pack and fragment kernels.  All give the same bits.  Times of 16 .. 2048 states in us:
+// - heads of up to 32: N; beyond 1024 query heads, where at least three of O's four wavefronts have a head, O (16 / 4 heads
+//   of 32, 32 tokens, 64 states 8.2 / 8.9, 256 states 17.4 / 15.0, 2048 states 121 / 84; 16 / 8: 17.2 / 18.6).
+// - up to 64: O where three of its four wavefronts have a head (16 / 4, 32 tokens, 1 state 8.7 / 8.6, 256 states 31 / 23 and
+//   P 28), P beyond 2048 workgroups where a group has more than one (32 / 4, 32 tokens, 384 states 55 / 51).  Groups of one,
+//   two and five: O up to one, four and four workgroups per compute unit, then N (16 / 16, 32 tokens, 4 states 8.8 / 8.2, 64
+//   states 11.9 / 14.7; 16 / 8, 32 tokens, 128 states 19.7 / 17.5, 8 tokens, 512 states 39 / 42; 30 / 6, 8 tokens, 64 states
+//   14.5 / 13.3, 256 states 37 / 42), of five P beyond 8192 query heads (8 tokens, 1024 states 127 / 110).
+// - up to 128: N; O where N has more than three workgroups per compute unit but O, with three of four wavefronts busy, at
+//   most one (20 / 5, 32 tokens, 48 states 19.1 / 16.4; 56 states 21.3 / 25.7); P for full groups of many states (20 / 5,
+//   32 tokens, 512 states 136.5 / 133.5, 2048 states 532 / 486; 32 / 4, 128 states 51 / 43; 30 / 6 never: 512 states 197 / 241).
+enum class ShortForm { HEAD, GROUP, PAIR };
+ShortForm short_form(int dhp, int B, int Hq, int Hkv) {
+    constexpr long CUS = 256;
+    const long group = Hq / Hkv, chunks = (group + 3) / 4, heads = (long)B * Hq, work = (long)B * Hkv * chunks;
+    const bool three_of_four = group >= 3 * chunks, full = 2 * group >= 7 * chunks;
+    if (dhp == 32) return three_of_four && heads > 4 * CUS ? ShortForm::GROUP : ShortForm::HEAD;
+    if (dhp == 64) {
+        if (!three_of_four) {
+            if (work <= (group == 1 ? 1 : 4) * CUS) return ShortForm::GROUP;
+            return group > 4 && heads > 32 * CUS ? ShortForm::PAIR : ShortForm::HEAD;
+        }
+        return chunks > 1 && work > 8 * CUS ? ShortForm::PAIR : ShortForm::GROUP;
+    }
+    if (three_of_four && heads > 3 * CUS && work <= CUS) return ShortForm::GROUP;
+    const bool many = chunks > 1 ? heads >= 16 * CUS : heads > 32 * CUS;
+    return full && many ? ShortForm::PAIR : ShortForm::HEAD;
+}
+
 template <int DHP, int VW>
 void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, hipStream_t s) {
-    if (p.NRB == 1 && (f.Hq / f.Hkv < 4 || (long)f.B * f.Hq <= SHORT_MAX_WORK)) {
+    const ShortForm form = p.NRB == 1 ? short_form(DHP, f.B, f.Hq, f.Hkv) : ShortForm::PAIR;
+    if (form == ShortForm::HEAD) {
         hipLaunchKernelGGL((attention_short_kernel<DHP, VW>), dim3((unsigned)(f.B * f.Hq)), dim3(DHP * 4), 0, s, f);
+        return;
+    }
+    if (form == ShortForm::GROUP) {                       // (NRB is 1: n_work counts the same workgroups)
+        hipLaunchKernelGGL((attention_group_kernel<DHP, VW>), dim3((unsigned)n_work), dim3(512), 0, s, f);
         return;
     }
     hipLaunchKernelGGL((attn_pack_kernel<DHP, VW>), pgrid, dim3(256), 0, s, p);

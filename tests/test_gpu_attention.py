@@ -1,9 +1,9 @@
 """GPU parity of the attention stage by itself: attention_forward (the kernels encoder_forward runs on
 the output of its q | k | v BitLinear) against the oracle's causal_gqa_attention, element by element.
 
-Three kernels sit behind the entry point and every one is reached here in both layouts:
-attention_f32_kernel (BRL_ATTN_F32), attn_pack_kernel + attention_frag_kernel (BRL_ATTN_MFMA) and
-attention_short_kernel (BRL_ATTN_MFMA, states of at most 32 tokens).
+Four forms sit behind the entry point and every one is reached here in both layouts: attention_f32_kernel
+(BRL_ATTN_F32), attn_pack_kernel + attention_frag_kernel (BRL_ATTN_MFMA) and, for states of at most 32 tokens,
+attention_short_kernel (a workgroup per query head) and attention_group_kernel (per four of them).
 
 Bound.  The oracle works in fp64 and rounds once.  The fp32 kernel accumulates dot products of
 head_dim terms and the softmax sums in fp32; the matrix-core kernels carry every operand as an fp16
@@ -179,8 +179,7 @@ def test_attention_argument_checks():
 
 @pytest.mark.parametrize("hq,hkv,dh,S", [(8, 2, 128, 27), (8, 1, 100, 32), (8, 2, 64, 1), (8, 2, 16, 9)])
 def test_short_state_kernels_meet_at_the_dispatch_line(hq, hkv, dh, S):
-    """1024 states x 8 heads are the last batch of the one-kernel path, one state more takes pack + fragment kernels:
-    the states they share get the same bits, and the last one matches the oracle."""
+    """1024 and 1025 states of 8 heads: the states they share get the same bits, and the last one matches the oracle."""
     B, R = _mods()
     qkv = synth.normal(37, 5, (1025 * S, (hq + 2 * hkv) * dh))
     one = _run(B, R, qkv[:1024 * S], [S] * 1024, S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA)
@@ -189,3 +188,37 @@ def test_short_state_kernels_meet_at_the_dispatch_line(hq, hkv, dh, S):
     ref = _oracle(qkv[1024 * S:], [S], hq, hkv, dh, 10000.0)[0]
     got = two[1024 * S:].reshape(ref.shape)
     assert np.abs(got - ref).max() <= ATTN_REL * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("hq,hkv,dh,batches", [
+    (20, 5, 128, (1, 38, 39, 51, 52, 409, 410)),       # query head; query head | group | query head | pair
+    (32, 4, 100, (24, 25, 32, 33, 127, 128)),          # two groups of four per key/value head
+    (30, 6, 128, (1, 60, 300)),                        # groups of five: query head only
+    (16, 16, 64, (1, 16, 17)),                         # group | query head
+    (32, 4, 64, (1, 256, 257)),                        # group | pair
+    (28, 4, 64, (1, 256, 257)),                        # the last wavefront of a group idle
+    (16, 8, 64, (1, 128, 129)),                        # group | query head
+    (30, 6, 64, (1, 85, 86, 273, 274)),                # groups of five: group | query head | pair
+    (16, 4, 32, (1, 64, 65, 200)),                     # query head | group
+    (24, 8, 16, (1, 42, 43)),
+    (16, 8, 32, (1, 130)),                             # groups of two: query head only
+])
+def test_short_state_forms_give_the_same_bits(hq, hkv, dh, batches):
+    """Batches on both sides of every line between the three forms of states of at most 32 tokens, uniform and ragged: the
+    states that they share get the same bits, first and last match the oracle."""
+    B, R = _mods()
+    n = batches[-1]
+    for S, lens in ((19, [19] * n), (None, [1 + (11 * i + 30) % 32 for i in range(n)])):
+        qkv = synth.normal(41, 5, (sum(lens), (hq + 2 * hkv) * dh))
+        want = None
+        for b in reversed(batches):
+            rows = sum(lens[:b])
+            print("short states", hq, hkv, dh, "uniform" if S else "ragged", b, flush=True)
+            got = _run(B, R, qkv[:rows], lens[:b], S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA, max_len=None if S else 32)
+            if want is None:
+                want = got
+                for i in (0, n - 1):
+                    r0 = sum(lens[:i])
+                    ref = _oracle(qkv[r0:r0 + lens[i]], lens[i:i + 1], hq, hkv, dh, 10000.0)[0]
+                    assert np.abs(got[r0:r0 + lens[i]].reshape(ref.shape) - ref).max() <= ATTN_REL * np.abs(ref).max()
+            assert np.array_equal(got, want[:rows]), b
