@@ -28,7 +28,8 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *    *_forward calls only enqueue kernels: no host synchronisation, no
  *    device-to-host copy.  bitlinear_quantize_weights (an offline step)
- *    synchronises the stream once so that it can report bad weights.
+ *    synchronises the stream once so that it can report bad weights; the first
+ *    such call allocates 4 KB of pinned host memory, which stays.
  *  - Non-finite activations are not checked: results are then unspecified
  *    (never out-of-bounds accesses).  Token ids outside [0, vocab) are clamped.
  *  - Limits: 1 <= K <= 9216 input features per BitLinear (a token row is

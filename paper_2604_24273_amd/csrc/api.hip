@@ -1,5 +1,6 @@
 // C ABI of the library (see include/bitrl.h): argument checks, workspace
 // carving and kernel sequencing.  No arithmetic of the method happens here.
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -94,25 +95,79 @@ ActBuf take_actbuf(Carver& c, int M, int K) {
     return a;
 }
 
-// Where the weight quantisers' kernels report bad weights: one pinned word per host thread, written over PCIe and
-// read after the stream has been waited for (a copy launch and its staging cost 12 us per matrix more).  Given back
-// when the thread ends; no call leaves a kernel behind that could still write it.
-struct PinnedFlag {
-    int* p = nullptr;
-    PinnedFlag() {
-        if (hipHostMalloc(reinterpret_cast<void**>(&p), sizeof(int), hipHostMallocPortable) != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
-        }
+// Where the weight quantisers' kernels report bad weights: a word of a pinned page, written over PCIe and read after the
+// stream has been waited for (a word of the workspace, a copy launch and its staging cost 12 us per matrix more).  The
+// page is allocated by the first call and stays: freeing pinned memory would wait for all work on the device.  A thread
+// keeps the word of its first call and gives it back when it ends (a word per call: 0.7 us more).  Where no word is left,
+// or the page cannot be had (another thread may be capturing), the word of the workspace serves.
+class FlagPage {
+public:
+    int* take() {
+        int* base = base_.load(std::memory_order_acquire);
+        if (!base && !(base = allocate())) return nullptr;
+        uint64_t free = free_.load(std::memory_order_relaxed);
+        while (free && !free_.compare_exchange_weak(free, free & (free - 1), std::memory_order_acquire)) {}
+        return free ? base + __builtin_ctzll(free) * STRIDE : nullptr;
     }
-    ~PinnedFlag() {
-        if (p) (void)hipHostFree(p);
+    void give(int* p) { free_.fetch_or(uint64_t(1) << ((p - base_.load(std::memory_order_relaxed)) / STRIDE), std::memory_order_release); }
+
+private:
+    static constexpr int WORDS = 64, STRIDE = 16;      // a cache line each
+    int* allocate() {
+        int* p = nullptr;
+        if (hipHostMalloc(reinterpret_cast<void**>(&p), WORDS * STRIDE * sizeof(int), hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        int* other = nullptr;
+        if (base_.compare_exchange_strong(other, p)) return p;
+        (void)hipHostFree(p);                          // another thread was first
+        return other;
+    }
+    std::atomic<int*> base_{nullptr};
+    std::atomic<uint64_t> free_{~uint64_t(0)};
+};
+FlagPage g_flag_page;                                  // (constant initialisation, nothing to destroy)
+
+struct ThreadFlag {
+    int* word = nullptr;
+    bool in_flight = false;                            // after an error a kernel might still write it: never given back
+    ~ThreadFlag() {
+        if (word && !in_flight) g_flag_page.give(word);
     }
 };
-int* pinned_flag() {
-    static thread_local PinnedFlag f;
-    return f.p;
-}
+
+// One call's flag: word() for the kernels, read() waits for the stream.
+class BadWeightFlag {
+public:
+    explicit BadWeightFlag(int* workspace_word) : mine_(of_thread()) {
+        if (!mine_.word) mine_.word = g_flag_page.take();
+        pinned_ = mine_.word && !mine_.in_flight;
+        word_ = pinned_ ? mine_.word : workspace_word;
+    }
+    int* word() {
+        if (pinned_) mine_.in_flight = true;
+        return word_;
+    }
+    int read(hipStream_t s, int& bad) {
+        if (!pinned_) BRL_HIP_CHECK(hipMemcpyAsync(&bad, word_, sizeof(int), hipMemcpyDeviceToHost, s));
+        BRL_HIP_CHECK(hipStreamSynchronize(s));
+        if (pinned_) {
+            mine_.in_flight = false;
+            bad = *static_cast<volatile int*>(word_);
+        }
+        return BRL_OK;
+    }
+
+private:
+    static ThreadFlag& of_thread() {
+        static thread_local ThreadFlag f;
+        return f;
+    }
+    ThreadFlag& mine_;
+    bool pinned_;
+    int* word_;
+};
 
 int check_linear_shape(int N, int K, const char* who) {
     BRL_REQUIRE(N >= 1 && K >= 1, "%s: N = %d, K = %d must be positive", who, N, K);
@@ -394,13 +449,13 @@ int bitlinear_quantize_weights(const float* W, int n_out, int k_in, float eps, v
     hipStream_t s = static_cast<hipStream_t>(stream);
     Carver c(workspace);
     double* partials = c.take<double>(1024);
-    int* flag = pinned_flag();
-    if (!flag) return hip_fail(hipErrorOutOfMemory, "quantize_weights: pinned flag");
+    BadWeightFlag flag(c.take<int>(1));
+    int bad = 0;
     if (int rc = launch_quantize_weights(W, n_out, k_in, eps, static_cast<uint32_t*>(packed_out), beta_out, codes_dbg,
-                                         partials, flag, s))
+                                         partials, flag.word(), s))
         return rc;
-    BRL_HIP_CHECK(hipStreamSynchronize(s));
-    BRL_REQUIRE(*static_cast<volatile int*>(flag) == 0, "quantize_weights: mean|W| is not finite");
+    if (int rc = flag.read(s, bad)) return rc;
+    BRL_REQUIRE(bad == 0, "quantize_weights: mean|W| is not finite");
     return BRL_OK;
 }
 
@@ -530,13 +585,13 @@ int bitlinear_quantize_weights_int8(const float* W, int n_out, int k_in, float e
     hipStream_t s = static_cast<hipStream_t>(stream);
     Carver c(workspace);
     float* partials = c.take<float>(1024);
-    int* flag = pinned_flag();
-    if (!flag) return hip_fail(hipErrorOutOfMemory, "quantize_weights_int8: pinned flag");
+    BadWeightFlag flag(c.take<int>(1));
+    int bad = 0;
     if (int rc = launch_quantize_weights_int8(W, n_out, k_in, eps, qmax, static_cast<int8_t*>(packed_out), scale_out, codes_dbg,
-                                              partials, flag, s))
+                                              partials, flag.word(), s))
         return rc;
-    BRL_HIP_CHECK(hipStreamSynchronize(s));
-    BRL_REQUIRE(*static_cast<volatile int*>(flag) == 0, "quantize_weights_int8: max|W| is not finite");
+    if (int rc = flag.read(s, bad)) return rc;
+    BRL_REQUIRE(bad == 0, "quantize_weights_int8: max|W| is not finite");
     return BRL_OK;
 }
 

@@ -118,6 +118,87 @@ def test_quantize_weights_special_matrices():
     assert ei.value.status == B.BRL_EINVAL
 
 
+def test_quantising_thread_ends_without_waiting_for_the_device():
+    """A loader thread that quantises on its own stream ends while another stream is still at work (about half a second of
+    a kernel that spins)."""
+    import os
+    import threading
+    import time
+    B, R = _mods()
+    W = R.dev(synth.normal(75, 1, (64, 256), 0.02))
+    packed, beta, ws = R.device_bytes(B.brl_packed_bytes(64, 256)), torch.empty(1, device="cuda"), R.device_bytes(1 << 16)
+    busy, own = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def quantise():
+        with torch.cuda.stream(own):
+            B.bitlinear_quantize_weights(W, 1e-5, packed, beta, None, ws)
+
+    def run():
+        t = threading.Thread(target=quantise)
+        t.start()
+        task = "/proc/self/task/%d" % t.native_id
+        t.join(60)
+        assert not t.is_alive()
+        limit = time.monotonic() + 5
+        while os.path.exists(task) and time.monotonic() < limit:     # join() returns before the thread's own clean-up
+            time.sleep(0.001)
+        assert not os.path.exists(task)
+
+    run()                                                # (first launches, the library's pinned page)
+    a, b, done = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+    with torch.cuda.stream(busy):
+        a.record()
+        torch.cuda._sleep(1000000)
+        b.record()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        torch.cuda._sleep(int(1000000 * 500.0 / max(a.elapsed_time(b), 0.05)))
+        done.record()
+    run()
+    ended_first = not done.query()
+    torch.cuda.synchronize()
+    assert ended_first
+
+
+def test_concurrent_quantising_threads_get_their_own_verdict():
+    """More threads at once than the library has pinned words; every third has a bad weight, and only it hears of it."""
+    import threading
+    B, R = _mods()
+    n, k, threads = 96, 640, 90
+    W = [synth.normal(77, i, (n, k), 0.02) for i in range(threads)]
+    for i in range(0, threads, 3):
+        W[i][5, i] = np.nan if i % 2 else np.inf
+    dev = [R.dev(w) for w in W]
+    packed = [R.device_bytes(B.brl_packed_int8_bytes(n, k)) for _ in range(threads)]
+    beta, ws = torch.empty((threads, 1), device="cuda"), [R.device_bytes(1 << 16) for _ in range(threads)]
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    got, gate = [None] * threads, threading.Barrier(threads)
+    torch.cuda.synchronize()
+
+    def quantise(i):
+        with torch.cuda.stream(streams[i % 4]):
+            gate.wait(60)
+            verdicts = []
+            for r in range(5):
+                try:
+                    if i % 2:
+                        B.bitlinear_quantize_weights(dev[i], 1e-5, packed[i], beta[i], None, ws[i])
+                    else:
+                        B.bitlinear_quantize_weights_int8(dev[i], 1e-5, 127, packed[i], beta[i], None, ws[i])
+                    verdicts.append("good")
+                except B.BitrlError as e:
+                    verdicts.append("bad" if e.status == B.BRL_EINVAL else str(e))
+            got[i] = verdicts
+
+    ts = [threading.Thread(target=quantise, args=(i,)) for i in range(threads)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join(60)
+    torch.cuda.synchronize()
+    assert got == [["good" if i % 3 else "bad"] * 5 for i in range(threads)]
+
+
 # ---------------------------------------------------------------- BitLinear
 
 def _run_bitlinear(B, R, pl, X, residual=None, taps=True):
