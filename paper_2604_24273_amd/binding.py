@@ -164,9 +164,14 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# the raw handle: building torch's Stream object first costs 2.9 us of a call that takes 10; not every torch has the short way
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the raw handle: building torch's Stream object first costs 2.9 us of a call that takes 10
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:

@@ -175,6 +175,20 @@ def test_bad_arguments_are_rejected_on_the_host(B):
     assert "differs" in err()
 
 
+def test_stream_handle_without_the_private_torch_call(B, monkeypatch):
+    """The current stream's handle comes from the public interface where torch has no raw call."""
+    import importlib.util
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=1234))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    spec = importlib.util.spec_from_file_location("binding_without_raw_streams", B.__file__)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    assert module._stream() == 1234
+
+
 def test_product_never_imports_the_oracle():
     pkg = os.path.join(ROOT, "paper_2604_24273_amd")
     for dirpath, _, files in os.walk(pkg):
