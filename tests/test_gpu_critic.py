@@ -201,6 +201,33 @@ def test_int8_weight_encoder(kw, b, s):
     assert np.array_equal(h_p, h)
 
 
+@pytest.mark.parametrize("f", [6400, 6392])
+def test_int8_gate_up_tiles_give_the_same_bits(f):
+    """The int8 gate | up product on both sides of its limits: up to 1024 blocks of 32 x 32 (1 and 2 states of 32 tokens),
+    64 x 64 tiles up to 1000 of them (3 and 10 states), LDS tiles beyond (11).  Integer sums: the states that the batches
+    share get the same bits.  Against the oracle as in the encoder test above; f off the blocks takes the ragged epilogue."""
+    B, R = _mods()
+    shape = synth.tiny_shape(n_layers=1, d=64, n_heads=2, n_kv_heads=1, head_dim=32, f=f, vocab=100)
+    host = []
+    enc = R.EncoderHandle(shape, seed=6, layer_sink=lambda l, w: host.append(w), int8_weights=True)
+    ids = synth.token_ids(6, 500, (11, 32), shape.vocab)
+    T, w = C.Int8Linear.from_fp32, host[0]
+    layer = O.LayerWeights(w["attn_norm_g"], T(w["Wq"]), T(w["Wk"]), T(w["Wv"]), w["attn_subln_g"], T(w["Wo"]),
+                           O.FFNWeights(w["ffn_norm_g"], T(w["W_gate"]), T(w["W_up"]), w["ffn_subln_g"], T(w["W_down"])))
+    cfg = O.EncoderConfig(1, 64, 2, 1, 32, f, shape.vocab, shape.rope_theta)
+    ref = O.encoder_forward(ids, synth.embedding_bf16(6, shape), [layer], synth.final_norm_gain(6, shape), cfg)
+    want = None
+    for b in (11, 10, 3, 2, 1):
+        print("int8 gate | up", f, b, flush=True)
+        h = enc.forward(R.dev(ids[:b]))
+        if want is None:
+            want = h
+            got = h.cpu().numpy()
+            assert min(cosine(got[i], ref[i]) for i in range(11)) >= 0.999
+            assert np.abs(got - ref).max() <= 5e-3 * np.abs(ref).max()
+        assert torch.equal(h, want[:b]), b
+
+
 @pytest.mark.parametrize("n_states,S", [(128, 128), (170, 96)])
 def test_int8_qkv_product_writing_attention_operands_matches_two_step_path(n_states, S):
     """Uniform batches at head_dim 128 with enough rows: the int8-weight q | k | v product writes the attention operands
