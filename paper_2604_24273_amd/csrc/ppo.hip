@@ -125,10 +125,6 @@ __global__ __launch_bounds__(GAE_THREADS) void gae_kernel(const float* __restric
     }
 }
 
-// out[b, o] = act(sum_i W[o, i] in(b, i) + bias[o]); a workgroup takes FO output units for FB consecutive
-// samples (weight rows and inputs are read once for all of them); its four wavefronts take a quarter of the
-// inputs each, sum in fp64 in lane order, fold, and the four parts are added in order.
-// in(b, i) = in64[b, i], or for the first layer the cached encoder output h[rows[b], i].
 // Rollout indices and actions are caller data read on the device: they are clamped into range so that a bad
 // entry can never address memory outside the rollout or the logits (its result is then meaningless, not a fault).
 __device__ inline int clamp_index(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
@@ -214,10 +210,11 @@ __global__ __launch_bounds__(256, 3) void ppo_first_layer_kernel(FirstArgs a) {
 // The layers above the first are small (256 -> 18, 256 -> 1): one workgroup runs the rest of both heads forward, the
 // clipped surrogate (Eq. 1), the entropy bonus and the value error with their gradients, and both heads backward on
 // activations and deltas in its LDS.  One launch (9.4 us, a chain of L2 and fp64 exp / log / tanh latencies) for what were
-// three (second layer 6 us, loss 14 us, deltas 5 us).  Used up to TAIL_MAX_UNITS (the LDS) and TAIL_MAX_WEIGHTS (1 MB of
-// weights per workgroup; beyond, sharing them over four samples as the level kernels below do reads less).
+// three (second layer 6 us, loss 14 us, deltas 5 us).  Used wherever the units fit the LDS, whatever weights every
+// workgroup then reads: a step at 64 samples of 2560 inputs 39 us against 73 with the level kernels below for hidden 256,
+// 64 / 158 for 256, 256 (136 k weights above the first layers), 149 / 257 for 480, 480 (470 k), 220 / 360 for a policy head
+// of 1000, 1000 (1 M); at 8 samples 35 / 56, 63 / 127, 149 / 200, 218 / 309, at 1024 three times ahead.
 constexpr int TAIL_MAX_UNITS = 2048;          // layer outputs of both heads together: activations and deltas in 32 KB of LDS
-constexpr size_t TAIL_MAX_WEIGHTS = 1 << 18;  // weights above the first layers: every sample's workgroup reads them all
 constexpr int TAIL_THREADS = 512;             // (256: 10.9 us against 9.4 at 512 first-layer units: every loop over units has two rounds)
 struct TailArgs {
     const double* z;                 // first-layer sums [splits][B][..]
@@ -356,6 +353,10 @@ __global__ __launch_bounds__(TAIL_THREADS) void ppo_tail_kernel(TailArgs a) {
 // ---- heads too wide for that: one launch per layer level forward and backward, one for the loss ------------------
 constexpr int FB = 4;        // samples per workgroup
 constexpr int FO = 4;        // output units per workgroup
+// out[b, o] = act(sum_i W[o, i] in(b, i) + bias[o]); a workgroup takes FO output units for FB consecutive
+// samples (weight rows and inputs are read once for all of them); its four wavefronts take a quarter of the
+// inputs each, sum in fp64 in lane order, fold, and the four parts are added in order.
+// in(b, i) = in64[b, i], or for the first layer the cached encoder output h[rows[b], i].
 // One launch runs the same layer level of both heads (they read the same rows of h and depend on nothing of
 // each other): the workgroups of problem 0 come first, then those of problem 1.
 struct FwdProblem {
@@ -386,9 +387,7 @@ __global__ __launch_bounds__(256) void ppo_forward_kernel(FwdArgs a) {
     const float* __restrict__ h = a.h;
     const int32_t* __restrict__ rows = a.rows;
     const int B = a.B, act = a.act;
-    // FO output units x FB samples per workgroup: a lane's weights and inputs are each loaded once and meet
-    // in FO * FB accumulators.  Per (sample, unit) the sum is what it was with one unit per workgroup: lane-
-    // strided over a quarter of the inputs per wavefront, butterfly, the four quarters in order.
+    // a lane's weights and inputs are each loaded once and meet in FO * FB accumulators
     __shared__ double part[4][FO][FB];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int ogroups = (out_dim + FO - 1) / FO;
@@ -857,15 +856,14 @@ PpoWs ppo_ws_layout(const Layout& L, int batch) {
         off += round_up_sz(bytes, PPO_ALIGN);
         return at;
     };
-    size_t units = 0, weights = 0;
+    size_t units = 0;
     for (int hd = 0; hd < 2; ++hd)
         for (int l = 0; l < L.head[hd].n; ++l) {
             W.act_off[hd][l] = take((size_t)batch * L.head[hd].dims[l + 1] * 8);
             W.delta_off[hd][l] = take((size_t)batch * L.head[hd].dims[l + 1] * 8);
             units += (size_t)L.head[hd].dims[l + 1];
-            if (l > 0) weights += (size_t)L.head[hd].dims[l + 1] * L.head[hd].dims[l];
         }
-    W.tail = units <= TAIL_MAX_UNITS && weights <= TAIL_MAX_WEIGHTS;
+    W.tail = units <= TAIL_MAX_UNITS;
     const int ncol = L.head[0].dims[1] + L.head[1].dims[1];
     const int tiles = (L.head[0].dims[1] + 15) / 16 + (L.head[1].dims[1] + 15) / 16;
     W.btiles = (batch + 63) / 64;

@@ -126,7 +126,7 @@ def test_no_normalisation_and_paper_hyperparameters_defaults():
     ([9, 5], [9, 3, 1], "relu", 6, 3),                    # less than one tile in every direction, heads of unequal depth
     ([1024, 40, 24, 70], [1024, 16, 1], "tanh", 260, 130),   # more actions than a wavefront, three sample blocks
     ([48, 1040, 30], [48, 1030, 1], "tanh", 48, 16),      # too many units for one workgroup per sample: a launch per level
-    ([40, 640, 500, 4], [40, 8, 1], "relu", 24, 12),      # too many weights above the first layer: likewise
+    ([40, 640, 500, 4], [40, 8, 1], "relu", 24, 12),      # 320 k weights above the first layer, units that still fit
 ])
 def test_head_update_at_tile_edges(dims_p, dims_v, act, T, batch):
     """Bounds as above: first-step statistics from identical parameters, parameter change relative to its largest."""
