@@ -1062,7 +1062,8 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
     const long t_narrow = (long)((g.nmb + 3) / 4) * ((g.nnb + 3) / 4);
     if (w.w8) {
         // int8 blobs: four times the weight bytes, so square tiles earlier (N = 2560, K = 6912: 900 tokens 36 against 54
-        // and 1750 tokens 54 against 74 for 128 x 128 tiles, K = 2560: 900 tokens 20 / 26, 1750 tokens 29.5 / 30.2)
+        // and 1750 tokens 54 against 74 for 128 x 128 tiles, K = 2560: 900 tokens 20 / 26, 1750 tokens 29.5 / 30.2); up to 1600 of
+        // them where k is long: 1700 x 2560 of K = 2560 35.0 (128 x 128) / 35.1, 4096 49.2 / 46.0, 9216 104 / 96.7
         if (n32 <= 256 && !glu) return launch_direct<1, 1, 16, 1, 4, true>(g, s);
         if (g.nmb <= 1 || (glu && n32 <= 1024)) return launch_direct<1, 2, 8, 1, 4, true>(g, s);
         if (!glu && (long)((g.nmb + 1) / 2) * g.nnb <= 700) return launch_direct<2, 1, 8, 1, 4, true>(g, s);
@@ -1086,9 +1087,11 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
         // 15.1 / 17.7 for 64 x 32; 900: 22 / 32 and 1750: 37 / 44 for 128 x 128, 2560: 52.6 / 48.4.  Four wavefronts
         // instead of eight once there are enough workgroups and k is short: 1750 x 2560 x 2560 20.1 / 21.6 (22.6 for 128 x
         // 128), 1300 x 3840 x 2560 21.5 / 23.5 (22.9), 1750 x 3840 x 2560 26.3 / 29 (24.8).
+        // (k short: 1300 x 2560 of K = 1024 16.4 with four / 19.2 with eight, 2560 22.6 / 24.9, 4096 30.2 / 31.9; from 5120 on
+        // eight is level or ahead: 37.4 / 37.8, 1000 x 4096 of 5120 37.0 / 36.5, of 9216 59.2 / 57.0)
         // (ragged columns finish element by element: one per thread there, 817 x 606 x 3200 13.4 / 15.9)
         if (n32 <= (g.fast_epilogue ? 256 : 512)) return launch_direct<1, 1, 16, 1, 4, false>(g, s);
-        if (n32x64 <= (g.nsb >= 32 ? 2500 : 960)) return launch_direct<1, 2, 8, 1, 4, false>(g, s);
+        if (n32x64 <= (g.nsb >= 40 ? 2500 : 960)) return launch_direct<1, 2, 8, 1, 4, false>(g, s);
         if (n32x64 <= 2500) return launch_direct<1, 2, 4, 1, 4, false>(g, s);
         // up to 450 tiles of 128 x 128: eight wavefronts of 64 x 32 on a tile (two per SIMD from one workgroup) instead of
         // four of 64 x 64: 1750 x 3840 x 2560 (420 tiles) 24.8 / 26.4, 2560 x 2560 x 2560 (400) 25.0 / 27.0; 600 tiles 38 / 34

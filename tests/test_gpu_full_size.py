@@ -102,7 +102,7 @@ def test_encoder_2b_shape_full_batch_sampled_states():
     assert np.all(np.isfinite(hp))
     assert _cos(hp[37], h20[0]) >= 0.999
     assert np.array_equal(hp[37], hl[37])      # padded or packed, among 64 or among 1024 states: the same bits
-    # one short state per call (the deployment shape): per-token quantisation, k-split GEMMs, one-kernel attention
+    # one short state per call (the deployment shape): per-token quantisation, direct GEMM tiles, one-kernel attention
     print("encoder 2B shape: one 20-token state", flush=True)
     h1 = enc.forward_packed(R.dev(ids[37, :20].astype(np.int32)), np.asarray([0, 20], np.int32)).cpu().numpy()
     assert _cos(h1[0], h20[0]) >= 0.999

@@ -219,8 +219,8 @@ def _run_bitlinear(B, R, pl, X, residual=None, taps=True):
     (1, 6912, 2560), (1, 2560, 6912), (2, 2560, 6912), (3, 200, 264), (4, 6912, 2560),   # GEMV path
     (5, 96, 128), (33, 200, 264), (64, 2560, 2560), (100, 640, 2560), (300, 1000, 520),
     (256, 6912, 2560), (257, 2560, 6912), (1100, 3200, 3200),
-    (600, 2560, 6912), (1300, 1000, 4608),                       # few 128 x 128 tiles, long k: k-split launches (ragged N in the second)
-    (200, 1000, 4608), (700, 264, 6912),                         # 64 x 32 tiles, k split inside the workgroup
+    (600, 2560, 6912), (1300, 1000, 4608),                       # direct 32 x 64 tiles on eight wavefronts, long k (ragged N in the second)
+    (200, 1000, 4608), (700, 264, 6912),                         # direct 32 x 32 tiles, k over sixteen wavefronts
     (2050, 8192, 264), (2048, 8200, 128),      # enough tiles for the 8-wavefront kernel, ragged edges
     (1024, 640, 2560), (1025, 640, 2560),      # last size of the one-workgroup-per-token quantiser, first of the one-wavefront-per-token one
     (1100, 64, 8640), (1030, 40, 8200),        # widest rows of the one-wavefront-per-token quantiser (34 chunks), ragged k
@@ -252,7 +252,8 @@ def test_bitlinear_forward_parity(m, n, k):
     (64, 4096, 136), (64, 4128, 136),           # 256 tiles of 32 x 32, one block more (32 x 64 tiles)
     (512, 1000, 136), (512, 1030, 136),         # ragged n: 512 tiles of 32 x 32, one block more
     (480, 4096, 264), (990, 1984, 264),         # 960 tiles of 32 x 64 on eight wavefronts, 961 on four
-    (990, 1984, 4096), (990, 1990, 4088),       # ... and on eight again where k is long; ragged n and k
+    (990, 1984, 4096), (990, 1990, 4088),       # ... with a longer k; ragged n and k
+    (990, 1984, 5120), (990, 1990, 5112), (990, 1984, 4992),   # ... and on eight again from 40 super-blocks of k on
     (1600, 3200, 136), (1312, 3904, 136),       # 2500 tiles of 32 x 64; 2501: 128 x 128 on eight wavefronts
     (1920, 3840, 136), (1408, 5248, 136),       # 450 tiles of 128 x 128, 451
     (70, 40, 8), (200, 70, 1032),               # fewer super-blocks of k than wavefronts, a remainder of one
@@ -297,9 +298,9 @@ def test_ffn_dispatch_edges(m, d, f):
 
 
 def test_bitlinear_forward_shape_sweep():
-    """Seeded random shapes across the dispatch boundaries (1-4 token path, 16- and 8-wavefront k-split tiles,
-    k-split tile launches, narrow and wide LDS tiles): integer stages exact, outputs identical, with and
-    without the taps (the two epilogue families) and with a residual."""
+    """Seeded random shapes across the dispatch boundaries (1-4 token path, direct tiles with k over 16, 8 and 4
+    wavefronts, narrow and wide LDS tiles): integer stages exact, outputs identical, with and without the taps
+    (the two epilogue families) and with a residual."""
     B, R = _mods()
     rng = np.random.default_rng(20241)
     shapes = []
@@ -408,7 +409,7 @@ def test_bitlinear_forward_batch(m, n, k, count, bf16):
 # ---------------------------------------------------------------------- FFN
 
 @pytest.mark.parametrize("m,d,f,bf16", [(256, 2560, 6912, True), (37, 256, 392, False), (3, 128, 264, True), (130, 3200, 8640, False),
-                                        (160, 256, 4224, False), (160, 4224, 512, False),    # k-split down / k-split gate|up (GLU)
+                                        (160, 256, 4224, False), (160, 4224, 512, False),    # long k in the down and in the gate|up (GLU) product
                                         # norms inside the one-wavefront-per-token quantiser: 34, 27 and 10 chunks per row,
                                         # groups of 8 tokens and (2100 at 6912 wide, 6200 at 2560 wide) of 16
                                         (1100, 128, 8640, False), (1100, 96, 6912, False), (2100, 96, 6912, False),
