@@ -669,7 +669,7 @@ def bench_critics(torch, B, R, synth, enc, ids, Bn: int, S: int, shape, steps: i
     out = {"int8_weight_encoder": {"ms_per_step": round(ms, 4), "states_per_s": round(Bn / ms * 1e3, 1),
                                    "weight_bytes": int(sum(t[k].packed.numel() for t in enc.keep[1::2] for k in t
                                                            if hasattr(t[k], "packed"))),
-                                   "gemm_kernel": "gemm_lds_w8_kernel<2,2,2,2>",
+                                   "gemm_kernel": "gemm_lds_w8_kernel<2,2,2,2>; q | k | v: gemm_lds_attn_kernel<true>",
                                    "gemm_ms_per_step": round(gms / steps, 4),
                                    "gemm_tops": round(ops / (gms * 1e-3) / 1e12, 2) if gms > 0 else 0.0}}
     dims = [shape.d, 256, 1]
@@ -684,7 +684,7 @@ def bench_critics(torch, B, R, synth, enc, ids, Bn: int, S: int, shape, steps: i
             e.forward(h1, want_each=False)
         torch.cuda.synchronize()
         ens["%d_heads_us" % n_members] = round((time.perf_counter() - t0) / 50 * 1e6, 1)
-    out["value_ensemble"] = dict(ens, batch=Bn, dims=dims, launches_per_call=3)
+    out["value_ensemble"] = dict(ens, batch=Bn, dims=dims, launches_per_call=2)
     return out
 
 
@@ -716,7 +716,7 @@ def bench_ppo(torch, B, R, synth, np, shape, want_cpu: bool, T: int = 2048, batc
     steps = epochs * (T // batch)
     out = {"rollout_steps": T, "batch": batch, "epochs": epochs, "optimiser_steps": steps, "ms_per_update": round(ms, 3),
            "us_per_optimiser_step": round(ms / steps * 1e3, 2), "trainable_params": int(tr.params.numel()),
-           "kernel_launches_per_update": steps * 8, "cpu_oracle": None}
+           "kernel_launches_per_update": steps * 4, "cpu_oracle": None}
     if want_cpu:
         from oracle import ppo_oracle as P
         adv_ref, ret_ref = P.gae(c["rewards"][0], c["values"][0], c["dones"][0], c["last_value"][0], 0.99, 0.95)
