@@ -119,45 +119,40 @@ def test_quantize_weights_special_matrices():
 
 
 def test_quantising_thread_ends_without_waiting_for_the_device():
-    """A loader thread that quantises on its own stream ends while another stream is still at work (about half a second of
-    a kernel that spins)."""
+    """A loader thread that has quantised ends while a stream is still at work (about half a second of a kernel that spins)."""
     import os
     import threading
     import time
     B, R = _mods()
     W = R.dev(synth.normal(75, 1, (64, 256), 0.02))
     packed, beta, ws = R.device_bytes(B.brl_packed_bytes(64, 256)), torch.empty(1, device="cuda"), R.device_bytes(1 << 16)
-    busy, own = torch.cuda.Stream(), torch.cuda.Stream()
-
-    def quantise():
-        with torch.cuda.stream(own):
-            B.bitlinear_quantize_weights(W, 1e-5, packed, beta, None, ws)
-
-    def run():
-        t = threading.Thread(target=quantise)
-        t.start()
-        task = "/proc/self/task/%d" % t.native_id
-        t.join(60)
-        assert not t.is_alive()
-        limit = time.monotonic() + 5
-        while os.path.exists(task) and time.monotonic() < limit:     # join() returns before the thread's own clean-up
-            time.sleep(0.001)
-        assert not os.path.exists(task)
-
-    run()                                                # (first launches, the library's pinned page)
-    a, b, done = (torch.cuda.Event(enable_timing=True) for _ in range(3))
-    with torch.cuda.stream(busy):
-        a.record()
-        torch.cuda._sleep(1000000)
-        b.record()
+    begin, end, done = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+    begin.record()
+    torch.cuda._sleep(1000000)
+    end.record()
     torch.cuda.synchronize()
-    with torch.cuda.stream(busy):
-        torch.cuda._sleep(int(1000000 * 500.0 / max(a.elapsed_time(b), 0.05)))
-        done.record()
-    run()
+    half_a_second = int(1000000 * 500.0 / max(begin.elapsed_time(end), 0.05))
+    quantised, may_end = threading.Event(), threading.Event()
+
+    def load():
+        B.bitlinear_quantize_weights(W, 1e-5, packed, beta, None, ws)
+        quantised.set()
+        may_end.wait(60)
+
+    t = threading.Thread(target=load)
+    t.start()
+    assert quantised.wait(60)
+    task = "/proc/self/task/%d" % t.native_id
+    torch.cuda._sleep(half_a_second)
+    done.record()
+    may_end.set()
+    t.join(60)
+    limit = time.monotonic() + 5
+    while os.path.exists(task) and time.monotonic() < limit:     # join() returns before the thread's own clean-up
+        time.sleep(0.001)
     ended_first = not done.query()
     torch.cuda.synchronize()
-    assert ended_first
+    assert not os.path.exists(task) and ended_first
 
 
 def test_concurrent_quantising_threads_get_their_own_verdict():
