@@ -8,6 +8,7 @@
 // One launch per layer and head with a wavefront per result took 86 us for 64 samples of 2560 -> 256 -> 18 and 1 (four
 // launches; 81 us even for one sample: 40 dependent rounds of loads per wavefront); the two launches take 14 us for 64
 // samples, 9.4 us for one, 75 us for 1024 (the launches per layer and head 1147 us).
+#include <climits>
 #include <cstring>
 
 #include "mlp_f64.hpp"
@@ -166,15 +167,10 @@ SetArgs set_layout(const MlpSet& s) {
     return a;
 }
 
-// The first layers' partial sums (never less than a smaller batch needs), then the hidden layers of the launch-per-level form
+// the first layers' partial sums (never less than a smaller batch needs)
 size_t sums_bytes(const SetArgs& a) {
     const MlpSet& s = a.s;
     return round_up_sz(first_layer_rows(a.tile_end[s.n - 1], s.B, s.dims[0][0]) * a.unit_end[0][s.n - 1] * sizeof(double), 256);
-}
-size_t hidden_units(const SetArgs& a) {
-    size_t t = 0;
-    for (int l = 0; l + 1 < a.depth; ++l) t += (size_t)a.unit_end[l][a.s.n - 1];
-    return t;
 }
 
 // Weights above the first layers that a lone workgroup goes through before a launch per level would be done, and the batch
@@ -184,19 +180,30 @@ size_t hidden_units(const SetArgs& a) {
 constexpr size_t HEAD_TAIL_WEIGHTS = 1 << 14;
 constexpr int HEAD_TAIL_BATCH = 128;
 
-bool one_workgroup_per_sample(const SetArgs& a) {
+// samples below which a call takes a launch per level instead
+int level_batch(const SetArgs& a) {
     size_t units = 0, weights = 0;
     for (int l = 0; l < a.depth; ++l) units += (size_t)a.unit_end[l][a.s.n - 1];
     for (int e = 0; e < a.s.n; ++e)
         for (int l = 1; l < a.s.layers[e]; ++l) weights += (size_t)a.s.dims[e][l] * a.s.dims[e][l + 1];
-    return units <= (size_t)HEAD_MAX_UNITS && (weights <= HEAD_TAIL_WEIGHTS || a.s.B >= HEAD_TAIL_BATCH);
+    if (units > (size_t)HEAD_MAX_UNITS) return INT_MAX;
+    return weights > HEAD_TAIL_WEIGHTS ? HEAD_TAIL_BATCH : 0;
+}
+
+// the hidden layers of the launch-per-level form, for every batch up to this one that takes it
+size_t hidden_bytes(const SetArgs& a) {
+    size_t units = 0;
+    for (int l = 0; l + 1 < a.depth; ++l) units += (size_t)a.unit_end[l][a.s.n - 1];
+    const int below = level_batch(a);
+    const size_t rows = below == 0 ? 0 : a.s.B < below ? a.s.B : below - 1;
+    return round_up_sz(rows * units * sizeof(double), 256);
 }
 
 }  // namespace
 
 size_t heads_workspace_bytes(const MlpSet& s) {
     const SetArgs a = set_layout(s);
-    return sums_bytes(a) + round_up_sz((size_t)s.B * hidden_units(a) * sizeof(double), 256);
+    return sums_bytes(a) + hidden_bytes(a);
 }
 
 int launch_heads(const MlpSet& s, void* workspace, hipStream_t stream) {
@@ -212,7 +219,7 @@ int launch_heads(const MlpSet& s, void* workspace, hipStream_t stream) {
     else if (a.splits == 1) hipLaunchKernelGGL((heads_first_kernel<true, 4>), grid, dim3(256), 0, stream, a);
     else if (few) hipLaunchKernelGGL((heads_first_kernel<false, 1>), grid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL((heads_first_kernel<false, 4>), grid, dim3(256), 0, stream, a);
-    if (one_workgroup_per_sample(a)) {
+    if (s.B >= level_batch(a)) {
         if (s.B <= HEAD_TAIL_FEW) hipLaunchKernelGGL(heads_tail_kernel<512>, dim3((unsigned)s.B), dim3(512), 0, stream, a);
         else hipLaunchKernelGGL(heads_tail_kernel<256>, dim3((unsigned)s.B), dim3(256), 0, stream, a);
     } else {
