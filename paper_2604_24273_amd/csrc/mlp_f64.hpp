@@ -9,7 +9,7 @@
 // a workgroup takes all groups of its tile one after the other: the same order both ways, so a result does not depend on
 // what shares the call, be it samples or other heads.
 // 64 x 2560 -> 2 x 256: 32 us with vector FMAs (four units x four samples per workgroup), 43 us with a wavefront per
-// result, 8.3 us here (bound by the latency of gathering the rows and of the 80 dependent MFMAs of a wavefront).
+// result, 8.4 us here (bound by the latency of gathering the rows and of the 80 dependent MFMAs of a wavefront).
 #pragma once
 
 #include "common.hpp"

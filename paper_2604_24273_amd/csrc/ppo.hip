@@ -209,13 +209,13 @@ __global__ __launch_bounds__(256, 3) void ppo_first_layer_kernel(FirstArgs a) {
 // ---- from the first layer's sums to every delta, one workgroup per sample ---------------------------------------
 // The layers above the first are small (256 -> 18, 256 -> 1): one workgroup runs the rest of both heads forward, the
 // clipped surrogate (Eq. 1), the entropy bonus and the value error with their gradients, and both heads backward on
-// activations and deltas in its LDS.  One launch (9.4 us, a chain of L2 and fp64 exp / log / tanh latencies) for what were
+// activations and deltas in its LDS.  One launch (8.6 us, a chain of L2 and fp64 exp / log / tanh latencies) for what were
 // three (second layer 6 us, loss 14 us, deltas 5 us).  Used wherever the units fit the LDS, whatever weights every
 // workgroup then reads: a step at 64 samples of 2560 inputs 39 us against 73 with the level kernels below for hidden 256,
 // 64 / 158 for 256, 256 (136 k weights above the first layers), 149 / 257 for 480, 480 (470 k), 220 / 360 for a policy head
 // of 1000, 1000 (1 M); at 8 samples 35 / 56, 63 / 127, 149 / 200, 218 / 309, at 1024 three times ahead.
 constexpr int TAIL_MAX_UNITS = 2048;          // layer outputs of both heads together: activations and deltas in 32 KB of LDS
-constexpr int TAIL_THREADS = 512;             // (256: 10.9 us against 9.4 at 512 first-layer units: every loop over units has two rounds)
+constexpr int TAIL_THREADS = 512;             // (256: 1.5 us more at 512 first-layer units: every loop over units has two rounds)
 struct TailArgs {
     const double* z;                 // first-layer sums [splits][B][..]
     int splits, B, A, T, act;
