@@ -357,3 +357,20 @@ def test_value_head_bits_do_not_depend_on_what_shares_the_call(dims):
         assert torch.equal(each[0], want[0][:batch]), (members_n, batch)
         if members_n > 1:
             assert torch.equal(each[-1], want[1][:batch]), (members_n, batch)
+
+
+@pytest.mark.parametrize("d,batch", [(1000, 577), (2560, 640), (70, 520)])
+def test_ensemble_of_many_tiles_gives_the_bits_of_few(d, batch):
+    """Eight members of 256 units: beyond 1024 tiles of 16 units x 64 samples a workgroup takes all groups of inputs of its
+    tile, up to there one of them.  Same bits, and the oracle's values."""
+    B, R = _mods()
+    members = [synth.mlp_params(33, 20 * e, [d, 256, 1]) for e in range(8)]
+    h = synth.normal(33, 399, (batch, d))
+    ens = R.ValueEnsemble(members, act=B.BRL_ACT_TANH)
+    print("ensemble, many tiles", d, batch, flush=True)
+    mean, each = ens.forward(R.dev(h))
+    ref_mean, ref_each = C.value_ensemble(h, [O.MLP(ws, bs, "tanh") for ws, bs in members])
+    assert np.abs(each.cpu().numpy() - ref_each).max() <= 2e-6 * max(np.abs(ref_each).max(), 1.0)
+    for lo, hi in ((0, 64), (64, 65), (100, 300), (batch - 16, batch)):
+        few_mean, few = ens.forward(R.dev(h[lo:hi]))
+        assert torch.equal(few, each[:, lo:hi]) and torch.equal(few_mean, mean[lo:hi]), (lo, hi)

@@ -125,6 +125,7 @@ def test_no_normalisation_and_paper_hyperparameters_defaults():
     ([2567, 250, 3], [2567, 17, 1], "tanh", 70, 67),      # inputs, units and samples off every tile; rows at odd addresses
     ([9, 5], [9, 3, 1], "relu", 6, 3),                    # less than one tile in every direction, heads of unequal depth
     ([1024, 40, 24, 70], [1024, 16, 1], "tanh", 260, 130),   # more actions than a wavefront, three sample blocks
+    ([1030, 256, 5], [1030, 250, 1], "tanh", 2100, 2090),    # more than 1024 tiles: a workgroup takes all inputs of its tile
     ([48, 1040, 30], [48, 1030, 1], "tanh", 48, 16),      # too many units for one workgroup per sample: a launch per level
     ([40, 640, 500, 4], [40, 8, 1], "relu", 24, 12),      # 320 k weights above the first layer, units that still fit
 ])
