@@ -235,6 +235,24 @@ struct TailArgs {
     double* row_terms;               // [4, B]
 };
 
+// Clipped surrogate of one sample (Eq. 1): the term, whether its gradient flows, and its derivative by log pi(action)
+struct Surrogate {
+    double term, active, coef;
+    __device__ Surrogate(double logp, double logp_old, double adv, double clip_eps) {
+        const double ratio = exp(logp - logp_old);
+        const double surr1 = ratio * adv;
+        const double surr2 = fmin(fmax(ratio, 1.0 - clip_eps), 1.0 + clip_eps) * adv;
+        term = fmin(surr1, surr2);
+        active = surr1 <= surr2 ? 1.0 : 0.0;
+        coef = -(active * adv * ratio);
+    }
+};
+// derivative of a sample's loss by one logit of log-probability lp, entropy ent
+__device__ inline double logit_slope(double coef, bool taken, double lp, double ent, double ent_coef, int B) {
+    const double p = exp(lp);
+    return (coef * ((taken ? 1.0 : 0.0) - p) + ent_coef * p * (lp + ent)) / (double)B;
+}
+
 __device__ inline double act_slope(double a, int act) { return act == BRL_ACT_RELU ? (a > 0.0 ? 1.0 : 0.0) : 1.0 - a * a; }
 
 __global__ __launch_bounds__(TAIL_THREADS) void ppo_tail_kernel(TailArgs a) {
@@ -293,20 +311,15 @@ __global__ __launch_bounds__(TAIL_THREADS) void ppo_tail_kernel(TailArgs a) {
         double se = 0.0;
         for (int k = tid; k < a.A; k += 64) se += exp(z[k] - m);
         const double lse = m + log(wave_sum(se));
-        const double ratio = exp((z[action] - lse) - logp_old);
-        const double surr1 = ratio * adv_r;
-        const double surr2 = fmin(fmax(ratio, 1.0 - a.clip_eps), 1.0 + a.clip_eps) * adv_r;
-        const double active = surr1 <= surr2 ? 1.0 : 0.0;
+        const Surrogate sg(z[action] - lse, logp_old, adv_r, a.clip_eps);
         double ent = 0.0;
         for (int k = tid; k < a.A; k += 64) {
             const double lp = z[k] - lse;
             ent -= exp(lp) * lp;
         }
         ent = wave_sum(ent);
-        const double coef = -(active * adv_r * ratio);
         for (int k = tid; k < a.A; k += 64) {
-            const double lp = z[k] - lse, p = exp(lp);
-            const double d = (coef * ((k == action ? 1.0 : 0.0) - p) + a.ent_coef * p * (lp + ent)) / (double)a.B;
+            const double d = logit_slope(sg.coef, k == action, z[k] - lse, ent, a.ent_coef, a.B);
             del[lp0 + k] = d;
             a.delta[0][a.n[0] - 1][(size_t)b * a.A + k] = d;
         }
@@ -314,10 +327,10 @@ __global__ __launch_bounds__(TAIL_THREADS) void ppo_tail_kernel(TailArgs a) {
             const double diff = out[lv] - ret, dv = diff / (double)a.B;
             del[lv] = dv;
             a.delta[1][a.n[1] - 1][b] = dv;
-            a.row_terms[0 * a.B + b] = fmin(surr1, surr2);
+            a.row_terms[0 * a.B + b] = sg.term;
             a.row_terms[1 * a.B + b] = ent;
             a.row_terms[2 * a.B + b] = diff * diff;
-            a.row_terms[3 * a.B + b] = 1.0 - active;
+            a.row_terms[3 * a.B + b] = 1.0 - sg.active;
         }
     }
     __syncthreads();
@@ -463,43 +476,11 @@ struct LossArgs {
     double* row_terms;        // [4, B] scratch
 };
 
-// One workgroup: advantage normalisation over the mini-batch, then one thread per sample for the
+// One workgroup: advantage normalisation over the mini-batch, then a few lanes per sample for the
 // clipped surrogate (Eq. 1), the entropy bonus and the value error, and their gradients at the heads' outputs.
 __global__ __launch_bounds__(256) void ppo_loss_kernel(LossArgs a) {
-    __shared__ double s_mean, s_inv;
-    __shared__ double red[256];
-    if (a.normalize_adv) {
-        // mean and (n - 1) standard deviation over the mini-batch: strided partial sums, then a fixed tree
-        double part = 0.0;
-        for (int b = threadIdx.x; b < a.B; b += 256) part += (double)a.adv[clamp_index(a.rows[b], a.T)];
-        red[threadIdx.x] = part;
-        __syncthreads();
-        for (int st = 128; st >= 1; st >>= 1) {
-            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-            __syncthreads();
-        }
-        const double mean = red[0] / (double)a.B;
-        __syncthreads();
-        part = 0.0;
-        for (int b = threadIdx.x; b < a.B; b += 256) {
-            const double d = (double)a.adv[clamp_index(a.rows[b], a.T)] - mean;
-            part += d * d;
-        }
-        red[threadIdx.x] = part;
-        __syncthreads();
-        for (int st = 128; st >= 1; st >>= 1) {
-            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            const double sd = a.B > 1 ? sqrt(red[0] / (double)(a.B - 1)) : 0.0;
-            s_mean = mean;
-            s_inv = 1.0 / (sd + a.adv_eps);
-        }
-    } else if (threadIdx.x == 0) {
-        s_mean = 0.0;
-        s_inv = 1.0;
-    }
+    __shared__ double scal[2];                      // mean and scale of the advantages
+    minibatch_scale(a.adv, a.rows, a.B, a.T, a.adv_eps, a.normalize_adv, scal);
     __syncthreads();
     // LG adjacent lanes share a sample: each takes every LG-th action; maxima and sums meet by butterfly
     constexpr int LG = 4;
@@ -509,7 +490,7 @@ __global__ __launch_bounds__(256) void ppo_loss_kernel(LossArgs a) {
         const bool live = b < a.B;
         const int bc = live ? b : a.B - 1;              // idle lanes shadow the last sample and store nothing
         const int r = clamp_index(a.rows[bc], a.T);
-        const double A = ((double)a.adv[r] - s_mean) * s_inv;
+        const double A = ((double)a.adv[r] - scal[0]) * scal[1];
         const double* z = a.logits + (size_t)bc * a.A;
         double m = z[0];
         for (int k = part; k < a.A; k += LG) m = fmax(m, z[k]);
@@ -521,12 +502,7 @@ __global__ __launch_bounds__(256) void ppo_loss_kernel(LossArgs a) {
         for (int off = 1; off < LG; off <<= 1) se += __shfl_xor(se, off, 64);
         const double lse = m + log(se);
         const int act = clamp_index(a.actions[r], a.A);
-        const double logp = z[act] - lse;
-        const double ratio = exp(logp - (double)a.logp_old[r]);
-        const double surr1 = ratio * A;
-        const double clipped = fmin(fmax(ratio, 1.0 - a.clip_eps), 1.0 + a.clip_eps);
-        const double surr2 = clipped * A;
-        const double active = surr1 <= surr2 ? 1.0 : 0.0;
+        const Surrogate sg(z[act] - lse, (double)a.logp_old[r], A, a.clip_eps);
         double ent = 0.0;
         for (int k = part; k < a.A; k += LG) {
             const double lp = z[k] - lse;
@@ -534,19 +510,15 @@ __global__ __launch_bounds__(256) void ppo_loss_kernel(LossArgs a) {
         }
 #pragma unroll
         for (int off = 1; off < LG; off <<= 1) ent += __shfl_xor(ent, off, 64);
-        const double coef = -(active * A * ratio);
         if (live) {
-            for (int k = part; k < a.A; k += LG) {
-                const double lp = z[k] - lse, p = exp(lp);
-                a.dlogits[(size_t)b * a.A + k] = (coef * ((k == act ? 1.0 : 0.0) - p) + a.ent_coef * p * (lp + ent)) / (double)a.B;
-            }
+            for (int k = part; k < a.A; k += LG) a.dlogits[(size_t)b * a.A + k] = logit_slope(sg.coef, k == act, z[k] - lse, ent, a.ent_coef, a.B);
             if (part == 0) {
                 const double diff = a.v[b] - (double)a.returns[r];
                 a.dv[b] = diff / (double)a.B;
-                a.row_terms[0 * a.B + b] = fmin(surr1, surr2);
+                a.row_terms[0 * a.B + b] = sg.term;
                 a.row_terms[1 * a.B + b] = ent;
                 a.row_terms[2 * a.B + b] = diff * diff;
-                a.row_terms[3 * a.B + b] = 1.0 - active;
+                a.row_terms[3 * a.B + b] = 1.0 - sg.active;
             }
         }
     }
