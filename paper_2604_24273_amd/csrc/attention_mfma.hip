@@ -595,8 +595,8 @@ size_t attention_mfma_ws_bytes(int B, int S, int n_heads, int n_kv_heads, int he
 
 namespace {
 
-// Which form states of one key block take.  N: a workgroup per (state, query head), O: per (state, four query heads of one
-// key/value head), P: the pack and fragment kernels.  All give the same bits.  Times of 16 .. 2048 states in us:
+// Which form states of one key block take.  N (HEAD): a workgroup per (state, query head), O (GROUP): per (state, four query
+// heads of one key/value head), P (PAIR): the pack and fragment kernels.  All give the same bits.  Times of 16 .. 2048 states in us:
 // - heads of up to 32: N; beyond 1024 query heads, where at least three of O's four wavefronts have a head, O (16 / 4 heads
 //   of 32, 32 tokens, 64 states 8.2 / 8.9, 256 states 17.4 / 15.0, 2048 states 121 / 84; 16 / 8: 17.2 / 18.6).
 // - up to 64: O where three of its four wavefronts have a head (16 / 4, 32 tokens, 1 state 8.7 / 8.6, 256 states 31 / 23 and

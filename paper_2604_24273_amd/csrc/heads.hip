@@ -7,7 +7,7 @@
 // it gives as a value head.
 // One launch per layer and head with a wavefront per result took 86 us for 64 samples of 2560 -> 256 -> 18 and 1 (four
 // launches; 81 us even for one sample: 40 dependent rounds of loads per wavefront); the two launches take 14 us for 64
-// samples, 9.4 us for one, 75 us for 1024 (the launches per layer and head 1147 us).
+// samples, 9.5 us for one, 77 us for 1024 (the launches per layer and head 1147 us).
 #include <climits>
 #include <cstring>
 
