@@ -6,8 +6,8 @@
 // the bits of a head do not depend on the launch form, the batch or the heads beside it: an ensemble's member gives what
 // it gives as a value head.
 // One launch per layer and head with a wavefront per result took 86 us for 64 samples of 2560 -> 256 -> 18 and 1 (four
-// launches; 81 us even for one sample: 40 dependent rounds of loads per wavefront); the two launches take 14 us for 64
-// samples, 9.5 us for one, 77 us for 1024 (the launches per layer and head 1147 us).
+// launches; 81 us even for one sample: 40 dependent rounds of loads per wavefront); the two launches take 13.5 us for 64
+// samples, 9.0 us for one, 71 us for 1024 (the launches per layer and head 1147 us).
 #include <climits>
 #include <cstring>
 
@@ -19,8 +19,8 @@ namespace {
 
 constexpr int HEAD_MAX_UNITS = 4096;           // layer outputs of all heads together: 32 KB of LDS
 // threads of a sample's workgroup: 512 up to two workgroups per compute unit, where every loop over units costs its
-// latency (64 samples of 2560 -> 256 -> 256 -> 18 and 1: 32 us, 51 us with 256), 256 beyond (1024 samples of 2560 -> 256 ->
-// 18 and 1: 77 us, 81 us with 512)
+// latency (2560 -> 256 -> 256 -> 18 and 1, 128 samples: 34.8 us, 45.3 us with 256; 512 samples: 69.1 us, 77.8 us), 256
+// beyond (2560 -> 256 -> 18 and 1, 1024 samples: 70.8 us, 73.9 us with 512; 4096 samples: 246 us, 260 us)
 constexpr int HEAD_TAIL_FEW = 512;
 
 // What is the same for every form.  Units of a layer level lie head after head; a head that has no such layer has none.
