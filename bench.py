@@ -382,10 +382,10 @@ def bench_layer(torch, B, R, synth, calls: int = 200):
     _drain_timing(B)
     gemm_us = gms / max(ng, 1) * 1e3
     return {"workload": "W 2048x2048 ternary, X 16x2048 fp32, seed 0", "calls": calls,
-            "wall_us_per_call": round(wall_us, 3), "quant_kernel_us": round(qms / max(nq, 1) * 1e3, 3),
+            "wall_us_per_call": round(wall_us, 3), "quant_kernel_us": round(qms / max(nq, 1) * 1e3, 3) if nq else None,
             "gemm_kernel_us": round(gemm_us, 3), "int8_ops": 2.0 * m * n * k,
             "gemm_tops": round(2.0 * m * n * k / (gemm_us * 1e-6) / 1e12, 3) if gemm_us > 0 else 0.0,
-            "note": "latency bound: 1.05 MB of packed weights and 0.134 GOP are below 0.2 us at either roofline"}
+            "note": "one launch, quantisation included; latency bound: 1.05 MB of packed weights and 0.134 GOP are below 0.2 us at either roofline"}
 
 
 def bench_ffn(torch, B, R, synth, calls: int = 200, m: int = 256, d: int = 2560, f: int = 6912):

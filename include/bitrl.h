@@ -121,7 +121,8 @@ int brl_unpack_codes(const void* packed, int n_out, int k_in, int8_t* codes_out,
  * x [M, K] of x_dtype; y [M, N] fp32; residual [M, N] fp32 or NULL (may alias
  * y).  Optional taps (NULL to skip): xq_dbg [M, K] int8, absmax_dbg [M] fp32
  * (the clamped a), acc_dbg [M, N] int32.
- * M <= 4 takes the bandwidth-bound GEMV path, larger M the int8 MFMA path.
+ * M <= 4 takes the bandwidth-bound GEMV path, larger M the int8 MFMA path (3..32
+ * tokens of up to 5120 features in one launch with their quantisation).
  * ------------------------------------------------------------------------ */
 size_t brl_bitlinear_workspace_bytes(int M, int N, int K);
 int bitlinear_forward(const void* packed, const float* beta, int N, int K,

@@ -68,6 +68,11 @@ constexpr size_t ALIGN = 256;
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+inline bool overlap(const void* p, size_t np, const void* q, size_t nq) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + nq && b < a + np;
+}
+
 struct Carver {
     char* base;
     size_t off;
@@ -196,7 +201,7 @@ void add_seg(WeightSegs& w, const void* packed, const float* beta, int N) {
     w.n_end[i] = (i ? w.n_end[i - 1] : 0) + N;
 }
 
-// the quantised activations of the MFMA path (the 1..4 token path needs no scratch)
+// the quantised activations of the MFMA path (the one-launch paths for a few tokens need no scratch)
 struct BitlinearWs {
     size_t act_off, total;
 };
@@ -489,6 +494,10 @@ int bitlinear_forward(const void* packed, const float* beta, int N, int K, const
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* base = static_cast<char*>(workspace);
+    // (one launch reads x while it writes y)
+    if (rows_product_eligible(M, N, K) && !overlap(x, (size_t)M * K * (x_dtype == BRL_BF16 ? 2 : 4), y, (size_t)M * N * 4))
+        return launch_rows_product(x, x_dtype, M, K, N, static_cast<const uint32_t*>(packed), beta, eps_act, y, residual,
+                                   xq_dbg, absmax_dbg, acc_dbg, s);
     if (M <= 4) {
         return launch_gemv(x, x_dtype, M, K, N, static_cast<const uint32_t*>(packed), beta, eps_act, y, residual, xq_dbg,
                            absmax_dbg, acc_dbg, s);
@@ -542,6 +551,10 @@ int bitlinear_forward_static(const void* packed, const float* beta, int N, int K
     BRL_REQUIRE(eps_act > 0.f, "bitlinear_forward_static: eps_act must be positive");
     if (int rc = check_linear_shape(N, K, "bitlinear_forward_static")) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // (one launch reads x while it writes y)
+    if (rows_product_eligible(M, N, K) && !overlap(x, (size_t)M * K * (x_dtype == BRL_BF16 ? 2 : 4), y, (size_t)M * N * 4))
+        return launch_rows_product(x, x_dtype, M, K, N, static_cast<const uint32_t*>(packed), beta, eps_act, y, residual,
+                                   xq_dbg, absmax_dbg, acc_dbg, s);
     if (M <= 4) {      // the 1..4 token path keeps everything in registers and LDS
         return launch_gemv(x, x_dtype, M, K, N, static_cast<const uint32_t*>(packed), beta, eps_act, y, residual, xq_dbg,
                            absmax_dbg, acc_dbg, s);

@@ -87,6 +87,16 @@ template <class T>
 __device__ __forceinline__ T wave_total(T v) { return wave_reduce(v, [](T a, T b) { return a + b; }); }
 __device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); }); }
 
+// ---- activation codes ----
+// four codes clamp(rne(v s), -127, 127) as bytes: adding 1.5 * 2^23 rounds to an integer (nearest, ties to even) and leaves
+// it in the low bits.  |v s| cannot pass 127 by more than its rounding, so only the lower clamp is needed (for NaN).
+__device__ __forceinline__ uint32_t quantise_four(const float (&v)[4], float s) {
+    uint32_t b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = __float_as_uint(fmaxf(v[e] * s, -127.f) + 12582912.f);
+    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
+}
+
 // ---- sizes ----
 constexpr int WAVE = 64;
 constexpr int NB = 32;        // rows of one weight block / tokens of one activation block
@@ -178,6 +188,11 @@ int launch_gemm_attn(const ActBuf& a, const WeightSegs& w, int M, int K, const A
 int launch_gemv(const void* x, int x_dtype, int M, int K, int N, const uint32_t* packed, const float* beta,
                 float eps_act, float* y, const float* residual, int8_t* xq_dbg, float* absmax_dbg,
                 int32_t* acc_dbg, hipStream_t s);
+// 3 .. 32 tokens in one launch, where that is ahead of quantisation and product by themselves
+bool rows_product_eligible(int M, int N, int K);
+int launch_rows_product(const void* x, int x_dtype, int M, int K, int N, const uint32_t* packed, const float* beta,
+                        float eps_act, float* y, const float* residual, int8_t* xq_dbg, float* absmax_dbg,
+                        int32_t* acc_dbg, hipStream_t s);
 int launch_gemv_batch(const void* const* packed, const float* const* beta, int N, int K, const void* const* x,
                       int x_dtype, int M, float eps_act, float* const* y, int count, hipStream_t s);
 

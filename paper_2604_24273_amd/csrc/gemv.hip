@@ -1,5 +1,6 @@
-// Bandwidth-bound BitLinear for 1..4 tokens: y = dequant(codes . quant(x)).
+// BitLinear for a handful of tokens in one launch: y = dequant(codes . quant(x)).
 //
+// gemv_kernel (1 .. 4 tokens):
 // One workgroup of 16 wavefronts owns one block of 32 output rows over the whole
 // k range, so no partial sums ever cross workgroups (no atomics, no fences).
 // The packed weights are streamed once with 16-byte-per-lane loads (a wavefront
@@ -197,6 +198,135 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
         part -= sq;
         const float d = fmaxf(m, g.eps_act) / 127.0f;
         float val = ((float)part * d) * beta;
+        if (g.residual) val = val + res;
+        g.y[o] = val;
+        if (g.acc_dbg) g.acc_dbg[o] = part;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// 3 .. 32 tokens in one launch, on the matrix cores.  A workgroup of 16 wavefronts owns 32 output rows over all of k, as in
+// gemv_kernel; every wavefront quantises whole tokens (RW of them, in its registers: no exchange between wavefronts), the
+// codes meet in LDS in MFMA operand order, a wavefront contracts every 16th super-block and the parts are added in LDS.
+// Every workgroup quantises all tokens again (what a compute unit spends its time on: some 20 vector instructions per four
+// values), a price that grows with tokens x k, against a launch, a pass through memory and the gap between two kernels.
+// Calls back to back, us, quantisation and product as two launches / here: 16 x 2048 x 2048 8.6 / 5.4 (what the host takes
+// for a call), 16 x 2560 x 5120 8.7 / 7.0, 32 x 8192 x 2560 8.6 / 7.7.
+// In LDS the 16-byte piece p (16 columns) of token r stands at slot (r + p) % (16 RW) of the piece's row: the dwords a
+// wavefront writes (one token, 16 pieces) and the pieces it reads (one super-block step, all tokens) fall on different banks.
+// ---------------------------------------------------------------------------
+typedef int rp_v4i __attribute__((ext_vector_type(4)));
+typedef int rp_v16i __attribute__((ext_vector_type(16)));
+typedef unsigned int rp_u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int rp_u32x2 __attribute__((ext_vector_type(2)));
+typedef const __attribute__((address_space(1))) char* rp_gptr;
+
+template <int RW, int NX, bool BF16>
+__global__ __launch_bounds__(GV_THREADS) void rows_product_kernel(GemvArgs g) {
+    constexpr int TOK = 16 * RW;                     // tokens the operand rows in LDS hold
+    constexpr int NS = (NX * 2 + 15) / 16;           // super-blocks of a wavefront
+    __shared__ __attribute__((aligned(16))) char aq[NX * 16 * TOK * 16];
+    __shared__ int red[GV_WAVES][16][64];
+    __shared__ float tok_d[TOK];
+    __shared__ int tok_sq[TOK];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int nb = blockIdx.x, K = g.K;
+
+    // everything the workgroup reads: activations first (needed first, and loads return in order), weights, the finishing
+    // threads' operands; all with clamped addresses, so that none waits for another
+    rp_u32x4 raw[RW][NX];
+#pragma unroll
+    for (int t = 0; t < RW; ++t) {
+        const rp_gptr row = (rp_gptr)g.x + (size_t)min(wave + 16 * t, g.M - 1) * K * (BF16 ? 2 : 4);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const unsigned k = (unsigned)min(4 * (lane + 64 * i), K - 4);
+            if constexpr (BF16) raw[t][i].xy = *(const __attribute__((address_space(1))) rp_u32x2*)(row + k * 2u);
+            else raw[t][i] = *(const __attribute__((address_space(1))) rp_u32x4*)(row + k * 4u);
+        }
+    }
+    rp_u32x4 w[NS];
+    const __attribute__((address_space(1))) rp_u32x4* wp = (const __attribute__((address_space(1))) rp_u32x4*)g.packed + (size_t)nb * g.nsb * 64;
+#pragma unroll
+    for (int u = 0; u < NS; ++u) w[u] = wp[(unsigned)(min(wave + 16 * u, g.nsb - 1) * 64 + lane)];
+    const float beta = *g.beta;
+    const int m = threadIdx.x >> 5, c = threadIdx.x & 31;            // the element this thread finishes
+    const bool finishes = m < g.M && nb * 32 + c < g.N;
+    const size_t o = (size_t)m * g.N + nb * 32 + c;
+    const float res = g.residual && finishes ? g.residual[o] : 0.f;
+
+#pragma unroll
+    for (int t = 0; t < RW; ++t) {
+        const int r = wave + 16 * t;
+        // (past the end of k a lane holds the row's last four values again: the maximum is the same, the code is zero)
+        float v[NX][4], amax = 0.f;
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const rp_u32x4 q = raw[t][i];
+            v[i][0] = __uint_as_float(BF16 ? q.x << 16 : q.x);
+            v[i][1] = __uint_as_float(BF16 ? q.x & 0xffff0000u : q.y);
+            v[i][2] = __uint_as_float(BF16 ? q.y << 16 : q.z);
+            v[i][3] = __uint_as_float(BF16 ? q.y & 0xffff0000u : q.w);
+            amax = fmaxf(fmaxf(fmaxf(fmaxf(amax, fabsf(v[i][0])), fabsf(v[i][1])), fabsf(v[i][2])), fabsf(v[i][3]));
+        }
+        const float ac = fmaxf(wave_max(amax), g.eps_act);
+        const float s = 127.0f / ac;
+        char* const at = aq + (lane >> 2) * (TOK * 16) + 4 * (lane & 3);
+        const int slot = (r + (lane >> 2)) % TOK;
+        int sum = 0;
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const uint32_t word = quantise_four(v[i], s) & (4 * (lane + 64 * i) < K ? ~0u : 0u);
+            sum = __builtin_amdgcn_sdot4((int)word, 0x01010101, sum, false);
+            *reinterpret_cast<uint32_t*>(at + i * (TOK * 256) + ((slot + 16 * i) % TOK) * 16) = word;
+        }
+        sum = wave_total(sum);
+        if (lane == 0) {
+            tok_d[r] = ac / 127.0f;
+            tok_sq[r] = sum;
+            if (g.absmax_dbg && nb == 0 && r < g.M) g.absmax_dbg[r] = ac;
+        }
+    }
+    __syncthreads();
+
+    if (g.xq_dbg && nb == 0) {
+        for (int i = threadIdx.x; i < g.M * (K / 4); i += GV_THREADS) {
+            const int t = i / (K / 4), k = 4 * (i % (K / 4)), p = k >> 4;
+            *reinterpret_cast<uint32_t*>(g.xq_dbg + (size_t)t * K + k) =
+                *reinterpret_cast<const uint32_t*>(aq + p * (TOK * 16) + ((t + p) % TOK) * 16 + (k & 15));
+        }
+    }
+
+    rp_v16i acc = {};
+    const int r = lane & (TOK - 1), hh = lane >> 5;                  // (RW = 1: rows 16 .. 31 repeat the first ones)
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        const int sb = wave + 16 * u;
+        if (sb >= g.nsb) break;
+#pragma unroll
+        for (int dd = 0; dd < 4; ++dd) {
+            const int p = sb * 8 + dd * 2 + hh;
+            const rp_v4i a = *reinterpret_cast<const rp_v4i*>(aq + p * (TOK * 16) + ((r + p) % TOK) * 16);
+            const uint32_t pw = w[u][dd];
+            const rp_v4i b = {(int)(pw & 0x03030303u), (int)((pw >> 2) & 0x03030303u), (int)((pw >> 4) & 0x03030303u),
+                              (int)((pw >> 6) & 0x03030303u)};
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc, 0, 0, 0);
+        }
+    }
+    const int parts = min(GV_WAVES, g.nsb);
+    if (wave < parts) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (RW == 2 || v < 8) red[wave][v][lane] = acc[v];
+    }
+    __syncthreads();
+
+    if (finishes) {
+        // register 4 (m / 8) + m % 4 of lane c + 32 (m / 4 % 2)
+        const int v = 4 * (m >> 3) + (m & 3), l = c + 32 * ((m >> 2) & 1);
+        int part = -tok_sq[m];
+        for (int q = 0; q < parts; ++q) part += red[q][v][l];
+        float val = ((float)part * tok_d[m]) * beta;
         if (g.residual) val = val + res;
         g.y[o] = val;
         if (g.acc_dbg) g.acc_dbg[o] = part;
@@ -476,6 +606,52 @@ int launch_gemv(const void* x, int x_dtype, int M, int K, int N, const uint32_t*
         default: set_error("gemv: M = %d out of range 1..4", M); return BRL_EINVAL;
     }
     BRL_LAUNCH_CHECK("gemv_kernel");
+    return BRL_OK;
+}
+
+// Does launch_rows_product take this product?  From three tokens on (gemv_kernel / here, us a call: 2 x 4096 x 4096 5.4 /
+// 6.4, 2 x 6912 x 2560 5.4 / 5.4, 3 x 6912 x 2560 6.2 / 5.4, 4 x 4096 x 4096 7.0 / 6.1, 4 x 2560 x 5120 8.0 / 6.9); as far as
+// a wavefront's registers and the operand rows beside the parts' 64 KB of LDS reach: 16 tokens of 5120, 32 of 2560 columns
+// (the slowest there, 27 x 8192 x 2560 in bf16: 8.5 as two launches, 7.8); one workgroup per compute unit and round, so not
+// past 256 of them.
+bool rows_product_eligible(int M, int N, int K) {
+    return M >= 3 && M <= 32 && round_up(N, NB) / NB <= 256 && K <= (M <= 16 ? 5120 : 2560);
+}
+
+int launch_rows_product(const void* x, int x_dtype, int M, int K, int N, const uint32_t* packed, const float* beta,
+                        float eps_act, float* y, const float* residual, int8_t* xq_dbg, float* absmax_dbg,
+                        int32_t* acc_dbg, hipStream_t s) {
+    GemvArgs g;
+    g.x = x; g.x_dtype = x_dtype; g.M = M; g.K = K; g.N = N;
+    g.nsb = round_up(K, SBK) / SBK;
+    g.packed = reinterpret_cast<const uint4*>(packed);
+    g.beta = beta; g.eps_act = eps_act; g.y = y; g.residual = residual;
+    g.xq_dbg = xq_dbg; g.absmax_dbg = absmax_dbg; g.acc_dbg = acc_dbg;
+    LaunchTimer tm(BRL_KC_GEMM_NARROW, s, 2.0 * (double)M * (double)N * (double)K);
+    const dim3 grid(round_up(N, NB) / NB);
+    auto launch = [&](auto rw, auto nx) {
+        constexpr int RW = decltype(rw)::value, NX = decltype(nx)::value;
+        if (x_dtype == BRL_BF16) hipLaunchKernelGGL((rows_product_kernel<RW, NX, true>), grid, dim3(GV_THREADS), 0, s, g);
+        else hipLaunchKernelGGL((rows_product_kernel<RW, NX, false>), grid, dim3(GV_THREADS), 0, s, g);
+    };
+    typedef std::integral_constant<int, 1> one;
+    typedef std::integral_constant<int, 2> two;
+    if (!rows_product_eligible(M, N, K)) {
+        set_error("rows product: %d tokens, %d x %d", M, N, K);
+        return BRL_EINVAL;
+    }
+    if (M <= 16) {
+        if (K <= 1024) launch(one(), std::integral_constant<int, 4>());
+        else if (K <= 2048) launch(one(), std::integral_constant<int, 8>());
+        else if (K <= 2560) launch(one(), std::integral_constant<int, 10>());
+        else if (K <= 4096) launch(one(), std::integral_constant<int, 16>());
+        else launch(one(), std::integral_constant<int, 20>());
+    } else {
+        if (K <= 1024) launch(two(), std::integral_constant<int, 4>());
+        else if (K <= 2048) launch(two(), std::integral_constant<int, 8>());
+        else launch(two(), std::integral_constant<int, 10>());
+    }
+    BRL_LAUNCH_CHECK("rows_product_kernel");
     return BRL_OK;
 }
 

@@ -272,6 +272,47 @@ def test_bitlinear_dispatch_edges(m, n, k):
     assert np.array_equal(y2.cpu().numpy(), O.bitlinear_forward(case["X"], codes, beta, residual=res))
 
 
+@pytest.mark.parametrize("m,n,k,bf16", [
+    (2, 64, 256, False), (3, 64, 256, False), (4, 33, 8, True), (15, 100, 1024, False),   # first token counts, ragged n, shortest k
+    (16, 8192, 1032, True), (16, 8193, 1032, False),          # 256 workgroups; one more (two launches)
+    (16, 70, 5120, False), (16, 70, 5128, False), (9, 40, 4104, True),                    # longest k at 16 tokens, past it
+    (17, 96, 2560, False), (17, 96, 2568, True), (32, 31, 2048, True), (32, 40, 2056, False),
+    (31, 64, 1024, False), (32, 64, 520, False), (33, 64, 520, False),                    # most tokens, past them
+])
+def test_bitlinear_few_tokens_in_one_launch(m, n, k, bf16):
+    """Both sides of every limit of the one-launch product for a few tokens, with taps, with a residual in place, through
+    the entry point without a workspace, and with a result that overwrites the input."""
+    B, R = _mods()
+    print("few tokens", m, n, k, bf16, flush=True)
+    case = synth.bitlinear_case(11, n, k, m)
+    x = R.dev(case["X"])
+    if bf16:
+        x = x.to(torch.bfloat16)
+    X = x.float().cpu().numpy()
+    codes, beta = O.ternary_quantize(case["W"])
+    taps = {}
+    y_ref = O.bitlinear_forward(X, codes, beta, taps=taps)
+    pl = R.quantize_linear(case["W"])
+    y, xq, am, acc, ws = _run_bitlinear(B, R, pl, x)
+    assert np.array_equal(xq.cpu().numpy(), taps["xq"])
+    assert np.array_equal(am.cpu().numpy().view(np.uint32), taps["absmax"].view(np.uint32))
+    assert np.array_equal(acc.cpu().numpy(), taps["acc"])
+    assert np.array_equal(y.cpu().numpy(), y_ref)
+    y2 = torch.empty_like(y)
+    B.bitlinear_forward_static(pl.packed, pl.beta, n, k, x, m, 1e-5, y2, None, None, None, None)
+    assert torch.equal(y2, y)
+    res = synth.normal(11, 7, (m, n))
+    y2.copy_(R.dev(res))
+    B.bitlinear_forward(pl.packed, pl.beta, n, k, x, m, 1e-5, y2, y2, None, None, None, ws.buf)
+    assert np.array_equal(y2.cpu().numpy(), O.bitlinear_forward(X, codes, beta, residual=res))
+    if m > 4 and not bf16:                       # the result in the input's place (past the one-token path it always could be)
+        both = torch.empty(m * max(n, k), dtype=torch.float32, device="cuda")
+        both[:m * k].copy_(x.reshape(-1))
+        out = both[:m * n].view(m, n)
+        B.bitlinear_forward(pl.packed, pl.beta, n, k, both[:m * k].view(m, k), m, 1e-5, out, None, None, None, None, ws.buf)
+        assert np.array_equal(out.cpu().numpy(), y_ref)
+
+
 @pytest.mark.parametrize("m,d,f", [
     (512, 136, 1024), (544, 136, 1000),         # 512 and 544 tiles of 32 tokens x 32 column pairs, the second ragged
     (1536, 136, 2048), (1664, 136, 2048),       # 192 and 208 wide tiles: 75 and 81 % of 256 compute units
