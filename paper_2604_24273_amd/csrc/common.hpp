@@ -96,6 +96,10 @@ __device__ __forceinline__ uint32_t quantise_four(const float (&v)[4], float s) 
     for (int e = 0; e < 4; ++e) b[e] = __float_as_uint(fmaxf(v[e] * s, -127.f) + 12582912.f);
     return __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
 }
+__device__ __forceinline__ uint32_t quantise_four(const float4& v, float s) {
+    const float e[4] = {v.x, v.y, v.z, v.w};
+    return quantise_four(e, s);
+}
 
 // ---- sizes ----
 constexpr int WAVE = 64;

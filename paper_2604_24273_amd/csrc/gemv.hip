@@ -131,13 +131,8 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
         for (int u = 0; u < NX; ++u) {
             const int k = 4 * ((int)threadIdx.x + GV_THREADS * u);
             if (k < Kp) {
-                const float4 v = xv[t][u];
-                const int q0 = (int)fminf(fmaxf(rintf(v.x * sc), -127.f), 127.f);
-                const int q1 = (int)fminf(fmaxf(rintf(v.y * sc), -127.f), 127.f);
-                const int q2 = (int)fminf(fmaxf(rintf(v.z * sc), -127.f), 127.f);
-                const int q3 = (int)fminf(fmaxf(rintf(v.w * sc), -127.f), 127.f);
-                qsum += q0 + q1 + q2 + q3;
-                const int word = (q0 & 0xff) | ((q1 & 0xff) << 8) | ((q2 & 0xff) << 16) | ((q3 & 0xff) << 24);
+                const int word = (int)quantise_four(xv[t][u], sc);
+                qsum = __builtin_amdgcn_sdot4(word, 0x01010101, qsum, false);
                 xq[t][k >> 2] = word;
                 if (g.xq_dbg && nb == 0 && t < g.M && k < K) *reinterpret_cast<int*>(g.xq_dbg + (size_t)t * K + k) = word;
             }
@@ -476,13 +471,9 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_batch_kernel(GemvBatchArgs g)
                 for (int u = 0; u < GV_X4; ++u) {
                     const int k = 4 * ((int)threadIdx.x + GV_THREADS * u);
                     if (k < Kc) {          // zeros from K to a whole number of chunks
-                        const float4 v = xv[t][u];
-                        const int q0 = (int)fminf(fmaxf(rintf(v.x * sc), -127.f), 127.f);
-                        const int q1 = (int)fminf(fmaxf(rintf(v.y * sc), -127.f), 127.f);
-                        const int q2 = (int)fminf(fmaxf(rintf(v.z * sc), -127.f), 127.f);
-                        const int q3 = (int)fminf(fmaxf(rintf(v.w * sc), -127.f), 127.f);
-                        qsum += q0 + q1 + q2 + q3;
-                        xq[t][k >> 2] = (q0 & 0xff) | ((q1 & 0xff) << 8) | ((q2 & 0xff) << 16) | ((q3 & 0xff) << 24);
+                        const int word = (int)quantise_four(xv[t][u], sc);
+                        qsum = __builtin_amdgcn_sdot4(word, 0x01010101, qsum, false);
+                        xq[t][k >> 2] = word;
                     }
                 }
                 qsum = wave_total(qsum);
