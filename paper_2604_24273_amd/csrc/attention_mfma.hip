@@ -57,6 +57,13 @@ __device__ inline uint4 pack8h(const float (&x)[8], bool lo_part) {
     return __builtin_bit_cast(uint4, r);
 }
 
+// a value the compiler must round to fp32: it would fold the last multiply into a conversion that follows (one rounding
+// instead of two), for one use of the value and not for another
+__device__ __forceinline__ float rounded(float x) {
+    asm("" : "+v"(x));
+    return x;
+}
+
 template <int VW> struct VecOf;
 template <> struct VecOf<4> { typedef float4 type; };
 template <> struct VecOf<2> { typedef float2 type; };
@@ -582,6 +589,284 @@ __global__ __launch_bounds__(512) void attention_group_kernel(FragArgs a) {
     }
 }
 
+// States of at most 64 tokens with heads of 128: no fragments through memory.  Bound by memory and by how much of it is in
+// flight: the pair of kernels above writes K and V once and reads them twice more than needed, waits for q before it asks
+// for them, and gives the queries past row 32, a few rows of each head, a wavefront per head.  Here a workgroup asks for the
+// fp32 rows of up to four query heads and of their key/value head at once, and stages the rotated K and the transposed V in
+// LDS itself (fragments as attn_pack_kernel lays them out).  The first 32 queries: a wavefront per head, one 32-column block
+// of the result at a time (one key block needs no running sums).  The queries beyond: workgroups of their own (ahead in the
+// grid, they take longer), all heads' rows one after the other in units of 32, a unit's columns shared out over the
+// wavefronts that have no unit.  The arithmetic per element and its order are those of the pair: same bits.
+// 1024 states of 15 .. 40 tokens, 20 / 5 heads: pack 80 + fragments 309 us, 213 here (725 MB once; 225 with q read in operand
+// order, 236 as two launches); 64 states 36 -> 19, 1 state 17 -> 11.  What other sizes take: short_form below.
+constexpr int ROWS_D = 128, ROWS_KS = AttnTile<ROWS_D>::KS;
+constexpr int ROWS_STAGE = AttnTile<ROWS_D>::KVFR * 64;
+struct RowsBlock {                                    // what a thread of 256 stages of a key block
+    float4 k[4], c[2], s[2];                          // eight components of a k row and their eight partners; rotary factors
+    float v[2][8];
+    // rows: the state's first row; kb: key block; rows past the state's end repeat the last one (never seen by a query)
+    __device__ __forceinline__ void request(const float* rows, int ld, int kcol, int vcol, int kb, int len, const float* cos_t,
+                                            const float* sin_t) {
+        const int t = threadIdx.x;
+        const int r = min(kb * 32 + (t >> 3), len - 1), comp = 16 * ((t >> 1) & 3) + 8 * (t & 1);
+        const float* kr = rows + (unsigned)(r * ld) + kcol + comp;
+        k[0] = *reinterpret_cast<const float4*>(kr);
+        k[1] = *reinterpret_cast<const float4*>(kr + 4);
+        k[2] = *reinterpret_cast<const float4*>(kr + 64);
+        k[3] = *reinterpret_cast<const float4*>(kr + 68);
+        c[0] = *reinterpret_cast<const float4*>(cos_t + r * 64 + comp);
+        c[1] = *reinterpret_cast<const float4*>(cos_t + r * 64 + comp + 4);
+        s[0] = *reinterpret_cast<const float4*>(sin_t + r * 64 + comp);
+        s[1] = *reinterpret_cast<const float4*>(sin_t + r * 64 + comp + 4);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int i = t + 256 * q, h = (i >> 5) & 1, tt = (i >> 6) & 1, d = 32 * (i >> 7) + (i & 31);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                v[q][e] = rows[(unsigned)(min(kb * 32 + 16 * tt + 8 * (e >> 2) + 4 * h + (e & 3), len - 1) * ld) + vcol + d];
+        }
+    }
+    __device__ __forceinline__ void commit(uint4* st) const;
+};
+
+// N components x and their partners y (64 components on), rotated and scaled, as fp16 hi and lo
+template <int N>
+__device__ __forceinline__ void rotate_split(const float (&x)[N], const float (&y)[N], const float (&c)[N], const float (&s)[N],
+                                             float scale, _Float16 __attribute__((ext_vector_type(N))) (&first)[2],
+                                             _Float16 __attribute__((ext_vector_type(N))) (&second)[2]) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const float t1 = rounded((x[e] * c[e] - y[e] * s[e]) * scale), t2 = rounded((y[e] * c[e] + x[e] * s[e]) * scale);
+        first[0][e] = (_Float16)t1;
+        first[1][e] = (_Float16)(t1 - (float)first[0][e]);
+        second[0][e] = (_Float16)t2;
+        second[1][e] = (_Float16)(t2 - (float)second[0][e]);
+    }
+}
+__device__ __forceinline__ void unpack8(const float4& a, const float4& b, float (&v)[8]) {
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
+
+// fragments as attn_pack_kernel lays them out in memory
+__device__ __forceinline__ void RowsBlock::commit(uint4* st) const {
+    const int t = threadIdx.x, r = t >> 3, ks = (t >> 1) & 3, kg = t & 1;
+    float x[8], y[8], cf[8], sf[8];
+    unpack8(k[0], k[1], x);
+    unpack8(k[2], k[3], y);
+    unpack8(c[0], c[1], cf);
+    unpack8(s[0], s[1], sf);
+    v8h a[2], b[2];
+    rotate_split<8>(x, y, cf, sf, 1.0f, a, b);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        st[(ks * 2 + p) * 64 + kg * 32 + r] = __builtin_bit_cast(uint4, a[p]);
+        st[((ks + 4) * 2 + p) * 64 + kg * 32 + r] = __builtin_bit_cast(uint4, b[p]);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int i = t + 256 * q, tt = (i >> 6) & 1, rb = i >> 7;
+        st[(ROWS_KS * 2 + (rb * 2 + tt) * 2 + 0) * 64 + (i & 63)] = pack8h(v[q], false);
+        st[(ROWS_KS * 2 + (rb * 2 + tt) * 2 + 1) * 64 + (i & 63)] = pack8h(v[q], true);
+    }
+}
+
+// The q fragments of a wavefront's 32 queries: four lanes read 64 neighbouring bytes of a row (and the 64 bytes of their
+// rotary partners), rotate and split them, and the wavefront's 16 KB of LDS turn them into operand order.  Read straight in
+// operand order a lane's 16 bytes have no neighbour in the same 64: 15 .. 40 tokens, 64 states 21.8 us, 19.2 this way.
+struct RowsQuery {
+    float4 x[2][4], y[2][4];
+    const float *cp[2], *sp[2];
+    // row(r), pos(r): the row of the head and the position of query r
+    template <class Row, class Pos>
+    __device__ __forceinline__ void request(Row&& row, Pos&& pos, const float* cos_t, const float* sin_t) {
+        const int lane = threadIdx.x & 63, part = 4 * (lane & 3);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = (lane >> 2) + 16 * i;
+            const float* p = row(r) + part;
+            cp[i] = cos_t + pos(r) * 64 + part;
+            sp[i] = sin_t + pos(r) * 64 + part;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                x[i][ks] = *reinterpret_cast<const float4*>(p + 16 * ks);
+                y[i][ks] = *reinterpret_cast<const float4*>(p + 64 + 16 * ks);
+            }
+        }
+    }
+    __device__ __forceinline__ void fragments(uint4* mine, float scale, v8h (&qh)[ROWS_KS], v8h (&ql)[ROWS_KS]) const {
+        typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+        const int lane = threadIdx.x & 63, part = lane & 3;
+        char* at = reinterpret_cast<char*>(mine) + (part >> 1) * 512 + (lane >> 2) * 16 + (part & 1) * 8;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const float4 cv = *reinterpret_cast<const float4*>(cp[i] + 16 * ks), sv = *reinterpret_cast<const float4*>(sp[i] + 16 * ks);
+                const float xf[4] = {x[i][ks].x, x[i][ks].y, x[i][ks].z, x[i][ks].w}, yf[4] = {y[i][ks].x, y[i][ks].y, y[i][ks].z, y[i][ks].w};
+                const float cf[4] = {cv.x, cv.y, cv.z, cv.w}, sf[4] = {sv.x, sv.y, sv.z, sv.w};
+                v4h a[2], b[2];
+                rotate_split<4>(xf, yf, cf, sf, scale, a, b);
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    *reinterpret_cast<v4h*>(at + (ks * 2 + p) * 1024 + i * 256) = a[p];
+                    *reinterpret_cast<v4h*>(at + ((ks + 4) * 2 + p) * 1024 + i * 256) = b[p];
+                }
+            }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int ks = 0; ks < ROWS_KS; ++ks) {
+            qh[ks] = __builtin_bit_cast(v8h, mine[(ks * 2 + 0) * 64 + lane]);
+            ql[ks] = __builtin_bit_cast(v8h, mine[(ks * 2 + 1) * 64 + lane]);
+        }
+    }
+};
+
+// 32 columns of the result, normalised
+__device__ __forceinline__ void store_columns(const v16f& o, float inv, float* op, int h) {
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+        float4 v;
+        v.x = o[4 * g4 + 0] * inv; v.y = o[4 * g4 + 1] * inv;
+        v.z = o[4 * g4 + 2] * inv; v.w = o[4 * g4 + 3] * inv;
+        *reinterpret_cast<float4*>(op + 8 * g4 + 4 * h) = v;
+    }
+}
+
+// workgroup w: up to four heads of one key/value head of one state
+struct RowsWork {
+    int b, j, c, group, len, kcol, vcol;
+    size_t row0;
+    const float* rows;
+    __device__ __forceinline__ RowsWork(const FragArgs& a, int w) {
+        group = a.Hq / a.Hkv;
+        const int chunks = (group + 3) / 4;
+        c = w % chunks;
+        j = (w / chunks) % a.Hkv;
+        b = w / (chunks * a.Hkv);
+        len = seq_len(a.sm, b, a.S);
+        row0 = (size_t)seq_row0(a.sm, b, a.S);
+        rows = a.qkv + row0 * a.ld;
+        kcol = (a.Hq + j) * ROWS_D;
+        vcol = (a.Hq + a.Hkv + j) * ROWS_D;
+    }
+};
+
+__device__ __forceinline__ void rows_first(const FragArgs& a, int w, uint4* st) {
+    using T = AttnTile<ROWS_D>;
+    const RowsWork k(a, w);
+    if (k.len <= 0) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int u = 4 * k.c + wave, head = k.j * k.group + min(u, k.group - 1);
+    const int qi = lane & 31, h = lane >> 5, pos = min(qi, k.len - 1);
+
+    RowsQuery q;
+    const float* qrows = k.rows + head * ROWS_D;
+    q.request([&](int r) { return qrows + (unsigned)(min(r, k.len - 1) * a.ld); }, [&](int r) { return min(r, k.len - 1); }, a.cos_t, a.sin_t);
+    RowsBlock kv;
+    kv.request(k.rows, a.ld, k.kcol, k.vcol, 0, k.len, a.cos_t, a.sin_t);
+    __builtin_amdgcn_sched_barrier(0);
+    v8h qh[ROWS_KS], ql[ROWS_KS];
+    q.fragments(st + wave * (ROWS_STAGE / 2), a.qscale, qh, ql);
+    __syncthreads();
+    kv.commit(st);
+    __syncthreads();
+    if (u >= k.group) return;
+
+    v16f s = T::scores([&](int ks, int plane) { return __builtin_bit_cast(v8h, st[(ks * 2 + plane) * 64 + lane]); }, qh, ql);
+    float m_run = -INFINITY, l_run = 0.f;
+    v8h ph[2], pl[2];
+    T::softmax(s, m_run, l_run, true, lane, ph, pl);
+    const float inv = 1.0f / (l_run + __shfl_xor(l_run, 32, 64));
+    float* op = a.out + (k.row0 + pos) * ((size_t)a.Hq * ROWS_D) + (size_t)head * ROWS_D;
+#pragma unroll
+    for (int r = 0; r < T::DB; ++r) {
+        v16f o;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[v] = 0.f;
+        T::values([&](int t, int plane) { return __builtin_bit_cast(v8h, st[(ROWS_KS * 2 + (r * 2 + t) * 2 + plane) * 64 + lane]); }, ph, pl, o);
+        if (qi < k.len) store_columns(o, inv, op + 32 * r, h);
+    }
+}
+
+// both key blocks against the wavefront's unit, NB 32-column blocks of its result from r0 on
+template <int NB>
+__device__ __forceinline__ void rows_tail_unit(const uint4* stage, const v8h (&qh)[ROWS_KS], const v8h (&ql)[ROWS_KS], int at,
+                                               int r0, bool live, float* op) {
+    using T = AttnTile<ROWS_D>;
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    v16f o[NB];
+#pragma unroll
+    for (int r = 0; r < NB; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[r][v] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+        const uint4* st = stage + kb * ROWS_STAGE;
+        v16f s = T::scores([&](int ks, int plane) { return __builtin_bit_cast(v8h, st[(ks * 2 + plane) * 64 + lane]); }, qh, ql);
+        v8h ph[2], pl[2];
+        const float alpha = T::softmax(s, m_run, l_run, kb == 1, h * 32 + at, ph, pl);
+#pragma unroll
+        for (int r = 0; r < NB; ++r) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[r][v] *= alpha;
+            T::values([&](int t, int plane) { return __builtin_bit_cast(v8h, st[(ROWS_KS * 2 + ((r0 + r) * 2 + t) * 2 + plane) * 64 + lane]); }, ph, pl, o[r]);
+        }
+    }
+    const float inv = 1.0f / (l_run + __shfl_xor(l_run, 32, 64));
+    if (live) {
+#pragma unroll
+        for (int r = 0; r < NB; ++r) store_columns(o[r], inv, op + 32 * (r0 + r), h);
+    }
+}
+
+__device__ __forceinline__ void rows_tail(const FragArgs& a, int w, uint4* st) {
+    const RowsWork k(a, w);
+    const int n_tail = k.len - 32;
+    if (n_tail <= 0) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // queries: all rows of the first head, then the next head's; 1, 2 or (3 or) 4 units of 32, a wavefront's share of one
+    const int n_q = min(4, k.group - 4 * k.c) * n_tail;
+    const int shift = n_q <= 32 ? 2 : n_q <= 64 ? 1 : 0;                  // log2 of the wavefronts of a unit
+    const int q0 = (wave >> shift) * 32;
+    auto query = [&](int r) { return min(q0 + r, n_q - 1); };
+    auto head_of = [&](int qc) { return k.j * k.group + 4 * k.c + qc / n_tail; };
+    auto pos_of = [&](int qc) { return 32 + qc % n_tail; };
+
+    RowsQuery q;
+    q.request([&](int r) { return k.rows + (unsigned)(pos_of(query(r)) * a.ld) + head_of(query(r)) * ROWS_D; },
+              [&](int r) { return pos_of(query(r)); }, a.cos_t, a.sin_t);
+    RowsBlock kv0, kv1;
+    kv0.request(k.rows, a.ld, k.kcol, k.vcol, 0, k.len, a.cos_t, a.sin_t);
+    kv1.request(k.rows, a.ld, k.kcol, k.vcol, 1, k.len, a.cos_t, a.sin_t);
+    __builtin_amdgcn_sched_barrier(0);
+    v8h qh[ROWS_KS], ql[ROWS_KS];
+    q.fragments(st + wave * (ROWS_STAGE / 2), a.qscale, qh, ql);
+    __syncthreads();
+    kv0.commit(st);
+    kv1.commit(st + ROWS_STAGE);
+    __syncthreads();
+    if ((wave >> shift) * 32 >= n_q) return;
+    const int qc = query(lane & 31), pos = pos_of(qc);
+    const bool live = q0 + (lane & 31) < n_q;
+    float* op = a.out + (k.row0 + pos) * ((size_t)a.Hq * ROWS_D) + (size_t)head_of(qc) * ROWS_D;
+    if (shift == 2) rows_tail_unit<1>(st, qh, ql, pos - 32, wave, live, op);
+    else if (shift == 1) rows_tail_unit<2>(st, qh, ql, pos - 32, 2 * (wave & 1), live, op);
+    else rows_tail_unit<4>(st, qh, ql, pos - 32, 0, live, op);
+}
+
+template <bool TAIL>
+__global__ __launch_bounds__(256, 2) void attention_rows_kernel(FragArgs a) {
+    __shared__ __attribute__((aligned(1024))) uint4 st[2 * ROWS_STAGE];
+    if constexpr (TAIL) {
+        const int half = gridDim.x >> 1, w = (int)blockIdx.x;
+        if (w < half) rows_tail(a, w, st);
+        else rows_first(a, w - half, st);
+    } else {
+        rows_first(a, (int)blockIdx.x, st);
+    }
+}
+
 inline int padded_head_dim(int dh) { return dh <= 32 ? 32 : (dh <= 64 ? 64 : 128); }
 
 }  // namespace
@@ -595,23 +880,34 @@ size_t attention_mfma_ws_bytes(int B, int S, int n_heads, int n_kv_heads, int he
 
 namespace {
 
-// Which form states of one key block take.  N (HEAD): a workgroup per (state, query head), O (GROUP): per (state, four query
-// heads of one key/value head), P (PAIR): the pack and fragment kernels.  All give the same bits.  Times of 16 .. 2048 states in us:
-// - heads of up to 32: N; beyond 1024 query heads, where at least three of O's four wavefronts have a head, O (16 / 4 heads
+// Which form states of one key block take, and at heads of 128 states of two.  N (HEAD): a workgroup per (state, query head),
+// O (GROUP): per (state, four query heads of one key/value head), R (ROWS): likewise, q, k and v from the rows, P (PAIR): the
+// pack and fragment kernels.  All give the same bits.  Times of 1 .. 2048 states in us:
+// - heads of 128, one block: N up to 512 query heads and for groups of one, else R (20 / 5, 20 tokens, 16 states 10.1 / 10.9,
+//   32 states 13.3 / 11.5, 64 states 19.7 / 15.7, 1024 states 212 (P) / 151; 12 / 4, 32 tokens, 32 states 11.0 / 11.6, 48 states
+//   14.7 / 12.2; 16 / 8, 20 tokens, 64 states 17.2 / 15.1; 16 / 16, 20 tokens, 512 states 106 / 131).
+//   Two blocks: R (20 / 5, 15 .. 40 tokens, P / R: 1 state 16.9 / 11.2, 64 states 36 / 19, 1024 states 374 / 213; 64 tokens: 16
+//   states 23.1 / 15.5, 1024 states 499 / 446; 16 / 16, 64 tokens, 64 states 54 / 51; never behind in 120 of them) but P for
+//   workgroups half empty of which there are many (30 / 6, 64 tokens, 32 states 37.9 / 33.7, 64 states 52.7 / 58.2).
+// - up to 32: N; beyond 1024 query heads, where at least three of O's four wavefronts have a head, O (16 / 4 heads
 //   of 32, 32 tokens, 64 states 8.2 / 8.9, 256 states 17.4 / 15.0, 2048 states 121 / 84; 16 / 8: 17.2 / 18.6).
 // - up to 64: O where three of its four wavefronts have a head (16 / 4, 32 tokens, 1 state 8.7 / 8.6, 256 states 31 / 23 and
 //   P 28), P beyond 2048 workgroups where a group has more than one (32 / 4, 32 tokens, 384 states 55 / 51).  Groups of one,
 //   two and five: O up to one, four and four workgroups per compute unit, then N (16 / 16, 32 tokens, 4 states 8.8 / 8.2, 64
 //   states 11.9 / 14.7; 16 / 8, 32 tokens, 128 states 19.7 / 17.5, 8 tokens, 512 states 39 / 42; 30 / 6, 8 tokens, 64 states
 //   14.5 / 13.3, 256 states 37 / 42), of five P beyond 8192 query heads (8 tokens, 1024 states 127 / 110).
-// - up to 128: N; O where N has more than three workgroups per compute unit but O, with three of four wavefronts busy, at
-//   most one (20 / 5, 32 tokens, 48 states 19.1 / 16.4; 56 states 21.3 / 25.7); P for full groups of many states (20 / 5,
-//   32 tokens, 512 states 136.5 / 133.5, 2048 states 532 / 486; 32 / 4, 128 states 51 / 43; 30 / 6 never: 512 states 197 / 241).
-enum class ShortForm { HEAD, GROUP, PAIR };
-ShortForm short_form(int dhp, int B, int Hq, int Hkv) {
+// - between 64 and 128 (100): N; O where N has more than three workgroups per compute unit but O, with three of four
+//   wavefronts busy, at most one; P for full groups of many states.  (The lines are those that heads of 128 had before R:
+//   20 / 5, 32 tokens, 48 states 19.1 / 16.4; 56 states 21.3 / 25.7; 512 states N 136.5 / P 133.5, 2048 states 532 / 486.)
+enum class ShortForm { HEAD, GROUP, ROWS, PAIR };
+ShortForm short_form(int dh, int nrb, int B, int Hq, int Hkv) {
     constexpr long CUS = 256;
+    const int dhp = padded_head_dim(dh);
     const long group = Hq / Hkv, chunks = (group + 3) / 4, heads = (long)B * Hq, work = (long)B * Hkv * chunks;
     const bool three_of_four = group >= 3 * chunks, full = 2 * group >= 7 * chunks;
+    if (dh == ROWS_D && nrb == 2) return group > 4 && !three_of_four && work > 2 * CUS ? ShortForm::PAIR : ShortForm::ROWS;
+    if (nrb > 1) return ShortForm::PAIR;
+    if (dh == ROWS_D) return group > 1 && heads > 2 * CUS ? ShortForm::ROWS : ShortForm::HEAD;
     if (dhp == 32) return three_of_four && heads > 4 * CUS ? ShortForm::GROUP : ShortForm::HEAD;
     if (dhp == 64) {
         if (!three_of_four) {
@@ -627,12 +923,19 @@ ShortForm short_form(int dhp, int B, int Hq, int Hkv) {
 
 template <int DHP, int VW>
 void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, hipStream_t s) {
-    const ShortForm form = p.NRB == 1 ? short_form(DHP, f.B, f.Hq, f.Hkv) : ShortForm::PAIR;
+    const ShortForm form = short_form(f.dh, p.NRB, f.B, f.Hq, f.Hkv);
     if (form == ShortForm::HEAD) {
         hipLaunchKernelGGL((attention_short_kernel<DHP, VW>), dim3((unsigned)(f.B * f.Hq)), dim3(DHP * 4), 0, s, f);
         return;
     }
-    if (form == ShortForm::GROUP) {                       // (NRB is 1: n_work counts the same workgroups)
+    if constexpr (DHP == ROWS_D && VW == 4) {             // heads of 128: never a workgroup per group
+        if (form == ShortForm::ROWS) {
+            const unsigned work = (unsigned)(f.B * f.Hkv * ((f.Hq / f.Hkv + 3) / 4));
+            if (p.NRB == 2) hipLaunchKernelGGL(attention_rows_kernel<true>, dim3(2 * work), dim3(256), 0, s, f);
+            else hipLaunchKernelGGL(attention_rows_kernel<false>, dim3(work), dim3(256), 0, s, f);
+            return;
+        }
+    } else if (form == ShortForm::GROUP) {                // (NRB is 1: n_work counts the same workgroups)
         hipLaunchKernelGGL((attention_group_kernel<DHP, VW>), dim3((unsigned)n_work), dim3(512), 0, s, f);
         return;
     }

@@ -1,9 +1,10 @@
 """GPU parity of the attention stage by itself: attention_forward (the kernels encoder_forward runs on
 the output of its q | k | v BitLinear) against the oracle's causal_gqa_attention, element by element.
 
-Four forms sit behind the entry point and every one is reached here in both layouts: attention_f32_kernel
-(BRL_ATTN_F32), attn_pack_kernel + attention_frag_kernel (BRL_ATTN_MFMA) and, for states of at most 32 tokens,
-attention_short_kernel (a workgroup per query head) and attention_group_kernel (per four of them).
+Five forms sit behind the entry point and every one is reached here in both layouts: attention_f32_kernel
+(BRL_ATTN_F32), attn_pack_kernel + attention_frag_kernel (BRL_ATTN_MFMA), for states of at most 32 tokens
+attention_short_kernel (a workgroup per query head) and attention_group_kernel (per four of them), and for heads of
+128 and states of at most 64 tokens attention_rows_kernel.
 
 Bound.  The oracle works in fp64 and rounds once.  The fp32 kernel accumulates dot products of
 head_dim terms and the softmax sums in fp32; the matrix-core kernels carry every operand as an fp16
@@ -222,3 +223,32 @@ def test_short_state_forms_give_the_same_bits(hq, hkv, dh, batches):
                     ref = _oracle(qkv[r0:r0 + lens[i]], lens[i:i + 1], hq, hkv, dh, 10000.0)[0]
                     assert np.abs(got[r0:r0 + lens[i]].reshape(ref.shape) - ref).max() <= ATTN_REL * np.abs(ref).max()
             assert np.array_equal(got, want[:rows]), b
+
+
+@pytest.mark.parametrize("hq,hkv,longest,batches", [
+    (20, 5, 64, (1, 70)), (12, 4, 64, (9,)), (16, 16, 64, (7, 70)),       # full groups, three of four, one head
+    (7, 1, 64, (66,)), (30, 6, 64, (42, 43)),                             # last wavefront idle; groups of five: rows | pair
+    (8, 2, 33, (5,)), (8, 2, 63, (64,)),
+    (20, 5, 32, (25, 26)), (16, 8, 32, (32, 33)), (5, 1, 32, (102, 103)),  # one key block: query head | rows
+    (16, 16, 32, (32, 33)),                                               # groups of one: query head
+])
+def test_states_of_two_key_blocks_give_the_bits_of_the_pair(hq, hkv, longest, batches):
+    """Heads of 128, every state length up to two key blocks: a larger bound on the lengths (three key blocks, which run
+    the pack and fragment kernels) changes no bit, a larger batch none of the states it shares, and single states match
+    the oracle."""
+    B, R = _mods()
+    n, dh = batches[-1], 128
+    for lens in ([1 + (27 * i + longest - 1) % longest for i in range(n)], [longest - 1] * n, [longest] * n):
+        uniform = lens[0] if len(set(lens)) == 1 else None
+        qkv = synth.normal(43, 5, (sum(lens), (hq + 2 * hkv) * dh))
+        print("two key blocks", hq, hkv, n, "uniform" if uniform else "ragged", longest, flush=True)
+        want = _run(B, R, qkv, lens, None, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA, max_len=96)
+        assert np.all(np.isfinite(want))
+        for b in batches:
+            rows = sum(lens[:b])
+            got = _run(B, R, qkv[:rows], lens[:b], uniform, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA, max_len=None if uniform else longest)
+            assert np.array_equal(got, want[:rows]), b
+        for i in (0, n - 1):
+            r0 = sum(lens[:i])
+            ref = _oracle(qkv[r0:r0 + lens[i]], lens[i:i + 1], hq, hkv, dh, 10000.0)[0]
+            assert np.abs(want[r0:r0 + lens[i]].reshape(ref.shape) - ref).max() <= ATTN_REL * np.abs(ref).max()
