@@ -64,6 +64,20 @@ __device__ __forceinline__ float rounded(float x) {
     return x;
 }
 
+// fp16 hi and lo of two values.  x - hi is exact in fp32, so the mixed-precision multiply-add (x * 1 - hi, fp16 operand and
+// result) rounds once, as subtraction and conversion would: two instructions for a pair of low parts instead of five.
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+    typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+    v2h h = {(_Float16)x0, (_Float16)x1};
+    hi = __builtin_bit_cast(uint32_t, h);
+    float one = 1.0f;                                // (opaque: a literal would turn the multiply-add back into a subtraction;
+    asm("" : "+s"(one));                             // likewise the pair, into two more conversions)
+    asm("" : "+v"(hi));
+    h = __builtin_bit_cast(v2h, hi);
+    const v2h l = {(_Float16)__builtin_fmaf(x0, one, -(float)h[0]), (_Float16)__builtin_fmaf(x1, one, -(float)h[1])};
+    lo = __builtin_bit_cast(uint32_t, l);
+}
+
 template <int VW> struct VecOf;
 template <> struct VecOf<4> { typedef float4 type; };
 template <> struct VecOf<2> { typedef float2 type; };
@@ -226,13 +240,14 @@ struct AttnTile {
     }
 
     // running softmax: probabilities of the block as fp16 hi / lo, returns the factor of what was accumulated before
-    static __device__ __forceinline__ float softmax(v16f& s, float& m_run, float& l_run, bool diagonal, int lane, v8h (&ph)[2], v8h (&pl)[2]) {
+    template <bool DIAG>
+    static __device__ __forceinline__ float softmax(v16f& s, float& m_run, float& l_run, int lane, v8h (&ph)[2], v8h (&pl)[2]) {
         const int qi = lane & 31, h = lane >> 5;
         float bmax = -INFINITY;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int key = 8 * (v >> 2) + 4 * h + (v & 3);     // position inside the block
-            if (diagonal && key > qi) s[v] = -INFINITY;         // causal: keys of later blocks are never visited
+            if (DIAG && key > qi) s[v] = -INFINITY;             // causal: keys of later blocks are never visited
             bmax = fmaxf(bmax, s[v]);
         }
         bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
@@ -240,12 +255,17 @@ struct AttnTile {
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         float psum = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float pv = __builtin_amdgcn_exp2f(s[v] - m_new);
-            psum += pv;
-            const _Float16 hi = (_Float16)pv;
-            ph[v >> 3][v & 7] = hi;
-            pl[v >> 3][v & 7] = (_Float16)(pv - (float)hi);
+        for (int t = 0; t < 2; ++t) {
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                const float p0 = __builtin_amdgcn_exp2f(s[8 * t + e] - m_new), p1 = __builtin_amdgcn_exp2f(s[8 * t + e + 1] - m_new);
+                psum += p0;
+                psum += p1;
+                split_pair(p0, p1, hi[e / 2], lo[e / 2]);
+            }
+            ph[t] = __builtin_bit_cast(v8h, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+            pl[t] = __builtin_bit_cast(v8h, make_uint4(lo[0], lo[1], lo[2], lo[3]));
         }
         l_run = l_run * alpha + psum;
         m_run = m_new;
@@ -265,11 +285,21 @@ struct AttnTile {
     }
 
     // one staged block of 32 keys against the wavefront's 32 queries
+    template <bool DIAG>
     static __device__ __forceinline__ void compute(const uint4* st, const v8h (&qh)[KS], const v8h (&ql)[KS], v16f (&o)[DB],
-                                          float& m_run, float& l_run, bool diagonal, int lane) {
+                                          float& m_run, float& l_run, int lane) {
         v16f s = scores([&](int ks, int plane) { return __builtin_bit_cast(v8h, st[(ks * 2 + plane) * 64 + lane]); }, qh, ql);
+        // the key fragments two steps ahead of their products: left to itself the compiler reads each one right before its
+        // use, a trip to LDS per product
+        __builtin_amdgcn_sched_group_barrier(SCHED_LDS_READ, 4, 0);
+#pragma unroll
+        for (int ks = 2; ks < KS; ++ks) {
+            __builtin_amdgcn_sched_group_barrier(SCHED_MFMA, 3, 0);
+            __builtin_amdgcn_sched_group_barrier(SCHED_LDS_READ, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(SCHED_MFMA, 6, 0);
         v8h ph[2], pl[2];
-        const float alpha = softmax(s, m_run, l_run, diagonal, lane, ph, pl);
+        const float alpha = softmax<DIAG>(s, m_run, l_run, lane, ph, pl);
 #pragma unroll
         for (int r = 0; r < DB; ++r) {
 #pragma unroll
@@ -277,6 +307,7 @@ struct AttnTile {
             values([&](int t, int plane) { return __builtin_bit_cast(v8h, st[(KS * 2 + (r * 2 + t) * 2 + plane) * 64 + lane]); }, ph, pl, o[r]);
         }
     }
+    static constexpr int SCHED_MFMA = 0x8, SCHED_LDS_READ = 0x100;
 };
 
 // WPG wavefronts (a multiple of 4) = WPG units of one key/value head share every K / V block.
@@ -292,7 +323,7 @@ __global__ __launch_bounds__(WPG * 64, 2) void attention_frag_kernel(FragArgs a)
     __shared__ __attribute__((aligned(1024))) uint4 stage0[T::KVFR * 64];
     __shared__ __attribute__((aligned(1024))) uint4 stage1[T::KVFR * 64];
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int group = a.Hq / a.Hkv;
     const int U = group * a.NRB;                      // (query block, head in group) units of one key/value head
     const int chunks = (U + WPG - 1) / WPG;
@@ -359,21 +390,25 @@ __global__ __launch_bounds__(WPG * 64, 2) void attention_frag_kernel(FragArgs a)
 
     const uint4* kv = a.KVF + (size_t)(b * a.Hkv + j) * a.NRB * T::KVFR * 64;
     T::template issue<WPG>(kv, stage0, wave, lane);
+    auto block = [&](const uint4* st, int kb) {
+        if (kb < qb) T::template compute<false>(st, qh, ql, o, m_run, l_run, lane);
+        else if (kb == qb) T::template compute<true>(st, qh, ql, o, m_run, l_run, lane);
+    };
     int kb = 0;
     for (; kb + 1 <= kb_max; kb += 2) {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         T::template issue<WPG>(kv + (size_t)(kb + 1) * T::KVFR * 64, stage1, wave, lane);
-        if (kb <= qb) T::compute(stage0, qh, ql, o, m_run, l_run, kb == qb, lane);
+        block(stage0, kb);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (kb + 2 <= kb_max) T::template issue<WPG>(kv + (size_t)(kb + 2) * T::KVFR * 64, stage0, wave, lane);
-        if (kb + 1 <= qb) T::compute(stage1, qh, ql, o, m_run, l_run, kb + 1 == qb, lane);
+        block(stage1, kb + 1);
     }
     if (kb <= kb_max) {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        if (kb <= qb) T::compute(stage0, qh, ql, o, m_run, l_run, kb == qb, lane);
+        block(stage0, kb);
     }
 
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
@@ -453,7 +488,7 @@ __global__ __launch_bounds__(DHP * 4) void attention_short_kernel(FragArgs a) {
     v16f s = T::scores([&](int ks, int plane) { return __builtin_bit_cast(v8h, staged_fragment<DHP>(kpark, ks, lane, plane)); }, qh, ql);
     float m_run = -INFINITY, l_run = 0.f;
     v8h ph[2], pl[2];
-    T::softmax(s, m_run, l_run, true, lane, ph, pl);
+    T::template softmax<true>(s, m_run, l_run, lane, ph, pl);
     v16f o;
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[v] = 0.f;
@@ -566,7 +601,7 @@ __global__ __launch_bounds__(512) void attention_group_kernel(FragArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[r][v] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
-    T::compute(kvst, qh, ql, o, m_run, l_run, true, lane);
+    T::template compute<true>(kvst, qh, ql, o, m_run, l_run, lane);
 
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
     const int pos = lane & 31;
@@ -775,7 +810,7 @@ __device__ __forceinline__ void rows_first(const FragArgs& a, int w, uint4* st) 
     v16f s = T::scores([&](int ks, int plane) { return __builtin_bit_cast(v8h, st[(ks * 2 + plane) * 64 + lane]); }, qh, ql);
     float m_run = -INFINITY, l_run = 0.f;
     v8h ph[2], pl[2];
-    T::softmax(s, m_run, l_run, true, lane, ph, pl);
+    T::template softmax<true>(s, m_run, l_run, lane, ph, pl);
     const float inv = 1.0f / (l_run + __shfl_xor(l_run, 32, 64));
     float* op = a.out + (k.row0 + pos) * ((size_t)a.Hq * ROWS_D) + (size_t)head * ROWS_D;
 #pragma unroll
@@ -805,7 +840,8 @@ __device__ __forceinline__ void rows_tail_unit(const uint4* stage, const v8h (&q
         const uint4* st = stage + kb * ROWS_STAGE;
         v16f s = T::scores([&](int ks, int plane) { return __builtin_bit_cast(v8h, st[(ks * 2 + plane) * 64 + lane]); }, qh, ql);
         v8h ph[2], pl[2];
-        const float alpha = T::softmax(s, m_run, l_run, kb == 1, h * 32 + at, ph, pl);
+        const float alpha = kb ? T::template softmax<true>(s, m_run, l_run, h * 32 + at, ph, pl)
+                               : T::template softmax<false>(s, m_run, l_run, h * 32 + at, ph, pl);
 #pragma unroll
         for (int r = 0; r < NB; ++r) {
 #pragma unroll
