@@ -78,6 +78,10 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
     lo = __builtin_bit_cast(uint32_t, l);
 }
 
+// k-steps of 16 components of a score.  Heads of 100 (the only ones whose rotary halves are not whole quads) end in the seventh:
+// the eighth would multiply zeros.
+template <int DHP, int VW> constexpr int k_steps = DHP == 128 && VW == 2 ? 7 : DHP / 16;
+
 template <int VW> struct VecOf;
 template <> struct VecOf<4> { typedef float4 type; };
 template <> struct VecOf<2> { typedef float2 type; };
@@ -215,13 +219,18 @@ struct QueryRows {
 
 template <int DHP, int VW>
 __global__ __launch_bounds__(256) void attn_pack_kernel(PackArgs a) {
-    constexpr int KS = DHP / 16, DB = DHP / 32;
+    constexpr int KS = k_steps<DHP, VW>, DB = DHP / 32;
     constexpr int KVFR = KS * 2 + DB * 4;             // 1 KB fragments per key block
     __shared__ __attribute__((aligned(16))) char park[128 * DHP];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int hd = blockIdx.x % a.Hkv;
-    const int rb = (blockIdx.x / a.Hkv) % a.NRB;
-    const int b = blockIdx.x / (a.Hkv * a.NRB);
+    // neighbouring heads on one XCD: their rows share lines where a head is no whole number of them (heads of 100: 1.09 GB
+    // fetched for 0.84 in the order of the workgroups; 398 -> 383 us for 64 states of 512 tokens)
+    const int n_work = a.B * a.NRB * a.Hkv, per_xcd = (n_work + 7) >> 3;
+    const int w = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (w >= n_work) return;
+    const int hd = w % a.Hkv;
+    const int rb = (w / a.Hkv) % a.NRB;
+    const int b = w / (a.Hkv * a.NRB);
     const int half = a.dh / 2;
     const int dq = a.Hq * a.dh, dkv = a.Hkv * a.dh;
     const int n_valid = min(32, seq_len(a.sm, b, a.S) - rb * 32);
@@ -235,8 +244,9 @@ __global__ __launch_bounds__(256) void attn_pack_kernel(PackArgs a) {
                                       a.sin_t + (size_t)rb * 32 * half, a.dh, 1.0f, park, lane, wave * (ITS / 4));
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < KS / 2; ++q) {
-        const int fr = wave * (KS / 2) + q;           // fragment = (k-step, plane)
+    for (int q = 0; q < (KS + 1) / 2; ++q) {
+        const int fr = q * 4 + wave;                  // fragment = (k-step, plane)
+        if (KS % 2 && fr >= 2 * KS) break;
         dst[fr * 64 + lane] = staged_fragment<DHP>(park, fr >> 1, lane, fr & 1);
     }
     // v head, transposed: lane (d, h) of (block r, step t) holds the keys 16 t + 8 (e >> 2) + 4 h + (e & 3)
@@ -270,18 +280,18 @@ struct FragArgs {
     float* out;           // [B*S, Hq*dh]
 };
 
-template <int DHP>
+template <int DHP, int VW>
 struct AttnTile {
-    static constexpr int KS = DHP / 16, DB = DHP / 32;
+    static constexpr int KS = k_steps<DHP, VW>, DB = DHP / 32;
     static constexpr int KVFR = KS * 2 + DB * 4;      // 1 KB fragments per key block (K hi/lo, then V hi/lo)
+    static constexpr int STAGE = (KVFR > DHP / 4 ? KVFR : DHP / 4) * 64;      // a block, or two wavefronts' parked queries
     // the WPG wavefronts of a workgroup copy KVFR / WPG fragments each
     template <int WPG>
     static __device__ inline void issue(const uint4* src, uint4* st, int wave, int lane) {
-        static_assert(KVFR % WPG == 0, "fragments divide evenly over the wavefronts");
 #pragma unroll
-        for (int c = 0; c < KVFR / WPG; ++c) {
+        for (int c = 0; c < (KVFR + WPG - 1) / WPG; ++c) {
             const int f = c * WPG + wave;
-            __builtin_amdgcn_global_load_lds(src + f * 64 + lane, st + f * 64, 16, 0, 0);
+            if (KVFR % WPG == 0 || f < KVFR) __builtin_amdgcn_global_load_lds(src + f * 64 + lane, st + f * 64, 16, 0, 0);
         }
     }
 
@@ -380,10 +390,10 @@ constexpr int ATTN_WPG = 4;
 // straight into the operand registers; otherwise they are staged from the fp32 rows here.
 template <int DHP, int VW, int WPG, bool QPRE = false>
 __global__ __launch_bounds__(WPG * 64, 2) void attention_frag_kernel(FragArgs a) {
-    using T = AttnTile<DHP>;
+    using T = AttnTile<DHP, VW>;
     constexpr int KS = T::KS, DB = T::DB;
-    __shared__ __attribute__((aligned(1024))) uint4 stage0[T::KVFR * 64];
-    __shared__ __attribute__((aligned(1024))) uint4 stage1[T::KVFR * 64];
+    __shared__ __attribute__((aligned(1024))) uint4 stage0[T::STAGE];
+    __shared__ __attribute__((aligned(1024))) uint4 stage1[T::STAGE];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int group = a.Hq / a.Hkv;
@@ -505,7 +515,7 @@ __global__ __launch_bounds__(WPG * 64, 2) void attention_frag_kernel(FragArgs a)
 // Same MFMAs in the same order as the general kernel: same bits.
 template <int DHP, int VW>
 __global__ __launch_bounds__(DHP * 4) void attention_short_kernel(FragArgs a) {
-    using T = AttnTile<DHP>;
+    using T = AttnTile<DHP, VW>;
     constexpr int KS = T::KS, DB = T::DB;                 // 2 DB wavefronts
     constexpr int REG = 128 * DHP;                        // bytes of one staged 32-row block (hi and lo planes)
     __shared__ __attribute__((aligned(1024))) char qpark[REG];
@@ -583,7 +593,7 @@ __global__ __launch_bounds__(DHP * 4) void attention_short_kernel(FragArgs a) {
 // general kernel: same bits.  Where each form runs and what it measured: short_form below.
 template <int DHP, int VW>
 __global__ __launch_bounds__(512) void attention_group_kernel(FragArgs a) {
-    using T = AttnTile<DHP>;
+    using T = AttnTile<DHP, VW>;
     constexpr int KS = T::KS, DB = T::DB;
     constexpr int REG = 128 * DHP;                        // bytes of one staged 32-row block (hi and lo planes)
     __shared__ __attribute__((aligned(1024))) char qpark[4 * REG];
@@ -642,8 +652,9 @@ __global__ __launch_bounds__(512) void attention_group_kernel(FragArgs a) {
         }
     } else {
 #pragma unroll
-        for (int q = 0; q < KS / 2; ++q) {
-            const int fr = (wave - 4) * (KS / 2) + q;     // fragment = (k-step, plane)
+        for (int q = 0; q < (KS + 1) / 2; ++q) {
+            const int fr = q * 4 + wave - 4;              // fragment = (k-step, plane)
+            if (KS % 2 && fr >= 2 * KS) break;
             kvst[fr * 64 + lane] = staged_fragment<DHP>(kpark, fr >> 1, lane, fr & 1);
         }
 #pragma unroll
@@ -699,8 +710,8 @@ __global__ __launch_bounds__(512) void attention_group_kernel(FragArgs a) {
 // wavefronts that have no unit.  The arithmetic per element and its order are those of the pair: same bits.
 // 1024 states of 15 .. 40 tokens, 20 / 5 heads: pack 80 + fragments 309 us, 213 here (725 MB once; 225 with q read in operand
 // order, 236 as two launches); 64 states 36 -> 19, 1 state 17 -> 11.  What other sizes take: short_form below.
-constexpr int ROWS_D = 128, ROWS_KS = AttnTile<ROWS_D>::KS;
-constexpr int ROWS_STAGE = AttnTile<ROWS_D>::KVFR * 64;
+constexpr int ROWS_D = 128, ROWS_KS = AttnTile<ROWS_D, 4>::KS;
+constexpr int ROWS_STAGE = AttnTile<ROWS_D, 4>::KVFR * 64;
 struct RowsBlock {                                    // what a thread of 256 stages of a key block
     float4 k[4], c[2], s[2];                          // eight components of a k row and their eight partners; rotary factors
     float v[2][8];
@@ -852,7 +863,7 @@ struct RowsWork {
 };
 
 __device__ __forceinline__ void rows_first(const FragArgs& a, int w, uint4* st) {
-    using T = AttnTile<ROWS_D>;
+    using T = AttnTile<ROWS_D, 4>;
     const RowsWork k(a, w);
     if (k.len <= 0) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -892,7 +903,7 @@ __device__ __forceinline__ void rows_first(const FragArgs& a, int w, uint4* st) 
 template <int NB>
 __device__ __forceinline__ void rows_tail_unit(const uint4* stage, const v8h (&qh)[ROWS_KS], const v8h (&ql)[ROWS_KS], int at,
                                                int r0, bool live, float* op) {
-    using T = AttnTile<ROWS_D>;
+    using T = AttnTile<ROWS_D, 4>;
     const int lane = threadIdx.x & 63, h = lane >> 5;
     v16f o[NB];
 #pragma unroll
@@ -1070,7 +1081,7 @@ int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& 
     f.sm = sm;
     f.n_work = B * n_kv_heads * chunks;
     f.out = out;
-    const dim3 pgrid((unsigned)((size_t)B * nrb * n_kv_heads));
+    const dim3 pgrid((unsigned)(8 * (((size_t)B * nrb * n_kv_heads + 7) / 8)));
     const bool v4 = (head_dim / 2) % 4 == 0;          // rotary halves and head rows 16-byte aligned
     LaunchTimer tm(BRL_KC_ATTENTION, s);
     if (dhp == 32) {
