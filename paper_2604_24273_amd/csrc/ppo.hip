@@ -6,7 +6,8 @@
 // gradients at their outputs, back-propagation, one global gradient-norm clip and an Adam step.
 // The products are tiny (64 x 2560 x 256), so a step is latency: it is laid out as four kernels
 // (first layer of both heads; everything between the first layer's outputs and its deltas, one
-// workgroup per sample; all weight gradients; gradient norm and Adam), the two large contractions
+// workgroup per sample; all weight gradients; gradient norm and Adam), of which the last takes the
+// next step's first along where it can, the two large contractions
 // on the fp64 matrix cores, every sum in fp64 in a fixed order: results do not depend on scheduling.
 // Parameters and optimiser state are fp32 in one flat buffer each (policy W_1, b_1, ..., W_L, b_L,
 // then the value head likewise); activations, deltas and gradients of a step live in fp64 scratch.
@@ -146,17 +147,19 @@ struct FirstArgs {
     double* scal;                    // [0] mean, [1] 1 / (deviation + eps)
 };
 
+// by the first 256 threads of a workgroup (the others keep step)
 __device__ void minibatch_scale(const float* adv, const int32_t* rows, int B, int T, double eps, int normalize, double* scal) {
     __shared__ double red[256];
     if (!normalize) {
         if (threadIdx.x == 0) { scal[0] = 0.0; scal[1] = 1.0; }
         return;
     }
+    const int tid = (int)threadIdx.x, first = tid < 256 ? tid : B;
     auto total = [&](double part) {                      // fixed tree
-        red[threadIdx.x] = part;
+        if (tid < 256) red[tid] = part;
         __syncthreads();
         for (int st = 128; st >= 1; st >>= 1) {
-            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+            if (tid < st) red[tid] += red[tid + st];
             __syncthreads();
         }
         const double r = red[0];
@@ -164,10 +167,10 @@ __device__ void minibatch_scale(const float* adv, const int32_t* rows, int B, in
         return r;
     };
     double part = 0.0;
-    for (int b = threadIdx.x; b < B; b += 256) part += (double)adv[clamp_index(rows[b], T)];
+    for (int b = first; b < B; b += 256) part += (double)adv[clamp_index(rows[b], T)];
     const double mean = total(part) / (double)B;
     part = 0.0;
-    for (int b = threadIdx.x; b < B; b += 256) {
+    for (int b = first; b < B; b += 256) {
         const double d = (double)adv[clamp_index(rows[b], T)] - mean;
         part += d * d;
     }
@@ -728,79 +731,255 @@ __global__ __launch_bounds__(NORM_THREADS) void ppo_norm_kernel(const double* __
     }
 }
 
-__global__ __launch_bounds__(256) void ppo_adam_kernel(AdamArgs a) {
-    __shared__ double red[256];
-    const size_t i0 = ((size_t)blockIdx.x * 256 + threadIdx.x) * ADAM_PER_THREAD;
-    // the elements are requested ahead of the norm; the buffers may start at any element, so the accesses ask for no more
-    const bool full = i0 + ADAM_PER_THREAD <= a.n;
+// min(1, max_norm / (norm + 1e-6)) from the partial sums, by a whole workgroup; the norm itself to `norm`.  The
+// order of the sum is that of 256 threads whatever the workgroup's size.
+template <int NT>
+__device__ inline double adam_scale(const AdamArgs& a, double (&red)[NT], double& norm) {
+    const int tid = (int)threadIdx.x;
+    double s = 0.0;
+    if (tid < 256) {
+        for (int i0p = 0; i0p < a.n_partials; i0p += 256 * 8) {      // eight of a thread's partial sums in flight
+            double t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = a.partial[min(i0p + u * 256 + tid, a.n_partials - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += i0p + u * 256 + tid < a.n_partials ? t[u] : 0.0;
+        }
+        red[tid] = s;
+    }
+    __syncthreads();
+    // ((t + 128) first, then the pair's 64: the tree of a halving reduction)
+    const int l = tid & 63;
+    norm = sqrt(wave_sum((red[l] + red[l + 128]) + (red[l + 64] + red[l + 192])));
+    return fmin(1.0, a.max_norm / (norm + 1e-6));
+}
+
+__device__ inline void adam_element(const AdamArgs& a, double scale, double step, double g, float& p, float& m, float& v) {
+    const double gi = g * scale;
+    const double mi = a.b1 * (double)m + (1.0 - a.b1) * gi;
+    const double vi = a.b2 * (double)v + (1.0 - a.b2) * gi * gi;
+    m = (float)mi;
+    v = (float)vi;
+    p = (float)((double)p - step * mi / (sqrt(vi * a.inv_c2) + a.eps));
+}
+
+// four neighbouring parameters with their state and gradients; the buffers may start at any element, so the accesses ask
+// for no more.  n: how many of the four there are (the others are neither read nor written).
+struct AdamQuad {
     float p[4], m[4], v[4];
     double g[4];
-    if (full) {
-        const v4f_u pv = *reinterpret_cast<const v4f_u*>(a.p + i0), mv = *reinterpret_cast<const v4f_u*>(a.m + i0);
-        const v4f_u vv = *reinterpret_cast<const v4f_u*>(a.v + i0);
-        const v2d_u g0 = *reinterpret_cast<const v2d_u*>(a.g + i0), g1 = *reinterpret_cast<const v2d_u*>(a.g + i0 + 2);
+    __device__ __forceinline__ void load_all(const AdamArgs& a, size_t i) {
+        const v4f_u pv = *reinterpret_cast<const v4f_u*>(a.p + i), mv = *reinterpret_cast<const v4f_u*>(a.m + i);
+        const v4f_u vv = *reinterpret_cast<const v4f_u*>(a.v + i);
+        const v2d_u g0 = *reinterpret_cast<const v2d_u*>(a.g + i), g1 = *reinterpret_cast<const v2d_u*>(a.g + i + 2);
         p[0] = pv.x; p[1] = pv.y; p[2] = pv.z; p[3] = pv.w;
         m[0] = mv.x; m[1] = mv.y; m[2] = mv.z; m[3] = mv.w;
         v[0] = vv.x; v[1] = vv.y; v[2] = vv.z; v[3] = vv.w;
         g[0] = g0.x; g[1] = g0.y; g[2] = g1.x; g[3] = g1.y;
-    } else {
+    }
+    __device__ __forceinline__ void load(const AdamArgs& a, size_t i, int n) {
+        if (n >= 4) { load_all(a, i); return; }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const bool in = i0 + e < a.n;
-            p[e] = in ? a.p[i0 + e] : 0.f; m[e] = in ? a.m[i0 + e] : 0.f; v[e] = in ? a.v[i0 + e] : 0.f;
-            g[e] = in ? a.g[i0 + e] : 0.0;
+            const bool in = e < n;
+            p[e] = in ? a.p[i + e] : 0.f; m[e] = in ? a.m[i + e] : 0.f; v[e] = in ? a.v[i + e] : 0.f;
+            g[e] = in ? a.g[i + e] : 0.0;
         }
     }
-    double s = 0.0;
-    for (int i0p = 0; i0p < a.n_partials; i0p += 256 * 8) {          // eight of a thread's partial sums in flight
-        double t[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = a.partial[min(i0p + u * 256 + (int)threadIdx.x, a.n_partials - 1)];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += i0p + u * 256 + (int)threadIdx.x < a.n_partials ? t[u] : 0.0;
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int st = 128; st >= 64; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    const double norm = sqrt(wave_sum(red[threadIdx.x & 63]));
-    const double scale = fmin(1.0, a.max_norm / (norm + 1e-6));
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const double gi = g[e] * scale;
-        const double mi = a.b1 * (double)m[e] + (1.0 - a.b1) * gi;
-        const double vi = a.b2 * (double)v[e] + (1.0 - a.b2) * gi * gi;
-        m[e] = (float)mi;
-        v[e] = (float)vi;
-        const double step = i0 + e < a.n_policy ? a.step_policy : a.step_value;
-        p[e] = (float)((double)p[e] - step * mi / (sqrt(vi * a.inv_c2) + a.eps));
-    }
-    if (full) {
-        *reinterpret_cast<v4f_u*>(a.p + i0) = v4f_u{p[0], p[1], p[2], p[3]};
-        *reinterpret_cast<v4f_u*>(a.m + i0) = v4f_u{m[0], m[1], m[2], m[3]};
-        *reinterpret_cast<v4f_u*>(a.v + i0) = v4f_u{v[0], v[1], v[2], v[3]};
-    } else {
+    __device__ __forceinline__ void store(const AdamArgs& a, size_t i, int n) const {
+        if (n >= 4) {
+            *reinterpret_cast<v4f_u*>(a.p + i) = v4f_u{p[0], p[1], p[2], p[3]};
+            *reinterpret_cast<v4f_u*>(a.m + i) = v4f_u{m[0], m[1], m[2], m[3]};
+            *reinterpret_cast<v4f_u*>(a.v + i) = v4f_u{v[0], v[1], v[2], v[3]};
+            return;
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (i0 + e < a.n) { a.p[i0 + e] = p[e]; a.m[i0 + e] = m[e]; a.v[i0 + e] = v[e]; }
+            if (e < n) { a.p[i + e] = p[e]; a.m[i + e] = m[e]; a.v[i + e] = v[e]; }
     }
-    if (blockIdx.x == 0 && a.stats && threadIdx.x < 64) {
-        double t[4];
+};
+
+// the five statistics of an update, by one wavefront
+__device__ inline void adam_stats(const AdamArgs& a, double norm) {
+    double t[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            double x = 0.0;
-            for (int b = threadIdx.x; b < a.B; b += 64) x += a.row_terms[(size_t)k * a.B + b];
-            t[k] = wave_sum(x);
+    for (int k = 0; k < 4; ++k) {
+        double x = 0.0;
+        for (int b = threadIdx.x; b < a.B; b += 64) x += a.row_terms[(size_t)k * a.B + b];
+        t[k] = wave_sum(x);
+    }
+    if (threadIdx.x == 0) {
+        const double n = (double)a.B;
+        a.stats[0] = (float)(-t[0] / n - a.ent_coef * t[1] / n);
+        a.stats[1] = (float)(0.5 * t[2] / n);
+        a.stats[2] = (float)(t[1] / n);
+        a.stats[3] = (float)(t[3] / n);
+        a.stats[4] = (float)norm;
+    }
+}
+
+// four parameters a thread, by a whole workgroup; returns the norm
+template <int NT>
+__device__ inline double adam_quad(const AdamArgs& a, size_t i0, int n, const double (&step)[4], double (&red)[NT]) {
+    AdamQuad q;                                      // requested ahead of the norm
+    q.load(a, i0, n);
+    double norm;
+    const double scale = adam_scale(a, red, norm);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) adam_element(a, scale, step[e], q.g[e], q.p[e], q.m[e], q.v[e]);
+    q.store(a, i0, n);
+    return norm;
+}
+__global__ __launch_bounds__(256) void ppo_adam_kernel(AdamArgs a) {
+    __shared__ double red[256];
+    const size_t i0 = ((size_t)blockIdx.x * 256 + threadIdx.x) * ADAM_PER_THREAD;
+    const int n = i0 < a.n ? (int)min((size_t)4, a.n - i0) : 0;
+    double step[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) step[e] = i0 + e < a.n_policy ? a.step_policy : a.step_value;
+    const double norm = adam_quad(a, i0, n, step, red);
+    if (blockIdx.x == 0 && a.stats && threadIdx.x < 64) adam_stats(a, norm);
+}
+
+// ---- one update's Adam and the next mini-batch's first layer in one launch ---------------------------------------
+// The first layers hold almost all parameters, and a workgroup of their contraction can be the only reader of its tile of
+// weights (16 units, a group of inputs): it updates the tile itself (neighbouring threads neighbouring parameters), keeps
+// the new weights in LDS and contracts them with all samples, 64 at a time.  Two wavefronts share a range of inputs, 32
+// samples each, so that a SIMD has two chains of fp64 instructions to alternate between; the samples' inputs are requested
+// ahead of everything else, the next samples' under the matrix instructions.  Further workgroups update the other
+// parameters, which only later launches read.  The arithmetic and its order are those of the two kernels by themselves.
+// Bound by the 42 MB of parameters, state and gradients (2 x 256 x 2560) and a chain of latencies: 13.8 us for 8.4 + 10.4 and
+// a launch; Adam's arithmetic shows with 0.4 us of it, the contraction's with 1.7.
+constexpr int FUSED_THREADS = 512;
+constexpr int FUSED_MAX_CHUNKS = 6;                  // chunks of 16 inputs per range: 3072 inputs, 25 KB of weights in LDS
+struct FusedArgs {
+    FirstArgs f;                                     // of the next mini-batch
+    AdamArgs a;                                      // of this one
+    size_t w0[2];                                    // where the first layers' weights start in the flat buffers
+    size_t rest0[2], rest_n[2];                      // the parameters behind them, per head
+    int tile_blocks, rest_blocks[2];                 // workgroups of the tiles, of each head's other parameters
+};
+// ROUNDS: quads of parameters per thread, half the chunks per range
+template <int ROUNDS>
+__global__ __launch_bounds__(FUSED_THREADS, 4) void ppo_adam_first_kernel(FusedArgs t) {
+    constexpr int LD = ROUNDS * 2 * 64 + 4;
+    constexpr int REQUEST_AT = ROUNDS > 2 ? ROUNDS - 2 : 0;              // (before, they would not fit the registers)
+    __shared__ double part[4][16][64];               // the ranges' sums
+    __shared__ double red[FUSED_THREADS];
+    __shared__ __attribute__((aligned(16))) float fresh[16][LD];
+    const AdamArgs& a = t.a;
+    const FirstArgs& f = t.f;
+    const int block = (int)blockIdx.x, tid = (int)threadIdx.x;
+    if (block >= t.tile_blocks) {
+        int rb = block - t.tile_blocks;
+        if (rb == t.rest_blocks[0] + t.rest_blocks[1]) {
+            minibatch_scale(f.adv, f.rows, f.B, f.T, f.adv_eps, f.normalize_adv, f.scal);
+            return;
         }
-        if (threadIdx.x == 0) {
-            const double n = (double)a.B;
-            a.stats[0] = (float)(-t[0] / n - a.ent_coef * t[1] / n);
-            a.stats[1] = (float)(0.5 * t[2] / n);
-            a.stats[2] = (float)(t[1] / n);
-            a.stats[3] = (float)(t[3] / n);
-            a.stats[4] = (float)norm;
+        const int hd = rb >= t.rest_blocks[0] ? 1 : 0;
+        if (hd) rb -= t.rest_blocks[0];
+        const size_t k0 = ((size_t)rb * FUSED_THREADS + tid) * ADAM_PER_THREAD;
+        const int n = k0 < t.rest_n[hd] ? (int)min((size_t)4, t.rest_n[hd] - k0) : 0;
+        const double step = hd ? a.step_value : a.step_policy;
+        const double norm = adam_quad(a, t.rest0[hd] + k0, n, {step, step, step, step}, red);
+        if (hd == 0 && rb == 0 && a.stats && tid < 64) adam_stats(a, norm);
+        return;
+    }
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), kk = lane >> 4;
+    const int range = wave & 3, half = wave >> 2;
+    const int split = block % f.splits, tile = block / f.splits;
+    const int hd = tile >= f.tiles[0] ? 1 : 0;
+    const int o0 = (tile - (hd ? f.tiles[0] : 0)) * 16, units = min(16, f.out_dim[hd] - o0);
+    const int d = f.d, chunks = d / 16, per = first_layer_range_chunks(d);
+
+    // inputs of the wavefront's samples, NC chunks at a time; past the last chunk some other, whose results are not used
+    constexpr int NC = ROUNDS < 3 ? 2 * ROUNDS : ROUNDS;     // (one or two batches)
+    const int c0 = (split * 4 + range) * per, nc = max(0, min(chunks, c0 + per) - c0);
+    v4f_u next[NC][2];
+    const float* hrow[2];
+    auto rows_of = [&](int bt) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            hrow[q] = f.h + (size_t)clamp_index(f.rows[min(bt * 64 + (half * 2 + q) * 16 + (lane & 15), f.B - 1)], f.T) * d;
+    };
+    auto request = [&](int cb) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                next[c][q] = *reinterpret_cast<const v4f_u*>(hrow[q] + min(c0 + cb + c, chunks - 1) * 16 + 4 * kk);
+    };
+    rows_of(0);
+
+    // the tile's parameters: 16 rows of 16 per quads
+    AdamQuad aq[ROUNDS];
+    unsigned at[ROUNDS];                             // (at most 2048 units of 4096 inputs)
+    int slot[ROUNDS];                                // in fresh, or -1
+    const int k_group = split * 64 * per;
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        const int j = tid + i * FUSED_THREADS, r = j / (16 * per), c = 4 * (j - r * 16 * per);
+        const bool live = r < units && k_group + c < d;
+        at[i] = (unsigned)t.w0[hd] + (unsigned)((o0 + min(r, units - 1)) * d + min(k_group + c, d - 4));
+        slot[i] = live ? r * LD + c : -1;
+        aq[i].load_all(a, at[i]);
+    }
+    double norm;
+    const double scale = adam_scale(a, red, norm), step = hd ? a.step_value : a.step_policy;
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        AdamQuad& q = aq[i];
+        if (i == REQUEST_AT) request(0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) adam_element(a, scale, step, q.g[e], q.p[e], q.m[e], q.v[e]);
+        if (slot[i] >= 0) {
+            *reinterpret_cast<float4*>(&fresh[0][0] + slot[i]) = make_float4(q.p[0], q.p[1], q.p[2], q.p[3]);
+            q.store(a, at[i], 4);
+        }
+    }
+    __syncthreads();
+
+    const int ncol = f.out_dim[0] + f.out_dim[1];
+    const float* wrow = &fresh[lane & 15][range * 16 * per + 4 * kk];
+    for (int bt = 0; bt < f.btiles; ++bt) {
+        v4d acc[2] = {};
+        for (int cb = 0; cb < max(nc, 1); cb += NC) {
+            v4f_u x[NC][2];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) x[c][q] = next[c][q];
+            if (cb + NC < nc) {
+                request(cb + NC);
+            } else if (bt + 1 < f.btiles) {
+                rows_of(bt + 1);
+                request(0);
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (cb + c >= nc) break;
+                const float4 wv = *reinterpret_cast<const float4*>(wrow + 16 * (cb + c));
+                const float w[4] = {wv.x, wv.y, wv.z, wv.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[c][q][e], (double)w[e], acc[q], 0, 0, 0);
+            }
+        }
+        if (bt) __syncthreads();                     // the block before has been read
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[range][(half * 2 + q) * 4 + v][lane] = acc[q][v];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int qv = wave * 2 + u, b = bt * 64 + (qv >> 2) * 16 + 4 * (qv & 3) + kk, o = o0 + (lane & 15);
+            if (b < f.B && o < f.out_dim[hd])
+                f.z[((size_t)split * f.B + b) * ncol + (hd ? f.out_dim[0] : 0) + o] =
+                    ((part[0][qv][lane] + part[1][qv][lane]) + part[2][qv][lane]) + part[3][qv][lane];
         }
     }
 }
@@ -984,17 +1163,40 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
         ta.actions = actions; ta.logp_old = logp_old; ta.adv = adv; ta.returns = returns; ta.scal = fl.scal;
         ta.clip_eps = (double)cfg->clip_eps; ta.ent_coef = (double)cfg->ent_coef; ta.row_terms = row_terms;
     }
+    // An update's Adam and the next first layer in one launch.  A workgroup then takes all samples of its tile, so past 64 of
+    // them only where the tiles alone fill the chip.  A step in us, two launches / one: 64 samples, hidden 256, 1024 inputs 28.5 /
+    // 26.4, 2560 inputs 37.6 / 34.9, hidden 64, 2560 inputs 28.8 / 26.1; 256 samples, hidden 256, 2560 inputs 68.3 / 65.5, hidden
+    // 64, 2560 inputs 42.8 / 48.9.  Rows of more than 3072 inputs spill (64 samples, hidden 256, 3200 inputs: 40.7 / 41.2).
+    const int range_chunks = first_layer_range_chunks(L.head[0].dims[0]), tile_blocks = (fl.tiles[0] + fl.tiles[1]) * W.splits;
+    const bool fused = W.tail && !norm_launch && fl.d % 16 == 0 && range_chunks <= FUSED_MAX_CHUNKS &&
+                       W.splits == first_layer_groups(fl.d) && (W.btiles == 1 || tile_blocks >= 256);
+    FusedArgs fu;
+    memset(&fu, 0, sizeof(fu));
+    if (fused) {
+        fu.f = fl;
+        fu.tile_blocks = tile_blocks;
+        for (int hd = 0; hd < 2; ++hd) {
+            const size_t end = hd ? L.n_params : L.n_policy, n_first = (size_t)fl.out_dim[hd] * fl.d;
+            fu.w0[hd] = L.head[hd].w_off[0];
+            fu.rest0[hd] = fu.w0[hd] + n_first;
+            fu.rest_n[hd] = end - fu.rest0[hd];
+            fu.rest_blocks[hd] = (int)((fu.rest_n[hd] + FUSED_THREADS * ADAM_PER_THREAD - 1) / (FUSED_THREADS * ADAM_PER_THREAD));
+        }
+    }
+    bool fused_ahead = false;                                        // this mini-batch's first layer ran with the last update
     const int depth = L.head[0].n > L.head[1].n ? L.head[0].n : L.head[1].n;
     long long step = *adam_step;
     for (int e = 0; e < epochs; ++e) {
         for (int mb = 0; mb < steps_per_epoch; ++mb) {
             const int32_t* rows = perm + (size_t)e * T + (size_t)mb * batch;
             if (W.tail) {
-                fl.rows = rows;
                 ta.rows = rows;
-                const unsigned blocks = (unsigned)((fl.tiles[0] + fl.tiles[1]) * W.splits * W.btiles) + 1;   // + the advantages' scale
-                if (W.splits == 1) hipLaunchKernelGGL(ppo_first_layer_kernel<true>, dim3(blocks), dim3(256), 0, s, fl);
-                else hipLaunchKernelGGL(ppo_first_layer_kernel<false>, dim3(blocks), dim3(256), 0, s, fl);
+                if (!fused_ahead) {                                  // (else the last update's launch has done it)
+                    fl.rows = rows;
+                    const unsigned blocks = (unsigned)((fl.tiles[0] + fl.tiles[1]) * W.splits * W.btiles) + 1;   // + the advantages' scale
+                    if (W.splits == 1) hipLaunchKernelGGL(ppo_first_layer_kernel<true>, dim3(blocks), dim3(256), 0, s, fl);
+                    else hipLaunchKernelGGL(ppo_first_layer_kernel<false>, dim3(blocks), dim3(256), 0, s, fl);
+                }
                 hipLaunchKernelGGL(ppo_tail_kernel, dim3(batch), dim3(TAIL_THREADS), 0, s, ta);
             } else {
                 // forward: level l of both heads in one launch
@@ -1058,6 +1260,16 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
             aa.step_value = (double)cfg->lr_value / c1;
             aa.inv_c2 = 1.0 / (1.0 - pow((double)cfg->adam_b2, (double)step));
             aa.stats = stats ? stats + ((size_t)e * steps_per_epoch + mb) * 5 : nullptr;
+            const bool last = mb + 1 == steps_per_epoch && e + 1 == epochs;
+            fused_ahead = fused && !last;
+            if (fused_ahead) {
+                fu.a = aa;
+                fu.f.rows = mb + 1 < steps_per_epoch ? rows + batch : perm + (size_t)(e + 1) * T;
+                const unsigned blocks = (unsigned)(fu.tile_blocks + fu.rest_blocks[0] + fu.rest_blocks[1]) + 1;   // + the advantages' scale
+                auto kernel = range_chunks <= 2 ? ppo_adam_first_kernel<1> : range_chunks <= 4 ? ppo_adam_first_kernel<2> : ppo_adam_first_kernel<3>;
+                hipLaunchKernelGGL(kernel, dim3(blocks), dim3(FUSED_THREADS), 0, s, fu);
+                continue;
+            }
             hipLaunchKernelGGL(ppo_adam_kernel, dim3((unsigned)((L.n_params + 256 * ADAM_PER_THREAD - 1) / (256 * ADAM_PER_THREAD))),
                                dim3(256), 0, s, aa);
         }

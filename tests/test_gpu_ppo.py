@@ -214,3 +214,30 @@ def test_gae_rollouts_share_workgroups(n_envs, T):
         scale = max(np.abs(a_ref).max(), np.abs(r_ref).max())
         assert np.abs(adv[e] - a_ref).max() <= 2e-7 * scale + 1e-7
         assert np.abs(ret[e] - r_ref).max() <= 2e-7 * scale + 1e-7
+
+
+@pytest.mark.parametrize("dims_p,dims_v,batch", [
+    ([1024, 64, 5], [1024, 64, 1], 64), ([1040, 40, 5], [1040, 24, 1], 33),       # one block of samples; ranges that end early
+    ([2048, 250, 3], [2048, 17, 1], 16), ([3072, 33, 4], [3072, 16, 1], 48),      # two and three rounds of parameters per thread
+    ([2560, 256, 18], [2560, 256, 1], 65), ([2560, 256, 18], [2560, 256, 1], 64),  # 256 tiles: any number of samples
+    ([1024, 64, 5], [1024, 64, 1], 65), ([3088, 33, 4], [3088, 16, 1], 48),       # either limit passed
+    ([48, 7], [48, 1], 16), ([64, 16, 8, 4], [64, 16, 1], 12),
+])
+def test_update_and_next_first_layer_share_a_launch(dims_p, dims_v, batch):
+    """A call per mini-batch never has a next first layer to take along, a call for all of them does: the same bits in
+    parameters, both moments and statistics.  (Against the oracle: test_head_update_matches_oracle.)"""
+    B, R = _mods()
+    T = 4 * batch
+    print("ppo", dims_p, dims_v, batch, flush=True)
+    c = synth.ppo_rollout_case(41, T, dims_p[0], dims_p[-1], 1)
+    pwb, vwb = synth.mlp_params(41, 60, dims_p), synth.mlp_params(41, 80, dims_v)
+    args = (R.dev(c["h"]), R.dev(c["actions"]), R.dev(c["logp_old"]), R.dev(synth.normal(41, 90, (T,))),
+            R.dev(synth.normal(41, 91, (T,))))
+    whole, single = R.PPOTrainer(pwb, vwb), R.PPOTrainer(pwb, vwb)
+    stats = whole.update(*args, R.dev(c["perm"]), batch)
+    ident = torch.arange(batch, dtype=torch.int32, device="cuda").view(1, batch)
+    parts = [single.update(*[x[rows].contiguous() for x in args], ident, batch)
+             for rows in R.dev(c["perm"])[0].long().view(4, batch)]
+    assert torch.equal(stats, torch.cat(parts))
+    for name in ("params", "adam_m", "adam_v"):
+        assert torch.equal(getattr(whole, name), getattr(single, name)), name
