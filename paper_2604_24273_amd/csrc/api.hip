@@ -739,10 +739,21 @@ int run_encoder_microbatch(const brl_encoder* enc, const EncWs& L, char* base, c
             if (int rc = launch_attention_mfma_prepacked(nb, S, enc->n_heads, enc->n_kv_heads, ao.kvf, ao.qf, att, s))
                 return rc;
         } else {
-        if (int rc = launch_gemm(act, wqkv, Mt, dq + 2 * dkv, d, qkv, L.big_ld_qkv, nullptr, nullptr, 0, s)) return rc;
+        // Other head sizes, same condition: the product writes the v fragments, the pack kernel is left with k.
+        const bool values = !sm.cu && enc->attn_precision == BRL_ATTN_MFMA &&
+                            gemm_values_eligible(Mt, enc->n_heads, enc->n_kv_heads, dh, S, w8);
+        if (values) {
+            ValueOperands vo;
+            vo.kvf = base + L.frag_off;
+            vo.S = S; vo.n_heads = enc->n_heads; vo.n_kv_heads = enc->n_kv_heads; vo.head_dim = dh;
+            attention_key_block(dh, vo.k_fragments, vo.fragments);
+            if (int rc = launch_gemm_values(act, wqkv, Mt, d, qkv, L.big_ld_qkv, vo, s)) return rc;
+        } else if (int rc = launch_gemm(act, wqkv, Mt, dq + 2 * dkv, d, qkv, L.big_ld_qkv, nullptr, nullptr, 0, s)) {
+            return rc;
+        }
         if (enc->attn_precision == BRL_ATTN_MFMA) {
             if (int rc = launch_attention_mfma(qkv, L.big_ld_qkv, nb, S, sm, enc->n_heads, enc->n_kv_heads, dh, cos_t,
-                                               sin_t, base + L.frag_off, att, s))
+                                               sin_t, base + L.frag_off, att, s, values))
                 return rc;
         } else {
             if (int rc = launch_attention_f32(qkv, L.big_ld_qkv, nb, S, sm, enc->n_heads, enc->n_kv_heads, dh, cos_t,

@@ -25,6 +25,8 @@
 //                     filled by direct global->LDS loads, double buffered.
 // V fragments are stored transposed with the keys of a block permuted so that
 // the 8 keys a lane's probabilities stand for are 16 contiguous bytes.
+// Where the q | k | v product has written the v fragments (uniform batches, other head sizes), attn_keys_kernel
+// takes the pack kernel's place.
 // Where the q | k | v product has already written the fragments (its epilogue does for
 // uniform batches at head_dim 128, q included), only attention_frag_kernel runs, in the
 // form that reads its q fragments straight into registers (launch_attention_mfma_prepacked).
@@ -264,6 +266,29 @@ __global__ __launch_bounds__(256) void attn_pack_kernel(PackArgs a) {
         dst[(KS * 2 + (r * 2 + tt) * 2 + 0) * 64 + ln] = pack8h(v, false);
         dst[(KS * 2 + (r * 2 + tt) * 2 + 1) * 64 + ln] = pack8h(v, true);
     }
+}
+
+// The k fragments alone, where the product has written the v fragments (whole key blocks, no ragged states).  Bound by
+// memory: a wavefront takes a key block of one head, every element read once, 16 bytes per lane and all of them in flight.
+// (64 states of 512 tokens, 32 heads of 100: 220 us, 0.89 GB; the pack kernel without its v part 294, with it 411.  Half a block
+// per wavefront, twice the wavefronts: 231.)
+template <int DHP, int VW>
+__global__ __launch_bounds__(256) void attn_keys_kernel(PackArgs a) {
+    constexpr int KS = k_steps<DHP, VW>, DB = DHP / 32, KVFR = KS * 2 + DB * 4;
+    __shared__ __attribute__((aligned(16))) char park[4][128 * DHP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n_work = a.B * a.NRB * a.Hkv, per_xcd = (n_work + 7) >> 3;          // neighbouring heads on one XCD, as above
+    const int at = (int)(blockIdx.x >> 3) * 4 + wave, w = (int)(blockIdx.x & 7) * per_xcd + at;
+    if (at >= per_xcd || w >= n_work) return;
+    const int hd = w % a.Hkv, rb = (w / a.Hkv) % a.NRB, b = w / (a.Hkv * a.NRB), half = a.dh / 2;
+    QueryRows<DHP, VW> k;
+    k.request(a.qkv + ((size_t)b * a.S + rb * 32) * a.ld + (a.Hq + hd) * a.dh, a.ld, 32, a.cos_t + (size_t)rb * 32 * half,
+              a.sin_t + (size_t)rb * 32 * half, half);
+    k.park(park[wave], half, 1.0f);
+    __builtin_amdgcn_wave_barrier();
+    uint4* dst = a.KVF + ((size_t)(b * a.Hkv + hd) * a.NRB + rb) * KVFR * 64;
+#pragma unroll
+    for (int fr = 0; fr < 2 * KS; ++fr) dst[fr * 64 + lane] = staged_fragment<DHP>(park[wave], fr >> 1, lane, fr & 1);
 }
 
 struct FragArgs {
@@ -1034,8 +1059,8 @@ ShortForm short_form(int dh, int nrb, int B, int Hq, int Hkv) {
 }
 
 template <int DHP, int VW>
-void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, hipStream_t s) {
-    const ShortForm form = short_form(f.dh, p.NRB, f.B, f.Hq, f.Hkv);
+void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, bool values_ready, hipStream_t s) {
+    const ShortForm form = values_ready ? ShortForm::PAIR : short_form(f.dh, p.NRB, f.B, f.Hq, f.Hkv);
     if (form == ShortForm::HEAD) {
         hipLaunchKernelGGL((attention_short_kernel<DHP, VW>), dim3((unsigned)(f.B * f.Hq)), dim3(DHP * 4), 0, s, f);
         return;
@@ -1051,7 +1076,12 @@ void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, h
         hipLaunchKernelGGL((attention_group_kernel<DHP, VW>), dim3((unsigned)n_work), dim3(512), 0, s, f);
         return;
     }
-    hipLaunchKernelGGL((attn_pack_kernel<DHP, VW>), pgrid, dim3(256), 0, s, p);
+    if (values_ready) {
+        const unsigned per_xcd = (unsigned)(((size_t)p.B * p.NRB * p.Hkv + 7) / 8);
+        hipLaunchKernelGGL((attn_keys_kernel<DHP, VW>), dim3(8 * ((per_xcd + 3) / 4)), dim3(256), 0, s, p);
+    } else {
+        hipLaunchKernelGGL((attn_pack_kernel<DHP, VW>), pgrid, dim3(256), 0, s, p);
+    }
     const dim3 agrid((unsigned)(8 * ((n_work + 7) / 8)));
     hipLaunchKernelGGL((attention_frag_kernel<DHP, VW, ATTN_WPG>), agrid, dim3(ATTN_WPG * 64), 0, s, f);
 }
@@ -1059,7 +1089,8 @@ void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, h
 }  // namespace
 
 int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& sm, int n_heads, int n_kv_heads,
-                          int head_dim, const float* cos_t, const float* sin_t, void* frag_ws, float* out, hipStream_t s) {
+                          int head_dim, const float* cos_t, const float* sin_t, void* frag_ws, float* out, hipStream_t s,
+                         bool values_ready) {
     if (head_dim % 4 != 0 || head_dim > 128 || ld % 4 != 0) {
         set_error("attention: head_dim %d must be a multiple of 4, at most 128 (row stride %d a multiple of 4)",
                   head_dim, ld);
@@ -1085,14 +1116,20 @@ int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& 
     const bool v4 = (head_dim / 2) % 4 == 0;          // rotary halves and head rows 16-byte aligned
     LaunchTimer tm(BRL_KC_ATTENTION, s);
     if (dhp == 32) {
-        if (v4) launch_pair<32, 4>(p, f, pgrid, f.n_work, s); else launch_pair<32, 2>(p, f, pgrid, f.n_work, s);
+        if (v4) launch_pair<32, 4>(p, f, pgrid, f.n_work, values_ready, s); else launch_pair<32, 2>(p, f, pgrid, f.n_work, values_ready, s);
     } else if (dhp == 64) {
-        if (v4) launch_pair<64, 4>(p, f, pgrid, f.n_work, s); else launch_pair<64, 2>(p, f, pgrid, f.n_work, s);
+        if (v4) launch_pair<64, 4>(p, f, pgrid, f.n_work, values_ready, s); else launch_pair<64, 2>(p, f, pgrid, f.n_work, values_ready, s);
     } else {
-        if (v4) launch_pair<128, 4>(p, f, pgrid, f.n_work, s); else launch_pair<128, 2>(p, f, pgrid, f.n_work, s);
+        if (v4) launch_pair<128, 4>(p, f, pgrid, f.n_work, values_ready, s); else launch_pair<128, 2>(p, f, pgrid, f.n_work, values_ready, s);
     }
     BRL_LAUNCH_CHECK("attention_mfma");
     return BRL_OK;
+}
+
+void attention_key_block(int head_dim, int& k_fragments, int& fragments) {
+    const int dhp = padded_head_dim(head_dim), ks = (head_dim / 2) % 4 && dhp == 128 ? k_steps<128, 2> : dhp / 16;
+    k_fragments = 2 * ks;
+    fragments = k_fragments + dhp / 8;                // two steps of 16 keys, hi and lo, for each 32 components
 }
 
 // The fragments (K / V and q) were written by the epilogue of the q | k | v product.

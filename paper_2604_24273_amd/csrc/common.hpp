@@ -185,6 +185,13 @@ struct AttnOperands {
     void* qf;             // q fragments [B][Hq][S/32][8][hi,lo][64 lanes] of 16 bytes
     int S, n_heads, n_kv_heads;
 };
+struct ValueOperands {
+    void* kvf;            // as above: the v fragments are written, the k fragments are left to the pack kernel
+    int S, n_heads, n_kv_heads, head_dim, k_fragments, fragments;      // of a key block: see attention_key_block
+};
+bool gemm_values_eligible(int M, int n_heads, int n_kv_heads, int head_dim, int S, int w8);
+int launch_gemm_values(const ActBuf& a, const WeightSegs& w, int M, int K, float* y, int ldy, const ValueOperands& out,
+                       hipStream_t s);
 bool gemm_attn_eligible(int M, int n_heads, int n_kv_heads, int head_dim, int S);
 int launch_gemm_attn(const ActBuf& a, const WeightSegs& w, int M, int K, const AttnOperands& out, hipStream_t s);
 
@@ -222,7 +229,9 @@ size_t attention_mfma_ws_bytes(int B, int S, int n_heads, int n_kv_heads, int he
 int launch_attention_mfma_prepacked(int B, int S, int n_heads, int n_kv_heads, const void* kvf, const void* qf, float* out,
                                     hipStream_t s);
 int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& sm, int n_heads, int n_kv_heads,
-                          int head_dim, const float* cos_t, const float* sin_t, void* frag_ws, float* out, hipStream_t s);
+                          int head_dim, const float* cos_t, const float* sin_t, void* frag_ws, float* out, hipStream_t s,
+                         bool values_ready = false);       // frag_ws already holds the v fragments (head_dim < 128, S > 32)
+void attention_key_block(int head_dim, int& k_fragments, int& fragments);
 int launch_embed(const uint16_t* table, const int32_t* ids, int M, int d, int vocab, float* x, hipStream_t s);
 // M rows in all; lengths (or nullptr) applies to the uniform layout only
 int launch_final_pool(const float* x, const float* gain, int B, int S, int M, int d, const int32_t* lengths,

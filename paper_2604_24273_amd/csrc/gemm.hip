@@ -73,6 +73,9 @@ struct GemmArgs {
     uint4* att_kvf;          // [B][Hkv][NRB][ K: [8][hi,lo] | V: [4][2][hi,lo] ][64 lanes]
     uint4* att_qf;           // [B][Hq][NRB][8][hi,lo][64 lanes]
     int att_S, att_nrb, att_Hq, att_Hkv;
+    // value-operand epilogue (the same product at other head sizes): the column blocks from att_v0 on leave as v fragments
+    // only, the others as fp32 rows - see epilogue_values
+    int att_v0, att_dh, att_kfr, att_kvfr;   // head size, 1 KB fragments of k and of k and v in a key block
 };
 
 // residual element(s) at flat index o (o % 4 == 0 for the four-wide form)
@@ -562,10 +565,54 @@ struct LdsTile {
     }
 };
 
-template <int TM, int TN, int WM, int WN, bool W8, bool ATTN = false>
+// The value columns of the q | k | v product of a uniform batch (32 | S) as the attention kernel's v fragments, any head
+// size: a lane's accumulator registers are eight keys of its column in the order of a fragment entry, twice, so nothing
+// has to be turned, and a column's head and component only decide where the entries go.  Entries of components past the
+// head are left as they are: they only reach output rows that no one stores.  The arithmetic is the plain epilogue's and
+// the pack kernel's, so the fragments hold the same bits.
+template <int TM, int TN>
+__device__ inline void epilogue_values(const GemmArgs& g, v16i (&acc)[TM][TN], int mb0, int nb0, const float (&beta)[TN],
+                                       int lane, int* scr) {
+    const int2* rows = park_rows<TM, TN>(g, mb0, lane, scr);
+    __builtin_amdgcn_wave_barrier();
+    const int dl = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        if (nb0 + j >= g.nnb) break;
+        const int col = (nb0 + j - g.att_v0) * 32 + dl, kvh = col / g.att_dh, d = col - kvh * g.att_dh;
+        const int at = (g.att_kfr + (d >> 5) * 4) * 64 + h * 32 + (d & 31);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int mb = mb0 + i;
+            if (mb >= g.nmb) continue;
+            const int b = (mb * 32) / g.att_S, rb = ((mb * 32) % g.att_S) >> 5;
+            uint4* dst = g.att_kvf + ((size_t)(b * g.att_Hkv + kvh) * g.att_nrb + rb) * ((size_t)g.att_kvfr * 64) + at;
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) {
+                half8 hi, lo;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int v = 8 * tt + e;
+                    const int2 rw = rows[i * 32 + 8 * (v >> 2) + 4 * h + (v & 3)];
+                    const float y = ((float)(acc[i][j][v] - rw.y) * __int_as_float(rw.x)) * beta[j];
+                    const _Float16 yh = half_of_rounded(y);
+                    hi[e] = yh;
+                    lo[e] = (_Float16)(y - (float)yh);
+                }
+                dst[tt * 128] = __builtin_bit_cast(uint4, hi);
+                dst[tt * 128 + 64] = __builtin_bit_cast(uint4, lo);
+            }
+        }
+    }
+}
+
+enum class LdsEpi { ROWS, ATTN, VALUES };
+
+template <int TM, int TN, int WM, int WN, bool W8, LdsEpi EPI = LdsEpi::ROWS>
 __device__ __forceinline__ void gemm_lds_body(const GemmArgs& g) {
     using Tile = LdsTile<TM, TN, WM, WN, W8>;
     constexpr int NW = Tile::NW;
+    constexpr bool ATTN = EPI == LdsEpi::ATTN;
     __shared__ __attribute__((aligned(1024))) uint4 stage0[Tile::STAGE];
     __shared__ __attribute__((aligned(1024))) uint4 stage1[Tile::STAGE];
 
@@ -649,6 +696,12 @@ __device__ __forceinline__ void gemm_lds_body(const GemmArgs& g) {
         static_assert(WN == 4 && TN == 2, "a 256-column tile is two heads of 128: four wavefronts of 32 + 32 columns");
         epilogue_attn<TM, TN>(g, acc, mb0, nb0, beta, lane, scr);
     } else {
+        if constexpr (EPI == LdsEpi::VALUES) {
+            if (nb0 >= g.att_v0) {                    // (TN divides att_v0)
+                epilogue_values<TM, TN>(g, acc, mb0, nb0, beta, lane, scr);
+                return;
+            }
+        }
         epilogue<TM, TN>(g, acc, mb0, nb0, beta, lane, scr);
     }
 }
@@ -662,7 +715,13 @@ __global__ __launch_bounds__(WM * WN * 64, 4) void gemm_lds_kernel(GemmArgs g) {
 // attention against 92 us, a pack kernel of 19 and 65 us; int8 weights 104 + 53 against 102 + 19 + 65.
 template <bool W8>
 __global__ __launch_bounds__(512, 4) void gemm_lds_attn_kernel(GemmArgs g) {
-    gemm_lds_body<2, 2, 2, 4, W8, true>(g);
+    gemm_lds_body<2, 2, 2, 4, W8, LdsEpi::ATTN>(g);
+}
+
+// the wide tile with the value-operand epilogue.  32768 tokens x 9600 x 3200, 32 heads of 100: 818 us and 220 of k fragments
+// against 811 and a pack kernel of 411.
+__global__ __launch_bounds__(512, 4) void gemm_lds_values_kernel(GemmArgs g) {
+    gemm_lds_body<2, 2, 2, 4, false, LdsEpi::VALUES>(g);
 }
 
 // the same tile loop on int8 weight blobs
@@ -969,20 +1028,8 @@ bool wide_tile_chosen(int nmb, int nnb) {
     return t_wide >= 2 * cus && fill_wide >= 0.95 * fill_narrow;
 }
 
-}  // namespace
-
-bool gemm_attn_eligible(int M, int n_heads, int n_kv_heads, int head_dim, int S) {
-    const int N = (n_heads + 2 * n_kv_heads) * head_dim;
-    return head_dim == 128 && S % 32 == 0 && M % 32 == 0 && M % S == 0 && N % 256 == 0 && wide_tile_chosen(M / 32, N / 32);
-}
-
-int launch_gemm_attn(const ActBuf& a, const WeightSegs& w, int M, int K, const AttnOperands& out, hipStream_t s) {
-    if (w.count != 3 || !gemm_attn_eligible(M, out.n_heads, out.n_kv_heads, 128, out.S) ||
-        w.n_end[0] != out.n_heads * 128 || w.n_end[1] - w.n_end[0] != out.n_kv_heads * 128 ||
-        w.n_end[2] - w.n_end[1] != out.n_kv_heads * 128) {
-        set_error("gemm: the attention-operand epilogue needs the q | k | v product of a uniform batch at head_dim 128");
-        return BRL_EINVAL;
-    }
+// the q | k | v product on the wide tile
+GemmArgs qkv_args(const ActBuf& a, const WeightSegs& w, int M, int K) {
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     g.A = reinterpret_cast<const uint4*>(a.q);
@@ -1001,18 +1048,67 @@ int launch_gemm_attn(const ActBuf& a, const WeightSegs& w, int M, int K, const A
     g.nnb = w.nb_end[2];
     g.nsb = round_up(K, SBK) / SBK;
     g.ops = 2.0 * (double)M * (double)w.n_end[2] * (double)K;
-    g.att_cos = out.cos_t; g.att_sin = out.sin_t; g.att_qscale = out.qscale;
-    g.att_kvf = static_cast<uint4*>(out.kvf); g.att_qf = static_cast<uint4*>(out.qf);
-    g.att_S = out.S; g.att_nrb = out.S / 32; g.att_Hq = out.n_heads; g.att_Hkv = out.n_kv_heads;
     g.tiles_m = (g.nmb + 3) / 4;
     g.tiles_n = (g.nnb + 7) / 8;
     g.group_m = 4;
-    const int total = g.tiles_m * g.tiles_n;
-    const int grid = ((total + 7) / 8) * 8;
+    return g;
+}
+
+}  // namespace
+
+bool gemm_attn_eligible(int M, int n_heads, int n_kv_heads, int head_dim, int S) {
+    const int N = (n_heads + 2 * n_kv_heads) * head_dim;
+    return head_dim == 128 && S % 32 == 0 && M % 32 == 0 && M % S == 0 && N % 256 == 0 && wide_tile_chosen(M / 32, N / 32);
+}
+
+int launch_gemm_attn(const ActBuf& a, const WeightSegs& w, int M, int K, const AttnOperands& out, hipStream_t s) {
+    if (w.count != 3 || !gemm_attn_eligible(M, out.n_heads, out.n_kv_heads, 128, out.S) ||
+        w.n_end[0] != out.n_heads * 128 || w.n_end[1] - w.n_end[0] != out.n_kv_heads * 128 ||
+        w.n_end[2] - w.n_end[1] != out.n_kv_heads * 128) {
+        set_error("gemm: the attention-operand epilogue needs the q | k | v product of a uniform batch at head_dim 128");
+        return BRL_EINVAL;
+    }
+    GemmArgs g = qkv_args(a, w, M, K);
+    g.att_cos = out.cos_t; g.att_sin = out.sin_t; g.att_qscale = out.qscale;
+    g.att_kvf = static_cast<uint4*>(out.kvf); g.att_qf = static_cast<uint4*>(out.qf);
+    g.att_S = out.S; g.att_nrb = out.S / 32; g.att_Hq = out.n_heads; g.att_Hkv = out.n_kv_heads;
     LaunchTimer tm(BRL_KC_GEMM_QKV_ATTN, s, g.ops);
-    if (w.w8) hipLaunchKernelGGL(gemm_lds_attn_kernel<true>, dim3(grid), dim3(512), 0, s, g);
-    else hipLaunchKernelGGL(gemm_lds_attn_kernel<false>, dim3(grid), dim3(512), 0, s, g);
+    const dim3 grid((unsigned)(((g.tiles_m * g.tiles_n + 7) / 8) * 8));
+    if (w.w8) hipLaunchKernelGGL(gemm_lds_attn_kernel<true>, grid, dim3(512), 0, s, g);
+    else hipLaunchKernelGGL(gemm_lds_attn_kernel<false>, grid, dim3(512), 0, s, g);
     BRL_LAUNCH_CHECK("gemm_lds_attn_kernel");
+    return BRL_OK;
+}
+
+// Whole key blocks of a uniform batch and column blocks that are all k or all v, where the wide tile is the one to take.
+// Encoders of four layers, width 1024, with / without (us): heads of 100, 8 states of 1024 tokens 2293 / 2499, 76 of 128 (8
+// heads) 847 / 970; of 64, 512 states of 64 tokens 4055 / 4433, 128 of 128 (4 of 16 heads have values) 1069 / 1093; of 32, 64 of
+// 128 tokens 720 / 758, 128 of 64 (8 of 32) 633 / 630; of 16, 64 of 128 tokens 864 / 957.  Heads of 128: gemm_attn_eligible.
+bool gemm_values_eligible(int M, int n_heads, int n_kv_heads, int head_dim, int S, int w8) {
+    const int dq = n_heads * head_dim, dkv = n_kv_heads * head_dim;
+    return !w8 && head_dim < 128 && S > 32 && S % 32 == 0 && M % S == 0 && dq % 32 == 0 && dkv % 32 == 0 &&
+           (dq + dkv) % 64 == 0 && wide_tile_chosen(M / 32, (dq + 2 * dkv) / 32);
+}
+
+int launch_gemm_values(const ActBuf& a, const WeightSegs& w, int M, int K, float* y, int ldy, const ValueOperands& out,
+                       hipStream_t s) {
+    if (w.count != 3 || !gemm_values_eligible(M, out.n_heads, out.n_kv_heads, out.head_dim, out.S, w.w8) ||
+        w.n_end[0] != out.n_heads * out.head_dim || w.n_end[1] - w.n_end[0] != out.n_kv_heads * out.head_dim ||
+        w.n_end[2] - w.n_end[1] != out.n_kv_heads * out.head_dim) {
+        set_error("gemm: the value-operand epilogue needs the q | k | v product of a uniform batch on the wide tile");
+        return BRL_EINVAL;
+    }
+    GemmArgs g = qkv_args(a, w, M, K);
+    g.y = y;
+    g.ldy = ldy;
+    g.fast_epilogue = ldy % 4 == 0 ? 1 : 0;
+    g.att_kvf = static_cast<uint4*>(out.kvf);
+    g.att_S = out.S; g.att_nrb = out.S / 32; g.att_Hq = out.n_heads; g.att_Hkv = out.n_kv_heads;
+    g.att_v0 = w.nb_end[1];
+    g.att_dh = out.head_dim; g.att_kfr = out.k_fragments; g.att_kvfr = out.fragments;
+    LaunchTimer tm(BRL_KC_GEMM, s, g.ops);
+    hipLaunchKernelGGL(gemm_lds_values_kernel, dim3((unsigned)(((g.tiles_m * g.tiles_n + 7) / 8) * 8)), dim3(512), 0, s, g);
+    BRL_LAUNCH_CHECK("gemm_lds_values_kernel");
     return BRL_OK;
 }
 

@@ -236,3 +236,32 @@ def test_fused_qkv_path_replays_from_a_hip_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(h, want), "replay %d differs from the eager result" % k
+
+
+@pytest.mark.timeout(900)
+@pytest.mark.parametrize("heads,kv_heads,head_dim,n_states,S", [
+    (8, 8, 100, 76, 128), (24, 8, 100, 64, 96),                      # heads across column blocks; states inside row tiles
+    (16, 4, 64, 128, 128), (8, 8, 32, 512, 64), (16, 16, 16, 512, 64),
+    (8, 8, 100, 76, 120), (12, 12, 100, 64, 96),                     # beside the rule: ragged key blocks, ragged segments
+])
+def test_qkv_product_writing_value_operands_matches_two_step_path(heads, kv_heads, head_dim, n_states, S):
+    """Uniform batches of whole key blocks at other head sizes: the q | k | v product writes the transposed v fragments
+    itself.  The same states one per call and back to back take the pack kernel: every bit of the pooled output must agree."""
+    from paper_2604_24273_amd import runtime as R
+    shape = synth.tiny_shape(n_layers=2, d=256, n_heads=heads, n_kv_heads=kv_heads, head_dim=head_dim, f=512, vocab=300,
+                             rope_theta=500000.0)
+    host = []
+    enc = R.EncoderHandle(shape, seed=7, layer_sink=lambda l, w: host.append(w))
+    ids = synth.token_ids(7, 500, (n_states, S), shape.vocab)
+    print("v fragments from the product:", heads, kv_heads, head_dim, n_states, S, flush=True)
+    h = enc.forward(R.dev(ids))
+    assert torch.equal(h, enc.forward(R.dev(ids)))
+    for b in (0, 1, n_states - 1):
+        assert torch.equal(h[b:b + 1], enc.forward(R.dev(ids[b:b + 1]))), b
+    cu = (np.arange(n_states + 1) * S).astype(np.int32)
+    assert torch.equal(h, enc.forward_packed(R.dev(ids.reshape(-1).astype(np.int32)), cu, max_len=S))
+    cfg = O.EncoderConfig(shape.n_layers, shape.d, shape.n_heads, shape.n_kv_heads, shape.head_dim, shape.f,
+                          shape.vocab, shape.rope_theta)
+    h_ref = O.encoder_forward(ids[-1:], synth.embedding_bf16(7, shape), _oracle_layers(host),
+                              synth.final_norm_gain(7, shape), cfg)
+    assert _cos(h.cpu().numpy()[-1], h_ref[0]) >= 0.999              # as above
