@@ -562,7 +562,33 @@ struct LdsTile {
                     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af, bf[j], acc[i][j], 0, 0, 0);
             }
         }
+        // Issue order.  Left to itself the compiler expands the codes of a k-step in one run between two batches of MFMAs, and
+        // reads int8 fragments right before their use.  Here each MFMA is followed by its share of the next k-step's
+        // expansion or by one read.  Ternary, wide tile, 8192 x 13824 x 2560 231.5 -> 230.7 us, 32768 x 17280 x 3200 1412 -> 1389
+        // (the 128-wide tile spills under it: + 2.7 %); int8, 8192 x 3840 x 2560 106 -> 101, 8192 x 13824 x 2560 317 -> 314.
+        if constexpr (W8) {
+            __builtin_amdgcn_sched_group_barrier(SCHED_LDS_READ, 4, 0);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                __builtin_amdgcn_sched_group_barrier(SCHED_MFMA, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(SCHED_LDS_READ, 1, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(SCHED_MFMA, 4, 0);
+        } else if constexpr (NW == 8 && TM == 2 && TN == 2) {
+            __builtin_amdgcn_sched_group_barrier(SCHED_LDS_READ, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(SCHED_VALU, 14, 0);         // the first k-step's codes: 7 per block
+#pragma unroll
+            for (int g = 0; g < 6; ++g) {
+                __builtin_amdgcn_sched_group_barrier(SCHED_MFMA, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(SCHED_VALU, 4, 0);
+                __builtin_amdgcn_sched_group_barrier(SCHED_LDS_READ, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(SCHED_MFMA, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(SCHED_VALU, 3, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(SCHED_MFMA, 4, 0);
+        }
     }
+    static constexpr int SCHED_VALU = 0x2, SCHED_MFMA = 0x8, SCHED_LDS_READ = 0x100;
 };
 
 // The value columns of the q | k | v product of a uniform batch (32 | S) as the attention kernel's v fragments, any head
