@@ -27,6 +27,7 @@
 //                      uniform batch at head_dim 128: its epilogue rotates q and k and
 //                      writes them and v as the fp16 hi / lo fragments the attention
 //                      kernel reads (no fp32 rows, no pack kernel).
+//                      gemm_lds_values_kernel writes v alone, other head sizes.
 //                      gemm_lds_w8_kernel is the same loop on int8 weight blobs.
 //   gemm_direct_kernel launches that would leave most compute units with one tile or
 //                      none: no LDS staging, the 4 to 16 wavefronts of a workgroup
@@ -1190,6 +1191,16 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
         if (g.nmb <= 1 || (glu && n32 <= 1024)) return launch_direct<1, 2, 8, 1, 4, true>(g, s);
         if (!glu && (long)((g.nmb + 1) / 2) * g.nnb <= 700) return launch_direct<2, 1, 8, 1, 4, true>(g, s);
         if (n64 <= (g.nsb >= 32 ? 1600 : 1000)) return launch_direct<2, 2, 4, 1, 3, true>(g, s);
+        // 128 x 256 tiles, two to a compute unit, where their last round is three quarters full or from six rounds on; otherwise
+        // 128 x 128, whose last round ends sooner.  Wide / narrow, quantisation included: 8192 x 3840 x 2560 (1.9 rounds) 109 /
+        // 114, 6144 x 2560 x 6912 (0.9) 154 / 165, 8192 x 13824 x 2560 (6.8) 364 / 373, 12288 x 2560 x 6912 (1.9) 314 / 330; 4096 x
+        // 2560 x 6912 (0.6) 120 / 112, 8192 x 2560 x 2560 (1.3) 84 / 82.7; by trace gate|up 4096 x 13824 x 2560 (3.4) 172 / 165,
+        // 4096 x 9600 x 3200 (2.4) 172 / 159, gate|up 4096 x 17280 x 3200 (4.3) 261 / 245.  Past the first round half a tile of
+        // padding in thirteen is too much (N = 3200: 9000 tokens 132 / 129, 20000 298 / 294; one in 38, N = 9600, is not: 723 / 744).
+        const long t_wide = (long)((g.nmb + 3) / 4) * ((g.nnb + 7) / 8), slots = 2L * device_cus();
+        const bool padded = t_wide > slots && 50 * (2 * t_wide - t_narrow) > t_narrow;
+        if (!padded && (t_wide >= 6 * slots || 4 * (t_wide % slots) >= 3 * slots || t_wide % slots == 0))
+            return launch_lds<2, 2, 2, 4, true>(g, s);
         return launch_lds<2, 2, 2, 2, true>(g, s);                     // 16 KB per stage
     }
     const long n32x64 = (long)g.nmb * ((g.nnb + 1) / 2);

@@ -228,6 +228,29 @@ def test_int8_gate_up_tiles_give_the_same_bits(f):
         assert torch.equal(h, want[:b]), b
 
 
+@pytest.mark.parametrize("m,n", [
+    (4096, 3072), (4096, 3040), (4065, 3330), (8192, 2048),     # three quarters of a round of 128 x 256 tiles, edges inside, a whole round
+    (4064, 2816), (8192, 2080), (9000, 3200),                   # beside the rule: 0.69 and 1.13 rounds, half a tile of padding in 13
+])
+def test_int8_wide_tile(m, n):
+    """Both sides of the rule that takes the 128 x 256 tile on int8 weights, as in the dispatch test above."""
+    test_int8_dispatch_edges(m, n, 136)
+
+
+@pytest.mark.parametrize("f", [6400, 6392])
+def test_int8_gate_up_on_the_wide_tile_gives_the_same_bits(f):
+    """Gate | up on 450 wide tiles (36 states of 32 tokens), on narrow ones beside the rule (42 and 11): the same bits.
+    (Against the oracle: the test above.)"""
+    B, R = _mods()
+    shape = synth.tiny_shape(n_layers=1, d=64, n_heads=2, n_kv_heads=1, head_dim=32, f=f, vocab=100)
+    enc = R.EncoderHandle(shape, seed=6, int8_weights=True)
+    ids = synth.token_ids(6, 500, (42, 32), shape.vocab)
+    want = enc.forward(R.dev(ids))
+    for b in (36, 11):
+        print("int8 gate | up, wide tile", f, b, flush=True)
+        assert torch.equal(enc.forward(R.dev(ids[:b])), want[:b]), b
+
+
 @pytest.mark.parametrize("n_states,S", [(128, 128), (170, 96)])
 def test_int8_qkv_product_writing_attention_operands_matches_two_step_path(n_states, S):
     """Uniform batches at head_dim 128 with enough rows: the int8-weight q | k | v product writes the attention operands
