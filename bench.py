@@ -662,14 +662,15 @@ def bench_critics(torch, B, R, synth, enc, ids, Bn: int, S: int, shape, steps: i
         run()
     torch.cuda.synchronize()
     B.brl_timing_enable(False)
-    n, gms, ops = B.brl_timing_read_ops(B.BRL_KC_GEMM_NARROW)
+    classes = [B.brl_timing_read_ops(k) for k in (B.BRL_KC_GEMM, B.BRL_KC_GEMM_NARROW)]     # 128 x 256 and 128 x 128 tiles
+    gms, ops = sum(c[1] for c in classes), sum(c[2] for c in classes)
     for k in range(len(B.KERNEL_CLASSES)):
         B.brl_timing_read(k)
     h1 = enc.forward(ids)
     out = {"int8_weight_encoder": {"ms_per_step": round(ms, 4), "states_per_s": round(Bn / ms * 1e3, 1),
                                    "weight_bytes": int(sum(t[k].packed.numel() for t in enc.keep[1::2] for k in t
                                                            if hasattr(t[k], "packed"))),
-                                   "gemm_kernel": "gemm_lds_w8_kernel<2,2,2,2>; q | k | v: gemm_lds_attn_kernel<true>",
+                                   "gemm_kernel": "gemm_lds_w8_kernel<2,2,2,4>, <2,2,2,2>; q | k | v (not counted): gemm_lds_attn_kernel<true>",
                                    "gemm_ms_per_step": round(gms / steps, 4),
                                    "gemm_tops": round(ops / (gms * 1e-3) / 1e12, 2) if gms > 0 else 0.0}}
     dims = [shape.d, 256, 1]
