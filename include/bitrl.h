@@ -117,6 +117,8 @@ int brl_unpack_codes(const void* packed, int n_out, int k_in, int8_t* codes_out,
  * (127 / a)), -127, 127); acc_tn = sum_k q_tk code_nk (int32, exact);
  * y_tn = (float(acc_tn) * (a / 127)) * beta (+ residual_tn), each fp32
  * operation rounded once, in that order.  No normalisation happens inside.
+ * 127 / a overflows fp32 below a = 3.8e-37 (only an eps_act as small lets a get
+ * there): the codes of such a token are +-127 by the sign of x, -127 for zeros.
  *
  * x [M, K] of x_dtype; y [M, N] fp32; residual [M, N] fp32 or NULL (may alias
  * y).  Optional taps (NULL to skip): xq_dbg [M, K] int8, absmax_dbg [M] fp32

@@ -89,11 +89,12 @@ __device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](fl
 
 // ---- activation codes ----
 // four codes clamp(rne(v s), -127, 127) as bytes: adding 1.5 * 2^23 rounds to an integer (nearest, ties to even) and leaves
-// it in the low bits.  |v s| cannot pass 127 by more than its rounding, so only the lower clamp is needed (for NaN).
+// it in the low bits.  Both clamps, before the rounding (one v_med3): v s is +-inf where s = 127 / a is (a < 3.8e-37), and
+// NaN gives -127.
 __device__ __forceinline__ uint32_t quantise_four(const float (&v)[4], float s) {
     uint32_t b[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) b[e] = __float_as_uint(fmaxf(v[e] * s, -127.f) + 12582912.f);
+    for (int e = 0; e < 4; ++e) b[e] = __float_as_uint(fminf(fmaxf(v[e] * s, -127.f), 127.f) + 12582912.f);
     return __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
 }
 __device__ __forceinline__ uint32_t quantise_four(const float4& v, float s) {

@@ -313,6 +313,47 @@ def test_bitlinear_few_tokens_in_one_launch(m, n, k, bf16):
         assert np.array_equal(out.cpu().numpy(), y_ref)
 
 
+@pytest.mark.parametrize("m,n,k", [
+    (1, 64, 256), (2, 70, 2560), (4, 64, 9216),       # one-launch kernels of a few tokens
+    (16, 64, 264), (32, 40, 2560),
+    (40, 64, 264), (1024, 32, 2560),                  # a workgroup per token
+    (1100, 64, 264), (1100, 32, 6912),                # a wavefront per token
+    (1100, 32, 9216),                                 # four of them
+])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_activation_codes_where_the_scale_overflows(m, n, k, bf16):
+    """Rows whose largest value is below 127 / FLT_MAX under a floor that small: 127 / a is infinite and every code is +-127
+    by its sign.  Rows just above have a finite scale, and other rows of the batch their usual codes.  (No zeros: the header
+    leaves 0 x inf to NaN's code.)"""
+    B, R = _mods()
+    print("scale overflows", m, n, k, bf16, flush=True)
+    case = synth.bitlinear_case(13, n, k, m)
+    X = case["X"]
+    X = np.where(X < 0, -1, 1).astype(np.float32) * np.maximum(np.abs(X), np.float32(0.5))      # (scaled below, still normal numbers)
+    for t, a in {0: 2e-37, 1: 3.75e-37, m - 1: 1.5e-37}.items():
+        if t < m:
+            X[t] *= np.float32(a / np.abs(X[t]).max())
+    if bf16:
+        X = synth.bf16_bits_to_f32(synth.to_bf16_bits(X))
+        x = R.bf16_from_bits(synth.to_bf16_bits(X))
+    else:
+        x = R.dev(X)
+    eps = 1e-38
+    codes, beta = O.ternary_quantize(case["W"])
+    taps = {}
+    with np.errstate(over="ignore", divide="ignore", under="ignore"):
+        O.bitlinear_forward(X, codes, beta, eps=eps, taps=taps)
+    assert np.array_equal(taps["xq"][m - 1], np.where(X[m - 1] > 0, 127, -127))
+    pl = R.quantize_linear(case["W"])
+    y = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    xq = torch.zeros((m, k), dtype=torch.int8, device="cuda")
+    am = torch.zeros((m,), dtype=torch.float32, device="cuda")
+    ws = R.Workspace(B.brl_bitlinear_workspace_bytes(m, n, k))
+    B.bitlinear_forward(pl.packed, pl.beta, n, k, x, m, eps, y, None, xq, am, None, ws.buf)
+    assert np.array_equal(xq.cpu().numpy(), taps["xq"])
+    assert np.array_equal(am.cpu().numpy().view(np.uint32), taps["absmax"].view(np.uint32))
+
+
 @pytest.mark.parametrize("m,d,f", [
     (512, 136, 1024), (544, 136, 1000),         # 512 and 544 tiles of 32 tokens x 32 column pairs, the second ragged
     (1536, 136, 2048), (1664, 136, 2048),       # 192 and 208 wide tiles: 75 and 81 % of 256 compute units
