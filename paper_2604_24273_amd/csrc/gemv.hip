@@ -470,8 +470,8 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_batch_kernel(GemvBatchArgs g)
 #pragma unroll
                 for (int u = 0; u < GV_X4; ++u) {
                     const int k = 4 * ((int)threadIdx.x + GV_THREADS * u);
-                    if (k < Kc) {          // zeros from K to a whole number of chunks
-                        const int word = (int)quantise_four(xv[t][u], sc);
+                    if (k < Kc) {          // zeros from K to a whole number of chunks (0 x inf would have a code)
+                        const int word = k < K ? (int)quantise_four(xv[t][u], sc) : 0;
                         qsum = __builtin_amdgcn_sdot4(word, 0x01010101, qsum, false);
                         xq[t][k >> 2] = word;
                     }

@@ -348,10 +348,18 @@ def test_activation_codes_where_the_scale_overflows(m, n, k, bf16):
     y = torch.empty((m, n), dtype=torch.float32, device="cuda")
     xq = torch.zeros((m, k), dtype=torch.int8, device="cuda")
     am = torch.zeros((m,), dtype=torch.float32, device="cuda")
+    acc = torch.zeros((m, n), dtype=torch.int32, device="cuda")
     ws = R.Workspace(B.brl_bitlinear_workspace_bytes(m, n, k))
-    B.bitlinear_forward(pl.packed, pl.beta, n, k, x, m, eps, y, None, xq, am, None, ws.buf)
+    B.bitlinear_forward(pl.packed, pl.beta, n, k, x, m, eps, y, None, xq, am, acc, ws.buf)
     assert np.array_equal(xq.cpu().numpy(), taps["xq"])
     assert np.array_equal(am.cpu().numpy().view(np.uint32), taps["absmax"].view(np.uint32))
+    assert np.array_equal(acc.cpu().numpy(), taps["acc"])
+    if m <= 4:                                        # the queued form has no taps: its results are the single call's
+        def ptr(t):
+            return torch.tensor([t.data_ptr()], dtype=torch.int64, device="cuda")
+        y2 = torch.empty_like(y)
+        B.bitlinear_forward_batch(ptr(pl.packed), ptr(pl.beta), n, k, ptr(x), B.BRL_BF16 if bf16 else B.BRL_F32, m, eps, ptr(y2), 1)
+        assert torch.equal(y2, y)
 
 
 @pytest.mark.parametrize("m,d,f", [
