@@ -123,8 +123,10 @@ int brl_unpack_codes(const void* packed, int n_out, int k_in, int8_t* codes_out,
  * x [M, K] of x_dtype; y [M, N] fp32; residual [M, N] fp32 or NULL (may alias
  * y).  Optional taps (NULL to skip): xq_dbg [M, K] int8, absmax_dbg [M] fp32
  * (the clamped a), acc_dbg [M, N] int32.
- * M <= 4 takes the bandwidth-bound GEMV path, larger M the int8 MFMA path (3..32
- * tokens of up to 5120 features in one launch with their quantisation).
+ * One launch: 1 and 2 tokens (bandwidth-bound GEMV); 3..16 of up to 5120
+ * features and 17..32 of up to 2048, N <= 8192 and y not overlapping x (int8
+ * MFMA); other 3 and 4 tokens (GEMV).  Everything else: quantisation, then
+ * the int8 MFMA product, so that y may overlap x there (never in a GEMV).
  * ------------------------------------------------------------------------ */
 size_t brl_bitlinear_workspace_bytes(int M, int N, int K);
 int bitlinear_forward(const void* packed, const float* beta, int N, int K,

@@ -206,7 +206,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
 // Every workgroup quantises all tokens again (what a compute unit spends its time on: some 20 vector instructions per four
 // values), a price that grows with tokens x k, against a launch, a pass through memory and the gap between two kernels.
 // Calls back to back, us, quantisation and product as two launches / here: 16 x 2048 x 2048 8.6 / 5.4 (what the host takes
-// for a call), 16 x 2560 x 5120 8.7 / 7.0, 32 x 8192 x 2560 8.6 / 7.7.
+// for a call; by GPU time 6.5 / 4.8), 16 x 2560 x 5120 8.7 / 7.0.  Where the line lies: rows_product_eligible below.
 // In LDS the 16-byte piece p (16 columns) of token r stands at slot (r + p) % (16 RW) of the piece's row: the dwords a
 // wavefront writes (one token, 16 pieces) and the pieces it reads (one super-block step, all tokens) fall on different banks.
 // ---------------------------------------------------------------------------
@@ -601,12 +601,16 @@ int launch_gemv(const void* x, int x_dtype, int M, int K, int N, const uint32_t*
 }
 
 // Does launch_rows_product take this product?  From three tokens on (gemv_kernel / here, us a call: 2 x 4096 x 4096 5.4 /
-// 6.4, 2 x 6912 x 2560 5.4 / 5.4, 3 x 6912 x 2560 6.2 / 5.4, 4 x 4096 x 4096 7.0 / 6.1, 4 x 2560 x 5120 8.0 / 6.9); as far as
-// a wavefront's registers and the operand rows beside the parts' 64 KB of LDS reach: 16 tokens of 5120, 32 of 2560 columns
-// (the slowest there, 27 x 8192 x 2560 in bf16: 8.5 as two launches, 7.8); one workgroup per compute unit and round, so not
-// past 256 of them.
+// 6.4, 2 x 6912 x 2560 5.4 / 5.4, 3 x 6912 x 2560 6.2 / 5.4, 4 x 4096 x 4096 7.0 / 6.1, 4 x 2560 x 5120 8.0 / 6.9); one
+// workgroup per compute unit and round, so not past 256 of them.  Up to 16 tokens as far as a wavefront's registers and the
+// operand rows beside the parts' 64 KB of LDS reach, 5120 columns: ahead there also by GPU time alone, in a captured graph whose
+// weights no other call reads (two launches / here: 16 x 8192 x 4096 8.5 / 7.2, x 5120 9.0 / 8.3; bf16, where this instance
+// spills four registers, 9.5 / 8.6, 16 x 2560 x 5120 9.3 / 8.3; on weights that every call reads again the bf16 one is level
+// from 4097 columns on, 0.93 to 1.05).  17 to 32 tokens only up to 2048: level by GPU time from 1025 on (32 x 8192 x 2048 7.6 /
+// 7.6, 17 x 2560 x 1280 1.02), a launch less for the host (8.2 / 7.3); at 2560 behind (24 x 4096 7.8 / 8.1, 32 x 128 7.3 / 7.8,
+// 32 x 8192 on resident weights 7.2 / 7.9) for 0 to 17 % of a call's time from the host.
 bool rows_product_eligible(int M, int N, int K) {
-    return M >= 3 && M <= 32 && round_up(N, NB) / NB <= 256 && K <= (M <= 16 ? 5120 : 2560);
+    return M >= 3 && M <= 32 && round_up(N, NB) / NB <= 256 && K <= (M <= 16 ? 5120 : 2048);
 }
 
 int launch_rows_product(const void* x, int x_dtype, int M, int K, int N, const uint32_t* packed, const float* beta,
@@ -639,8 +643,7 @@ int launch_rows_product(const void* x, int x_dtype, int M, int K, int N, const u
         else launch(one(), std::integral_constant<int, 20>());
     } else {
         if (K <= 1024) launch(two(), std::integral_constant<int, 4>());
-        else if (K <= 2048) launch(two(), std::integral_constant<int, 8>());
-        else launch(two(), std::integral_constant<int, 10>());
+        else launch(two(), std::integral_constant<int, 8>());
     }
     BRL_LAUNCH_CHECK("rows_product_kernel");
     return BRL_OK;

@@ -276,7 +276,8 @@ def test_bitlinear_dispatch_edges(m, n, k):
     (2, 64, 256, False), (3, 64, 256, False), (4, 33, 8, True), (15, 100, 1024, False),   # first token counts, ragged n, shortest k
     (16, 8192, 1032, True), (16, 8193, 1032, False),          # 256 workgroups; one more (two launches)
     (16, 70, 5120, False), (16, 70, 5128, False), (9, 40, 4104, True),                    # longest k at 16 tokens, past it
-    (17, 96, 2560, False), (17, 96, 2568, True), (32, 31, 2048, True), (32, 40, 2056, False),
+    (17, 96, 2560, False), (17, 96, 2568, True),              # (two launches)
+    (32, 31, 2048, True), (17, 40, 2048, False), (32, 40, 2056, False),                   # longest k at 32 tokens, past it
     (31, 64, 1024, False), (32, 64, 520, False), (33, 64, 520, False),                    # most tokens, past them
 ])
 def test_bitlinear_few_tokens_in_one_launch(m, n, k, bf16):
