@@ -1191,15 +1191,24 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
         if (g.nmb <= 1 || (glu && n32 <= 1024)) return launch_direct<1, 2, 8, 1, 4, true>(g, s);
         if (!glu && (long)((g.nmb + 1) / 2) * g.nnb <= 700) return launch_direct<2, 1, 8, 1, 4, true>(g, s);
         if (n64 <= (g.nsb >= 32 ? 1600 : 1000)) return launch_direct<2, 2, 4, 1, 3, true>(g, s);
-        // 128 x 256 tiles, two to a compute unit, where their last round is three quarters full or from six rounds on; otherwise
-        // 128 x 128, whose last round ends sooner.  Wide / narrow, quantisation included: 8192 x 3840 x 2560 (1.9 rounds) 109 /
-        // 114, 6144 x 2560 x 6912 (0.9) 154 / 165, 8192 x 13824 x 2560 (6.8) 364 / 373, 12288 x 2560 x 6912 (1.9) 314 / 330; 4096 x
-        // 2560 x 6912 (0.6) 120 / 112, 8192 x 2560 x 2560 (1.3) 84 / 82.7; by trace gate|up 4096 x 13824 x 2560 (3.4) 172 / 165,
-        // 4096 x 9600 x 3200 (2.4) 172 / 159, gate|up 4096 x 17280 x 3200 (4.3) 261 / 245.  Past the first round half a tile of
-        // padding in thirteen is too much (N = 3200: 9000 tokens 132 / 129, 20000 298 / 294; one in 38, N = 9600, is not: 723 / 744).
-        const long t_wide = (long)((g.nmb + 3) / 4) * ((g.nnb + 7) / 8), slots = 2L * device_cus();
-        const bool padded = t_wide > slots && 50 * (2 * t_wide - t_narrow) > t_narrow;
-        if (!padded && (t_wide >= 6 * slots || 4 * (t_wide % slots) >= 3 * slots || t_wide % slots == 0))
+        // 128 x 256 tiles, two to a compute unit, or 128 x 128, four to one, whose last round ends sooner.  Wide / narrow in us,
+        // quantisation included, 290 shapes in graphs:
+        // - the fullest compute unit must not have more to do: 5000 x 2560 x 2560 (2 wide or 4 narrow tiles) 57.3 / 61.7, 8192 x 2048 x
+        //   2560 (2, 4) 68.9 / 71.6, 8192 x 3840 x 2560 (4, 8) 112 / 117; but 4096 x 3072 x 2560 (2, 3) 55.0 / 51.9, 6144 x 2048 x 2560 (2,
+        //   3) 58.3 / 55.4, 6144 x 3072 x 2560 (3, 5) 81.5 / 77.7;
+        // - the last round three quarters full: 7040 x 6624 x 2560 (2.8) 1.02; 8320 x 9152 x 2560 (4.6) 0.995, 4096 x 6592 x 1024 (1.6) 0.96;
+        // - from six rounds on neither matters for gate|up or long k (1.01 to 1.04; 6.06 of them at 12032 x 8320: K = 4096 level, 2560 349 /
+        //   334), from seven on down to K = 2560 (9600 x 12864 1.02, 12544 x 11008 1.01, 24576 x 9600 of 3200 1.02; 29312 x 4352 0.99);
+        // - k not short past the first round: 4864 x 13568 (3.9) of K = 1024 104 / 105, 1536 139.5 / 144; 20184 x 4032 (4.9) 157 / 152, 197 /
+        //   202; 7680 x 12928 (6.0) 163 / 160, 212 / 212 (gate|up 16384 x 8192 of K = 1024 still 1.02);
+        // - next to no tiles of padding (one in 55 at 2048 x 7008 x 6912: 1.07, one in 75 at N = 9600: 932 / 954; one in 25 at N = 3200: 4096 tokens
+        //   60.6 / 59.7, 9000 132 / 129; the worst let through: 1024 x 12928 x 1024 0.965; N = 128, all of them double: 49152 tokens 173 / 160; N = 640, 16384 tokens 81 / 71).
+        const long t_wide = (long)((g.nmb + 3) / 4) * ((g.nnb + 7) / 8), cus = device_cus(), slots = 2 * cus;
+        const bool padded = 50 * (2 * t_wide - t_narrow) > t_narrow;
+        const bool level = 2 * ((t_wide + cus - 1) / cus) <= (t_narrow + cus - 1) / cus;
+        const bool full_round = 4 * (t_wide % slots) >= 3 * slots || t_wide % slots == 0;
+        const bool many = t_wide >= (glu || g.nsb >= 32 ? 6 : 7) * slots && (glu || g.nsb >= 20);
+        if (!padded && (many || (level && full_round && (t_wide <= slots || glu || g.nsb >= 12))))
             return launch_lds<2, 2, 2, 4, true>(g, s);
         return launch_lds<2, 2, 2, 2, true>(g, s);                     // 16 KB per stage
     }

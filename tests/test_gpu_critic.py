@@ -229,12 +229,20 @@ def test_int8_gate_up_tiles_give_the_same_bits(f):
 
 
 @pytest.mark.parametrize("m,n", [
-    (4096, 3072), (4096, 3040), (4065, 3330), (8192, 2048),     # three quarters of a round of 128 x 256 tiles, edges inside, a whole round
-    (4064, 2816), (8192, 2080), (9000, 3200),                   # beside the rule: 0.69 and 1.13 rounds, half a tile of padding in 13
+    (4193, 3072), (4100, 3290), (8192, 2048),                   # 396 and 429 tiles of 128 x 256, rows and columns ending inside a tile; 512
+    (4096, 3072), (4096, 3040),                                 # beside the rule: no more than three 128 x 128 tiles per compute unit,
+    (4064, 2816), (8192, 2080),                                 # 0.69 and 1.13 rounds,
+    (4065, 3330), (9000, 3200), (49152, 128), (24576, 320),     # padding: one tile in 27, one in 25, every other, one in three
 ])
 def test_int8_wide_tile(m, n):
     """Both sides of the rule that takes the 128 x 256 tile on int8 weights, as in the dispatch test above."""
     test_int8_dispatch_edges(m, n, 136)
+
+
+@pytest.mark.parametrize("m,n,k", [(8192, 3840, 1536), (8192, 3840, 1400)])
+def test_int8_wide_tile_past_the_first_round(m, n, k):
+    """Twelve super-blocks of k on 1.9 rounds of 128 x 256 tiles; eleven on 128 x 128."""
+    test_int8_dispatch_edges(m, n, k)
 
 
 @pytest.mark.parametrize("f", [6400, 6392])
