@@ -1164,12 +1164,14 @@ int ppo_head_update(const brl_ppo_config* cfg, float* params, float* adam_m, flo
         ta.clip_eps = (double)cfg->clip_eps; ta.ent_coef = (double)cfg->ent_coef; ta.row_terms = row_terms;
     }
     // An update's Adam and the next first layer in one launch.  A workgroup then takes all samples of its tile, so past 64 of
-    // them only where the tiles alone fill the chip.  A step in us, two launches / one: 64 samples, hidden 256, 1024 inputs 28.5 /
-    // 26.4, 2560 inputs 37.6 / 34.9, hidden 64, 2560 inputs 28.8 / 26.1; 256 samples, hidden 256, 2560 inputs 68.3 / 65.5, hidden
-    // 64, 2560 inputs 42.8 / 48.9.  Rows of more than 3072 inputs spill (64 samples, hidden 256, 3200 inputs: 40.7 / 41.2).
+    // them only where the tiles alone fill the chip, and up to 256: the tiles of 64 samples that two launches spread evenly are
+    // then more than the launch is worth.  A step in us, two launches / one: 64 samples, hidden 256, 1024 inputs 28.5 / 26.4, 2560
+    // inputs 37.6 / 34.9, hidden 64, 2560 inputs 28.8 / 26.1; 256 samples, hidden 256, 2560 inputs 68.3 / 65.5, hidden 64, 2560
+    // inputs 42.8 / 48.9; hidden 256, 2560 inputs, 512 samples 106.6 / 107.4, 1024 samples 186.4 / 194.4, two hidden layers of 320
+    // 321 / 351.  Rows of more than 3072 inputs spill (64 samples, hidden 256, 3200 inputs: 40.7 / 41.2).
     const int range_chunks = first_layer_range_chunks(L.head[0].dims[0]), tile_blocks = (fl.tiles[0] + fl.tiles[1]) * W.splits;
     const bool fused = W.tail && !norm_launch && fl.d % 16 == 0 && range_chunks <= FUSED_MAX_CHUNKS &&
-                       W.splits == first_layer_groups(fl.d) && (W.btiles == 1 || tile_blocks >= 256);
+                       W.splits == first_layer_groups(fl.d) && (W.btiles == 1 || (W.btiles <= 4 && tile_blocks >= 256));
     FusedArgs fu;
     memset(&fu, 0, sizeof(fu));
     if (fused) {

@@ -219,7 +219,8 @@ def test_gae_rollouts_share_workgroups(n_envs, T):
 @pytest.mark.parametrize("dims_p,dims_v,batch", [
     ([1024, 64, 5], [1024, 64, 1], 64), ([1040, 40, 5], [1040, 24, 1], 33),       # one block of samples; ranges that end early
     ([2048, 250, 3], [2048, 17, 1], 16), ([3072, 33, 4], [3072, 16, 1], 48),      # two and three rounds of parameters per thread
-    ([2560, 256, 18], [2560, 256, 1], 65), ([2560, 256, 18], [2560, 256, 1], 64),  # 256 tiles: any number of samples
+    ([2560, 256, 18], [2560, 256, 1], 65), ([2560, 256, 18], [2560, 256, 1], 64),  # 256 tiles: up to four blocks of samples
+    ([2560, 256, 18], [2560, 256, 1], 256), ([2560, 256, 18], [2560, 256, 1], 257),
     ([1024, 64, 5], [1024, 64, 1], 65), ([3088, 33, 4], [3088, 16, 1], 48),       # either limit passed
     ([48, 7], [48, 1], 16), ([64, 16, 8, 4], [64, 16, 1], 12),
 ])
