@@ -302,6 +302,7 @@ struct FragArgs {
     int B, S, NRB, Hq, Hkv, dh;
     SeqMap sm;
     int n_work;           // B * Hkv * chunks
+    int turn;             // 1: the chunks of queries start one further on from head to head (chunk_turn)
     float* out;           // [B*S, Hq*dh]
 };
 
@@ -424,14 +425,12 @@ __global__ __launch_bounds__(WPG * 64, 2) void attention_frag_kernel(FragArgs a)
     const int group = a.Hq / a.Hkv;
     const int U = group * a.NRB;                      // (query block, head in group) units of one key/value head
     const int chunks = (U + WPG - 1) / WPG;
-    // Consecutive work items (the chunks of one key/value head) run on one XCD and share its L2.  Workgroups go to the four
-    // shader engines of an XCD in turn, whether or not one of them has room, and a later chunk of queries has more keys: the
-    // chunks start one further on from head to head, or with four of them one engine would get all the long ones (it did:
-    // 1.2 wavefronts per SIMD instead of 2, heads of 100, 64 states of 512 tokens 715 -> 597 us).
+    // Consecutive work items (the chunks of one key/value head) run on one XCD and share its L2; the longest chunks of a head
+    // come first, unless that would put them all on one shader engine (chunk_turn).
     const int per_xcd = (a.n_work + 7) >> 3;
     const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (w >= a.n_work) return;
-    const int c = chunks - 1 - (w + w / chunks) % chunks;
+    const int c = chunks - 1 - (w + a.turn * (w / chunks)) % chunks;
     const int j = (w / chunks) % a.Hkv;
     const int b = w / (chunks * a.Hkv);
     const int len = seq_len(a.sm, b, a.S);
@@ -1058,6 +1057,19 @@ ShortForm short_form(int dh, int nrb, int B, int Hq, int Hkv) {
     return full && many ? ShortForm::PAIR : ShortForm::HEAD;
 }
 
+// Workgroups go to the four shader engines of an XCD in turn, whether or not one of them has room, and a later chunk of queries
+// has more keys: where a head has a multiple of four chunks, one engine would get all the long ones (four chunks, heads of 100, 64
+// states of 512 tokens: 1.2 wavefronts per SIMD instead of 2, 715 -> 597 us).  Then the chunks start one further on from head
+// to head.  That gives up the order by length, so it takes enough heads to make up for it, more for many chunks.  Gain at 1 / 4 / 8
+// / 16 / 48 heads per XCD, heads of 64, 100 and 128 alike: 4 chunks 1 / 1 / 1 / 1 / 1.05, 8 chunks 1 / 1 / 1.09 / 1.08 / 1.10, 12 chunks
+// 1 / 0.95 / 0.89 to 1 / 1.03 / 1.08 (1.04 at 12), 16 chunks 1 / 1.05 / 1.01 / 1.04 / 1.07 (0.92 at 6), 20 chunks 1 / 0.85 to 1 / 1 /
+// 1.02 / 1.04, 32 chunks 1 / 0.91 / 0.98 / 1.01 / 1.02; any other number at most 1.04, mostly a loss (3: 0.93 to 1, 5: 0.92 to 1.01, 7: 0.85
+// to 1, 40 chunks of one head per XCD 0.80).
+int chunk_turn(int chunks, int heads) {
+    const int per_xcd = heads / 8;
+    return chunks % 4 == 0 && (chunks <= 8 || (per_xcd >= 12 && 2 * per_xcd >= chunks)) ? 1 : 0;
+}
+
 template <int DHP, int VW>
 void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, bool values_ready, hipStream_t s) {
     const ShortForm form = values_ready ? ShortForm::PAIR : short_form(f.dh, p.NRB, f.B, f.Hq, f.Hkv);
@@ -1111,6 +1123,7 @@ int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& 
     f.KVF = p.KVF; f.QF = nullptr; f.B = B; f.S = S; f.NRB = nrb; f.Hq = n_heads; f.Hkv = n_kv_heads; f.dh = head_dim;
     f.sm = sm;
     f.n_work = B * n_kv_heads * chunks;
+    f.turn = chunk_turn(chunks, B * n_kv_heads);
     f.out = out;
     const dim3 pgrid((unsigned)(8 * (((size_t)B * nrb * n_kv_heads + 7) / 8)));
     const bool v4 = (head_dim / 2) % 4 == 0;          // rotary halves and head rows 16-byte aligned
@@ -1151,6 +1164,7 @@ int launch_attention_mfma_prepacked(int B, int S, int n_heads, int n_kv_heads, c
     f.B = B; f.S = S; f.NRB = nrb; f.Hq = n_heads; f.Hkv = n_kv_heads; f.dh = dh;
     f.sm.cu = nullptr; f.sm.b0 = 0;
     f.n_work = B * n_kv_heads * chunks;
+    f.turn = chunk_turn(chunks, B * n_kv_heads);
     f.out = out;
     LaunchTimer tm(BRL_KC_ATTENTION, s);
     const dim3 agrid((unsigned)(8 * ((f.n_work + 7) / 8)));

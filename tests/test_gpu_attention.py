@@ -252,3 +252,24 @@ def test_states_of_two_key_blocks_give_the_bits_of_the_pair(hq, hkv, longest, ba
             r0 = sum(lens[:i])
             ref = _oracle(qkv[r0:r0 + lens[i]], lens[i:i + 1], hq, hkv, dh, 10000.0)[0]
             assert np.abs(want[r0:r0 + lens[i]].reshape(ref.shape) - ref).max() <= ATTN_REL * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("S,batches", [
+    (384, (1, 24, 23)),                    # twelve chunks per head: their order turns from twelve heads per XCD on
+    (1024, (1, 32, 31)),                   # thirty-two: from sixteen on
+    (224, (2, 1)), (256, (2, 1)),          # seven never, eight always
+])
+def test_order_of_query_chunks_changes_no_bit(S, batches):
+    """The order in which a head's chunks of queries are dispatched turns from head to head or not: states that two batches
+    share get the same bits, and the last one matches the oracle."""
+    B, R = _mods()
+    hq, hkv, dh = 16, 4, 32
+    n = max(batches)
+    qkv = synth.normal(47, 5, (n * S, (hq + 2 * hkv) * dh))
+    print("query chunks", S, batches, flush=True)
+    want = _run(B, R, qkv, [S] * n, S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA)
+    for b in batches:
+        if b != n:
+            assert np.array_equal(_run(B, R, qkv[:b * S], [S] * b, S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA), want[:b * S]), b
+    ref = _oracle(qkv[(n - 1) * S:], [S], hq, hkv, dh, 10000.0)[0]
+    assert np.abs(want[(n - 1) * S:].reshape(ref.shape) - ref).max() <= ATTN_REL * np.abs(ref).max()
