@@ -101,8 +101,11 @@ __device__ inline int plane_offset(int r, int chunk) {
 }
 
 // NIT of the block's load instructions, from it_begin on: a share of the rows for each of several wavefronts.  The count
-// is a template argument so that all of a wavefront's loads are in flight together (at most 32 / VW of them).
-template <int DHP, int VW, int NIT = 32 / (64 / (DHP / VW))>
+// is a template argument so that a wavefront's loads can be in flight together (at most 32 / VW of them); the compiler decides
+// how many are, by the registers it wants.  AT_ONCE: all of them, whatever it wants.  For attention_short_kernel on heads of
+// up to 32, where it had come to take four trips to memory (heads of 32, 1 state of 32 tokens 8.3 us, 6.7 at once; 1024 states 31.0 /
+// 28.7); wider heads need the wavefronts more (100, 64 states of 32 tokens 31.3 / 32.6; 64 level).
+template <int DHP, int VW, int NIT = 32 / (64 / (DHP / VW)), bool AT_ONCE = false>
 __device__ __forceinline__ void stage_rope_rows(const float* rows, int ld, int n_valid, const float* cp, const float* sp,
                                                 int dh, float scale, char* region, int lane, int it_begin = 0) {
     typedef typename VecOf<VW>::type V;
@@ -116,20 +119,29 @@ __device__ __forceinline__ void stage_rope_rows(const float* rows, int ld, int n
     const int ds = in_head ? d : 0;
     const int i = in_head ? (first ? d : d - half) : 0;
     const int dp = in_head ? (first ? d + half : d - half) : 0;
+    static_assert(!AT_ONCE || NIT * VW <= 16, "64 registers of a lane");
+    V xs[NIT], xp[NIT], cs[NIT], sn[NIT];
+    auto request = [&](int u) {
+        const int rc = min((it_begin + u) * RPI + lane / LPR, n_valid - 1);
+        const float* row = rows + (size_t)rc * ld;
+        xs[u] = *reinterpret_cast<const V*>(row + ds);
+        xp[u] = *reinterpret_cast<const V*>(row + dp);
+        cs[u] = *reinterpret_cast<const V*>(cp + (size_t)rc * half + i);
+        sn[u] = *reinterpret_cast<const V*>(sp + (size_t)rc * half + i);
+    };
+    if constexpr (AT_ONCE) {
+#pragma unroll
+        for (int u = 0; u < NIT; ++u) request(u);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll(NIT < 32 / VW ? NIT : 32 / VW)
     for (int u = 0; u < NIT; ++u) {
-        const int it = it_begin + u;
-        const int r = it * RPI + lane / LPR;
-        const int rc = min(r, n_valid - 1);
-        const float* row = rows + (size_t)rc * ld;
-        const V xs = *reinterpret_cast<const V*>(row + ds);
-        const V xp = *reinterpret_cast<const V*>(row + dp);
-        const V cs = *reinterpret_cast<const V*>(cp + (size_t)rc * half + i);
-        const V sn = *reinterpret_cast<const V*>(sp + (size_t)rc * half + i);
-        const float* fs = reinterpret_cast<const float*>(&xs);
-        const float* fp = reinterpret_cast<const float*>(&xp);
-        const float* fc = reinterpret_cast<const float*>(&cs);
-        const float* fn = reinterpret_cast<const float*>(&sn);
+        if constexpr (!AT_ONCE) request(u);
+        const int r = (it_begin + u) * RPI + lane / LPR;
+        const float* fs = reinterpret_cast<const float*>(&xs[u]);
+        const float* fp = reinterpret_cast<const float*>(&xp[u]);
+        const float* fc = reinterpret_cast<const float*>(&cs[u]);
+        const float* fn = reinterpret_cast<const float*>(&sn[u]);
         const bool keep = in_head && r < n_valid;
         float v[VW];
 #pragma unroll
@@ -162,7 +174,9 @@ __device__ inline uint4 staged_fragment(const char* region, int ks, int lane, in
 // once, every load in flight together), rotate, scale and split them into the same planes.  dh / 2 need not be a multiple of
 // four: the last lanes then repeat components of their neighbours.  Rows past the last repeat it (no one stores them).
 // Against stage_rope_rows (every element twice, a quarter of the loads in flight): heads of 100, 1 state of 128 tokens 22.6 ->
-// 21.1 us, 64 states 234 -> 203, pack kernel included.
+// 21.1 us, 64 states 234 -> 203, pack kernel included; 16 / 16 heads of 64, 16 states of 96 tokens 20.4 -> 16.4.  Not ahead
+// everywhere: 256 states of 128 tokens with 16 / 16 heads of 64 or 128, which memory bounds, 218 -> 227 and 421 -> 432, one state of
+// 64 with heads of 16 10.2 -> 10.6 (with the read-ahead of compute).
 template <int DHP, int VW>
 struct QueryRows {
     static constexpr int NQ = DHP / 32;               // groups of 16 components of a first half
@@ -573,7 +587,7 @@ __global__ __launch_bounds__(DHP * 4) void attention_short_kernel(FragArgs a) {
                 vv[tt][e] = col[(unsigned)(min(row, len - 1) * a.ld)];
             }
     }
-    stage_rope_rows<DHP, VW, ITS / DB>(rows + (first ? head * a.dh : dq + j * a.dh), a.ld, len, a.cos_t, a.sin_t, a.dh,
+    stage_rope_rows<DHP, VW, ITS / DB, DHP == 32>(rows + (first ? head * a.dh : dq + j * a.dh), a.ld, len, a.cos_t, a.sin_t, a.dh,
                                        first ? a.qscale : 1.0f, first ? qpark : kpark, lane, share * (ITS / DB));
     __syncthreads();
     if (!first) return;
