@@ -80,8 +80,8 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
     lo = __builtin_bit_cast(uint32_t, l);
 }
 
-// k-steps of 16 components of a score.  Heads of 100 (the only ones whose rotary halves are not whole quads) end in the seventh:
-// the eighth would multiply zeros.
+// k-steps of 16 components of a score.  Heads of 100 end in the seventh, the eighth would multiply zeros; so may all of up to 112
+// whose rotary halves are not whole quads, and wider ones of that kind are refused (attn_head_dim_ok).
 template <int DHP, int VW> constexpr int k_steps = DHP == 128 && VW == 2 ? 7 : DHP / 16;
 
 template <int VW> struct VecOf;
@@ -1017,7 +1017,17 @@ __global__ __launch_bounds__(256, 2) void attention_rows_kernel(FragArgs a) {
     }
 }
 
-inline int padded_head_dim(int dh) { return dh <= 32 ? 32 : (dh <= 64 ? 64 : 128); }
+constexpr int padded_head_dim(int dh) { return dh <= 32 ? 32 : (dh <= 64 ? 64 : 128); }
+constexpr int head_k_steps(int dh) {
+    const int dhp = padded_head_dim(dh);
+    return dhp == 128 ? ((dh / 2) % 4 ? k_steps<128, 2> : k_steps<128, 4>) : dhp / 16;
+}
+// what the kernels can do: rows of whole quads, rotary halves that hold one (QueryRows), no component past the last k-step
+constexpr bool attn_head_dim_ok(int dh) { return dh % 4 == 0 && dh >= 8 && dh <= 128 && dh <= 16 * head_k_steps(dh); }
+static_assert(attn_head_dim_ok(16) && attn_head_dim_ok(32) && attn_head_dim_ok(64) && attn_head_dim_ok(100) && attn_head_dim_ok(128),
+              "the head sizes the entry points accept");
+static_assert(!attn_head_dim_ok(4) && !attn_head_dim_ok(102) && attn_head_dim_ok(108) && !attn_head_dim_ok(116) &&
+              attn_head_dim_ok(120) && !attn_head_dim_ok(124) && !attn_head_dim_ok(132), "and what no kernel can do");
 
 }  // namespace
 
@@ -1117,8 +1127,8 @@ void launch_pair(const PackArgs& p, const FragArgs& f, dim3 pgrid, int n_work, b
 int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& sm, int n_heads, int n_kv_heads,
                           int head_dim, const float* cos_t, const float* sin_t, void* frag_ws, float* out, hipStream_t s,
                          bool values_ready) {
-    if (head_dim % 4 != 0 || head_dim > 128 || ld % 4 != 0) {
-        set_error("attention: head_dim %d must be a multiple of 4, at most 128 (row stride %d a multiple of 4)",
+    if (!attn_head_dim_ok(head_dim) || ld % 4 != 0) {
+        set_error("attention: head_dim %d must be a multiple of 4 from 8 to 112, or of 8 up to 128 (row stride %d a multiple of 4)",
                   head_dim, ld);
         return BRL_EINVAL;
     }
@@ -1154,8 +1164,8 @@ int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& 
 }
 
 void attention_key_block(int head_dim, int& k_fragments, int& fragments) {
-    const int dhp = padded_head_dim(head_dim), ks = (head_dim / 2) % 4 && dhp == 128 ? k_steps<128, 2> : dhp / 16;
-    k_fragments = 2 * ks;
+    const int dhp = padded_head_dim(head_dim);
+    k_fragments = 2 * head_k_steps(head_dim);
     fragments = k_fragments + dhp / 8;                // two steps of 16 keys, hi and lo, for each 32 components
 }
 
