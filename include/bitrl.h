@@ -329,9 +329,9 @@ int encoder_forward_packed(const brl_encoder* enc /* HOST */, const int32_t* ids
  * cu_seqlens[b] .. cu_seqlens[b+1]-1 (DEVICE and HOST copies of the same
  * [B+1] int32 array, lengths in 1..S, else BRL_EINVAL) and S bounds the
  * lengths.  head_dim in {16, 32, 64, 100, 128}; attn_precision BRL_ATTN_*.
- * With BRL_ATTN_MFMA, states of at most 32 tokens take one of two one-kernel
- * forms where these are ahead, everything else the pack + fragment kernels; all
- * give the same bits.
+ * With BRL_ATTN_MFMA, states of at most 32 tokens (head_dim 128: 64) take one of
+ * three one-kernel forms where these are ahead, everything else the pack +
+ * fragment kernels; all give the same bits.
  * ------------------------------------------------------------------------ */
 size_t brl_attention_workspace_bytes(int B, int S, int n_heads, int n_kv_heads, int head_dim);
 int attention_forward(const float* qkv, int B, int S,

@@ -747,7 +747,8 @@ __global__ __launch_bounds__(512) void attention_group_kernel(FragArgs a) {
 // grid, they take longer), all heads' rows one after the other in units of 32, a unit's columns shared out over the
 // wavefronts that have no unit.  The arithmetic per element and its order are those of the pair: same bits.
 // 1024 states of 15 .. 40 tokens, 20 / 5 heads: pack 80 + fragments 309 us, 213 here (725 MB once; 225 with q read in operand
-// order, 236 as two launches); 64 states 36 -> 19, 1 state 17 -> 11.  What other sizes take: short_form below.
+// order, 236 as two launches); 64 states 36 -> 19, 1 state 17 -> 11.  What other sizes take: short_form below.  (The layout of
+// rows and fragments is that of heads of 128; none for other head sizes has been built, they keep the pair past 32 tokens.)
 constexpr int ROWS_D = 128, ROWS_KS = AttnTile<ROWS_D, 4>::KS;
 constexpr int ROWS_STAGE = AttnTile<ROWS_D, 4>::KVFR * 64;
 struct RowsBlock {                                    // what a thread of 256 stages of a key block
@@ -1056,9 +1057,12 @@ namespace {
 //   two and five: O up to one, four and four workgroups per compute unit, then N (16 / 16, 32 tokens, 4 states 8.8 / 8.2, 64
 //   states 11.9 / 14.7; 16 / 8, 32 tokens, 128 states 19.7 / 17.5, 8 tokens, 512 states 39 / 42; 30 / 6, 8 tokens, 64 states
 //   14.5 / 13.3, 256 states 37 / 42), of five P beyond 8192 query heads (8 tokens, 1024 states 127 / 110).
-// - between 64 and 128 (100): N; O where N has more than three workgroups per compute unit but O, with three of four
-//   wavefronts busy, at most one; P for full groups of many states.  (The lines are those that heads of 128 had before R:
-//   20 / 5, 32 tokens, 48 states 19.1 / 16.4; 56 states 21.3 / 25.7; 512 states N 136.5 / P 133.5, 2048 states 532 / 486.)
+// - between 64 and 128 (100; N / O / P): N; O where N has more than three workgroups per compute unit but O, with three of four
+//   wavefronts busy, at most one; P for full groups of many states (20 / 5, 20 tokens, 32 states 14.1 / 13.8 / 16.4, 38 states 14.1 /
+//   13.9 / 16.6, 48 states 16.5 / 14.5 / 17.4, 56 states 18.9 / 23.6 / 21.1, 1024 states 257 / 249 / 190; 32 tokens, 512 states 158 / 168 /
+//   123; 32 / 32, 32 tokens, 64 states 30 / 82 / 52, 1024 states 565 / 1574 / 874).  P's line was drawn for heads of 128: at 100 P is
+//   ahead of it already in full groups of 256 states (20 tokens 54 / 55 / 44, 32 tokens 62 / 66 / 55; 409 of 32 95 / 103 / 102) and
+//   in groups of five (30 / 6, 20 tokens, 1024 states 378 / 549 / 334).
 enum class ShortForm { HEAD, GROUP, ROWS, PAIR };
 ShortForm short_form(int dh, int nrb, int B, int Hq, int Hkv) {
     constexpr long CUS = 256;

@@ -1110,7 +1110,9 @@ int launch_gemm_attn(const ActBuf& a, const WeightSegs& w, int M, int K, const A
 // Whole key blocks of a uniform batch and column blocks that are all k or all v, where the wide tile is the one to take.
 // Encoders of four layers, width 1024, with / without (us): heads of 100, 8 states of 1024 tokens 2293 / 2499, 76 of 128 (8
 // heads) 847 / 970; of 64, 512 states of 64 tokens 4055 / 4433, 128 of 128 (4 of 16 heads have values) 1069 / 1093; of 32, 64 of
-// 128 tokens 720 / 758, 128 of 64 (8 of 32) 633 / 630; of 16, 64 of 128 tokens 864 / 957.  Heads of 128: gemm_attn_eligible.
+// 128 tokens 720 / 758, 128 of 64 (8 of 32) 633 / 630; of 16, 64 of 128 tokens 864 / 957; 2 of 32 of 64, 128 states of 128
+// tokens 1556 / 1547, 256 of 64 level.  Heads of 128: gemm_attn_eligible.  int8 weights: that kernel has not been built, they keep
+// the pack kernel.
 bool gemm_values_eligible(int M, int n_heads, int n_kv_heads, int head_dim, int S, int w8) {
     const int dq = n_heads * head_dim, dkv = n_kv_heads * head_dim;
     return !w8 && head_dim < 128 && S > 32 && S % 32 == 0 && M % S == 0 && dq % 32 == 0 && dkv % 32 == 0 &&

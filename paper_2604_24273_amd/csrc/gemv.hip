@@ -209,6 +209,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(GemvArgs g) {
 // for a call; by GPU time 6.5 / 4.8), 16 x 2560 x 5120 8.7 / 7.0.  Where the line lies: rows_product_eligible below.
 // In LDS the 16-byte piece p (16 columns) of token r stands at slot (r + p) % (16 RW) of the piece's row: the dwords a
 // wavefront writes (one token, 16 pieces) and the pieces it reads (one super-block step, all tokens) fall on different banks.
+// Ternary weights only: a form for int8 blobs, whose few-token products run gemm_direct_kernel, has not been built.
 // ---------------------------------------------------------------------------
 typedef int rp_v4i __attribute__((ext_vector_type(4)));
 typedef int rp_v16i __attribute__((ext_vector_type(16)));

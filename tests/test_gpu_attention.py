@@ -192,9 +192,11 @@ def test_short_state_kernels_meet_at_the_dispatch_line(hq, hkv, dh, S):
 
 
 @pytest.mark.parametrize("hq,hkv,dh,batches", [
-    (20, 5, 128, (1, 38, 39, 51, 52, 409, 410)),       # query head; query head | group | query head | pair
+    (20, 5, 100, (1, 38, 39, 51, 52, 409, 410)),       # query head; query head | group | query head | pair
     (32, 4, 100, (24, 25, 32, 33, 127, 128)),          # two groups of four per key/value head
-    (30, 6, 128, (1, 60, 300)),                        # groups of five: query head only
+    (30, 6, 100, (1, 60, 300)),                        # groups of five: query head only
+    (20, 5, 128, (1, 25, 26, 38, 39, 51, 52, 409, 410)),   # query head | rows
+    (30, 6, 128, (1, 17, 18, 60, 300)),                # query head | rows, the second workgroup of a group with one head
     (16, 16, 64, (1, 16, 17)),                         # group | query head
     (32, 4, 64, (1, 256, 257)),                        # group | pair
     (28, 4, 64, (1, 256, 257)),                        # the last wavefront of a group idle
@@ -205,8 +207,9 @@ def test_short_state_kernels_meet_at_the_dispatch_line(hq, hkv, dh, S):
     (16, 8, 32, (1, 130)),                             # groups of two: query head only
 ])
 def test_short_state_forms_give_the_same_bits(hq, hkv, dh, batches):
-    """Batches on both sides of every line between the three forms of states of at most 32 tokens, uniform and ragged: the
-    states that they share get the same bits, first and last match the oracle."""
+    """Batches on both sides of every line between the four forms of states of at most 32 tokens (a workgroup per query head,
+    per group of four, the same from the fp32 rows, the pair of kernels), uniform and ragged: the states that they share get
+    the same bits, first and last match the oracle."""
     B, R = _mods()
     n = batches[-1]
     for S, lens in ((19, [19] * n), (None, [1 + (11 * i + 30) % 32 for i in range(n)])):

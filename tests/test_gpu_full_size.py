@@ -242,6 +242,7 @@ def test_fused_qkv_path_replays_from_a_hip_graph():
 @pytest.mark.parametrize("heads,kv_heads,head_dim,n_states,S", [
     (8, 8, 100, 76, 128), (24, 8, 100, 64, 96),                      # heads across column blocks; states inside row tiles
     (16, 4, 64, 128, 128), (8, 8, 32, 512, 64), (16, 16, 16, 512, 64),
+    (8, 8, 100, 99, 96), (8, 8, 100, 101, 96), (16, 4, 64, 255, 64),  # the last row tile one, three, two blocks of four
     (8, 8, 100, 76, 120), (12, 12, 100, 64, 96),                     # beside the rule: ragged key blocks, ragged segments
 ])
 def test_qkv_product_writing_value_operands_matches_two_step_path(heads, kv_heads, head_dim, n_states, S):
