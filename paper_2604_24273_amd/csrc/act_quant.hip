@@ -332,12 +332,14 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_wave_kernel(QK a) {
         for (int c = 0; c < NC; ++c) {
             const int k = 4 * (lane + 64 * c);
             const uint32_t word = quantise_four(v[c], sc);
-            if (k < a.Kp) {                    // (what lies past it takes no part in the sum: 0 x inf has a code)
-                sum = __builtin_amdgcn_sdot4((int)word, 0x01010101, sum, false);
-                myrow[k >> 2] = word;
-            }
+            sum = __builtin_amdgcn_sdot4((int)word, 0x01010101, sum, false);
+            if (k < a.Kp) myrow[k >> 2] = word;
             if (a.xq_rowmajor && live && k < K) *reinterpret_cast<uint32_t*>(a.xq_rowmajor + (size_t)row * K + k) = word;
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if (sc == INFINITY) {                  // zeros past Kp have counted with -127 (up to it the product subtracts them again)
+            for (int c = 0; c < NC; ++c)
+                if (4 * (lane + 64 * c) >= a.Kp) sum += 4 * 127;
         }
         sum = wave_total(sum);
         if (lane == 0 && live) {
@@ -428,7 +430,7 @@ __global__ __launch_bounds__(NWV * 64) void act_quant_row_kernel(QK a) {
 #pragma unroll
     for (int i = 0; i < HV4; ++i) {
         const int k = 4 * (lane + 64 * (NWV * i + wave));
-        const uint32_t word = k < K ? quantise_four(v[i], s) : 0u;       // (0 x inf would have a code)
+        const uint32_t word = quantise_four(v[i], s) & (k < K ? ~0u : 0u);       // (0 x inf would have a code)
         sum = __builtin_amdgcn_sdot4((int)word, 0x01010101, sum, false);
         if (a.xq_rowmajor && k < K) *reinterpret_cast<uint32_t*>(a.xq_rowmajor + (size_t)row * K + k) = word;
         // lanes 4 j .. 4 j + 3 hold 16 consecutive k: lane 4 j writes them as one piece of the tile (quad_perm broadcasts)

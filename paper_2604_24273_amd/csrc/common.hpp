@@ -90,7 +90,7 @@ __device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](fl
 // ---- activation codes ----
 // four codes clamp(rne(v s), -127, 127) as bytes: adding 1.5 * 2^23 rounds to an integer (nearest, ties to even) and leaves
 // it in the low bits.  Both clamps, before the rounding (one v_med3): v s is +-inf where s = 127 / a is (a < 3.8e-37), and
-// NaN gives -127.
+// NaN gives -127; so do the zeros past a row's end with such a scale, which must not count then.
 __device__ __forceinline__ uint32_t quantise_four(const float (&v)[4], float s) {
     uint32_t b[4];
 #pragma unroll
