@@ -47,6 +47,7 @@ struct PackArgs {
     const float* cos_t;   // [S, dh/2]
     const float* sin_t;
     uint4* KVF;           // [B][Hkv][NRB][ K: [KS][hi,lo] | V: [DB][2][hi,lo] ][64 lanes]
+    int by_xcd;           // neighbouring heads on one XCD (pack_by_xcd), else the order of the workgroups
 };
 
 __device__ inline uint4 pack8h(const float (&x)[8], bool lo_part) {
@@ -175,8 +176,8 @@ __device__ inline uint4 staged_fragment(const char* region, int ks, int lane, in
 // four: the last lanes then repeat components of their neighbours.  Rows past the last repeat it (no one stores them).
 // Against stage_rope_rows (every element twice, a quarter of the loads in flight): heads of 100, 1 state of 128 tokens 22.6 ->
 // 21.1 us, 64 states 234 -> 203, pack kernel included; 16 / 16 heads of 64, 16 states of 96 tokens 20.4 -> 16.4.  Not ahead
-// everywhere: 256 states of 128 tokens with 16 / 16 heads of 64 or 128, which memory bounds, 218 -> 227 and 421 -> 432, one state of
-// 64 with heads of 16 10.2 -> 10.6 (with the read-ahead of compute).
+// everywhere: 256 states of 128 tokens with 16 / 16 heads of 64, which memory bounds, 218 -> 227, one state of 64 with heads of 16 10.2
+// -> 10.6 (with the read-ahead of compute).
 template <int DHP, int VW>
 struct QueryRows {
     static constexpr int NQ = DHP / 32;               // groups of 16 components of a first half
@@ -239,10 +240,8 @@ __global__ __launch_bounds__(256) void attn_pack_kernel(PackArgs a) {
     constexpr int KVFR = KS * 2 + DB * 4;             // 1 KB fragments per key block
     __shared__ __attribute__((aligned(16))) char park[128 * DHP];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // neighbouring heads on one XCD: their rows share lines where a head is no whole number of them (heads of 100: 1.09 GB
-    // fetched for 0.84 in the order of the workgroups; 398 -> 383 us for 64 states of 512 tokens)
     const int n_work = a.B * a.NRB * a.Hkv, per_xcd = (n_work + 7) >> 3;
-    const int w = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    const int w = a.by_xcd ? (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     if (w >= n_work) return;
     const int hd = w % a.Hkv;
     const int rb = (w / a.Hkv) % a.NRB;
@@ -1085,6 +1084,14 @@ ShortForm short_form(int dh, int nrb, int B, int Hq, int Hkv) {
     return full && many ? ShortForm::PAIR : ShortForm::HEAD;
 }
 
+// The pack kernel's work by XCD: neighbouring heads then share lines where a head is no whole number of them (heads of 100: 1.09
+// GB fetched for 0.84 in the order of the workgroups; 398 -> 383 us for 64 states of 512 tokens), and the fragment kernel finds
+// what its XCD wrote in that L2 (gain up to 32 MB of fragments: 1.0 to 1.28, any head size).  Heads of 128 are whole lines; from 100 MB
+// of their fragments on the plain order is level or ahead (16 / 16, by XCD / plain: 64 states of 72 tokens, 96 MB 60.3 / 61.3, of 128,
+// 128 MB 106 / 104, of 256, 256 MB 238 / 228, 128 of 96, 192 MB 172 / 162; 20 / 5, 120 to 160 MB 0.994 to 1.004).  Heads of 64: 0.97 to 1.06
+// there, of 32 and 16 1.0 to 1.16.
+bool pack_by_xcd(int head_dim, size_t fragment_bytes) { return head_dim != 128 || fragment_bytes <= (size_t)100 << 20; }
+
 // Workgroups go to the four shader engines of an XCD in turn, whether or not one of them has room, and a later chunk of queries
 // has more keys: where a head has a multiple of four chunks, one engine would get all the long ones (four chunks, heads of 100, 64
 // states of 512 tokens: 1.2 wavefronts per SIMD instead of 2, 715 -> 597 us).  Then the chunks start one further on from head
@@ -1145,6 +1152,7 @@ int launch_attention_mfma(const float* qkv, int ld, int B, int S, const SeqMap& 
     p.sm = sm;
     p.cos_t = cos_t; p.sin_t = sin_t;
     p.KVF = static_cast<uint4*>(frag_ws);
+    p.by_xcd = pack_by_xcd(head_dim, attention_mfma_ws_bytes(B, S, n_heads, n_kv_heads, head_dim)) ? 1 : 0;
     FragArgs f;
     f.qkv = qkv; f.ld = ld; f.cos_t = cos_t; f.sin_t = sin_t;
     f.qscale = (float)(1.0 / sqrt((double)head_dim)) * 1.4426950408889634f;

@@ -276,3 +276,16 @@ def test_order_of_query_chunks_changes_no_bit(S, batches):
             assert np.array_equal(_run(B, R, qkv[:b * S], [S] * b, S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA), want[:b * S]), b
     ref = _oracle(qkv[(n - 1) * S:], [S], hq, hkv, dh, 10000.0)[0]
     assert np.abs(want[(n - 1) * S:].reshape(ref.shape) - ref).max() <= ATTN_REL * np.abs(ref).max()
+
+
+def test_order_of_packing_changes_no_bit():
+    """Heads of 128 whose fragments take just under and over 100 MB (133 and 134 states of three key blocks): the pack kernel's
+    work goes by XCD or in plain order, the states they share get the same bits, and the last one matches the oracle."""
+    B, R = _mods()
+    hq, hkv, dh, S, n = 8, 8, 128, 96, 134
+    qkv = synth.normal(53, 5, (n * S, (hq + 2 * hkv) * dh))
+    two = _run(B, R, qkv, [S] * n, S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA)
+    one = _run(B, R, qkv[:(n - 1) * S], [S] * (n - 1), S, hq, hkv, dh, 10000.0, B.BRL_ATTN_MFMA)
+    assert np.array_equal(one, two[:(n - 1) * S])
+    ref = _oracle(qkv[(n - 1) * S:], [S], hq, hkv, dh, 10000.0)[0]
+    assert np.abs(two[(n - 1) * S:].reshape(ref.shape) - ref).max() <= ATTN_REL * np.abs(ref).max()
