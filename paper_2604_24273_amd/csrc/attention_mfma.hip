@@ -1048,7 +1048,11 @@ namespace {
 // pack and fragment kernels.  All give the same bits.  Times of 1 .. 2048 states in us:
 // - heads of 128, one block: N up to 512 query heads and for groups of one, else R (20 / 5, 20 tokens, 16 states 10.1 / 10.9,
 //   32 states 13.3 / 11.5, 64 states 19.7 / 15.7, 1024 states 212 (P) / 151; 12 / 4, 32 tokens, 32 states 11.0 / 11.6, 48 states
-//   14.7 / 12.2; 16 / 8, 20 tokens, 64 states 17.2 / 15.1; 16 / 16, 20 tokens, 512 states 106 / 131).
+//   14.7 / 12.2; 16 / 8, 20 tokens, 64 states 17.2 / 15.1; 16 / 16, 20 tokens, 512 states 106 / 131).  Groups of two and five leave
+//   wavefronts of R idle: N while some compute units have a second workgroup of R but none more than three of N, or a third
+//   of R but none more than six (groups of two: five) of N.  R / N, over 1300 shapes: groups of two, 257 to 384 and 513 to 640
+//   workgroups of R 1.05 and 1.06 (0.95 to 1.12), 385 to 512 0.83 to 0.95, 641 to 768 0.95 to 1.02; of five, 257 to 304 1.10, 308
+//   to 352 0.97, 513 to 608 1.07, 610 and 612 1.04 to 1.07.
 //   Two blocks: R (20 / 5, 15 .. 40 tokens, P / R: 1 state 16.9 / 11.2, 64 states 36 / 19, 1024 states 374 / 213; 64 tokens: 16
 //   states 23.1 / 15.5, 1024 states 499 / 446; 16 / 16, 64 tokens, 64 states 54 / 51; never behind in 120 of them) but P for
 //   workgroups half empty of which there are many (30 / 6, 64 tokens, 32 states 37.9 / 33.7, 64 states 52.7 / 58.2).
@@ -1073,7 +1077,10 @@ ShortForm short_form(int dh, int nrb, int B, int Hq, int Hkv) {
     const bool three_of_four = group >= 3 * chunks, full = 2 * group >= 7 * chunks;
     if (dh == ROWS_D && nrb == 2) return group > 4 && !three_of_four && work > 2 * CUS ? ShortForm::PAIR : ShortForm::ROWS;
     if (nrb > 1) return ShortForm::PAIR;
-    if (dh == ROWS_D) return group > 1 && heads > 2 * CUS ? ShortForm::ROWS : ShortForm::HEAD;
+    if (dh == ROWS_D) {
+        const bool few = (work > CUS && heads <= 3 * CUS) || (work > 2 * CUS && heads <= (group == 2 ? 5 : 6) * CUS);
+        return group > 1 && heads > 2 * CUS && (three_of_four || !few) ? ShortForm::ROWS : ShortForm::HEAD;
+    }
     if (dhp == 32) return three_of_four && heads > 4 * CUS ? ShortForm::GROUP : ShortForm::HEAD;
     if (dhp == 64) {
         if (!three_of_four) {

@@ -197,6 +197,8 @@ def test_short_state_kernels_meet_at_the_dispatch_line(hq, hkv, dh, S):
     (30, 6, 100, (1, 60, 300)),                        # groups of five: query head only
     (20, 5, 128, (1, 25, 26, 38, 39, 51, 52, 409, 410)),   # query head | rows
     (30, 6, 128, (1, 17, 18, 60, 300)),                # query head | rows, the second workgroup of a group with one head
+    (30, 6, 128, (21, 22, 25, 26, 42, 43, 51, 52)),    # groups of five: rows | query head | rows | query head | rows
+    (16, 8, 128, (48, 49, 64, 65, 80, 81)),            # groups of two: query head | rows | query head | rows
     (16, 16, 64, (1, 16, 17)),                         # group | query head
     (32, 4, 64, (1, 256, 257)),                        # group | pair
     (28, 4, 64, (1, 256, 257)),                        # the last wavefront of a group idle
@@ -233,6 +235,7 @@ def test_short_state_forms_give_the_same_bits(hq, hkv, dh, batches):
     (7, 1, 64, (66,)), (30, 6, 64, (42, 43)),                             # last wavefront idle; groups of five: rows | pair
     (8, 2, 33, (5,)), (8, 2, 63, (64,)),
     (20, 5, 32, (25, 26)), (16, 8, 32, (32, 33)), (5, 1, 32, (102, 103)),  # one key block: query head | rows
+    (16, 8, 32, (48, 49)),                                                # likewise, past one and a half workgroups per compute unit
     (16, 16, 32, (32, 33)),                                               # groups of one: query head
 ])
 def test_states_of_two_key_blocks_give_the_bits_of_the_pair(hq, hkv, longest, batches):
