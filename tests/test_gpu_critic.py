@@ -239,9 +239,10 @@ def test_int8_wide_tile(m, n):
     test_int8_dispatch_edges(m, n, 136)
 
 
-@pytest.mark.parametrize("m,n,k", [(8192, 3840, 1536), (8192, 3840, 1400)])
+@pytest.mark.parametrize("m,n,k", [(8192, 3840, 1536), (8192, 3840, 1400), (15400, 1930, 1544), (15500, 1930, 1544)])
 def test_int8_wide_tile_past_the_first_round(m, n, k):
-    """Twelve super-blocks of k on 1.9 rounds of 128 x 256 tiles; eleven on 128 x 128."""
+    """Twelve super-blocks of k on 1.9 rounds of 128 x 256 tiles; eleven on 128 x 128.  Likewise 1.89 rounds with ragged rows
+    and columns; 1.91 on 128 x 128, past nine tenths of the last one."""
     test_int8_dispatch_edges(m, n, k)
 
 
