@@ -1198,12 +1198,11 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
         // - the fullest compute unit must not have more to do: 5000 x 2560 x 2560 (2 wide or 4 narrow tiles) 57.3 / 61.7, 8192 x 2048 x
         //   2560 (2, 4) 68.9 / 71.6, 8192 x 3840 x 2560 (4, 8) 112 / 117; but 4096 x 3072 x 2560 (2, 3) 55.0 / 51.9, 6144 x 2048 x 2560 (2,
         //   3) 58.3 / 55.4, 6144 x 3072 x 2560 (3, 5) 81.5 / 77.7;
-        // - the last round three quarters full and, past the first, below 32 super-blocks of k and not for gate|up, not all but full (more
-        //   than nine tenths of it, a whole number of rounds apart): many of those lose, why is not known (11684 x 2697 x 2888 (1.98) 215 / 196, 3782 x 12803
-        //   x 3960 (2.99) 343 / 316, 7330 x 8761 x 1528 (3.96) 276 / 255; but 21199 x 1522 x 3744 (1.95) 271 / 282; 44 of them 0.988 on
-        //   average, 0.91 to 1.04; the 621 others that take the wide tile 1.025, 0.95 to 1.11; layers whose
-        //   gate|up is as full, 1094 of them, 1.00 to 1.01 on average, 0.97 to 1.03).  7040 x 6624 x 2560 (2.8) 1.02; 8320 x 9152 x 2560
-        //   (4.6) 0.995, 4096 x 6592 x 1024 (1.6) 0.96;
+        // - the last round three quarters full: 7040 x 6624 x 2560 (2.8) 1.02; 8320 x 9152 x 2560 (4.6) 0.995, 4096 x 6592 x 1024 (1.6)
+        //   0.96.  But past the first round not all but full (more than nine tenths of it, whole rounds apart): many of those lose, why
+        //   is not known (11684 x 2697 x 2888 (1.98) 215 / 196, 3782 x 12803 x 3960 (2.99) 343 / 316, 7330 x 8761 x 1528 (3.96) 276 /
+        //   255; 21199 x 1522 x 3744 (1.95) 271 / 282; 44 of them 0.988, 0.91 to 1.04, the 621 others that take the wide tile 1.025,
+        //   0.95 to 1.11).  Not so from 32 super-blocks of k on (1.03, 0.95 to 1.11) and for gate|up (1094 layers 1.00 to 1.01, 0.97 to 1.03);
         // - from six rounds on neither matters for gate|up or long k (1.01 to 1.04; 6.06 of them at 12032 x 8320: K = 4096 level, 2560 349 /
         //   334), from seven on down to K = 2560 (9600 x 12864 1.02, 12544 x 11008 1.01, 24576 x 9600 of 3200 1.02; 29312 x 4352 0.99);
         // - k not short past the first round: 4864 x 13568 (3.9) of K = 1024 104 / 105, 1536 139.5 / 144; 20184 x 4032 (4.9) 157 / 152, 197 /

@@ -611,9 +611,10 @@ int launch_gemv(const void* x, int x_dtype, int M, int K, int N, const uint32_t*
 // operand rows beside the parts' 64 KB of LDS reach, 5120 columns: ahead there also by GPU time alone, in a captured graph whose
 // weights no other call reads (two launches / here: 16 x 8192 x 4096 8.5 / 7.2, x 5120 9.0 / 8.3; bf16, where this instance
 // spills four registers, 9.5 / 8.6, 16 x 2560 x 5120 9.3 / 8.3; on weights that every call reads again the bf16 one is level
-// from 4097 columns on, 0.93 to 1.05).  17 to 32 tokens only up to 2048: level by GPU time from 1025 on (32 x 8192 x 2048 7.6 /
-// 7.6, 17 x 2560 x 1280 1.02), a launch less for the host (8.2 / 7.3); at 2560 behind (24 x 4096 7.8 / 8.1, 32 x 128 7.3 / 7.8,
-// 32 x 8192 on resident weights 7.2 / 7.9) for 0 to 17 % of a call's time from the host.
+// from 4097 columns on, 0.93 to 1.05).  17 to 32 tokens only up to 2048: ahead by GPU time up to 1024 columns (1.23 to 1.32 over
+// 3700 shapes), within 3 % from there on (fp32 1.01 up to 1536 and 0.99 up to 2048, bf16 0.99 and 0.97; from 2048 rows on 2 %
+// less), a launch less for the host (32 x 8192 x 2048 8.2 / 7.3); at 2560 behind (24 x 4096 7.8 / 8.1, 32 x 128 7.3 / 7.8, 32 x
+// 8192 on resident weights 7.2 / 7.9) for 0 to 17 % of a call's time from the host.
 bool rows_product_eligible(int M, int N, int K) {
     return M >= 3 && M <= 32 && round_up(N, NB) / NB <= 256 && K <= (M <= 16 ? 5120 : 2048);
 }
