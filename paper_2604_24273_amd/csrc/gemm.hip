@@ -1202,7 +1202,7 @@ int launch_gemm(const ActBuf& a, const WeightSegs& w, int M, int N, int K, float
         //   0.96.  But past the first round not all but full (more than nine tenths of it, whole rounds apart): many of those lose, why
         //   is not known (11684 x 2697 x 2888 (1.98) 215 / 196, 3782 x 12803 x 3960 (2.99) 343 / 316, 7330 x 8761 x 1528 (3.96) 276 /
         //   255; 21199 x 1522 x 3744 (1.95) 271 / 282; 44 of them 0.988, 0.91 to 1.04, the 621 others that take the wide tile 1.025,
-        //   0.95 to 1.11).  Not so from 32 super-blocks of k on (1.03, 0.95 to 1.11) and for gate|up (1094 layers 1.00 to 1.01, 0.97 to 1.03);
+        //   0.95 to 1.11).  Not so from 32 super-blocks of k on (28 of them 1.024, 0.95 to 1.08) and for gate|up (1094 layers 1.00 to 1.01, 0.97 to 1.03);
         // - from six rounds on neither matters for gate|up or long k (1.01 to 1.04; 6.06 of them at 12032 x 8320: K = 4096 level, 2560 349 /
         //   334), from seven on down to K = 2560 (9600 x 12864 1.02, 12544 x 11008 1.01, 24576 x 9600 of 3200 1.02; 29312 x 4352 0.99);
         // - k not short past the first round: 4864 x 13568 (3.9) of K = 1024 104 / 105, 1536 139.5 / 144; 20184 x 4032 (4.9) 157 / 152, 197 /
